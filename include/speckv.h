@@ -149,9 +149,10 @@ size_t speckv_workspace_bytes(const speckv_params *p);
 
 /* Launch plan the host derives for these parameters, for diagnostics and tests (no GPU needed):
  * info[0] waves per scoring workgroup, [1] 32-row blocks per wave, [2] row super-blocks per KV group,
- * [3] keys per chunk of the scoring sweeps, [4] unmasked chunks over all sequences, [5] keys per LDS
- * tile, [6] parts a row is split into for selection (1: one workgroup per row), [7] keys per such
- * part, [8] kernels of the unmasked scoring sweeps: bit 0 set when the row-statistics sweep, bit 1
+ * [3] keys per chunk of the scoring sweeps, [4] unmasked chunks over all sequences, [5] keys per tile
+ * (chunks and masked tails start at multiples of it; a tile may pass through LDS in two halves), [6]
+ * parts a row is split into for selection (1: one workgroup per row), [7] keys per such part, [8]
+ * kernels of the unmasked scoring sweeps: bit 0 set when the row-statistics sweep, bit 1
  * when the column-reduction sweep keeps the query rows stationary in LDS (clear: key tiles streamed
  * through LDS), [9] 1 for max reduction, [10] 1 when the key-tile row-statistics sweep sums
  * against fixed reference exponents and is followed by a repair launch (sweeps of several rounds of

@@ -107,10 +107,10 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   }
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
   if (units > (int64_t)1 << 24) return SPECKV_ERR_UNSUPPORTED;       // grid sizes stay far below 2^31
-  // Keys [0, tail0) of a sequence are complete LDS tiles visible to every observation row
+  // Keys [0, tail0) of a sequence are complete tiles visible to every observation row
   // (key <= m); they are cut into chunks of KC keys.  The rest is one masked tail chunk.
   const int rowb = d.D * d.elt;
-  const int kt = rowb <= 128 ? 256 : rowb <= 256 ? 128 : 64;          // keys per LDS tile of the scoring kernels
+  const int kt = rowb <= 128 ? 256 : rowb <= 256 ? 128 : 64;          // Tile::ALIGN of the scoring kernels
   int64_t fast_keys = 0;
   for (int s = 0; s < d.S; ++s) {
     const int n_s = t.cu[s + 1] - t.cu[s];

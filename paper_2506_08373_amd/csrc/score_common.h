@@ -35,6 +35,8 @@ constexpr float kNegBig = -1.0e30f;    // finite stand-in for "no key seen yet"
 // Row statistics against a fixed reference (score_sweep.h): a segment of kAnchorTiles tiles after
 // which a row sum has reached 2^126 (or is not a number) is repeated with the online step.
 constexpr int kAnchorTiles = 2;
+// the sum's exponent is carried into the reference when it has grown by this many binary orders
+constexpr int kAnchorGrowth = 4;
 // What each wavefront of a chunk workgroup of the row-statistics sweep leaves for the repair
 // launch: [0] the number of segments to repeat, [1 .. kFailListed] the first ones by number,
 // [kFailWords - 1] the segment from which on every segment is to be repeated when there are more
@@ -91,7 +93,12 @@ struct Tile {
   static constexpr int ROWB = D * ELT;          // bytes per key / query row
   static constexpr int C16 = ROWB / 16;         // 16-byte chunks per row
   static constexpr int NCS = C16 / 2;           // chunk steps (each lane half owns NCS chunks)
-  static constexpr int KT = ROWB <= 128 ? 256 : ROWB <= 256 ? 128 : 64;   // keys per LDS tile (32 KiB)
+  // Keys per LDS tile: 32 KiB, except 16 KiB where a row is 128 bytes.  Those sweeps need half the
+  // registers, so that with the smaller tile two workgroups share a CU and one works while the other
+  // waits at its tile barrier (prompt-token selection, 16 layers x 64K keys: column sweep 430 us with
+  // 256-key tiles and one workgroup, 395 us with 128-key tiles).
+  static constexpr int KT = ROWB <= 256 ? 128 : 64;
+  static constexpr int ALIGN = ROWB <= 128 ? 256 : KT;     // chunks and masked tails start at multiples of this many keys
   static constexpr int TILE_BYTES = KT * ROWB;
   static constexpr int RPB = ROWB >= 256 ? 1 : 256 / ROWB;   // rows per 256-byte bank sweep
   static constexpr int SWZ = (C16 < 16 ? C16 : 16) - 1;      // xor mask applied to the chunk index

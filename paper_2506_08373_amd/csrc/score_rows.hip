@@ -1,5 +1,4 @@
-// The row-statistics sweep (pass 1) of the importance scoring: see score_sweep.h.  A translation
-// unit of its own so that the two sweeps can be compiled with different scheduling strategies.
+// The row-statistics sweep (pass 1) of the importance scoring: see score_sweep.h.
 #include "score_sweep.h"
 
 namespace speckv {

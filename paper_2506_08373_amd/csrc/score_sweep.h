@@ -30,9 +30,8 @@
 // 16-byte chunks of the head dimension (half l/32 reads chunks [half*NCS, half*NCS+NCS)), so the
 // contraction is over all d channels whatever order the hardware assigns inside a slice.
 //
-// This header holds the sweep kernels and their launcher.  It is compiled into two translation
-// units, one per sweep (score_rows.hip, score_cols.hip), because the two want different
-// instruction scheduling strategies from the compiler (see build.py).
+// This header holds the sweep kernels and their launcher, compiled into two translation units, one per
+// sweep (score_rows.hip, score_cols.hip).
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -43,10 +42,14 @@ namespace speckv {
 namespace {
 
 
+// Column partials of a tile are complete one unit into the next tile and are read a tile later
+// (see do_tile): three tiles' worth is alive at a time, kept modulo four.
+constexpr int kCsumBuffers = 4;
+
 template <int ELT, int D, int MB, int NW>
 constexpr size_t score_lds_bytes() {
   using TL = Tile<ELT, D>;
-  return (size_t)2 * TL::TILE_BYTES + (size_t)2 * NW * MB * TL::KT * sizeof(float);
+  return (size_t)2 * TL::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * TL::KT * sizeof(float);
 }
 
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
@@ -101,7 +104,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   }
   const int n_host = A.t.cu[s + 1] - A.t.cu[s];          // row stride of the score layouts
   const int n_s = live_len(d, A.t, s);                    // tokens that exist (device-side count honoured)
-  const int tail0 = live_tail0(d, A.t, s, n_s, KT);
+  const int tail0 = live_tail0(d, A.t, s, n_s, TL::ALIGN);
   if (MASKED) {
     key_begin = tail0;
     key_end = n_s;
@@ -131,7 +134,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   const bool paired = PASS == 2 && RED == 1 && !MASKED && MB == 2 && nblk == NW * MB && blocks_per_head % 2 == 0;
   auto block_of = [&](int rb) { return paired ? wv * MB + rb : rb * NW + wv; };
   if (PASS == 2)   // slots of skipped blocks must read as zero when the tile partials are merged
-    for (int x = tid; x < 2 * NW * MB * KT; x += NW * 64) csum[x] = 0.f;
+    for (int x = tid; x < kCsumBuffers * NW * MB * KT; x += NW * 64) csum[x] = 0.f;
 
   // head and first observation row of each of this wave's 32-row blocks (a block never mixes
   // heads, so one division per block replaces one per row)
@@ -179,7 +182,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   }
   // the first tile is requested before anything else is loaded, so that its latency overlaps
   // with the Q fragment and row normaliser loads below
-  const int first_tile = REPAIR ? seg * kAnchorTiles : 0;
+  const int first_tile = REPAIR ? 1 + seg * kAnchorTiles : 0;
   if (ntiles > first_tile) SPECKV_LOAD_TILE(first_tile, 0)
 
   // ---- Q fragments of this wave's row blocks, resident for the whole sweep
@@ -255,7 +258,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   if (tid < KT) {                                                                            \
     const int key_ = key_begin + (tile_) * KT + tid;                                         \
     if (key_ < key_end) {                                                                    \
-      const float *cp_ = csum + (size_t)((tile_) & 1) * NW * MB * KT + tid;                  \
+      const float *cp_ = csum + (size_t)((tile_) % kCsumBuffers) * NW * MB * KT + tid;                  \
       float total_ = 0.f;                                                                    \
       if (RED == 0) {                                                                        \
         _Pragma("unroll") for (int w2 = 0; w2 < NW; ++w2) total_ += cp_[w2 * KT];            \
@@ -282,132 +285,70 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
-  // Row statistics of an unmasked chunk.  The chunk's first 32-key block gives each row its reference
-  // exponent (the block's maximum, found by the online step); every later block only adds
-  // 2^(score - reference) to the row's sum: no maximum search, no rescaling.  After every segment the
-  // sum's own exponent moves into the reference (a few integer and float operations, no branch),
-  // which keeps the sum near 2^-shift with shift = 100 - ceil(log2(keys per chunk)): a term that
-  // underflows (below 2^-126) beside it is less than 2^-25 / (keys per chunk) of the sum, so all
-  // of a chunk's keys together stay below fp32 resolution, and a score may exceed everything the
-  // row has seen before its segment by 126 + shift binary orders (146 nats for 32K-key chunks)
-  // before the sum overflows.  An overflow is sticky (infinity stays infinity), so it is looked for
-  // once per segment of kAnchorTiles tiles (kAnchorLimit; also NaN): the wavefront then goes back
-  // to the pairs it had before the segment, notes the segment on its list in A.fail and goes on;
-  // the repair launch behind this one (REPAIR) sweeps the noted segments with the online step on
-  // every block and adds their pairs.  (The same second sweep as code inside this kernel, inlined,
-  // outlined or as a compact loop, costs the first sweep the 3 % it is there to gain.)
+  // Row statistics of an unmasked chunk.  The chunk's first tile gives each row its reference exponent
+  // (its maximum, found by the online step); every later block only adds 2^(score - reference) to the
+  // row's sum: no maximum search, no rescaling.  After a segment (kAnchorTiles tiles, counted from the
+  // second tile) in which the sum has grown by 2^kAnchorGrowth or more its exponent moves into the
+  // reference, which keeps the sum between 2^-shift and 2^(kAnchorGrowth-shift) with shift = 100 -
+  // ceil(log2(keys per chunk)): a term that underflows (below 2^-126) beside it is less than 2^-25 /
+  // (keys per chunk) of the sum, so all of a chunk's keys together stay below fp32 resolution, and a
+  // score may exceed everything the row has seen before its segment by 126 + shift - kAnchorGrowth
+  // binary orders (143 nats for 32K-key chunks) before the sum overflows.  An overflow is sticky
+  // (infinity stays infinity), so it is looked for once per segment (kAnchorLimit; also NaN): the
+  // wavefront then goes back to the pairs it had before the segment, notes the segment on its list in
+  // A.fail and goes on; the repair launch behind this one (REPAIR) sweeps the noted segments with
+  // the online step on every block and adds their pairs.  (The same second sweep as code inside
+  // this kernel, inlined, outlined or as a compact loop, costs the first sweep the 3 % it is
+  // there to gain.)
+  constexpr bool kAnchored = PASS == 1 && !MASKED && !REPAIR && RED == 1;
   const int anchor_shift = 100 - (32 - __builtin_clz((unsigned)max(A.g.KC, 2) - 1u));
-  int fresh_tile = 0;                // the tile whose first block finds the reference (no pair yet)
-
-  // one tile of the sweep; the LDS buffer index is a compile-time constant so that every LDS
-  // address below is a register plus an immediate
-  auto do_tile = [&](int tile, auto buf_c, auto anchored_c) {
-    constexpr int buf = decltype(buf_c)::value;
-    if (tile + 1 < ntiles) SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
-    if (PASS == 2 && tile > 0) SPECKV_FLUSH_TILE(tile - 1)
-    const int tk0 = key_begin + tile * KT;
-    if (!MASKED) {
-      // Per 32-key block the MB accumulator chains of this wave are interleaved MFMA by MFMA
-      // (no back-to-back dependent MFMAs); the fragments of the next block are fetched while
-      // the vector pipe turns the scores into probabilities.  The second wave on the SIMD
-      // runs its MFMAs underneath that vector work.
-      // NACT = number of active row blocks of this wave (compile-time copy of nact)
-      // anchored: row statistics against the fixed reference (see above), else the online step
-      auto fast_tile = [&](auto nact_c, auto anchored_c) {
-        constexpr int NACT = decltype(nact_c)::value;
-        constexpr bool anchored = decltype(anchored_c)::value;
-        u32x4 bf[NCS];
-        SPECKV_LOAD_BFRAG(bf, buf, 0)
+  float l_before[MB];                 // the sums at the start of the current segment
+  int n_failed = 0;
+  int listed[kFailListed + 1];        // uniform: lives in scalar registers
+  if (kAnchored) {
 #pragma unroll
-        for (int kb = 0; kb < KT / 32; ++kb) {
-          f32x16 acc[NACT];
+    for (int i = 0; i <= kFailListed; ++i) listed[i] = 0;
+  }
+  // The segment is over (every block of it is in the sums): keep it or leave it to the repair launch.
+  // Usually the sums are still small and nothing but this comparison happens (2.5 % on the sweep
+  // against moving the exponent after every segment).
+  const float grown = __builtin_ldexpf(1.f, kAnchorGrowth - anchor_shift);
+  auto end_segment = [&](int segment) {
+    bool look = false;
 #pragma unroll
-          for (int rb = 0; rb < NACT; ++rb) acc[rb] = (f32x16){0};
-          // pass 2: the compiler may not move vector work of the neighbouring key blocks across the
-          // MFMA chains or the fragment loads (measured: the column sweep 1.5 % faster, the step 0.5 %
-          // since the chip is power-limited; the same barriers cost the row-statistics sweep 5 %;
-          // wave priorities (s_setprio) around the MFMAs do no more than the barrier they imply)
-          if (PASS == 2) __builtin_amdgcn_sched_barrier(0);
+    for (int rb = 0; rb < MB; ++rb) look |= !(lrun[rb] < grown);
+    if (__builtin_amdgcn_ballot_w64(look) != 0 || n_failed > kFailListed) {           // seldom
+      bool out_of_range = false;
 #pragma unroll
-          for (int cs = 0; cs < NCS; ++cs)
+      for (int rb = 0; rb < MB; ++rb) out_of_range |= !(lrun[rb] < kAnchorLimit);
+      // The decision is the wavefront's own (its rows are nobody else's): no barrier, no exchange.
+      // (A full list: every later segment is left to the repair as well, overflowed or not.)
+      if (__builtin_amdgcn_ballot_w64(out_of_range) != 0 || n_failed > kFailListed) {
 #pragma unroll
-            for (int rb = 0; rb < NACT; ++rb)
-              acc[rb] = PASS == 1 ? mma_chunk<DT>(bf[cs], qf[rb][cs], acc[rb]) : mma_chunk<DT>(qf[rb][cs], bf[cs], acc[rb]);
-          if (PASS == 2) __builtin_amdgcn_sched_barrier(0);
-          if (kb + 1 < KT / 32) SPECKV_LOAD_BFRAG(bf, buf, kb + 1)
-          if (PASS == 2) __builtin_amdgcn_sched_barrier(0);
-          if (PASS == 1 && anchored && !(kb == 0 && tile == fresh_tile)) {
+        for (int rb = 0; rb < MB; ++rb) lrun[rb] = l_before[rb];
 #pragma unroll
-            for (int rb = 0; rb < NACT; ++rb) {
-              const float nm = -mrun[rb];
-              float sum = 0.f;
+        for (int i = 0; i <= kFailListed; ++i)
+          if (i == n_failed) listed[i] = segment;
+        ++n_failed;
+      } else {                                         // the sum's exponent above 2^-shift goes into the reference
 #pragma unroll
-              for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][i], c2, nm));
-              lrun[rb] += sum;
-            }
-          } else if (PASS == 1) {
-#pragma unroll
-            for (int rb = 0; rb < NACT; ++rb) {
-              // branch-free online softmax step for the lane's query row
-              float tmax = fmaxf(fmaxf(acc[rb][0], acc[rb][1]), acc[rb][2]);
-#pragma unroll
-              for (int i = 3; i < 15; i += 2) tmax = fmaxf(fmaxf(tmax, acc[rb][i]), acc[rb][i + 1]);
-              tmax = fmaxf(tmax, acc[rb][15]);
-              const float mnew = fmaxf(mrun[rb], tmax * c2);
-              const float scale = __builtin_amdgcn_exp2f(mrun[rb] - mnew);
-              const float nm = -mnew;
-              float sum = 0.f;
-#pragma unroll
-              for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][i], c2, nm));
-              lrun[rb] = fmaf(lrun[rb], scale, sum);
-              mrun[rb] = mnew;
-              if (anchored) {      // the chunk's first block: move the reference up for the blocks that follow
-                lrun[rb] = __builtin_ldexpf(lrun[rb], -anchor_shift);
-                mrun[rb] += (float)anchor_shift;
-              }
-            }
-          } else {
-            // the 16 probabilities of a row block: all multiply-adds, then all exp2, then the reduction
-            // as a tree, so that no instruction waits on the one issued just before it (against
-            // two batches of 8 with a serial sum: the column sweep 2.4 % faster, the step 0.8 %)
-            float colsum = 0.f;
-#pragma unroll
-            for (int rb = 0; rb < NACT; ++rb) {
-              if (RED == 1 && !(paired && rb > 0)) colsum = 0.f;
-              float x[16];
-#pragma unroll
-              for (int i = 0; i < 16; ++i) x[i] = fmaf(acc[rb][i], c2, nlse[rb][i]);
-#pragma unroll
-              for (int i = 0; i < 16; ++i) x[i] = __builtin_amdgcn_exp2f(x[i]);
-              __builtin_amdgcn_sched_barrier(0);
-              if (RED == 0) {
-                colsum += (((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]))) +
-                          (((x[8] + x[9]) + (x[10] + x[11])) + ((x[12] + x[13]) + (x[14] + x[15])));
-              } else {
-                const float t0 = fmaxf(fmaxf(x[0], x[1]), x[2]), t1 = fmaxf(fmaxf(x[3], x[4]), x[5]);
-                const float t2 = fmaxf(fmaxf(x[6], x[7]), x[8]), t3 = fmaxf(fmaxf(x[9], x[10]), x[11]);
-                const float t4 = fmaxf(fmaxf(x[12], x[13]), x[14]);
-                colsum = fmaxf(fmaxf(colsum, fmaxf(fmaxf(t0, t1), t2)), fmaxf(fmaxf(t3, t4), x[15]));
-              }
-              __builtin_amdgcn_sched_barrier(0);
-              if (RED == 1 && !paired) {   // one value per 32-row block: blocks of a head are merged at the flush
-                colsum = max_other_half(colsum);
-                if (half == 0) csum[(size_t)buf * NW * MB * KT + (rb * NW + wv) * KT + kb * 32 + l32] = colsum;
-              }
-            }
-            if (RED == 0) {
-              colsum = add_other_half(colsum);
-              if (half == 0) csum[(size_t)buf * NW * MB * KT + wv * KT + kb * 32 + l32] = colsum;
-            } else if (paired) {       // the maximum over both blocks of the pair, slot wv
-              colsum = max_other_half(colsum);
-              if (half == 0) csum[(size_t)buf * NW * MB * KT + wv * KT + kb * 32 + l32] = colsum;
-            }
-          }
+        for (int rb = 0; rb < MB; ++rb) {
+          const int up = lrun[rb] > 0.f ? max(__builtin_amdgcn_frexp_expf(lrun[rb]) + anchor_shift, 0) : 0;
+          lrun[rb] = __builtin_ldexpf(lrun[rb], -up);
+          mrun[rb] += (float)up;
         }
-      };
-      if (nact == MB) fast_tile(std::integral_constant<int, MB>{}, anchored_c);
-      else if (MB > 1 && nact == 1) fast_tile(std::integral_constant<int, 1>{}, anchored_c);
-    } else {
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb) l_before[rb] = lrun[rb];
+  };
+
+  if constexpr (MASKED) {
+    for (int tile = 0; tile < ntiles; ++tile) {
+      const int buf = tile & 1;
+      if (tile + 1 < ntiles) SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
+      if (PASS == 2 && tile > 0) SPECKV_FLUSH_TILE(tile - 1)
+      const int tk0 = key_begin + tile * KT;
       // Tail tiles: keys above m are hidden from some window rows; keys >= n_s do not exist.
 #pragma unroll 1
       for (int kb = 0; kb < KT / 32; ++kb) {
@@ -442,6 +383,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         } else {
           float colsum = 0.f;
           const int key = tk0 + kb * 32 + l32;
+          float *dst = csum + (size_t)(tile % kCsumBuffers) * NW * MB * KT + kb * 32 + l32;
 #pragma unroll
           for (int rb = 0; rb < MB; ++rb) {
             if (rb >= nact) continue;
@@ -462,73 +404,189 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
               float cm = 0.f;
 #pragma unroll
               for (int i = 0; i < 16; ++i) cm = fmaxf(cm, p[i]);
-              cm = max_other_half(cm);
-              if (half == 0) csum[(size_t)buf * NW * MB * KT + (rb * NW + wv) * KT + kb * 32 + l32] = cm;
+              dst[(rb * NW + wv) * KT] = max_other_half(cm);
             }
           }
+          if (RED == 0) dst[wv * KT] = add_other_half(colsum);
+        }
+      }
+      // the next tile must have landed in LDS, and every wave must be done with this one
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    if (PASS == 2 && ntiles > 0) SPECKV_FLUSH_TILE(ntiles - 1)
+  } else {
+    // The unmasked sweep is software-pipelined in every wave.  A unit is one 32-key x 32-row block: while
+    // its chain of MFMAs runs (a chain on one accumulator issues at the full rate), the wave turns the
+    // block of the unit before it into probabilities, so that each wave by itself keeps both pipes
+    // busy.  (Without this the two waves of a SIMD, released together by the tile barrier, do
+    // their matrix work together and then their vector work together.)  The last unit of a tile is
+    // finished beside the first MFMAs of the next tile, where it also covers the latency of that tile's
+    // first fragment reads.  The key fragments are reloaded in place, each as soon as its last MFMA of the
+    // current key block is issued.
+    // What bounds a 32x32 block at d = 128: an MFMA holds the vector issue port for about 8 cycles, an
+    // exp2 8, a multiply-add or add 4, hence 8*8 + 16*(8 + 4 + 4) = 324 cycles of issue for 256 cycles of
+    // matrix work.
+    // Measured on 32 layers x 128K keys, 512 rows per KV head: 4.35 -> 4.07 ms (row statistics), 4.21 ->
+    // 4.15 ms (column sums), 458 -> 416 and 436 -> 432 cycles per 32x32 block; the clock falls with the
+    // stalls (power limit), so the time gains less than the cycles where calls follow each other.
+    // Units of both row blocks at once (the next key block's 16 MFMAs beside 96 vector
+    // instructions), 16x16x32 MFMAs and explicit instruction ratios measure the same or worse.
+    // NACT = number of active row blocks of this wave (nact): the whole sweep is one straight piece of
+    // code per number, so that the open block and the row state never move between registers
+    // (1.7 % on the row statistics).
+    constexpr int KB = KT / 32;
+    auto sweep = [&](auto nact_c) {
+      constexpr int NACT = decltype(nact_c)::value;
+      f32x16 acc[2];                   // blocks of the units: the open one in one, the next one in the other
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;    // nothing open: probabilities of 2^-inf = 0
+      float colsum = 0.f;              // pass 2: the lane's key, over the row blocks of the current key block
+
+      // turns the scores x of row block rb into probabilities; pass 2: of key block kb, into partial buffer cbuf
+      auto finish_unit = [&](const f32x16 &x, int rb, int kb, int cbuf, auto anchored_c) {
+        if constexpr (PASS == 1 && decltype(anchored_c)::value) {
+          const float nm = -mrun[rb];
+          float sum = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(x[i], c2, nm));
+          lrun[rb] += sum;
+          asm volatile("" : "+v"(lrun[rb]));      // stays in its unit (the compiler would sink it to the next use)
+        } else if constexpr (PASS == 1) {
+          // branch-free online softmax step for the lane's query row
+          float tmax = fmaxf(fmaxf(x[0], x[1]), x[2]);
+#pragma unroll
+          for (int i = 3; i < 15; i += 2) tmax = fmaxf(fmaxf(tmax, x[i]), x[i + 1]);
+          tmax = fmaxf(tmax, x[15]);
+          const float mnew = fmaxf(mrun[rb], tmax * c2);
+          const float scale = __builtin_amdgcn_exp2f(mrun[rb] - mnew);
+          const float nm = -mnew;
+          float sum = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(x[i], c2, nm));
+          lrun[rb] = fmaf(lrun[rb], scale, sum);
+          mrun[rb] = mnew;
+          asm volatile("" : "+v"(lrun[rb]), "+v"(mrun[rb]));
+        } else {
+          if (rb == 0 || (RED == 1 && !paired)) colsum = 0.f;
+          float p[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nlse[rb][i]));
           if (RED == 0) {
-            colsum = add_other_half(colsum);
-            if (half == 0) csum[(size_t)buf * NW * MB * KT + wv * KT + kb * 32 + l32] = colsum;
+            colsum += (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
+                      (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15])));
+          } else {
+            const float t0 = fmaxf(fmaxf(p[0], p[1]), p[2]), t1 = fmaxf(fmaxf(p[3], p[4]), p[5]);
+            const float t2 = fmaxf(fmaxf(p[6], p[7]), p[8]), t3 = fmaxf(fmaxf(p[9], p[10]), p[11]);
+            const float t4 = fmaxf(fmaxf(p[12], p[13]), p[14]);
+            colsum = fmaxf(fmaxf(colsum, fmaxf(fmaxf(t0, t1), t2)), fmaxf(fmaxf(t3, t4), p[15]));
+          }
+          // sum (or the maximum over a block pair): one value per wave, slot wv; otherwise one per 32-row
+          // block, blocks of a head are merged at the flush.  Both halves write the same value.
+          float *dst = csum + (size_t)cbuf * NW * MB * KT + kb * 32 + l32;
+          if (RED == 0) {
+            if (rb == NACT - 1) dst[wv * KT] = add_other_half(colsum);
+          } else if (!paired || rb == NACT - 1) {
+            dst[paired ? wv * KT : (rb * NW + wv) * KT] = max_other_half(colsum);
+          }
+          asm volatile("" : "+v"(colsum));
+        }
+      };
+
+      // One tile of the sweep; the LDS buffer index is a compile-time constant so that every LDS
+      // address below is a register plus an immediate.  Pass 2 flushes the tile before last: its last
+      // column partials were written in the previous tile's first unit.
+      // anchored: row statistics against the fixed reference (see above), else the online step
+      auto do_tile = [&](int tile, auto buf_c, auto anchored_c) {
+        constexpr int buf = decltype(buf_c)::value;
+        constexpr bool anchored = decltype(anchored_c)::value;
+        if (tile + 1 < ntiles) SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
+        if (PASS == 2 && tile > 1) SPECKV_FLUSH_TILE(tile - 2)
+        if constexpr (NACT > 0) {
+          u32x4 bf[NCS];
+          SPECKV_LOAD_BFRAG(bf, buf, 0)
+#pragma unroll
+          for (int u = 0; u < KB * NACT; ++u) {
+            const int kb = u / NACT, rb = u % NACT;
+            f32x16 &x = acc[u & 1];
+            x = (f32x16){0};
+#pragma unroll
+            for (int cs = 0; cs < NCS; ++cs) {
+              x = PASS == 1 ? mma_chunk<DT>(bf[cs], qf[rb][cs], x) : mma_chunk<DT>(qf[rb][cs], bf[cs], x);
+              if (rb == NACT - 1 && kb + 1 < KB)
+                bf[cs] = *reinterpret_cast<const u32x4 *>(kbuf + buf * TILE_BYTES + (kb + 1) * 32 * ROWB + foff[cs]);
+            }
+            const int pu = (u + KB * NACT - 1) % (KB * NACT);      // the unit before (of the tile before for u = 0)
+            finish_unit(acc[(u & 1) ^ 1], pu % NACT, pu / NACT,
+                        (u == 0 ? tile + kCsumBuffers - 1 : tile) % kCsumBuffers, anchored_c);
+            // the compiler may not move work of the neighbouring units across: without this it piles up
+            // fragment reads and open blocks until the registers spill
+            __builtin_amdgcn_sched_barrier(0);
+            if (kAnchored && anchored && u == 0 && buf == 1 && tile > 1) end_segment((tile - 3) / kAnchorTiles);
           }
         }
-      }
-    }
-    // the next tile must have landed in LDS, and every wave must be done with this one
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-  };
-  // tiles [t0, t1), t0 even (its tile sits in LDS buffer 0)
-  auto run_tiles = [&](int t0, int t1, auto anchored_c) {
-    for (int tile = t0; tile < t1; tile += 2) {
-      do_tile(tile, std::integral_constant<int, 0>{}, anchored_c);
-      if (tile + 1 < t1) do_tile(tile + 1, std::integral_constant<int, 1>{}, anchored_c);
-    }
-  };
-  if constexpr (REPAIR) {
-    run_tiles(first_tile, min(ntiles, first_tile + kAnchorTiles), std::false_type{});
-  } else if constexpr (PASS == 1 && !MASKED && RED == 1) {
-    int n_failed = 0;
-    int listed[kFailListed + 1];       // uniform: lives in scalar registers
+        // the next tile must have landed in LDS, and every wave must be done with this one
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+      };
+      // tiles [t0, t1); tile t0 sits in LDS buffer `buf`
+      auto run_tiles = [&](int t0, int t1, auto buf_c, auto anchored_c) {
+        constexpr int buf = decltype(buf_c)::value;
+        for (int tile = t0; tile < t1; tile += 2) {
+          do_tile(tile, std::integral_constant<int, buf>{}, anchored_c);
+          if (tile + 1 < t1) do_tile(tile + 1, std::integral_constant<int, buf ^ 1>{}, anchored_c);
+        }
+      };
+      // the open unit (the last one of a tile: it always sits in acc[1])
+      auto drain = [&](int last_tile, auto anchored_c) {
+        if constexpr (NACT > 0) finish_unit(acc[1], NACT - 1, KB - 1, last_tile % kCsumBuffers, anchored_c);
 #pragma unroll
-    for (int i = 0; i <= kFailListed; ++i) listed[i] = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += kAnchorTiles) {
-      const int t1 = min(ntiles, t0 + kAnchorTiles);
-      float m_before[MB], l_before[MB];
+        for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
+      };
+      using buf0 = std::integral_constant<int, 0>;
+      using buf1 = std::integral_constant<int, 1>;
+      if constexpr (REPAIR) {
+        const int end = min(ntiles, first_tile + kAnchorTiles);
+        run_tiles(first_tile, end, buf0{}, std::false_type{});
+        drain(end - 1, std::false_type{});
+      } else if constexpr (kAnchored) {
+        if (ntiles > 0) {
+          do_tile(0, buf0{}, std::false_type{});       // finds the references
+          drain(0, std::false_type{});
 #pragma unroll
-      for (int rb = 0; rb < MB; ++rb) { m_before[rb] = mrun[rb]; l_before[rb] = lrun[rb]; }
-      run_tiles(t0, t1, std::true_type{});
-      bool out_of_range = false;
-#pragma unroll
-      for (int rb = 0; rb < MB; ++rb) out_of_range |= !(lrun[rb] < kAnchorLimit);
-      // The decision is the wavefront's own (its rows are nobody else's): no barrier, no exchange.
-      // (A full list: every later segment is left to the repair as well, overflowed or not.)
-      if (__builtin_amdgcn_ballot_w64(out_of_range) != 0 || n_failed > kFailListed) {            // rare
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb) { mrun[rb] = m_before[rb]; lrun[rb] = l_before[rb]; }
-        if (fresh_tile == t0) fresh_tile = t1;         // still no pair: the next segment finds the reference
-#pragma unroll
-        for (int i = 0; i <= kFailListed; ++i)
-          if (i == n_failed) listed[i] = t0 / kAnchorTiles;
-        ++n_failed;
-      } else {                                         // the sum's exponent above 2^-shift goes into the reference
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-          const int up = lrun[rb] > 0.f ? max(__builtin_amdgcn_frexp_expf(lrun[rb]) + anchor_shift, 0) : 0;
-          lrun[rb] = __builtin_ldexpf(lrun[rb], -up);
-          mrun[rb] += (float)up;
+          for (int rb = 0; rb < MB; ++rb) {            // moves them up for the blocks that follow
+            lrun[rb] = __builtin_ldexpf(lrun[rb], -anchor_shift);
+            mrun[rb] += (float)anchor_shift;
+            l_before[rb] = lrun[rb];
+          }
+          run_tiles(1, ntiles, buf1{}, std::true_type{});
+          drain(ntiles - 1, std::true_type{});
+          if (ntiles > 1) end_segment((ntiles - 2) / kAnchorTiles);
+        }
+      } else if (ntiles > 0) {
+        run_tiles(0, ntiles, buf0{}, std::false_type{});
+        drain(ntiles - 1, std::false_type{});
+        if (PASS == 2) {
+          __syncthreads();
+          if (ntiles > 1) SPECKV_FLUSH_TILE(ntiles - 2)
+          SPECKV_FLUSH_TILE(ntiles - 1)
         }
       }
-    }
-    if (lane <= kFailListed + 1) {
-      int32_t *mine = A.fail + ((int64_t)bid * NW + wv) * kFailWords;
-      int v = n_failed;
+    };
+    // (the barriers inside count wavefronts, whichever copy of the code they are in)
+    if (nact == MB) sweep(std::integral_constant<int, MB>{});
+    else if (MB > 1 && nact == 1) sweep(std::integral_constant<int, 1>{});
+    else sweep(std::integral_constant<int, 0>{});
+    if constexpr (kAnchored) {
+      if (lane <= kFailListed + 1) {
+        int32_t *mine = A.fail + ((int64_t)bid * NW + wv) * kFailWords;
+        int v = n_failed;
 #pragma unroll
-      for (int i = 0; i <= kFailListed; ++i)
-        if (lane == i + 1) v = listed[i];
-      mine[lane] = v;                  // [0] count, [1 ..] segments, the last one the start of the rest
+        for (int i = 0; i <= kFailListed; ++i)
+          if (lane == i + 1) v = listed[i];
+        mine[lane] = v;                  // [0] count, [1 ..] segments, the last one the start of the rest
+      }
     }
-  } else {
-    run_tiles(0, ntiles, std::false_type{});
   }
 
   if (PASS == 1) {
@@ -556,8 +614,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         }
       }
     }
-  } else if (ntiles > 0) {
-    SPECKV_FLUSH_TILE(ntiles - 1)
   }
 }
 

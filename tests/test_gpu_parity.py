@@ -1401,3 +1401,18 @@ def test_more_than_65535_layer_head_units(S):
         for g in range(H):
             assert_indices_valid(got[layer, g], ref[layer][0]["pooled"][g], n, w.n_window, w.c_max,
                                  "many units l%d g%d" % (layer, g))
+
+
+@pytest.mark.parametrize("mode", ["fixed", "online"])
+@pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 128, 3), ("f16", 64, 5), ("f32", 128, 3)])
+def test_sweep_of_few_tiles(S, monkeypatch, mode, dtype, head_dim, group):
+    """The software-pipelined sweeps on chunks of one to six key tiles (an open block carried from tile
+    to tile, segments that start at the second one), with waves of two, one and no row blocks."""
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", mode)
+    tile = {("f32", 128): 64, ("f16", 64): 256}.get((dtype, head_dim), 128)
+    for tiles in (1, 2, 3, 4, 6):
+        w = workloads.SpecKVWorkload(name="few_tiles", n_layers=1, n_q_heads=2 * group, n_kv_heads=2, head_dim=head_dim,
+                                     seq_lens=(tile * tiles + 40, tile * (tiles + 1) + 33), n_window=32, n_lookahead=32,
+                                     pool_k=7, c_max=60, dtype=dtype, sm_scale=head_dim ** -0.5, n_planted=2,
+                                     channel_scale=(0.5, 4.0), seed=70 + tiles)
+        check_full_path(S, w, reduce="sum" if tiles % 2 else "max")
