@@ -29,6 +29,7 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // one 128-bit lane access
 
 constexpr float kNegBig = -1.0e30f;    // finite stand-in for "no key seen yet"

@@ -16,7 +16,7 @@
 // Work split: a workgroup owns RSB = NW*MB*32 rows (all of them when M <= RSB) and one chunk of
 // keys.  Each wave keeps the MFMA fragments of its MB 32-row blocks of Q in registers for the
 // whole sweep; K tiles of KT keys stream HBM -> LDS directly (global_load_lds, double buffered,
-// no staging registers).  The LDS tile is unpadded; the 16-byte chunks of a row are stored at
+// no staging registers; fp32 tiles pass through registers, where they are split, see Operand).  The LDS tile is unpadded; the 16-byte chunks of a row are stored at
 // slot = chunk ^ swizzle(row) so that the 128-bit fragment reads of 16 consecutive keys hit 16
 // different bank groups.  Every wave reads all K fragments of a tile.
 // Pass 1 multiplies with K as the A operand, so a lane holds 16 keys of ONE query row and the
@@ -24,7 +24,8 @@
 // so a lane holds 16 rows of ONE key and the column sum is an in-lane add, one cross-half add and
 // a cross-wave add through LDS.  No atomics anywhere: results are bit-reproducible.
 //
-// MFMA operand layout used (v_mfma_f32_32x32x16_bf16, v_mfma_f32_32x32x16_f16, v_mfma_f32_32x32x2_f32): lane l holds
+// MFMA operand layout used (v_mfma_f32_32x32x16_bf16, v_mfma_f32_32x32x16_f16; v_mfma_f32_32x32x2_f32
+// for fp32 blocks whose scores are not finite): lane l holds
 // row (A) or column (B) l%32 and the k-slice selected by l/32; the result register i of lane l
 // is element (8*(i/4) + 4*(l/32) + i%4, l%32).  Both operands take their k-slices from the same
 // 16-byte chunks of the head dimension (half l/32 reads chunks [half*NCS, half*NCS+NCS)), so the
@@ -46,10 +47,48 @@ namespace {
 // (see do_tile): three tiles' worth is alive at a time, kept modulo four.
 constexpr int kCsumBuffers = 4;
 
-template <int ELT, int D, int MB, int NW>
+// How a sweep holds its operands.  bf16 and f16 rows are used as they are.  An fp32 row becomes three
+// bf16 rows ("planes") that add up to it exactly, v = v0 + v1 + v2 with each part the rounded
+// remainder of the ones before it (3 x 9 significant bits, |v1| <= 2^-9 |v|, |v2| <= 2^-18 |v|), and a
+// product of two rows becomes the six products of planes a, b with a + b <= 2, smallest first in the
+// fp32 accumulator.  The three that are left out are below 2^-26 of a term, a quarter of the rounding an
+// fp32 product chain adds per term.  The fp32 matrix instruction runs at 1/16 of the bf16 rate (4096
+// cycles per 32x32 block at d = 128), six bf16 products take 1536.  Measured against it: scoring, two
+// selections and the gather of 2 layers x 8209 keys, 72 rows x 4 heads per group, 355 -> 214 us; one
+// layer of 32K keys, 32 heads of 128, max, 327 -> 204 us; 4 layers x 60K keys, heads of 64, 581 -> 347 us.
+// The raw scores' error against 64-bit sums is 3 to 24 % smaller than with the fp32 instruction (fewer
+// roundings in the accumulator: rel 2.1e-7 to 9.2e-7 after 2.5e-7 to 1.05e-6, eight shapes).
+template <int DT, int D>
+struct Operand {
+  static constexpr bool SPLIT = DT == kF32;
+  static constexpr int PLANES = SPLIT ? 3 : 1;
+  static constexpr int MMA_DT = SPLIT ? kBf16 : DT;            // type of the operands the matrix cores see
+  using TL = Tile<2, D>;                                      // LDS layout of one plane
+  static constexpr int KT = Tile<elt_bytes(DT), D>::KT, ALIGN = Tile<elt_bytes(DT), D>::ALIGN;
+  static constexpr int PLANE_BYTES = KT * TL::ROWB, TILE_BYTES = PLANES * PLANE_BYTES;
+};
+
+template <int DT, int D, int MB, int NW>
 constexpr size_t score_lds_bytes() {
-  using TL = Tile<ELT, D>;
-  return (size_t)2 * TL::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * TL::KT * sizeof(float);
+  using OP = Operand<DT, D>;
+  return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float);
+}
+
+// Eight fp32 values (two 16-byte chunks) as one 16-byte chunk per bf16 plane.
+__device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float r0 = __uint_as_float(j < 2 ? lo[2 * j] : hi[2 * j - 4]);
+    float r1 = __uint_as_float(j < 2 ? lo[2 * j + 1] : hi[2 * j - 3]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const bf16x2 b = {(__bf16)r0, (__bf16)r1};               // round to nearest even, v_cvt_pk_bf16_f32
+      const unsigned u = __builtin_bit_cast(unsigned, b);
+      plane[p][j] = u;
+      r0 -= __uint_as_float(u << 16);
+      r1 -= __uint_as_float(u & 0xffff0000u);
+    }
+  }
 }
 
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
@@ -70,11 +109,15 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
                                            const bool wave_takes_part = true) {
   static_assert(!REPAIR || (PASS == 1 && !MASKED), "only the row-statistics sweep is repaired");
   constexpr int ELT = elt_bytes(DT);
-  using TL = Tile<ELT, D>;
-  constexpr int ROWB = TL::ROWB, NCS = TL::NCS, KT = TL::KT, TILE_BYTES = TL::TILE_BYTES;
+  using OP = Operand<DT, D>;
+  using TL = typename OP::TL;
+  constexpr bool SPLIT = OP::SPLIT;
+  constexpr int ROWB = TL::ROWB, NCS = TL::NCS, KT = OP::KT, TILE_BYTES = OP::TILE_BYTES;
+  constexpr int PLANE_BYTES = OP::PLANE_BYTES, PLANES = OP::PLANES;
   constexpr int RSB = NW * MB * 32;
   constexpr int SEG_PER_WAVE = TILE_BYTES / 1024 / NW;   // 1 KiB (one wave-wide 128-bit load) segments
   constexpr int RPS = 1024 / ROWB;                        // tile rows per segment
+  constexpr int SPLIT_CHUNKS = KT * (D / 8) / (NW * 64);   // fp32: groups of 8 channels a thread splits per tile
   static_assert(TILE_BYTES % (1024 * NW) == 0, "tile load must divide evenly over the waves");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char *kbuf = smem;
@@ -104,7 +147,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   }
   const int n_host = A.t.cu[s + 1] - A.t.cu[s];          // row stride of the score layouts
   const int n_s = live_len(d, A.t, s);                    // tokens that exist (device-side count honoured)
-  const int tail0 = live_tail0(d, A.t, s, n_s, TL::ALIGN);
+  const int tail0 = live_tail0(d, A.t, s, n_s, OP::ALIGN);
   if (MASKED) {
     key_begin = tail0;
     key_end = n_s;
@@ -180,22 +223,59 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           (__attribute__((address_space(3))) void *)(kbuf + (buf_) * TILE_BYTES + seg_ * 1024), 16, 0, 0); \
     }                                                                                         \
   }
+  // fp32: the tile passes through registers, split into its planes on the way.  SPECKV_FETCH_TILE
+  // requests it, SPECKV_STORE_TILE (before the barrier that hands the tile over) splits and stores it.
+  u32x4 raw[SPLIT ? SPLIT_CHUNKS : 1][2];
+#define SPECKV_FETCH_TILE(tile_)                                                              \
+  _Pragma("unroll") for (int it = 0; it < SPLIT_CHUNKS; ++it) {                               \
+    const int e_ = it * NW * 64 + tid, r_ = e_ / (D / 8), c_ = e_ % (D / 8);                  \
+    const int k_ = key_begin + (tile_) * KT + r_;                                             \
+    /* rows past the end of the sequence re-read its last key; they are masked later */       \
+    const char *src_ = kbase + (int64_t)(MASKED ? min(k_, n_s - 1) : k_) * tokb + c_ * 32;    \
+    raw[it][0] = *reinterpret_cast<const u32x4 *>(src_);                                      \
+    raw[it][1] = *reinterpret_cast<const u32x4 *>(src_ + 16);                                 \
+  }
+#define SPECKV_STORE_TILE(buf_)                                                               \
+  _Pragma("unroll") for (int it = 0; it < SPLIT_CHUNKS; ++it) {                               \
+    const int e_ = it * NW * 64 + tid, r_ = e_ / (D / 8), c_ = e_ % (D / 8);                  \
+    u32x4 part_[3];                                                                           \
+    split_chunk(raw[it][0], raw[it][1], part_);                                               \
+    _Pragma("unroll") for (int p = 0; p < 3; ++p)                                             \
+      *reinterpret_cast<u32x4 *>(kbuf + (buf_) * TILE_BYTES + p * PLANE_BYTES + r_ * ROWB +   \
+                                 ((c_ ^ TL::swizzle(r_)) * 16)) = part_[p];                   \
+  }
   // the first tile is requested before anything else is loaded, so that its latency overlaps
   // with the Q fragment and row normaliser loads below
   const int first_tile = REPAIR ? 1 + seg * kAnchorTiles : 0;
-  if (ntiles > first_tile) SPECKV_LOAD_TILE(first_tile, 0)
+  if (ntiles > first_tile) {
+    if constexpr (SPLIT) SPECKV_FETCH_TILE(first_tile)
+    else SPECKV_LOAD_TILE(first_tile, 0)
+  }
 
   // ---- Q fragments of this wave's row blocks, resident for the whole sweep
-  u32x4 qf[MB][NCS];
+  u32x4 qf[MB][PLANES * NCS];
+  // the lane's share (half) of its query row in row block rb
+  auto query_row = [&](int rb, bool valid) {
+    const int hh = blk_head[rb], i = blk_i0[rb] + l32;
+    return A.q + ((int64_t)layer * d.q_sl + (int64_t)s * d.q_ss + (int64_t)(valid ? i : 0) * d.q_sr +
+                  (int64_t)(g * d.G + (valid ? hh : 0)) * d.q_sh) * ELT + half * (D / 2) * ELT;
+  };
 #pragma unroll
   for (int rb = 0; rb < MB; ++rb) {
     const bool valid = SPECKV_ROW_VALID(rb, l32);
-    const int hh = blk_head[rb], i = blk_i0[rb] + l32;
-    const char *qp = A.q + ((int64_t)layer * d.q_sl + (int64_t)s * d.q_ss + (int64_t)(valid ? i : 0) * d.q_sr +
-                            (int64_t)(g * d.G + (valid ? hh : 0)) * d.q_sh) * ELT + (half * NCS) * 16;
+    const char *qp = query_row(rb, valid);
 #pragma unroll
-    for (int cs = 0; cs < NCS; ++cs)
-      qf[rb][cs] = valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 16) : (u32x4)(0u);
+    for (int cs = 0; cs < NCS; ++cs) {
+      if constexpr (SPLIT) {
+        u32x4 part[3];
+        split_chunk(valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 32) : (u32x4)(0u),
+                    valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 32 + 16) : (u32x4)(0u), part);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) qf[rb][p * NCS + cs] = part[p];
+      } else {
+        qf[rb][cs] = valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 16) : (u32x4)(0u);
+      }
+    }
   }
 
   // ---- per-pass row state
@@ -244,9 +324,39 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   uint32_t foff[NCS];
 #pragma unroll
   for (int cs = 0; cs < NCS; ++cs) foff[cs] = l32 * ROWB + (((half * NCS + cs) ^ TL::swizzle(l32)) * 16);
-#define SPECKV_LOAD_BFRAG(dst_, buf_, kb_)                                                     \
-  _Pragma("unroll") for (int cs = 0; cs < NCS; ++cs)                                          \
-    dst_[cs] = *reinterpret_cast<const u32x4 *>(kbuf + (buf_) * TILE_BYTES + (kb_) * 32 * ROWB + foff[cs]);
+  // chunk cs of key block kb_ in plane p_ (fp32: the smallest plane comes first)
+#define SPECKV_FRAG(buf_, p_, kb_, cs_) \
+  (*reinterpret_cast<const u32x4 *>(kbuf + (buf_) * TILE_BYTES + (p_) * PLANE_BYTES + (kb_) * 32 * ROWB + foff[cs_]))
+#define SPECKV_LOAD_BFRAG(dst_, buf_, kb_) \
+  _Pragma("unroll") for (int cs = 0; cs < NCS; ++cs) dst_[cs] = SPECKV_FRAG(buf_, PLANES - 1, kb_, cs);
+  // adds the products of key chunk bf (chunk cs, plane kp) and row block rb to the scores x
+  auto add_products = [&](f32x16 &x, const u32x4 &bf, int kp, int rb, int cs) {
+#pragma unroll
+    for (int qp = PLANES - 1 - kp; qp >= 0; --qp)
+      x = PASS == 1 ? mma_chunk<OP::MMA_DT>(bf, qf[rb][qp * NCS + cs], x) : mma_chunk<OP::MMA_DT>(qf[rb][qp * NCS + cs], bf, x);
+  };
+  // The planes of an infinity, a NaN or a number that bf16 rounds to infinity multiply to NaN where fp32
+  // products would not: a block with a score that is not finite is computed again from memory with the fp32
+  // instruction (one multiply-add per score to look for it, beside 24 or 48 MFMAs).  key0: the block's first key.
+  auto recompute_unless_finite = [&](f32x16 &x, int rb, int key0) {
+    if constexpr (SPLIT) {
+      float probe = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) probe = fmaf(x[i], 0.f, probe);       // NaN if any score is infinite or NaN
+      if (__builtin_amdgcn_ballot_w64(!(probe == 0.f)) != 0) {
+        const bool valid = SPECKV_ROW_VALID(rb, l32);
+        const char *qp = query_row(rb, valid);
+        const char *kp = kbase + (int64_t)min(key0 + l32, n_s - 1) * tokb + half * (D / 2) * ELT;
+        x = (f32x16){0};
+#pragma unroll 1
+        for (int cs = 0; cs < D / 8; ++cs) {
+          const u32x4 kc = *reinterpret_cast<const u32x4 *>(kp + cs * 16);
+          const u32x4 qc = valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 16) : (u32x4)(0u);
+          x = PASS == 1 ? mma_chunk<kF32>(kc, qc, x) : mma_chunk<kF32>(qc, kc, x);
+        }
+      }
+    }
+  };
 
   // cross-wave merge of the column partials of one finished tile (pass 2)
   float *plane_out = nullptr;
@@ -282,6 +392,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     }                                                                                        \
   }
 
+  if constexpr (SPLIT) {
+    if (ntiles > first_tile) SPECKV_STORE_TILE(0)
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
@@ -346,22 +459,38 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   if constexpr (MASKED) {
     for (int tile = 0; tile < ntiles; ++tile) {
       const int buf = tile & 1;
-      if (tile + 1 < ntiles) SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
+      if (tile + 1 < ntiles) {
+        if constexpr (SPLIT) SPECKV_FETCH_TILE(tile + 1)
+        else SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
+      }
       if (PASS == 2 && tile > 0) SPECKV_FLUSH_TILE(tile - 1)
       const int tk0 = key_begin + tile * KT;
       // Tail tiles: keys above m are hidden from some window rows; keys >= n_s do not exist.
 #pragma unroll 1
       for (int kb = 0; kb < KT / 32; ++kb) {
         if (tk0 + kb * 32 >= key_end) break;               // nothing but padding from here on
+        // scores of row block rb against key block kb
         u32x4 bf[NCS];
-        SPECKV_LOAD_BFRAG(bf, buf, kb)
+        if constexpr (!SPLIT) SPECKV_LOAD_BFRAG(bf, buf, kb)
+        auto scores = [&](int rb) {
+          f32x16 acc = {0};
+#pragma unroll
+          for (int kp = PLANES - 1; kp >= 0; --kp) {
+            if constexpr (SPLIT) {
+#pragma unroll
+              for (int cs = 0; cs < NCS; ++cs) bf[cs] = SPECKV_FRAG(buf, kp, kb, cs);
+            }
+#pragma unroll
+            for (int cs = 0; cs < NCS; ++cs) add_products(acc, bf[cs], kp, rb, cs);
+          }
+          recompute_unless_finite(acc, rb, tk0 + kb * 32);
+          return acc;
+        };
         if (PASS == 1) {
 #pragma unroll
           for (int rb = 0; rb < MB; ++rb) {
             if (rb >= nact) continue;
-            f32x16 acc = {0};
-#pragma unroll
-            for (int cs = 0; cs < NCS; ++cs) acc = mma_chunk<DT>(bf[cs], qf[rb][cs], acc);
+            f32x16 acc = scores(rb);
             // lane: query row (wv*MB+rb)*32 + l32; keys tk0 + kb*32 + 8*(i/4) + 4*half + i%4
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -387,9 +516,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 #pragma unroll
           for (int rb = 0; rb < MB; ++rb) {
             if (rb >= nact) continue;
-            f32x16 acc = {0};
-#pragma unroll
-            for (int cs = 0; cs < NCS; ++cs) acc = mma_chunk<DT>(qf[rb][cs], bf[cs], acc);
+            f32x16 acc = scores(rb);
             // lane: key tk0 + kb*32 + l32; rows (wv*MB+rb)*32 + 8*(i/4) + 4*half + i%4
             float p[16];
 #pragma unroll
@@ -409,6 +536,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           }
           if (RED == 0) dst[wv * KT] = add_other_half(colsum);
         }
+      }
+      if constexpr (SPLIT) {
+        if (tile + 1 < ntiles) SPECKV_STORE_TILE(buf ^ 1)
       }
       // the next tile must have landed in LDS, and every wave must be done with this one
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -441,6 +571,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       f32x16 acc[2];                   // blocks of the units: the open one in one, the next one in the other
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;    // nothing open: probabilities of 2^-inf = 0
+      bool open = false;               // a unit waits in acc[1] (fp32: only then are its scores looked at)
       float colsum = 0.f;              // pass 2: the lane's key, over the row blocks of the current key block
 
       // turns the scores x of row block rb into probabilities; pass 2: of key block kb, into partial buffer cbuf
@@ -500,7 +631,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       auto do_tile = [&](int tile, auto buf_c, auto anchored_c) {
         constexpr int buf = decltype(buf_c)::value;
         constexpr bool anchored = decltype(anchored_c)::value;
-        if (tile + 1 < ntiles) SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
+        if (tile + 1 < ntiles) {
+          if constexpr (SPLIT) SPECKV_FETCH_TILE(tile + 1)
+          else SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
+        }
         if (PASS == 2 && tile > 1) SPECKV_FLUSH_TILE(tile - 2)
         if constexpr (NACT > 0) {
           u32x4 bf[NCS];
@@ -511,12 +645,18 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
             f32x16 &x = acc[u & 1];
             x = (f32x16){0};
 #pragma unroll
-            for (int cs = 0; cs < NCS; ++cs) {
-              x = PASS == 1 ? mma_chunk<DT>(bf[cs], qf[rb][cs], x) : mma_chunk<DT>(qf[rb][cs], bf[cs], x);
-              if (rb == NACT - 1 && kb + 1 < KB)
-                bf[cs] = *reinterpret_cast<const u32x4 *>(kbuf + buf * TILE_BYTES + (kb + 1) * 32 * ROWB + foff[cs]);
+            for (int kp = PLANES - 1; kp >= 0; --kp) {
+#pragma unroll
+              for (int cs = 0; cs < NCS; ++cs) {
+                add_products(x, bf[cs], kp, rb, cs);
+                if (kp > 0) bf[cs] = SPECKV_FRAG(buf, kp - 1, kb, cs);
+                else if (rb == NACT - 1 && kb + 1 < KB) bf[cs] = SPECKV_FRAG(buf, PLANES - 1, kb + 1, cs);
+                else if (SPLIT && rb < NACT - 1) bf[cs] = SPECKV_FRAG(buf, PLANES - 1, kb, cs);
+              }
             }
             const int pu = (u + KB * NACT - 1) % (KB * NACT);      // the unit before (of the tile before for u = 0)
+            if (SPLIT && (u > 0 || open))
+              recompute_unless_finite(acc[(u & 1) ^ 1], pu % NACT, key_begin + (u == 0 ? tile - 1 : tile) * KT + pu / NACT * 32);
             finish_unit(acc[(u & 1) ^ 1], pu % NACT, pu / NACT,
                         (u == 0 ? tile + kCsumBuffers - 1 : tile) % kCsumBuffers, anchored_c);
             // the compiler may not move work of the neighbouring units across: without this it piles up
@@ -524,6 +664,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
             __builtin_amdgcn_sched_barrier(0);
             if (kAnchored && anchored && u == 0 && buf == 1 && tile > 1) end_segment((tile - 3) / kAnchorTiles);
           }
+        }
+        open = true;
+        if constexpr (SPLIT) {
+          if (tile + 1 < ntiles) SPECKV_STORE_TILE(buf ^ 1)
         }
         // the next tile must have landed in LDS, and every wave must be done with this one
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -539,7 +683,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       };
       // the open unit (the last one of a tile: it always sits in acc[1])
       auto drain = [&](int last_tile, auto anchored_c) {
-        if constexpr (NACT > 0) finish_unit(acc[1], NACT - 1, KB - 1, last_tile % kCsumBuffers, anchored_c);
+        if constexpr (NACT > 0) {
+          if (SPLIT && open) recompute_unless_finite(acc[1], NACT - 1, key_begin + last_tile * KT + (KB - 1) * 32);
+          finish_unit(acc[1], NACT - 1, KB - 1, last_tile % kCsumBuffers, anchored_c);
+        }
+        open = false;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
       };
@@ -619,6 +767,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 
 #undef SPECKV_ROW_VALID
 #undef SPECKV_LOAD_TILE
+#undef SPECKV_FETCH_TILE
+#undef SPECKV_STORE_TILE
+#undef SPECKV_FRAG
 #undef SPECKV_LOAD_BFRAG
 #undef SPECKV_FLUSH_TILE
 
@@ -727,7 +878,7 @@ hipError_t launch_sweep(const ScoreArgs &A0, size_t lds, hipStream_t st) {
 // workgroup geometry of A.
 template <int DT, int D, int MB, int NW, int PASS>
 hipError_t sweep_for_geometry(const ScoreArgs &A, hipStream_t st) {
-  const size_t lds = score_lds_bytes<elt_bytes(DT), D, MB, NW>();
+  const size_t lds = score_lds_bytes<DT, D, MB, NW>();
   if constexpr (PASS == 1) {
     if (score_rows_fixed_reference(A.d, A.g)) return launch_sweep<DT, D, MB, NW, 1, 1>(A, lds, st);
     return launch_sweep<DT, D, MB, NW, 1, 0>(A, lds, st);

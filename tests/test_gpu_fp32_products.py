@@ -1,0 +1,99 @@
+"""fp32 scoring: rows split into three bf16 parts against 64-bit results, at the edges of the split."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def S():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2506_08373_amd as lib
+    lib.load_library()
+    return lib
+
+
+def raw_scores(S, q, k, n_window, sm_scale, reduce="sum"):
+    """Raw scores [Hkv, n] of one layer and one sequence."""
+    hkv, n = k.shape[2], k.shape[1]
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=n_window, pool_k=7, c_max=16, sm_scale=sm_scale, reduce=reduce)
+    ws = torch.empty(S.workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    out = torch.full((2, 1, hkv * n), -1.0, dtype=torch.float32, device="cuda")
+    S.speckv_score(p, q, k, out[0], out[1], ws)
+    return out[1].view(hkv, n)
+
+
+def exact_scores(q, k, n_window, sm_scale, reduce="sum"):
+    rows, hq = q.shape[2], q.shape[3]
+    n, hkv = k.shape[1], k.shape[2]
+    m, group = n - n_window, hq // hkv
+    row = torch.arange(rows, device="cuda")
+    last = torch.where(row < n_window, m + row, torch.full_like(row, n - 1))
+    hidden = torch.arange(n, device="cuda")[None, :] > last[:, None]
+    ref = torch.zeros(hkv, n, dtype=torch.float64, device="cuda")
+    for h in range(hq):
+        logits = (q[0, 0, :, h].double() @ k[0, :, h // group].double().t()) * sm_scale
+        p = torch.softmax(logits.masked_fill(hidden, -math.inf), dim=1)
+        ref[h // group] += p.sum(0) if reduce == "sum" else p.amax(0)
+    return ref
+
+
+def draw(seed, n, rows, hq, hkv, d):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    q = torch.randn(1, 1, rows, hq, d, generator=gen, device="cuda")
+    return q, torch.randn(1, n, hkv, d, generator=gen, device="cuda"), gen
+
+
+# one and several row blocks per wave, padded rows, chunks of one tile to several, tails of every kind
+@pytest.mark.parametrize("d,group,rows,n", [(128, 1, 9, 130), (128, 4, 72, 1193), (128, 8, 33, 577), (64, 2, 17, 259),
+                                            (64, 4, 128, 2077), (64, 7, 40, 700)])
+@pytest.mark.parametrize("reduce", ["sum", "max"])
+def test_every_product_of_the_parts_counts(S, d, group, rows, n, reduce):
+    """One channel per query row is not zero, so a logit is one product of two 24-bit numbers of size up to
+    40.  Allowed: the products left out (2^-26 of it), one rounding for each of the five sums (2^-24),
+    and the same again in the multiply-add of the softmax: below 40 * 8 * 2^-24 = 2e-5, in the numerator
+    and in the normaliser, and 1e-6 for sums and exp2.  A missing product shows as 40 * 2^-17 = 3e-4."""
+    q, k, gen = draw(5, n, rows, group * 2, 2, d)
+    keep = torch.randint(0, d, (1, 1, rows, group * 2, 1), generator=gen, device="cuda")
+    q = torch.where(torch.arange(d, device="cuda") == keep, 3 + q.abs() / 2, torch.zeros_like(q))
+    k = k.clamp(-3, 3)
+    scale = 40.0 / float(q.max() * 3)
+    got, want = raw_scores(S, q, k, min(rows, 16), scale, reduce).double(), exact_scores(q, k, min(rows, 16), scale, reduce)
+    assert ((got - want).abs() <= 4.1e-5 * want).all(), float(((got - want).abs() / want).max())
+
+
+def test_scaling_by_powers_of_two_changes_no_bit(S):
+    """Q * 2^e, K * 2^-e: the parts scale with the number, down to parts of 2^-121."""
+    q, k, _ = draw(6, 900, 40, 4, 2, 128)
+    k = torch.where(k.abs() < 2.0 ** -6, torch.zeros_like(k), k)
+    base = raw_scores(S, q, k, 16, 128 ** -0.5)
+    for e in (60, -60, 97):
+        assert torch.equal(raw_scores(S, q * 2.0 ** e, k * 2.0 ** -e, 16, 128 ** -0.5), base), e
+
+
+@pytest.mark.parametrize("d,group,n", [(128, 2, 700), (64, 8, 1100)])
+def test_infinities_and_numbers_above_the_bf16_range(S, d, group, n):
+    """Keys with an infinite channel against queries that are positive there get the score exp(-inf) = 0; numbers
+    that bf16 rounds to infinity, and query channels that have zero parts, give finite products."""
+    q, k, _ = draw(7, n, 64, group * 2, 2, d)      # whole row blocks: a zero row times an infinity is NaN in any product
+    q[..., 3] = 2.0 ** -126                 # its two smaller parts are zero
+    q[..., 5] = q[..., 5].abs() + 1.0
+    far = [0, 31, 32, 63, 64, n // 2, n - 60, n - 20, n - 1]       # first and last blocks of tiles, chunk and tail
+    k[0, far[::2], :, 3] = 3.4e38           # finite; the nearest bf16 number is infinity
+    k[0, far[1::2], 0, 5] = -math.inf
+    got, want = raw_scores(S, q, k, 16, d ** -0.5).double(), exact_scores(q, k, 16, d ** -0.5)
+    assert (got[0, far[1::2]] == 0).all()
+    assert ((got - want).abs() <= 1e-4 * want).all(), float(((got - want).abs() / want.clamp(min=1e-300)).max())
+
+
+def test_nan_stays_with_its_head(S):
+    q, k, _ = draw(8, 500, 24, 4, 2, 128)
+    k[0, 77, 1, 9] = math.nan
+    got = raw_scores(S, q, k, 16, 128 ** -0.5)
+    assert torch.isnan(got[1]).any() and torch.isfinite(got[0]).all()
+    want = exact_scores(q, k, 16, 128 ** -0.5)
+    assert ((got[0].double() - want[0]).abs() <= 1e-4 * want[0]).all()
