@@ -7,8 +7,9 @@
 //    smaller index, ascending, then the window m..n_in-1 (Alg. 1 "Select KVs").
 //    MSD radix select on order-preserving 32-bit keys (digits of 11 + 11 + 10 bits).  One
 //    workgroup per row; every step is deterministic.  The histogram of the first digit comes
-//    from the pooling kernel in the fused calls (else from one read of the row); rows of up to
-//    about 229K entries are then read once more: entries above the threshold's bin are
+//    from the pooling kernel in the fused calls (else from one read of the row); short rows (16K
+//    entries, 32K without the counts) stay in registers, others of up to about 229K entries are
+//    then read once more: entries above the threshold's bin are
 //    selected outright, the few inside it settle the other two digits in LDS.  Longer rows, and
 //    rows with more than 4096 entries in that bin, take one read per digit plus an ordered
 //    compaction.  A workgroup is bound by its vector ALU, so the per-element work is kept
@@ -432,6 +433,194 @@ __device__ __forceinline__ void emit_selected(const float *__restrict__ x, int m
   }
 }
 
+// ---- rows of up to kRegMaxVec vectors: held in registers, read once ----
+// A short row is a chain of latencies, not of work: one read, three digits, one emission.  Every thread keeps
+// its part of the row as ordered keys in registers, so that no digit reads memory again, the three digits'
+// counters are cleared together up front, and a digit costs three barriers.  A wavefront holds a contiguous
+// part of the row (positions then need one exchange of wavefront totals, not one per tile).
+// 32 keys per thread is what 1024 threads can hold in their 128 registers each.  A digit costs every key a
+// compare and a masked LDS atomic, where select_after_prefix below visits only the bin's own entries a second
+// time: with the first digit given that is the better way for rows above 16K entries, without it the read and
+// the counting it saves decide.  Kernel times, select_after_prefix -> here: first digit given, 1K entries
+// 11.1 -> 7.4 us, 4K 12.0 -> 9.9, 16K (256 rows) 18.4 -> 17.2, 32K 16.5 -> 16.8; not given, 8K 14.4 -> 10.9,
+// one row of 32K 30.4 -> 19.0.
+constexpr int kRegIters = 8;                                     // 128-bit vectors a thread holds
+constexpr int kRegMaxVec = kRegIters * kSelThreads;              // vectors of a row, partial ones at its ends included
+constexpr int kRegMaxVecCounted = kRegMaxVec / 2;                // ... with less to gain (first digit or threshold known)
+constexpr int kRegCopies = 4, kRegStride = 2048 + 8;             // copies of a digit's counters, in different banks
+struct RegShared {
+  uint32_t second[kRegCopies * kRegStride], third[kRegCopies * (1024 + 8)], first[kHistCopies * kRegStride];
+  uint32_t wave_tot[4][kSelWaves];
+  uint32_t found[3][2];
+};
+
+// Vectors of 16 aligned bytes that the row touches; `shift`: entries of the first one that lie before the row.
+__device__ __forceinline__ int row_vectors(const float *x, int m, int *shift) {
+  *shift = (int)((uint32_t)(reinterpret_cast<uintptr_t>(x) >> 2) & 3u);
+  return (m + *shift + 3) >> 2;
+}
+__device__ __forceinline__ bool row_in_registers(const float *x, int m, bool counted) {
+  int shift;
+  return row_vectors(x, m, &shift) <= (counted ? kRegMaxVecCounted : kRegMaxVec);
+}
+
+struct RegRow {
+  uint32_t key[4 * kRegIters];      // ordered keys, at least 1; 0: not an entry of the row
+  int n_it, j0;                     // vectors per thread in use; row index of key[0] (+256 per vector)
+};
+
+__device__ __forceinline__ void load_row(const float *__restrict__ x, int m, RegRow &r) {
+  int shift;
+  const int nvec = row_vectors(x, m, &shift);
+  r.n_it = (nvec + kSelThreads - 1) / kSelThreads;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  r.j0 = 4 * (wv * r.n_it * 64 + lane) - shift;
+  float4 val[kRegIters];
+#pragma unroll
+  for (int i = 0; i < kRegIters; ++i) {
+    const int j = r.j0 + 256 * i;
+    val[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < r.n_it && j >= 0 && j + 3 < m) val[i] = *reinterpret_cast<const float4 *>(x + j);
+  }
+#pragma unroll
+  for (int i = 0; i < kRegIters; ++i) {
+    const int j = r.j0 + 256 * i;
+    if (i < r.n_it) {
+      const bool whole = j >= 0 && j + 3 < m;
+      if (!whole) {                                             // the row's ends, and vectors outside
+        val[i].x = j >= 0 && j < m ? x[j] : 0.f;
+        val[i].y = j + 1 >= 0 && j + 1 < m ? x[j + 1] : 0.f;
+        val[i].z = j + 2 >= 0 && j + 2 < m ? x[j + 2] : 0.f;
+        val[i].w = j + 3 >= 0 && j + 3 < m ? x[j + 3] : 0.f;
+      }
+      const float e4[4] = {val[i].x, val[i].y, val[i].z, val[i].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t k = max(ordered_key(e4[c]), 1u);
+        r.key[4 * i + c] = whole || (j + c >= 0 && j + c < m) ? k : 0u;
+      }
+    }
+  }
+}
+
+// Writes, ascending, the indices of the row's entries above the key thr (at least 1) and of its first need_eq
+// entries equal to it.
+__device__ __forceinline__ void emit_from_registers(const RegRow &r, uint32_t thr, uint32_t need_eq,
+                                                    int32_t *__restrict__ out, uint32_t *wave_tot) {
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  uint32_t marks[kRegIters], before[kRegIters];     // entries above (bits 0-3) and equal (4-7); both counted before (16 bits each)
+  uint32_t run = 0;
+#pragma unroll
+  for (int i = 0; i < kRegIters; ++i) {
+    if (i < r.n_it) {
+      uint32_t g4 = 0, q4 = 0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        g4 |= r.key[4 * i + c] > thr ? 1u << c : 0u;
+        q4 |= r.key[4 * i + c] == thr ? 1u << c : 0u;
+      }
+      const uint32_t n = __popc(g4) | (__popc(q4) << 16);
+      uint32_t total;
+      before[i] = run + wave_exclusive_scan(n, &total);
+      marks[i] = g4 | (q4 << 4);
+      run += total;
+    }
+  }
+  if (lane == 0) wave_tot[wv] = run;
+  __syncthreads();
+  uint32_t base = 0;                                // a row has at most 2^15 entries: neither half overflows
+#pragma unroll
+  for (int w2 = 0; w2 < kSelWaves; ++w2) base += w2 < wv ? wave_tot[w2] : 0u;
+#pragma unroll
+  for (int i = 0; i < kRegIters; ++i) {
+    if (i < r.n_it && marks[i] != 0) {
+      uint32_t gt = (base + before[i]) & 0xffffu, eq = (base + before[i]) >> 16;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool is_gt = (marks[i] >> c) & 1u, is_eq = (marks[i] >> (4 + c)) & 1u;
+        if (is_gt || (is_eq && eq < need_eq)) out[gt + min(eq, need_eq)] = r.j0 + 256 * i + c;
+        gt += is_gt;
+        eq += is_eq;
+      }
+    }
+  }
+}
+
+// select_top_row for a row that fits registers.  Entries outside the row have the smallest key of all, so they
+// never change the rank of one inside.
+__device__ __forceinline__ void select_in_registers(const float *__restrict__ x, int m, int count,
+                                                    int32_t *__restrict__ out, RegShared &sh,
+                                                    const uint32_t *__restrict__ first_digit) {
+  const int tid = threadIdx.x;
+  const int b0 = 2047 - 2 * tid, b1 = 2046 - 2 * tid;           // threads in order walk the bins downwards
+  uint32_t c0 = 0, c1 = 0;
+  if (first_digit != nullptr) { c0 = first_digit[b0]; c1 = first_digit[b1]; }
+  RegRow r;
+  load_row(x, m, r);
+  for (int b = tid; b < kRegCopies * kRegStride; b += kSelThreads) sh.second[b] = 0;
+  for (int b = tid; b < kRegCopies * (1024 + 8); b += kSelThreads) sh.third[b] = 0;
+  uint32_t remaining = (uint32_t)count;
+  // c0, c1: the thread's counts of the digits d0 > d1; returns the digit that holds the remaining-th largest
+  // entry and makes `remaining` its rank among the entries with that digit
+  auto decide = [&](int level, int d0, int d1, uint32_t n0, uint32_t n1) {
+    uint32_t total;
+    const uint32_t above = block_exclusive_scan(n0 + n1, sh.wave_tot[level], &total);
+    if (above < remaining && remaining <= above + n0) {
+      sh.found[level][0] = (uint32_t)d0;
+      sh.found[level][1] = remaining - above;
+    } else if (above + n0 < remaining && remaining <= above + n0 + n1) {
+      sh.found[level][0] = (uint32_t)d1;
+      sh.found[level][1] = remaining - above - n0;
+    }
+    __syncthreads();
+    remaining = sh.found[level][1];
+    return sh.found[level][0];
+  };
+  if (first_digit == nullptr) {
+    for (int b = tid; b < kHistCopies * kRegStride; b += kSelThreads) sh.first[b] = 0;
+    __syncthreads();
+    uint32_t *h = sh.first + (tid % kHistCopies) * kRegStride;
+#pragma unroll
+    for (int i = 0; i < kRegIters; ++i)
+      if (i < r.n_it) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (r.key[4 * i + c] != 0) atomicAdd(&h[r.key[4 * i + c] >> 21], 1u);
+      }
+    __syncthreads();
+#pragma unroll
+    for (int cp = 0; cp < kHistCopies; ++cp) { c0 += sh.first[cp * kRegStride + b0]; c1 += sh.first[cp * kRegStride + b1]; }
+  }
+  const uint32_t d0 = decide(0, b0, b1, c0, c1);                // (its barriers also order the clearing)
+  uint32_t *h2 = sh.second + (tid % kRegCopies) * kRegStride, *h3 = sh.third + (tid % kRegCopies) * (1024 + 8);
+#pragma unroll
+  for (int i = 0; i < kRegIters; ++i)
+    if (i < r.n_it) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (r.key[4 * i + c] >> 21 == d0) atomicAdd(&h2[(r.key[4 * i + c] >> 10) & 2047u], 1u);
+    }
+  __syncthreads();
+  c0 = c1 = 0;
+#pragma unroll
+  for (int cp = 0; cp < kRegCopies; ++cp) { c0 += sh.second[cp * kRegStride + b0]; c1 += sh.second[cp * kRegStride + b1]; }
+  const uint32_t p22 = (d0 << 11) | decide(1, b0, b1, c0, c1);
+#pragma unroll
+  for (int i = 0; i < kRegIters; ++i)
+    if (i < r.n_it) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (r.key[4 * i + c] >> 10 == p22) atomicAdd(&h3[r.key[4 * i + c] & 1023u], 1u);
+    }
+  __syncthreads();
+  c0 = 0;
+#pragma unroll
+  for (int cp = 0; cp < kRegCopies; ++cp) c0 += sh.third[cp * (1024 + 8) + 1023 - tid];
+  const uint32_t thr = (p22 << 10) | decide(2, 1023 - tid, 0, c0, 0u);
+  emit_from_registers(r, thr, remaining, out, sh.wave_tot[3]);
+}
+
 // ---- rows of up to kFastMaxVec vectors: one more read once a digit or two are decided ----
 // With the leading digit(s) of the threshold decided, the keys that start the same way form one
 // range of floats.  Entries above it are selected whatever the other digits turn out to be
@@ -472,6 +661,7 @@ struct FastShared {
   uint32_t found[2];
 };
 constexpr size_t kSelLdsBytes = sizeof(FastShared) > sizeof(SelShared) ? sizeof(FastShared) : sizeof(SelShared);
+static_assert(sizeof(RegShared) <= kSelLdsBytes, "one LDS block serves every way of selecting");
 
 // Smallest and largest float whose ordered key starts with the `bits` (11 or 22) leading bits of
 // `prefix`.  Ranges that hold NaN patterns are cut at the infinities, and a range that would end at
@@ -736,6 +926,10 @@ __device__ __forceinline__ void select_after_prefix(const float *__restrict__ x,
 __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int m, int count,
                                                int32_t *__restrict__ out, unsigned char *lds,
                                                const uint32_t *__restrict__ first_digit = nullptr) {
+  if (row_in_registers(x, m, first_digit != nullptr)) {
+    select_in_registers(x, m, count, out, *reinterpret_cast<RegShared *>(lds), first_digit);
+    return;
+  }
   SelShared &sh = *reinterpret_cast<SelShared *>(lds);
   const RowSplit rs = split_row(x, m);
   uint32_t prefix = 0, mask = 0, remaining = (uint32_t)count;
@@ -1081,7 +1275,11 @@ __global__ __launch_bounds__(kSelThreads) void select_ada_kernel(Dims d, SeqTab 
   if (count <= 0) return;
   const uint32_t *st = state + (int64_t)ls * kAdaStateWords(d.Hkv);
   const uint32_t known = st[2 + 2 * d.Hkv + g];
-  if (known & 0x80000000u)
+  if ((known & 0x80000000u) && row_in_registers(row, m, true)) {
+    RegRow r;
+    load_row(row, m, r);
+    emit_from_registers(r, max(st[0], 1u), known & 0x7fffffffu, out, reinterpret_cast<RegShared *>(sel_lds)->wave_tot[3]);
+  } else if (known & 0x80000000u)
     emit_selected(row, m, split_row(row, m), st[0], known & 0x7fffffffu, out, *reinterpret_cast<SelShared *>(sel_lds));
   else select_top_row(row, m, count, out, sel_lds);
 }
