@@ -465,7 +465,7 @@ __device__ __forceinline__ bool row_in_registers(const float *x, int m, bool cou
 }
 
 struct RegRow {
-  uint32_t key[4 * kRegIters];      // ordered keys, at least 1; 0: not an entry of the row
+  uint32_t key[4 * kRegIters];      // ordered keys; 0, the smallest, for what is not an entry of the row
   int n_it, j0;                     // vectors per thread in use; row index of key[0] (+256 per vector)
 };
 
@@ -496,16 +496,16 @@ __device__ __forceinline__ void load_row(const float *__restrict__ x, int m, Reg
       const float e4[4] = {val[i].x, val[i].y, val[i].z, val[i].w};
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const uint32_t k = max(ordered_key(e4[c]), 1u);
+        const uint32_t k = ordered_key(e4[c]);
         r.key[4 * i + c] = whole || (j + c >= 0 && j + c < m) ? k : 0u;
       }
     }
   }
 }
 
-// Writes, ascending, the indices of the row's entries above the key thr (at least 1) and of its first need_eq
-// entries equal to it.
-__device__ __forceinline__ void emit_from_registers(const RegRow &r, uint32_t thr, uint32_t need_eq,
+// Writes, ascending, the indices of the row's entries above the key thr and of its first need_eq entries
+// equal to it.
+__device__ __forceinline__ void emit_from_registers(const RegRow &r, int m, uint32_t thr, uint32_t need_eq,
                                                     int32_t *__restrict__ out, uint32_t *wave_tot) {
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -519,6 +519,11 @@ __device__ __forceinline__ void emit_from_registers(const RegRow &r, uint32_t th
       for (int c = 0; c < 4; ++c) {
         g4 |= r.key[4 * i + c] > thr ? 1u << c : 0u;
         q4 |= r.key[4 * i + c] == thr ? 1u << c : 0u;
+      }
+      if (thr == 0) {                               // key 0 (a NaN's) is also what the vectors outside hold
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if ((uint32_t)(r.j0 + 256 * i + c) >= (uint32_t)m) q4 &= ~(1u << c);
       }
       const uint32_t n = __popc(g4) | (__popc(q4) << 16);
       uint32_t total;
@@ -548,7 +553,7 @@ __device__ __forceinline__ void emit_from_registers(const RegRow &r, uint32_t th
 }
 
 // select_top_row for a row that fits registers.  Entries outside the row have the smallest key of all, so they
-// never change the rank of one inside.
+// never change the rank of one inside (they may be counted beside a key of 0 in the lowest bins, behind it).
 __device__ __forceinline__ void select_in_registers(const float *__restrict__ x, int m, int count,
                                                     int32_t *__restrict__ out, RegShared &sh,
                                                     const uint32_t *__restrict__ first_digit) {
@@ -586,7 +591,7 @@ __device__ __forceinline__ void select_in_registers(const float *__restrict__ x,
       if (i < r.n_it) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          if (r.key[4 * i + c] != 0) atomicAdd(&h[r.key[4 * i + c] >> 21], 1u);
+          if ((uint32_t)(r.j0 + 256 * i + c) < (uint32_t)m) atomicAdd(&h[r.key[4 * i + c] >> 21], 1u);
       }
     __syncthreads();
 #pragma unroll
@@ -618,7 +623,7 @@ __device__ __forceinline__ void select_in_registers(const float *__restrict__ x,
 #pragma unroll
   for (int cp = 0; cp < kRegCopies; ++cp) c0 += sh.third[cp * (1024 + 8) + 1023 - tid];
   const uint32_t thr = (p22 << 10) | decide(2, 1023 - tid, 0, c0, 0u);
-  emit_from_registers(r, thr, remaining, out, sh.wave_tot[3]);
+  emit_from_registers(r, m, thr, remaining, out, sh.wave_tot[3]);
 }
 
 // ---- rows of up to kFastMaxVec vectors: one more read once a digit or two are decided ----
@@ -1278,7 +1283,7 @@ __global__ __launch_bounds__(kSelThreads) void select_ada_kernel(Dims d, SeqTab 
   if ((known & 0x80000000u) && row_in_registers(row, m, true)) {
     RegRow r;
     load_row(row, m, r);
-    emit_from_registers(r, max(st[0], 1u), known & 0x7fffffffu, out, reinterpret_cast<RegShared *>(sel_lds)->wave_tot[3]);
+    emit_from_registers(r, m, st[0], known & 0x7fffffffu, out, reinterpret_cast<RegShared *>(sel_lds)->wave_tot[3]);
   } else if (known & 0x80000000u)
     emit_selected(row, m, split_row(row, m), st[0], known & 0x7fffffffu, out, *reinterpret_cast<SelShared *>(sel_lds));
   else select_top_row(row, m, count, out, sel_lds);

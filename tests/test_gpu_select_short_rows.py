@@ -42,6 +42,26 @@ def test_select_on_short_rows(S, m):
             assert np.array_equal(got[g], want), (c_max, g)
 
 
+@pytest.mark.parametrize("m", [3, 261, 4099, 16390])
+def test_every_bit_pattern_has_its_own_rank(S, m):
+    """NaNs rank by their bits too, down to the lowest pattern of all, which vectors outside a row share."""
+    H, n_window = 4, 1 if m % 2 == 0 else 2
+    n = m + n_window
+    rng = np.random.default_rng(m)
+    bits = rng.choice(np.array([0xffffffff, 0xfffffffe, 0xfffffffd, 0xff800000, 0x7fffffff], np.uint32), (H, n))
+    bits[1, :] = 0xffffffff
+    pooled = torch.from_numpy(bits.view(np.int32)).cuda().view(torch.float32).reshape(1, -1)
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000)).astype(np.float64)     # exact: below 2^53
+    for c_max in sorted({1, m // 3, m * 2 // 3, m - 1}):
+        p = S.SpecKVParams(n_layers=1, n_q_heads=H, n_kv_heads=H, head_dim=64, seq_lens=(n,), n_window=n_window,
+                           n_lookahead=1, pool_k=7, c_max=c_max, dtype=torch.bfloat16, sm_scale=1.0)
+        idx = torch.full((1, H * S.total_keep(p)), -1, dtype=torch.int32, device="cuda")
+        S.speckv_select(p, pooled, idx)
+        got = idx.cpu().numpy().reshape(H, -1)
+        for g in range(H):
+            assert np.array_equal(got[g], orc.keep_indices(key[g, :m], n, n_window, c_max)), (c_max, g)
+
+
 @pytest.mark.parametrize("n_in", [521, 4099, 16390, 16447, 16450, 16451])
 def test_fused_call_selects_what_its_scores_say(S, n_in):
     """The fused call hands selection the first digit's counts; its indices are those of the scores that
