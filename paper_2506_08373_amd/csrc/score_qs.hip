@@ -366,10 +366,11 @@ int qs_max_blocks(const ScoreArgs &A) {
 }  // namespace
 
 bool qs_supported(const ScoreArgs &A, int pass) {
-  // Default: only the row-statistics sweep at d = 64, where the vector pipe is the limit and this
-  // kernel's reference-exponent step (no maximum search) measures 12 % faster than the online step
-  // of the tile-streaming kernel.  Everywhere else the two dataflows end at the same matrix-pipe
-  // utilisation and the tile-streaming kernel is equal or slightly ahead.  The environment can
+  // Default: only the row-statistics sweep at d = 64, where the vector pipe is the limit.  Prompt-token
+  // selection (16 layers x 64K keys, 64 rows per head) takes 890 us with it and 905 us with the
+  // tile-streaming kernel; this kernel for the column sweep as well, 955 us.  Not ahead everywhere:
+  // prompt compression (8 layers x 32K keys, 65 rows per head) takes 370 us with it, 351 us without.
+  // At d = 128 the tile-streaming kernel is ahead for both sweeps.  The environment can
   // override the choice: SPECKV_SCORE_KERNEL=tile (never), qs (both sweeps), qs1 / qs2 (that sweep
   // only).  Read on every call so that a test can switch it.
   const char *e = std::getenv("SPECKV_SCORE_KERNEL");
