@@ -65,8 +65,9 @@ typedef enum {
   SPECKV_ERR_RUNTIME = -4      /* the HIP runtime refused a launch                          */
 } speckv_status;
 
-/* Number type of q, k and v.  Products are exact in fp32 for all three; accumulation, softmax and
- * scores are fp32 (the paper does not fix a precision). */
+/* Number type of q, k and v.  Products of bf16 and f16 numbers are exact in fp32, products of fp32 numbers
+ * are formed to 2^-34 of themselves; accumulation, softmax and scores are fp32 (the paper does not fix a
+ * precision). */
 typedef enum { SPECKV_BF16 = 0, SPECKV_F32 = 1, SPECKV_F16 = 2 } speckv_dtype;
 
 /* Reduction over the observation rows of one query head (Alg. 1 reduce step).  SUM is Eq. 1's

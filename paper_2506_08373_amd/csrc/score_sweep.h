@@ -48,16 +48,22 @@ namespace {
 constexpr int kCsumBuffers = 4;
 
 // How a sweep holds its operands.  bf16 and f16 rows are used as they are.  An fp32 row becomes three
-// bf16 rows ("planes") that add up to it exactly, v = v0 + v1 + v2 with each part the rounded
-// remainder of the ones before it (3 x 9 significant bits, |v1| <= 2^-9 |v|, |v2| <= 2^-18 |v|), and a
-// product of two rows becomes the six products of planes a, b with a + b <= 2, smallest first in the
-// fp32 accumulator.  The three that are left out are below 2^-26 of a term, a quarter of the rounding an
-// fp32 product chain adds per term.  The fp32 matrix instruction runs at 1/16 of the bf16 rate (4096
-// cycles per 32x32 block at d = 128), six bf16 products take 1536.  Measured against it: scoring, two
-// selections and the gather of 2 layers x 8209 keys, 72 rows x 4 heads per group, 355 -> 214 us; one
-// layer of 32K keys, 32 heads of 128, max, 327 -> 204 us; 4 layers x 60K keys, heads of 64, 581 -> 347 us.
-// The raw scores' error against 64-bit sums is 3 to 24 % smaller than with the fp32 instruction (fewer
-// roundings in the accumulator: rel 2.1e-7 to 9.2e-7 after 2.5e-7 to 1.05e-6, eight shapes).
+// bf16 rows ("planes") that add up to it exactly, v = v0 + v1 + v2 with each part the remainder of the ones
+// before it, rounded to bf16's 8 significant bits: |v1| <= 2^-8 |v|, |v2| <= 2^-17 |v|, and what is left after
+// three parts of a 24-bit number is zero.  A product of
+// two rows becomes eight products of planes; only v2 w2, below 2^-34 of a term, is left out.  (v1 w2 and v2 w1
+// reach 2^-25 of a term each, half the rounding of an fp32 sum: without them the error of rows with few
+// non-zero channels grew.)  The seven lower products are summed in an accumulator of their own and added to the
+// sum of the leading ones v0 w0 with one fp32 addition: the matrix instruction truncates what it adds
+// beside a much larger number, up to a quarter of a last place, as often as there are chunks.
+// Error of a logit against 64-bit sums, in 2^-24 of its size, rms / largest, fp32 instruction -> here (4096 keys x
+// 32 rows with the given number of non-zero channels at d = 128): 1 channel 0.49 / 1.05 -> 0.49 / 1.05, 2 channels
+// 0.50 / 1.5 -> 0.45 / 1.1, 4 channels 0.61 / 1.9 -> 0.47 / 1.0, 128 channels of one sign 3.0 / 13 -> 0.46 / 0.9,
+// of both signs 2.7 / 11 -> 1.1 / 4.6.  One channel with six products: 0.66 / 2.1.
+// The fp32 matrix instruction runs at 1/16 of the bf16 rate (4096 cycles per 32x32 block at d = 128), eight
+// bf16 products take 2048.  Calls measured with it -> here: 4 layers x 16K keys, 32 heads of 128, 128 rows 1092 ->
+// 845 us; 4 layers x 32K keys, 32 heads of 64, 128 rows 1279 -> 893 us; 8 layers x 16K keys, heads of 64, 32 rows
+// 348 -> 315 us.
 template <int DT, int D>
 struct Operand {
   static constexpr bool SPLIT = DT == kF32;
@@ -329,15 +335,18 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   (*reinterpret_cast<const u32x4 *>(kbuf + (buf_) * TILE_BYTES + (p_) * PLANE_BYTES + (kb_) * 32 * ROWB + foff[cs_]))
 #define SPECKV_LOAD_BFRAG(dst_, buf_, kb_) \
   _Pragma("unroll") for (int cs = 0; cs < NCS; ++cs) dst_[cs] = SPECKV_FRAG(buf_, PLANES - 1, kb_, cs);
-  // adds the products of key chunk bf (chunk cs, plane kp) and row block rb to the scores x
-  auto add_products = [&](f32x16 &x, const u32x4 &bf, int kp, int rb, int cs) {
+  // adds the product of key chunk bf (chunk cs of some plane) and plane qp of row block rb to the scores x
+  auto add_product = [&](f32x16 &x, const u32x4 &bf, int qp, int rb, int cs) {
+    x = PASS == 1 ? mma_chunk<OP::MMA_DT>(bf, qf[rb][qp * NCS + cs], x) : mma_chunk<OP::MMA_DT>(qf[rb][qp * NCS + cs], bf, x);
+  };
+  // fp32: the same for every plane of the rows that goes with key plane kp, the leading pair left out
+  auto add_lower_products = [&](f32x16 &x, const u32x4 &bf, int kp, int rb, int cs) {
 #pragma unroll
-    for (int qp = PLANES - 1 - kp; qp >= 0; --qp)
-      x = PASS == 1 ? mma_chunk<OP::MMA_DT>(bf, qf[rb][qp * NCS + cs], x) : mma_chunk<OP::MMA_DT>(qf[rb][qp * NCS + cs], bf, x);
+    for (int qp = kp == PLANES - 1 ? PLANES - 2 : PLANES - 1; qp >= (kp == 0 ? 1 : 0); --qp) add_product(x, bf, qp, rb, cs);
   };
   // The planes of an infinity, a NaN or a number that bf16 rounds to infinity multiply to NaN where fp32
   // products would not: a block with a score that is not finite is computed again from memory with the fp32
-  // instruction (one multiply-add per score to look for it, beside 24 or 48 MFMAs).  key0: the block's first key.
+  // instruction (one multiply-add per score to look for it, beside 32 or 64 MFMAs).  key0: the block's first key.
   auto recompute_unless_finite = [&](f32x16 &x, int rb, int key0) {
     if constexpr (SPLIT) {
       float probe = 0.f;
@@ -473,15 +482,21 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         u32x4 bf[NCS];
         if constexpr (!SPLIT) SPECKV_LOAD_BFRAG(bf, buf, kb)
         auto scores = [&](int rb) {
-          f32x16 acc = {0};
+          f32x16 acc = {0}, low = {0};
+          if constexpr (SPLIT) {
 #pragma unroll
-          for (int kp = PLANES - 1; kp >= 0; --kp) {
-            if constexpr (SPLIT) {
+            for (int kp = PLANES - 1; kp >= 0; --kp) {
 #pragma unroll
               for (int cs = 0; cs < NCS; ++cs) bf[cs] = SPECKV_FRAG(buf, kp, kb, cs);
-            }
 #pragma unroll
-            for (int cs = 0; cs < NCS; ++cs) add_products(acc, bf[cs], kp, rb, cs);
+              for (int cs = 0; cs < NCS; ++cs) add_lower_products(low, bf[cs], kp, rb, cs);
+            }
+          }
+#pragma unroll
+          for (int cs = 0; cs < NCS; ++cs) add_product(acc, bf[cs], 0, rb, cs);
+          if constexpr (SPLIT) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] += low[i];
           }
           recompute_unless_finite(acc, rb, tk0 + kb * 32);
           return acc;
@@ -642,23 +657,43 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 #pragma unroll
           for (int u = 0; u < KB * NACT; ++u) {
             const int kb = u / NACT, rb = u % NACT;
-            f32x16 &x = acc[u & 1];
-            x = (f32x16){0};
+            const int pu = (u + KB * NACT - 1) % (KB * NACT);      // the unit before (of the tile before for u = 0)
+            const int pbuf = (u == 0 ? tile + kCsumBuffers - 1 : tile) % kCsumBuffers;
+            if constexpr (SPLIT) {
+              // the open unit is finished beside the lower products, the leading ones then take its registers
+              f32x16 low = {0};
 #pragma unroll
-            for (int kp = PLANES - 1; kp >= 0; --kp) {
+              for (int kp = PLANES - 1; kp >= 0; --kp) {
+#pragma unroll
+                for (int cs = 0; cs < NCS; ++cs) {
+                  add_lower_products(low, bf[cs], kp, rb, cs);
+                  if (kp > 0) bf[cs] = SPECKV_FRAG(buf, kp - 1, kb, cs);
+                }
+              }
+              f32x16 &x = acc[1];
+              if (u > 0 || open)
+                recompute_unless_finite(x, pu % NACT, key_begin + (u == 0 ? tile - 1 : tile) * KT + pu / NACT * 32);
+              finish_unit(x, pu % NACT, pu / NACT, pbuf, anchored_c);
+              __builtin_amdgcn_sched_barrier(0);
+              x = (f32x16){0};
 #pragma unroll
               for (int cs = 0; cs < NCS; ++cs) {
-                add_products(x, bf[cs], kp, rb, cs);
-                if (kp > 0) bf[cs] = SPECKV_FRAG(buf, kp - 1, kb, cs);
-                else if (rb == NACT - 1 && kb + 1 < KB) bf[cs] = SPECKV_FRAG(buf, PLANES - 1, kb + 1, cs);
-                else if (SPLIT && rb < NACT - 1) bf[cs] = SPECKV_FRAG(buf, PLANES - 1, kb, cs);
+                add_product(x, bf[cs], 0, rb, cs);
+                if (rb < NACT - 1) bf[cs] = SPECKV_FRAG(buf, PLANES - 1, kb, cs);
+                else if (kb + 1 < KB) bf[cs] = SPECKV_FRAG(buf, PLANES - 1, kb + 1, cs);
               }
+#pragma unroll
+              for (int i = 0; i < 16; ++i) x[i] += low[i];
+            } else {
+              f32x16 &x = acc[u & 1];
+              x = (f32x16){0};
+#pragma unroll
+              for (int cs = 0; cs < NCS; ++cs) {
+                add_product(x, bf[cs], 0, rb, cs);
+                if (rb == NACT - 1 && kb + 1 < KB) bf[cs] = SPECKV_FRAG(buf, 0, kb + 1, cs);
+              }
+              finish_unit(acc[(u & 1) ^ 1], pu % NACT, pu / NACT, pbuf, anchored_c);
             }
-            const int pu = (u + KB * NACT - 1) % (KB * NACT);      // the unit before (of the tile before for u = 0)
-            if (SPLIT && (u > 0 || open))
-              recompute_unless_finite(acc[(u & 1) ^ 1], pu % NACT, key_begin + (u == 0 ? tile - 1 : tile) * KT + pu / NACT * 32);
-            finish_unit(acc[(u & 1) ^ 1], pu % NACT, pu / NACT,
-                        (u == 0 ? tile + kCsumBuffers - 1 : tile) % kCsumBuffers, anchored_c);
             // the compiler may not move work of the neighbouring units across: without this it piles up
             // fragment reads and open blocks until the registers spill
             __builtin_amdgcn_sched_barrier(0);

@@ -54,9 +54,10 @@ def draw(seed, n, rows, hq, hkv, d):
 @pytest.mark.parametrize("reduce", ["sum", "max"])
 def test_every_product_of_the_parts_counts(S, d, group, rows, n, reduce):
     """One channel per query row is not zero, so a logit is one product of two 24-bit numbers of size up to
-    40.  Allowed: the products left out (2^-26 of it), one rounding for each of the five sums (2^-24),
-    and the same again in the multiply-add of the softmax: below 40 * 8 * 2^-24 = 2e-5, in the numerator
-    and in the normaliser, and 1e-6 for sums and exp2.  A missing product shows as 40 * 2^-17 = 3e-4."""
+    40.  Allowed: the product left out (2^-34 of it), one rounding for each of the sums (2^-24 for the last
+    one, together less than that for the lower ones), and the same again in the multiply-add of the
+    softmax: below 40 * 8 * 2^-24 = 2e-5, in the numerator and in the normaliser, and 1e-6 for sums and
+    exp2.  A missing product of the larger parts shows as 40 * 2^-17 = 3e-4."""
     q, k, gen = draw(5, n, rows, group * 2, 2, d)
     keep = torch.randint(0, d, (1, 1, rows, group * 2, 1), generator=gen, device="cuda")
     q = torch.where(torch.arange(d, device="cuda") == keep, 3 + q.abs() / 2, torch.zeros_like(q))
@@ -97,3 +98,50 @@ def test_nan_stays_with_its_head(S):
     assert torch.isnan(got[1]).any() and torch.isfinite(got[0]).all()
     want = exact_scores(q, k, 16, 128 ** -0.5)
     assert ((got[0].double() - want[0]).abs() <= 1e-4 * want[0]).all()
+
+
+def logit_spread(S, q, k, sm_scale):
+    """q [H, d], k [n, H, d], one row per head: by how much the logits that the raw scores stand for differ from
+    64-bit ones, largest minus smallest per head (which cancels the normaliser), in 2^-24 of the head's largest."""
+    n, H, d = k.shape
+    p = S.SpecKVParams.for_tensors(q.view(1, 1, 1, H, d), k.view(1, n, H, d), seq_lens=[n], n_window=0, pool_k=1, c_max=16,
+                                   sm_scale=sm_scale)
+    ws = torch.empty(S.workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    out = torch.empty(2, 1, H * n, dtype=torch.float32, device="cuda")
+    S.speckv_score(p, q.view(1, 1, 1, H, d), k.view(1, n, H, d), out[0], out[1], ws)
+    to_log2 = float(torch.tensor(sm_scale, dtype=torch.float32) * torch.tensor(math.log2(math.e), dtype=torch.float32))
+    want = (q.double() * k.double()).sum(-1).t() * to_log2
+    err = out[1].view(H, n).double().log2() - want
+    return float(((err.amax(1) - err.amin(1)) / (want.abs().amax(1) * 2.0 ** -24)).max())
+
+
+def narrow(seed, n, H, d, channels):
+    """Rows with `channels` non-zero channels in [1, 1.5) and keys in [1, 1.02): with sm_scale 72 / channels the
+    logits are near 130 binary orders and differ by three at most, so a row's scores are all ordinary numbers."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    q = torch.zeros(H, d, device="cuda")
+    q.scatter_(1, torch.rand(H, d, generator=gen, device="cuda").argsort(1)[:, :channels],
+               1 + torch.rand(H, channels, generator=gen, device="cuda") / 2)
+    q[0] = torch.where(q[0] != 0, 1 + 2.0 ** -8 - 2.0 ** -17, 0.0)       # both smaller parts as large as they can be
+    k = 1 + torch.rand(n, H, d, generator=gen, device="cuda") * 0.02
+    k[:64, 0] = 1 + 2.0 ** -8 - 2.0 ** -17
+    return q, k
+
+
+# In 2^-24 of a logit's size, either way: the leading products and their sums are exact here, the addition of the
+# lower ones rounds once (1); the lower sum is below 2^-7 of the whole and rounded at that size by at most five
+# matrix instructions per non-zero channel or group of 16 channels (0.04 each channel); the softmax's multiply-add
+# ends near -11 (half a last place is 2^-21, 0.07 of the unit at 112 binary orders and more) and exp2 is
+# good to one (0.03).
+@pytest.mark.parametrize("channels,allowed", [(1, 2.3), (2, 2.4), (4, 2.6), (16, 2.9)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_with_few_channels_are_rounded_as_fp32_products(S, d, channels, allowed):
+    q, k = narrow(11, 1024, 16, d, channels)
+    assert logit_spread(S, q, k, 72.0 / channels) <= allowed
+
+
+def test_small_products_keep_their_last_bits(S):
+    """Logits of 2^-120 before sm_scale: their lower products lie below the smallest normal number."""
+    q, k = narrow(13, 512, 8, 128, 1)
+    assert logit_spread(S, q * 2.0 ** -60, k * 2.0 ** -60, 72.0 * 2.0 ** 120) <= 2.4
