@@ -50,7 +50,7 @@ constexpr int kCsumBuffers = 4;
 // How a sweep holds its operands.  bf16 and f16 rows are used as they are.  An fp32 row becomes three
 // bf16 rows ("planes") that add up to it exactly, v = v0 + v1 + v2 with each part the remainder of the ones
 // before it, rounded to bf16's 8 significant bits: |v1| <= 2^-8 |v|, |v2| <= 2^-17 |v|, and what is left after
-// three parts of a 24-bit number is zero.  A product of
+// three parts of a 24-bit number is zero (numbers near the ends of the range: see split_chunk).  A product of
 // two rows becomes eight products of planes; only v2 w2, below 2^-34 of a term, is left out.  (v1 w2 and v2 w1
 // reach 2^-25 of a term each, half the rounding of an fp32 sum: without them the error of rows with few
 // non-zero channels grew.)  The seven lower products are summed in an accumulator of their own and added to the
@@ -80,12 +80,19 @@ constexpr size_t score_lds_bytes() {
   return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float);
 }
 
-// Eight fp32 values (two 16-byte chunks) as one 16-byte chunk per bf16 plane.
+// Bits of 2^-103.  The last bit of a smaller number lies below 2^-126, where a plane's numbers end.
+constexpr unsigned kSplitMin = (127u - 103u) << 23;
+
+// Eight fp32 values (two 16-byte chunks) as one 16-byte chunk per bf16 plane.  A number that three planes do
+// not hold (between 0 and 2^-103 in size; infinite, NaN or nearer to 2^128 than to the largest bf16 number)
+// gets a plane that makes every product with it NaN: see recompute_unless_finite.
 __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float r0 = __uint_as_float(j < 2 ? lo[2 * j] : hi[2 * j - 4]);
     float r1 = __uint_as_float(j < 2 ? lo[2 * j + 1] : hi[2 * j - 3]);
+    // zero is exact (2 * bits - 1 wraps around), a smaller number than kSplitMin is not
+    const bool tiny0 = 2 * __float_as_uint(r0) - 1 < 2 * kSplitMin - 1, tiny1 = 2 * __float_as_uint(r1) - 1 < 2 * kSplitMin - 1;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const bf16x2 b = {(__bf16)r0, (__bf16)r1};               // round to nearest even, v_cvt_pk_bf16_f32
@@ -94,6 +101,7 @@ __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3
       r0 -= __uint_as_float(u << 16);
       r1 -= __uint_as_float(u & 0xffff0000u);
     }
+    plane[0][j] |= (tiny0 ? 0x7fffu : 0u) | (tiny1 ? 0x7fff0000u : 0u);       // a NaN
   }
 }
 
@@ -344,8 +352,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 #pragma unroll
     for (int qp = kp == PLANES - 1 ? PLANES - 2 : PLANES - 1; qp >= (kp == 0 ? 1 : 0); --qp) add_product(x, bf, qp, rb, cs);
   };
-  // The planes of an infinity, a NaN or a number that bf16 rounds to infinity multiply to NaN where fp32
-  // products would not: a block with a score that is not finite is computed again from memory with the fp32
+  // Numbers that three planes do not hold (see split_chunk) and overflowing sums leave NaN or infinity where
+  // fp32 products might not: a block with a score that is not finite is computed again from memory with the fp32
   // instruction (one multiply-add per score to look for it, beside 32 or 64 MFMAs).  key0: the block's first key.
   auto recompute_unless_finite = [&](f32x16 &x, int rb, int key0) {
     if constexpr (SPLIT) {

@@ -141,6 +141,19 @@ def test_rows_with_few_channels_are_rounded_as_fp32_products(S, d, channels, all
     assert logit_spread(S, q, k, 72.0 / channels) <= allowed
 
 
+@pytest.mark.parametrize("e", [-96, -102, -104, -110, -117, -125])
+def test_small_operands_keep_their_last_bits(S, e):
+    """2^e times the same values on one side, 2^-e on the other: below 2^-103 three bf16 parts no longer hold them."""
+    q, k = narrow(12, 512, 8, 128, 1)
+    assert logit_spread(S, q * 2.0 ** e, k * 2.0 ** -e, 72.0) <= 2.4
+    assert logit_spread(S, q * 2.0 ** -e, k * 2.0 ** e, 72.0) <= 2.4
+    empty = torch.where(q == 0, 1.0, 0.0).argmax(1)                        # a channel that its row does not use
+    q.scatter_(1, empty[:, None], 1.0)
+    k.scatter_(2, empty.expand(512, 8)[..., None], 0.0)
+    k[::97] = torch.where(k[::97] == 0, 2.0 ** e, k[::97])                 # some blocks hold such a number
+    assert logit_spread(S, q, k, 72.0) <= 2.4
+
+
 def test_small_products_keep_their_last_bits(S):
     """Logits of 2^-120 before sm_scale: their lower products lie below the smallest normal number."""
     q, k = narrow(13, 512, 8, 128, 1)
