@@ -443,7 +443,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   // Usually the sums are still small and nothing but this comparison happens (2.5 % on the sweep
   // against moving the exponent after every segment).
   const float grown = __builtin_ldexpf(1.f, kAnchorGrowth - anchor_shift);
-  auto end_segment = [&](int segment) {
+  // new_reference(rb, r): a reference for a row that has none yet (every score it has seen is -infinity, so that
+  // r is below everything and the first segment with a finite score overflows); without it every segment
+  // of the chunk would overflow.
+  auto end_segment = [&](int segment, auto new_reference) {
     bool look = false;
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb) look |= !(lrun[rb] < grown);
@@ -455,7 +458,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       // (A full list: every later segment is left to the repair as well, overflowed or not.)
       if (__builtin_amdgcn_ballot_w64(out_of_range) != 0 || n_failed > kFailListed) {
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) lrun[rb] = l_before[rb];
+        for (int rb = 0; rb < MB; ++rb) {
+          lrun[rb] = l_before[rb];
+          if (!(l_before[rb] > 0.f)) mrun[rb] = new_reference(rb, mrun[rb]);
+        }
 #pragma unroll
         for (int i = 0; i <= kFailListed; ++i)
           if (i == n_failed) listed[i] = segment;
@@ -705,7 +711,18 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
             // the compiler may not move work of the neighbouring units across: without this it piles up
             // fragment reads and open blocks until the registers spill
             __builtin_amdgcn_sched_barrier(0);
-            if (kAnchored && anchored && u == 0 && buf == 1 && tile > 1) end_segment((tile - 3) / kAnchorTiles);
+            if (kAnchored && anchored && u == 0 && buf == 1 && tile > 1) {
+              // scores at hand for a new reference: this unit's and those of the unit before it, the other row block's
+              // where there are two (fp32: only this unit's, for the first row block)
+              end_segment((tile - 3) / kAnchorTiles, [&](int rb_, float r) {
+                if (SPLIT && rb_ != 0) return r;
+                const f32x16 &s_ = acc[SPLIT || rb_ != 0 ? 1 : 0];
+                float top = s_[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) top = fmaxf(top, s_[i]);
+                return fmaxf(top * c2, kNegBig) + (float)anchor_shift;
+              });
+            }
           }
         }
         open = true;
@@ -752,7 +769,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           }
           run_tiles(1, ntiles, buf1{}, std::true_type{});
           drain(ntiles - 1, std::true_type{});
-          if (ntiles > 1) end_segment((ntiles - 2) / kAnchorTiles);
+          if (ntiles > 1) end_segment((ntiles - 2) / kAnchorTiles, [](int, float r) { return r; });
         }
       } else if (ntiles > 0) {
         run_tiles(0, ntiles, buf0{}, std::false_type{});

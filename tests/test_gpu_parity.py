@@ -1416,3 +1416,47 @@ def test_sweep_of_few_tiles(S, monkeypatch, mode, dtype, head_dim, group):
                                      pool_k=7, c_max=60, dtype=dtype, sm_scale=head_dim ** -0.5, n_planted=2,
                                      channel_scale=(0.5, 4.0), seed=70 + tiles)
         check_full_path(S, w, reduce="sum" if tiles % 2 else "max")
+
+
+@pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 128, 3), ("f16", 128, 1), ("bf16", 64, 8),
+                                                  ("bf16", 64, 3), ("f32", 128, 3), ("f32", 64, 3)])
+@pytest.mark.parametrize("hidden_tiles", [1, 3])
+def test_rows_that_start_with_minus_infinity_are_repaired_once(S, monkeypatch, dtype, head_dim, group, hidden_tiles):
+    """Scores of -infinity over the first tiles of every chunk leave the rows without a reference exponent; the
+    first segment with a finite score overflows and is left to the repair launch, the ones behind it are not."""
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", "fixed")
+    monkeypatch.setenv("SPECKV_SCORE_KERNEL", "tile")
+    L, H, n, n_window, rows = 8, 8, 8400, 32, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(90)
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
+    q = torch.randn(L, 1, rows, H * group, head_dim, generator=gen, device="cuda")
+    k = torch.randn(L, n, H, head_dim, generator=gen, device="cuda")
+    q[..., 5] = q[..., 5].abs() + 1
+    q, k = q.to(dt), k.to(dt)
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=n_window, pool_k=7, c_max=100, sm_scale=head_dim ** -0.5)
+    info = S.plan_info(p)
+    assert info["fixed_reference_rows"] == 1 and info["q_stationary"] == 0
+    tile = 64 if (dtype, head_dim) == ("f32", 128) else 128
+    assert info["chunk_keys"] >= 12 * tile
+    for c in range(info["n_chunks"]):
+        k[:, c * info["chunk_keys"]:c * info["chunk_keys"] + (hidden_tiles - 1) * tile + (tile if hidden_tiles == 1 else 10), :, 5] = -math.inf
+    ws = alloc_ws(S, p)
+    out = torch.empty((2, L, H * n), dtype=torch.float32, device="cuda")
+    S.speckv_score(p, q, k, out[0], out[1], ws)
+    for layer in (0, L - 1):
+        for h in (0, H - 1):
+            last = torch.cat([n - n_window + torch.arange(n_window), torch.full((rows - n_window,), n - 1)]).cuda()
+            hidden = torch.arange(n, device="cuda")[None, :] > last[:, None]
+            want = torch.zeros(n, dtype=torch.float64, device="cuda")
+            for x in range(group):
+                logits = (q[layer, 0, :, h * group + x].double() @ k[layer, :, h].double().t()) * head_dim ** -0.5
+                want += torch.softmax(logits.masked_fill(hidden, -math.inf), dim=1).sum(0)
+            got = out[1, layer].view(H, n)[h].double()
+            assert ((got - want).abs() <= 1e-4 * want).all(), (layer, h, float(((got - want).abs() / want.clamp(min=1e-300)).max()))
+    # the wavefronts' lists of segments behind the partial pairs: [workgroup][wave][8], word 0 the number noted
+    units = L * H * info["row_super_blocks"]
+    pairs = units * (info["n_chunks"] + 1) * info["waves"] * info["blocks_per_wave"] * 32
+    groups = (info["n_chunks"] * L * H + 7) // 8 * 8 * info["row_super_blocks"]
+    noted = ws.view(torch.int32)[2 * pairs:2 * pairs + groups * info["waves"] * 8].view(groups, info["waves"], 8)[..., 0]
+    assert int(noted.max()) == 1
