@@ -85,14 +85,15 @@ constexpr unsigned kSplitMin = (127u - 103u) << 23;
 
 // Eight fp32 values (two 16-byte chunks) as one 16-byte chunk per bf16 plane.  A number that three planes do
 // not hold (between 0 and 2^-103 in size; infinite, NaN or nearer to 2^128 than to the largest bf16 number)
-// gets a plane that makes every product with it NaN: see recompute_unless_finite.
+// makes its chunk's leading plane, and with it every score of its row, NaN: see recompute_unless_finite.  (Two
+// vector instructions a number; with them the calls take 0 to 3 % longer.)
 __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3]) {
+  unsigned least = ~0u;               // of 2 * bits - 1, which is largest for zero
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float r0 = __uint_as_float(j < 2 ? lo[2 * j] : hi[2 * j - 4]);
     float r1 = __uint_as_float(j < 2 ? lo[2 * j + 1] : hi[2 * j - 3]);
-    // zero is exact (2 * bits - 1 wraps around), a smaller number than kSplitMin is not
-    const bool tiny0 = 2 * __float_as_uint(r0) - 1 < 2 * kSplitMin - 1, tiny1 = 2 * __float_as_uint(r1) - 1 < 2 * kSplitMin - 1;
+    least = min(least, min(2 * __float_as_uint(r0) - 1, 2 * __float_as_uint(r1) - 1));
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const bf16x2 b = {(__bf16)r0, (__bf16)r1};               // round to nearest even, v_cvt_pk_bf16_f32
@@ -101,8 +102,8 @@ __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3
       r0 -= __uint_as_float(u << 16);
       r1 -= __uint_as_float(u & 0xffff0000u);
     }
-    plane[0][j] |= (tiny0 ? 0x7fffu : 0u) | (tiny1 ? 0x7fff0000u : 0u);       // a NaN
   }
+  plane[0][0] |= least < 2 * kSplitMin - 1 ? 0x7fffu : 0u;
 }
 
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
