@@ -74,10 +74,20 @@ struct Operand {
   static constexpr int PLANE_BYTES = KT * TL::ROWB, TILE_BYTES = PLANES * PLANE_BYTES;
 };
 
+// fp32 with two row blocks per wave (d = 64): three planes of query fragments for both blocks leave no
+// registers for the blocks' row normalisers in the column sweep (with them 10 spilled inside the loop, 28 before
+// recompute_unless_finite made its addresses on the spot), so each wave keeps them in LDS and reads the 16 of
+// a block beside its products.  4 layers x 32K keys, 4 heads x 128 rows per group: 892 -> 874 us; 2 layers, 8
+// heads: 162 -> 154 us.  One row block per wave and two super-blocks measure 896 and 151 us, with twice the planes
+// in the workspace.
+template <int DT, int MB>
+constexpr bool normalisers_in_lds() { return DT == kF32 && MB == 2; }
+
 template <int DT, int D, int MB, int NW>
 constexpr size_t score_lds_bytes() {
   using OP = Operand<DT, D>;
-  return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float);
+  return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float) +
+         (normalisers_in_lds<DT, MB>() ? NW * MB * 32 * sizeof(float) : 0);
 }
 
 // Bits of 2^-103.  The last bit of a smaller number lies below 2^-126, where a plane's numbers end.
@@ -269,16 +279,16 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 
   // ---- Q fragments of this wave's row blocks, resident for the whole sweep
   u32x4 qf[MB][PLANES * NCS];
-  // the lane's share (half) of its query row in row block rb
-  auto query_row = [&](int rb, bool valid) {
-    const int hh = blk_head[rb], i = blk_i0[rb] + l32;
+  // the lane's share (half) of query row r32 of row block rb
+  auto query_row = [&](int rb, int r32, bool valid) {
+    const int hh = blk_head[rb], i = blk_i0[rb] + r32;
     return A.q + ((int64_t)layer * d.q_sl + (int64_t)s * d.q_ss + (int64_t)(valid ? i : 0) * d.q_sr +
                   (int64_t)(g * d.G + (valid ? hh : 0)) * d.q_sh) * ELT + half * (D / 2) * ELT;
   };
 #pragma unroll
   for (int rb = 0; rb < MB; ++rb) {
     const bool valid = SPECKV_ROW_VALID(rb, l32);
-    const char *qp = query_row(rb, valid);
+    const char *qp = query_row(rb, l32, valid);
 #pragma unroll
     for (int cs = 0; cs < NCS; ++cs) {
       if constexpr (SPLIT) {
@@ -295,25 +305,39 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 
   // ---- per-pass row state
   float mrun[MB], lrun[MB];          // pass 1: lane = one query row per row block
-  float nlse[MB][16];                // pass 2: lane = 16 rows per row block
+  constexpr bool LSE_LDS = PASS == 2 && normalisers_in_lds<DT, MB>();
+  float nlse[LSE_LDS ? 1 : MB][16];  // pass 2: lane = 16 rows per row block
+  float *lds_lse = csum + (size_t)kCsumBuffers * NW * MB * KT + wv * MB * 32;      // ... or in LDS, this wave's blocks
   if (PASS == 1) {
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb) { mrun[rb] = kNegBig; lrun[rb] = 0.f; }
   } else {
     const float *lp = A.lse + (((int64_t)layer * d.Hkv + g) * d.S + s) * ((int64_t)A.g.RS * RSB);
+    auto row_lse = [&](int rb, int r32) {
+      const bool valid = SPECKV_ROW_VALID(rb, r32);
+      const int io = blk_i0[rb] + r32;
+      float v = -lp[rs * RSB + block_of(rb) * 32 + r32];  // the lse buffer covers the padded rows
+      if (d.weight_rows && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
+      return valid ? v : -INFINITY;                       // padded rows contribute 2^-inf = 0
+    };
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb)
+    for (int rb = 0; rb < MB; ++rb) {
+      if constexpr (LSE_LDS) {
+        if (half == 0) lds_lse[rb * 32 + l32] = row_lse(rb, l32);
+      } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int r32 = 8 * (i >> 2) + 4 * half + (i & 3);
-        const int lr = block_of(rb) * 32 + r32;
-        const bool valid = SPECKV_ROW_VALID(rb, r32);
-        const int io = blk_i0[rb] + r32;
-        float v = -lp[rs * RSB + lr];                       // the lse buffer covers the padded rows
-        if (d.weight_rows && io < d.w) v += log2f((float)(io + 1) / (float)d.w);   // row weight folded in
-        nlse[rb][i] = valid ? v : -INFINITY;                // padded rows contribute 2^-inf = 0
+        for (int i = 0; i < 16; ++i) nlse[rb][i] = row_lse(rb, 8 * (i >> 2) + 4 * half + (i & 3));
       }
+    }
   }
+  // the negated normalisers of the lane's 16 rows in row block rb
+  auto load_lse = [&](int rb, float (&nl)[16]) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if constexpr (LSE_LDS) nl[i] = lds_lse[rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+      else nl[i] = nlse[rb][i];
+    }
+  };
 
   // ---- masked sweep: last key each row may see (window row i sees keys <= m + i, a lookahead
   // row the whole prompt), computed once instead of per score
@@ -362,9 +386,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 #pragma unroll
       for (int i = 0; i < 16; ++i) probe = fmaf(x[i], 0.f, probe);       // NaN if any score is infinite or NaN
       if (__builtin_amdgcn_ballot_w64(!(probe == 0.f)) != 0) {
-        const bool valid = SPECKV_ROW_VALID(rb, l32);
-        const char *qp = query_row(rb, valid);
-        const char *kp = kbase + (int64_t)min(key0 + l32, n_s - 1) * tokb + half * (D / 2) * ELT;
+        int r32 = l32;
+        asm volatile("" : "+v"(r32));  // the addresses are made here, not kept in registers through the sweep
+        const bool valid = SPECKV_ROW_VALID(rb, r32);
+        const char *qp = query_row(rb, r32, valid);
+        const char *kp = kbase + (int64_t)min(key0 + r32, n_s - 1) * tokb + half * (D / 2) * ELT;
         x = (f32x16){0};
 #pragma unroll 1
         for (int cs = 0; cs < D / 8; ++cs) {
@@ -548,9 +574,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
             if (rb >= nact) continue;
             f32x16 acc = scores(rb);
             // lane: key tk0 + kb*32 + l32; rows (wv*MB+rb)*32 + 8*(i/4) + 4*half + i%4
-            float p[16];
+            float p[16], nl[16];
+            load_lse(rb, nl);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(acc[i], c2, nlse[rb][i]));
+            for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(acc[i], c2, nl[i]));
 #pragma unroll
             for (int i = 0; i < 16; ++i)
               if (key > last2[rb][i]) p[i] = 0.f;
@@ -602,6 +629,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;    // nothing open: probabilities of 2^-inf = 0
       bool open = false;               // a unit waits in acc[1] (fp32: only then are its scores looked at)
+      float top_before = 0.f;          // pass 1, fp32: largest score of the unit before a segment's last look
       float colsum = 0.f;              // pass 2: the lane's key, over the row blocks of the current key block
 
       // turns the scores x of row block rb into probabilities; pass 2: of key block kb, into partial buffer cbuf
@@ -630,9 +658,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           asm volatile("" : "+v"(lrun[rb]), "+v"(mrun[rb]));
         } else {
           if (rb == 0 || (RED == 1 && !paired)) colsum = 0.f;
-          float p[16];
+          float p[16], nl[16];
+          load_lse(rb, nl);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nlse[rb][i]));
+          for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nl[i]));
           if (RED == 0) {
             colsum += (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
                       (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15])));
@@ -689,6 +718,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
               if (u > 0 || open)
                 recompute_unless_finite(x, pu % NACT, key_begin + (u == 0 ? tile - 1 : tile) * KT + pu / NACT * 32);
               finish_unit(x, pu % NACT, pu / NACT, pbuf, anchored_c);
+              if (kAnchored && NACT == 2 && u == 0) {              // see end_segment below
+                top_before = x[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) top_before = fmaxf(top_before, x[i]);
+              }
               __builtin_amdgcn_sched_barrier(0);
               x = (f32x16){0};
 #pragma unroll
@@ -714,13 +748,15 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
             __builtin_amdgcn_sched_barrier(0);
             if (kAnchored && anchored && u == 0 && buf == 1 && tile > 1) {
               // scores at hand for a new reference: this unit's and those of the unit before it, the other row block's
-              // where there are two (fp32: only this unit's, for the first row block)
-              end_segment((tile - 3) / kAnchorTiles, [&](int rb_, float r) {
-                if (SPLIT && rb_ != 0) return r;
-                const f32x16 &s_ = acc[SPLIT || rb_ != 0 ? 1 : 0];
-                float top = s_[0];
+              // where there are two (fp32: this unit has its registers by now, their maximum is kept)
+              end_segment((tile - 3) / kAnchorTiles, [&](int rb_, float) {
+                float top = top_before;
+                if (!SPLIT || rb_ == 0) {
+                  const f32x16 &s_ = acc[SPLIT || rb_ != 0 ? 1 : 0];
+                  top = s_[0];
 #pragma unroll
-                for (int i = 1; i < 16; ++i) top = fmaxf(top, s_[i]);
+                  for (int i = 1; i < 16; ++i) top = fmaxf(top, s_[i]);
+                }
                 return fmaxf(top * c2, kNegBig) + (float)anchor_shift;
               });
             }

@@ -1419,7 +1419,7 @@ def test_sweep_of_few_tiles(S, monkeypatch, mode, dtype, head_dim, group):
 
 
 @pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 128, 3), ("f16", 128, 1), ("bf16", 64, 8),
-                                                  ("bf16", 64, 3), ("f32", 128, 3), ("f32", 64, 3)])
+                                                  ("bf16", 64, 3), ("f32", 128, 3), ("f32", 64, 3), ("f32", 64, 8)])
 @pytest.mark.parametrize("hidden_tiles", [1, 3])
 def test_rows_that_start_with_minus_infinity_are_repaired_once(S, monkeypatch, dtype, head_dim, group, hidden_tiles):
     """Scores of -infinity over the first tiles of every chunk leave the rows without a reference exponent; the
