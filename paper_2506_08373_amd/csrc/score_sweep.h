@@ -603,7 +603,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     }
     if (PASS == 2 && ntiles > 0) SPECKV_FLUSH_TILE(ntiles - 1)
   } else {
-    // The unmasked sweep is software-pipelined in every wave.  A unit is one 32-key x 32-row block: while
+    // The unmasked sweep is software-pipelined in every wave (but see PIPELINED).  A unit is one 32-key x 32-row block: while
     // its chain of MFMAs runs (a chain on one accumulator issues at the full rate), the wave turns the
     // block of the unit before it into probabilities, so that each wave by itself keeps both pipes
     // busy.  (Without this the two waves of a SIMD, released together by the tile barrier, do
@@ -623,6 +623,12 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     // code per number, so that the open block and the row state never move between registers
     // (1.7 % on the row statistics).
     constexpr int KB = KT / 32;
+    // The column sweep of 8 waves x 1 row block at d = 128 is better off without: pipelined it needs 177 registers,
+    // so one workgroup has the CU; a unit's block finished right behind its MFMAs leaves 123 and two workgroups
+    // (80 KiB of LDS each), whose four waves a SIMD overlap by themselves.  32 layers x 16K keys, 4 heads x 64
+    // rows 729 -> 709 us, 28 layers x 60K, 7 x 32 rows 1087 -> 1051 us, 5 x 32 rows 1162 -> 1114 us (before any
+    // pipelining 727, 1085, 1140 us).
+    constexpr bool PIPELINED = !(PASS == 2 && MB == 1 && NW == 8 && D == 128 && !SPLIT);
     auto sweep = [&](auto nact_c) {
       constexpr int NACT = decltype(nact_c)::value;
       f32x16 acc[2];                   // blocks of the units: the open one in one, the next one in the other
@@ -733,6 +739,15 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
               }
 #pragma unroll
               for (int i = 0; i < 16; ++i) x[i] += low[i];
+            } else if constexpr (!PIPELINED) {
+              f32x16 &x = acc[1];
+              x = (f32x16){0};
+#pragma unroll
+              for (int cs = 0; cs < NCS; ++cs) {
+                add_product(x, bf[cs], 0, rb, cs);
+                if (rb == NACT - 1 && kb + 1 < KB) bf[cs] = SPECKV_FRAG(buf, 0, kb + 1, cs);
+              }
+              finish_unit(x, rb, kb, tile % kCsumBuffers, anchored_c);
             } else {
               f32x16 &x = acc[u & 1];
               x = (f32x16){0};
@@ -780,7 +795,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       };
       // the open unit (the last one of a tile: it always sits in acc[1])
       auto drain = [&](int last_tile, auto anchored_c) {
-        if constexpr (NACT > 0) {
+        if constexpr (NACT > 0 && PIPELINED) {
           if (SPLIT && open) recompute_unless_finite(acc[1], NACT - 1, key_begin + last_tile * KT + (KB - 1) * 32);
           finish_unit(acc[1], NACT - 1, KB - 1, last_tile % kCsumBuffers, anchored_c);
         }

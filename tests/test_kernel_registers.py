@@ -25,21 +25,35 @@ def code_objects(blob):
             at += 24 + id_len
 
 
-def test_scoring_sweeps_do_not_spill(tmp_path):
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{symbol: (vector registers, spilled ones)} of the scoring kernels in the built library."""
     if not (os.path.exists(READELF) and os.path.exists(library_path())):
         pytest.skip("needs the built library and llvm-readelf")
-    seen, spilled = 0, []
     with open(library_path(), "rb") as f:
         blob = f.read()
+    found = {}
     for i, elf in enumerate(code_objects(blob)):
-        path = tmp_path / ("%d.elf" % i)
+        path = tmp_path_factory.mktemp("elf") / ("%d.elf" % i)
         path.write_bytes(elf)
         notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
         for kernel in re.split(r"\n\s*- \.agpr_count:", notes)[1:]:
             symbol = re.search(r"\.symbol:\s*(\S+)", kernel).group(1)
-            if "score_kernel" not in symbol and "score_qs_kernel" not in symbol:
-                continue
-            seen += 1
-            if int(re.search(r"\.vgpr_spill_count:\s*(\d+)", kernel).group(1)):
-                spilled.append(symbol)
-    assert seen > 100 and not spilled, spilled
+            if "score_kernel" in symbol or "score_qs_kernel" in symbol:
+                found[symbol] = tuple(int(re.search(r"\." + key + r":\s*(\d+)", kernel).group(1))
+                                      for key in ("vgpr_count", "vgpr_spill_count"))
+    assert len(found) > 100
+    return found
+
+
+def test_scoring_sweeps_do_not_spill(kernels):
+    assert not [symbol for symbol, (_, spilled) in kernels.items() if spilled]
+
+
+@pytest.mark.parametrize("dtype", [0, 2])
+@pytest.mark.parametrize("reduce_max", [0, 1])
+def test_two_workgroups_of_the_eight_block_column_sweep_share_a_cu(kernels, dtype, reduce_max):
+    """16-bit rows, d = 128, 8 waves x 1 row block: four waves per SIMD have 128 registers each."""
+    name = "score_kernel_colsILi%dELi128ELi1ELi8ELi2ELi%dELb0EE" % (dtype, reduce_max)
+    counts = [n for symbol, (n, _) in kernels.items() if name in symbol]
+    assert len(counts) == 1 and counts[0] <= 128
