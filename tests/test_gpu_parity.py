@@ -1404,18 +1404,66 @@ def test_more_than_65535_layer_head_units(S):
 
 
 @pytest.mark.parametrize("mode", ["fixed", "online"])
-@pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 128, 3), ("f16", 64, 5), ("f32", 128, 3)])
+@pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 128, 3), ("f16", 64, 5), ("bf16", 64, 3),
+                                                  ("f32", 128, 3), ("f32", 64, 5)])
 def test_sweep_of_few_tiles(S, monkeypatch, mode, dtype, head_dim, group):
     """The software-pipelined sweeps on chunks of one to six key tiles (an open block carried from tile
     to tile, segments that start at the second one), with waves of two, one and no row blocks."""
     monkeypatch.setenv("SPECKV_ROW_STATISTICS", mode)
+    monkeypatch.setenv("SPECKV_SCORE_KERNEL", "tile")           # d = 64: not the Q-stationary row statistics
     tile = {("f32", 128): 64, ("f16", 64): 256}.get((dtype, head_dim), 128)
     for tiles in (1, 2, 3, 4, 6):
         w = workloads.SpecKVWorkload(name="few_tiles", n_layers=1, n_q_heads=2 * group, n_kv_heads=2, head_dim=head_dim,
                                      seq_lens=(tile * tiles + 40, tile * (tiles + 1) + 33), n_window=32, n_lookahead=32,
                                      pool_k=7, c_max=60, dtype=dtype, sm_scale=head_dim ** -0.5, n_planted=2,
                                      channel_scale=(0.5, 4.0), seed=70 + tiles)
+        info = S.plan_info(make_params(S, w))
+        assert info["q_stationary"] == 0 and info["n_chunks"] > 0 and info["fixed_reference_rows"] == (mode == "fixed")
         check_full_path(S, w, reduce="sum" if tiles % 2 else "max")
+
+
+def fixed_reference_case(S, monkeypatch, dtype, head_dim, group, seed):
+    """8 layers x 8 KV heads x 8400 keys, 64 rows per head, tile-streaming row statistics with fixed references."""
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", "fixed")
+    monkeypatch.setenv("SPECKV_SCORE_KERNEL", "tile")
+    L, H, n, rows = 8, 8, 8400, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
+    q = torch.randn(L, 1, rows, H * group, head_dim, generator=gen, device="cuda")
+    k = torch.randn(L, n, H, head_dim, generator=gen, device="cuda")
+    q[..., 5] = q[..., 5].abs() + 1
+    q, k = q.to(dt), k.to(dt)
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=32, pool_k=7, c_max=100, sm_scale=head_dim ** -0.5)
+    info = S.plan_info(p)
+    assert info["fixed_reference_rows"] == 1 and info["q_stationary"] == 0
+    tile = 64 if (dtype, head_dim) == ("f32", 128) else 128
+    assert info["chunk_keys"] >= 12 * tile
+    return p, q, k, info, tile
+
+
+def check_raw_scores_and_count_noted(S, p, q, k, info, rel, floor):
+    """Raw scores of a few heads against 64-bit ones (within rel * score + floor * largest); returns how many
+    segments each wavefront left to the repair launch."""
+    L, n, H, d = k.shape
+    rows, group, n_window = q.shape[2], q.shape[3] // H, 32
+    ws = alloc_ws(S, p)
+    out = torch.empty((2, L, H * n), dtype=torch.float32, device="cuda")
+    S.speckv_score(p, q, k, out[0], out[1], ws)
+    last = torch.cat([n - n_window + torch.arange(n_window), torch.full((rows - n_window,), n - 1)]).cuda()
+    hidden = torch.arange(n, device="cuda")[None, :] > last[:, None]
+    for layer in (0, L - 1):
+        for h in (0, H - 1):
+            want = torch.zeros(n, dtype=torch.float64, device="cuda")
+            for x in range(group):
+                logits = (q[layer, 0, :, h * group + x].double() @ k[layer, :, h].double().t()) * d ** -0.5
+                want += torch.softmax(logits.masked_fill(hidden, -math.inf), dim=1).sum(0)
+            got = out[1, layer].view(H, n)[h].double()
+            assert ((got - want).abs() <= rel * want + floor * want.max()).all(), (layer, h, float((got - want).abs().max()))
+    # the wavefronts' lists of segments behind the partial pairs: [workgroup][wave][8], word 0 the number noted
+    pairs = L * H * info["row_super_blocks"] * (info["n_chunks"] + 1) * info["waves"] * info["blocks_per_wave"] * 32
+    groups = (info["n_chunks"] * L * H + 7) // 8 * 8 * info["row_super_blocks"]
+    return ws.view(torch.int32)[2 * pairs:2 * pairs + groups * info["waves"] * 8].view(groups, info["waves"], 8)[..., 0]
 
 
 @pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 128, 3), ("f16", 128, 1), ("bf16", 64, 8),
@@ -1424,39 +1472,26 @@ def test_sweep_of_few_tiles(S, monkeypatch, mode, dtype, head_dim, group):
 def test_rows_that_start_with_minus_infinity_are_repaired_once(S, monkeypatch, dtype, head_dim, group, hidden_tiles):
     """Scores of -infinity over the first tiles of every chunk leave the rows without a reference exponent; the
     first segment with a finite score overflows and is left to the repair launch, the ones behind it are not."""
-    monkeypatch.setenv("SPECKV_ROW_STATISTICS", "fixed")
-    monkeypatch.setenv("SPECKV_SCORE_KERNEL", "tile")
-    L, H, n, n_window, rows = 8, 8, 8400, 32, 64
-    gen = torch.Generator(device="cuda")
-    gen.manual_seed(90)
-    dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
-    q = torch.randn(L, 1, rows, H * group, head_dim, generator=gen, device="cuda")
-    k = torch.randn(L, n, H, head_dim, generator=gen, device="cuda")
-    q[..., 5] = q[..., 5].abs() + 1
-    q, k = q.to(dt), k.to(dt)
-    p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=n_window, pool_k=7, c_max=100, sm_scale=head_dim ** -0.5)
-    info = S.plan_info(p)
-    assert info["fixed_reference_rows"] == 1 and info["q_stationary"] == 0
-    tile = 64 if (dtype, head_dim) == ("f32", 128) else 128
-    assert info["chunk_keys"] >= 12 * tile
+    p, q, k, info, tile = fixed_reference_case(S, monkeypatch, dtype, head_dim, group, 90)
     for c in range(info["n_chunks"]):
         k[:, c * info["chunk_keys"]:c * info["chunk_keys"] + (hidden_tiles - 1) * tile + (tile if hidden_tiles == 1 else 10), :, 5] = -math.inf
-    ws = alloc_ws(S, p)
-    out = torch.empty((2, L, H * n), dtype=torch.float32, device="cuda")
-    S.speckv_score(p, q, k, out[0], out[1], ws)
-    for layer in (0, L - 1):
-        for h in (0, H - 1):
-            last = torch.cat([n - n_window + torch.arange(n_window), torch.full((rows - n_window,), n - 1)]).cuda()
-            hidden = torch.arange(n, device="cuda")[None, :] > last[:, None]
-            want = torch.zeros(n, dtype=torch.float64, device="cuda")
-            for x in range(group):
-                logits = (q[layer, 0, :, h * group + x].double() @ k[layer, :, h].double().t()) * head_dim ** -0.5
-                want += torch.softmax(logits.masked_fill(hidden, -math.inf), dim=1).sum(0)
-            got = out[1, layer].view(H, n)[h].double()
-            assert ((got - want).abs() <= 1e-4 * want).all(), (layer, h, float(((got - want).abs() / want.clamp(min=1e-300)).max()))
-    # the wavefronts' lists of segments behind the partial pairs: [workgroup][wave][8], word 0 the number noted
-    units = L * H * info["row_super_blocks"]
-    pairs = units * (info["n_chunks"] + 1) * info["waves"] * info["blocks_per_wave"] * 32
-    groups = (info["n_chunks"] * L * H + 7) // 8 * 8 * info["row_super_blocks"]
-    noted = ws.view(torch.int32)[2 * pairs:2 * pairs + groups * info["waves"] * 8].view(groups, info["waves"], 8)[..., 0]
-    assert int(noted.max()) == 1
+    assert int(check_raw_scores_and_count_noted(S, p, q, k, info, 1e-4, 0.0).max()) == 1
+
+
+@pytest.mark.parametrize("dtype,head_dim,group", [("bf16", 128, 8), ("bf16", 64, 8), ("f16", 64, 2), ("bf16", 64, 4),
+                                                  ("f32", 128, 2), ("f32", 64, 2), ("f32", 64, 8)])
+@pytest.mark.parametrize("every", [False, True])
+def test_outliers_at_segment_borders(S, monkeypatch, dtype, head_dim, group, every):
+    """Keys whose score for one row lies 220 nats above every one before them, first or last of a segment of
+    two tiles: two segments of a chunk, or all of them (more than a wavefront lists one by one)."""
+    p, q, k, info, tile = fixed_reference_case(S, monkeypatch, dtype, head_dim, group, 91)
+    segments = (info["chunk_keys"] // tile - 1) // 2
+    for layer in range(k.shape[0]):
+        for h in range(k.shape[2]):
+            row = q[layer, 0, (7 * layer + 5 * h) % 64, h * group + (layer + h) % group].float()
+            for i, s in enumerate(range(segments) if every else (1, segments - 1)):
+                at = tile * (1 + 2 * s) + (0 if i % 2 == 0 else 2 * tile - 1)
+                k[layer, at, h] = (row * (220.0 * (i + 1) * head_dim ** 0.5 / row.pow(2).sum())).to(k.dtype)
+    # logits of up to 220 * 21 = 4620, rounded a few times at that size: 4620 * 2^-22 = 1.1e-3
+    noted = int(check_raw_scores_and_count_noted(S, p, q, k, info, 2e-3, 1e-6).max())
+    assert segments >= 7 and noted == (info["chunk_keys"] // tile // 2 if every else 2)     # a full list: the rest as well
