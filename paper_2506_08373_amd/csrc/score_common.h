@@ -94,13 +94,7 @@ struct Tile {
   static constexpr int ROWB = D * ELT;          // bytes per key / query row
   static constexpr int C16 = ROWB / 16;         // 16-byte chunks per row
   static constexpr int NCS = C16 / 2;           // chunk steps (each lane half owns NCS chunks)
-  // Keys per LDS tile: 32 KiB, except 16 KiB where a row is 128 bytes.  Those sweeps need half the
-  // registers, so that with the smaller tile two workgroups share a CU and one works while the other
-  // waits at its tile barrier (prompt-token selection, 16 layers x 64K keys: column sweep 430 us with
-  // 256-key tiles and one workgroup, 395 us with 128-key tiles).
-  static constexpr int KT = ROWB <= 256 ? 128 : 64;
-  static constexpr int ALIGN = ROWB <= 128 ? 256 : KT;     // chunks and masked tails start at multiples of this many keys
-  static constexpr int TILE_BYTES = KT * ROWB;
+  static constexpr int ALIGN = ROWB <= 128 ? 256 : ROWB <= 256 ? 128 : 64;     // chunks and masked tails start at multiples of this many keys
   static constexpr int RPB = ROWB >= 256 ? 1 : 256 / ROWB;   // rows per 256-byte bank sweep
   static constexpr int SWZ = (C16 < 16 ? C16 : 16) - 1;      // xor mask applied to the chunk index
   __device__ static inline int swizzle(int row) { return (row / RPB) & SWZ; }

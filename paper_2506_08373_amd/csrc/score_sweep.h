@@ -64,13 +64,21 @@ constexpr int kCsumBuffers = 4;
 // bf16 products take 2048.  Calls measured with it -> here: 4 layers x 16K keys, 32 heads of 128, 128 rows 1092 ->
 // 845 us; 4 layers x 32K keys, 32 heads of 64, 128 rows 1279 -> 893 us; 8 layers x 16K keys, heads of 64, 32 rows
 // 348 -> 315 us.
-template <int DT, int D>
+template <int DT, int D, int MB>
 struct Operand {
   static constexpr bool SPLIT = DT == kF32;
   static constexpr int PLANES = SPLIT ? 3 : 1;
   static constexpr int MMA_DT = SPLIT ? kBf16 : DT;            // type of the operands the matrix cores see
   using TL = Tile<2, D>;                                      // LDS layout of one plane
-  static constexpr int KT = Tile<elt_bytes(DT), D>::KT, ALIGN = Tile<elt_bytes(DT), D>::ALIGN;
+  static constexpr int ALIGN = Tile<elt_bytes(DT), D>::ALIGN;
+  // Keys per LDS tile: 32 KiB of keys, except where a row is 128 bytes and a wave has one row block.  The column
+  // sweep of 8 such waves has 101 registers, and with 16 KiB tiles (64 KiB of LDS in all) two workgroups share
+  // a CU and one works while the other waits at its tile barrier: prompt-token selection, 16 layers x 64K keys 917 us
+  // with 256-key tiles, 874 with 128; 16 layers x 40K, 4 heads x 64 rows 580 and 561 us.  With two row blocks a
+  // wave has 151 to 160 registers and one workgroup the CU either way, so that the smaller tile only doubles
+  // the barriers: prompt compression, 8 layers x 32K keys, 346 us with 256-key tiles, 363 with 128; 4 layers x 100K,
+  // 4 heads x 80 rows, max 603 and 633 us, sum the same.
+  static constexpr int KT = ALIGN == 256 && MB == 1 ? 128 : ALIGN;
   static constexpr int PLANE_BYTES = KT * TL::ROWB, TILE_BYTES = PLANES * PLANE_BYTES;
 };
 
@@ -85,7 +93,7 @@ constexpr bool normalisers_in_lds() { return DT == kF32 && MB == 2; }
 
 template <int DT, int D, int MB, int NW>
 constexpr size_t score_lds_bytes() {
-  using OP = Operand<DT, D>;
+  using OP = Operand<DT, D, MB>;
   return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float) +
          (normalisers_in_lds<DT, MB>() ? NW * MB * 32 * sizeof(float) : 0);
 }
@@ -134,7 +142,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
                                            const bool wave_takes_part = true) {
   static_assert(!REPAIR || (PASS == 1 && !MASKED), "only the row-statistics sweep is repaired");
   constexpr int ELT = elt_bytes(DT);
-  using OP = Operand<DT, D>;
+  using OP = Operand<DT, D, MB>;
   using TL = typename OP::TL;
   constexpr bool SPLIT = OP::SPLIT;
   constexpr int ROWB = TL::ROWB, NCS = TL::NCS, KT = OP::KT, TILE_BYTES = OP::TILE_BYTES;

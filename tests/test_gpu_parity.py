@@ -1423,10 +1423,12 @@ def test_sweep_of_few_tiles(S, monkeypatch, mode, dtype, head_dim, group):
 
 
 def fixed_reference_case(S, monkeypatch, dtype, head_dim, group, seed):
-    """8 layers x 8 KV heads x 8400 keys, 64 rows per head, tile-streaming row statistics with fixed references."""
+    """8 layers x 8 KV heads, 64 rows per head, tile-streaming row statistics with fixed references; at least 12 key
+    tiles a chunk."""
     monkeypatch.setenv("SPECKV_ROW_STATISTICS", "fixed")
     monkeypatch.setenv("SPECKV_SCORE_KERNEL", "tile")
-    L, H, n, rows = 8, 8, 8400, 64
+    tile = 64 if (dtype, head_dim) == ("f32", 128) else 256 if (dtype != "f32", head_dim, group > 4) == (True, 64, True) else 128
+    L, H, n, rows = 8, 8, 16800 if tile == 256 else 8400, 64
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
     dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
@@ -1437,7 +1439,6 @@ def fixed_reference_case(S, monkeypatch, dtype, head_dim, group, seed):
     p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=32, pool_k=7, c_max=100, sm_scale=head_dim ** -0.5)
     info = S.plan_info(p)
     assert info["fixed_reference_rows"] == 1 and info["q_stationary"] == 0
-    tile = 64 if (dtype, head_dim) == ("f32", 128) else 128
     assert info["chunk_keys"] >= 12 * tile
     return p, q, k, info, tile
 
