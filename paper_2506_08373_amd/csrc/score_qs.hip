@@ -366,10 +366,12 @@ int qs_max_blocks(const ScoreArgs &A) {
 }  // namespace
 
 bool qs_supported(const ScoreArgs &A, int pass) {
-  // Default: only the row-statistics sweep at d = 64, where the vector pipe is the limit.  Prompt-token
-  // selection (16 layers x 64K keys, 64 rows per head) takes 890 us with it and 905 us with the
-  // tile-streaming kernel; this kernel for the column sweep as well, 955 us.  Not ahead everywhere:
-  // prompt compression (8 layers x 32K keys, 65 rows per head) takes 370 us with it, 351 us without.
+  // Default: only the row-statistics sweep at d = 64, where the vector pipe is the limit.  The line was drawn
+  // when the tile-streaming kernel searched every block's maximum there, and no longer lies where the two cross.
+  // Scoring with 4 query heads per KV head, us with this kernel for the row statistics / with the tile-streaming kernel
+  // for both sweeps (with this kernel for both): 64 rows per head, 16 layers x 64K keys 849-888 / 860 (906), 16 x 32K
+  // 455 / 450 (483), 4 x 64K 221 / 213 (242); 65 rows, 8 x 32K 307 / 296 (322), 4 x 16K 111 / 93 (124);
+  // 128 rows, 16 x 32K 838 / 776 (869); one layer of 32K, 64 rows 62 / 49 (72), 128 rows 97 / 74 (114).
   // At d = 128 the tile-streaming kernel is ahead for both sweeps.  The environment can
   // override the choice: SPECKV_SCORE_KERNEL=tile (never), qs (both sweeps), qs1 / qs2 (that sweep
   // only).  Read on every call so that a test can switch it.

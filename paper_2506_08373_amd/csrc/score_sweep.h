@@ -62,8 +62,8 @@ constexpr int kCsumBuffers = 4;
 // of both signs 2.7 / 11 -> 1.1 / 4.6.  One channel with six products: 0.66 / 2.1.
 // The fp32 matrix instruction runs at 1/16 of the bf16 rate (4096 cycles per 32x32 block at d = 128), eight
 // bf16 products take 2048.  Calls measured with it -> here: 4 layers x 16K keys, 32 heads of 128, 128 rows 1092 ->
-// 845 us; 4 layers x 32K keys, 32 heads of 64, 128 rows 1279 -> 893 us; 8 layers x 16K keys, heads of 64, 32 rows
-// 348 -> 315 us.
+// 845 us; 4 layers x 32K keys, 32 heads of 64, 128 rows 1279 -> 874 us; 8 layers x 16K keys, heads of 64, 32 rows
+// 348 -> 310 us.
 template <int DT, int D, int MB>
 struct Operand {
   static constexpr bool SPLIT = DT == kF32;

@@ -113,7 +113,11 @@ inline int64_t score_chunk_workgroups(const Dims &d, const ScoreGeom &g) {
 // True when the key-tile row-statistics sweep sums against fixed reference exponents and a repair
 // launch follows it.  That pays when the sweep runs for several rounds of workgroups; in a
 // one-round sweep the repair launch (a few microseconds when it has nothing to do, a segment's
-// duration when it has) costs more than the first sweep gains.
+// duration when it has) costs about what the first sweep gains.  Scoring at the 8B shape, 128 rows per head, us
+// fixed / online by workgroups of a sweep: 136 (one layer of 8K keys) 52.5-55 / 51-52.5; 240 (32K) 93 / 92.5;
+// 256 (128K) 275-279 / 279-285; 288 (3 layers x 40K) 326 / 335; 432 (6 x 32K) 488 / 505; 528 (2 x 128K) 576 / 594;
+// 640 (16 x 16K) 583 / 603.  They cross near one round, below the line, which dates from kernels before the reference
+// came from a whole tile.
 // The environment can override the choice (read on every call so that a test can switch it):
 // SPECKV_ROW_STATISTICS=fixed (always) or online (never).
 inline bool score_rows_fixed_reference(const Dims &d, const ScoreGeom &g) {
