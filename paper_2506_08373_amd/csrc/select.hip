@@ -361,9 +361,15 @@ __device__ __forceinline__ uint32_t decide_digit(SelShared &sh, int pass, uint32
   return decide_from_counts(sh, pass, c0, c1, prefix, mask, remaining);
 }
 
+// True when keys that start with the `bits` leading bits of `prefix` may belong to infinities or NaNs.
+__device__ __forceinline__ bool beyond_floats(uint32_t prefix, int bits) {
+  const uint32_t last = prefix | (uint32_t)(0xffffffffull >> bits);
+  return last >= 0xff800000u || (prefix & ~(uint32_t)(0xffffffffull >> bits)) <= 0x007fffffu;
+}
+
 // Writes, ascending, the indices of the entries of x[0..m) above the threshold key and of the
 // first need_eq entries equal to it (compared as floats: the same order as the keys, with -0
-// equal to +0).
+// equal to +0; thresholds at or beyond the infinities are compared by key).
 // x may be a slice of a longer row: index_base is the row index of x[0] and run_gt / run_eq
 // start at the numbers of entries above / equal to the threshold that precede the slice.
 __device__ __forceinline__ void emit_selected(const float *__restrict__ x, int m, RowSplit rs,
@@ -372,6 +378,20 @@ __device__ __forceinline__ void emit_selected(const float *__restrict__ x, int m
                                               uint32_t run_gt = 0, uint32_t run_eq = 0, int index_base = 0) {
   const int tid = threadIdx.x;
   const float thr = __uint_as_float(raw_prefix_of(thr_key, 0xffffffffu));
+  if (beyond_floats(thr_key, 32)) {            // seldom: NaNs take part, which only the keys rank
+    for (int j0 = 0, buf = 0; j0 < m; j0 += kSelThreads, buf ^= 1) {
+      const int j = j0 + tid;
+      const uint32_t key = j < m ? ordered_key(x[j]) : 0u;
+      const bool is_gt = j < m && key > thr_key, is_eq = j < m && key == thr_key;
+      uint32_t total;
+      const uint32_t before = block_exclusive_scan((is_gt ? 1u : 0u) | (is_eq ? 1u << 16 : 0u), sh.wave_tot[buf], &total);
+      const uint32_t gt_b = run_gt + (before & 0xffffu), eq_b = run_eq + (before >> 16);
+      if (is_gt || (is_eq && eq_b < need_eq)) out[gt_b + min(eq_b, need_eq)] = index_base + j;
+      run_gt += total & 0xffffu;
+      run_eq += total >> 16;
+    }
+    return;
+  }
   // the scalars before the first vector: every thread tracks the counts, thread 0 writes
   for (int j = 0; j < rs.lead; ++j) {
     const float xj = x[j];
@@ -946,13 +966,13 @@ __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int 
     histogram_pass(x, m, rs, prefix, mask, 21, 2048, sh);
     in_bin = decide_digit(sh, 0, prefix, mask, remaining);
   }
-  if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap) {
+  if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 11)) {
     select_after_prefix(x, m, rs, prefix, 11, remaining, out, *reinterpret_cast<FastShared *>(lds));
     return;
   }
   histogram_pass(x, m, rs, prefix, mask, 10, 2048, sh);
   in_bin = decide_digit(sh, 1, prefix, mask, remaining);
-  if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap) {
+  if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 22)) {
     select_after_prefix(x, m, rs, prefix, 22, remaining, out, *reinterpret_cast<FastShared *>(lds));
     return;
   }
@@ -1314,15 +1334,18 @@ __global__ __launch_bounds__(kSelThreads) void expand_kernel(
     }
     uint32_t total;
     uint32_t pos = written + block_exclusive_scan((uint32_t)fresh, wave_tot[buf], &total);
+    // with `sel` ascending and complete neither limit is ever met; no other `sel` may write outside the outputs
+    pos = min(pos, (uint32_t)n_in);
+    fresh = min(fresh, n_in - (int)pos);
     for (int e = 0; e < fresh; ++e) {
       idx_out[pos + e] = start + e;
       ids_out[pos + e] = token_ids[start + e];
     }
-    written += total;
+    written = min(written + total, (uint32_t)n_in);
   }
   const int m = n_in - n_window;
   const int last_hi = count > 0 ? min(n_in - 1, sel[count - 1] + nb) : -1;
-  const int wstart = max(m, last_hi + 1);
+  const int wstart = max(max(m, last_hi + 1), (int)written);       // the last: holds anyway (see above)
   for (int j = wstart + tid; j < n_in; j += kSelThreads) {
     idx_out[written + (j - wstart)] = j;
     ids_out[written + (j - wstart)] = token_ids[j];

@@ -88,3 +88,55 @@ def test_fused_call_selects_what_its_scores_say(S, n_in):
 def test_rows_just_too_long_for_registers(S, in_bin):
     """The limits of the path that reads a row once more, at a length that does not fit registers."""
     test_gpu_parity.test_select_around_the_limits_of_the_one_read_path(S, 32780, in_bin)
+
+
+def ordered_keys(bits):
+    return np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000)).astype(np.float64)      # exact: below 2^53
+
+
+@pytest.mark.parametrize("m", [32775, 70001, 300000])
+@pytest.mark.parametrize("kind", ["one NaN", "two NaNs", "infinities", "minus infinities"])
+def test_long_rows_whose_threshold_is_no_ordinary_number(S, m, kind):
+    """Rows that do not fit registers (300000: split over workgroups) where the last score kept is a NaN or an
+    infinity: ranked by their bits, ties to the lower index, every slot written, as in short rows."""
+    H, n = 2, m + 1
+    rng = np.random.default_rng(m)
+    bits = rng.random((H, n), dtype=np.float32).view(np.uint32)
+    if kind == "one NaN":
+        bits[:] = 0x7fc00000
+    elif kind == "two NaNs":
+        bits[:] = np.where(rng.random((H, n)) < 0.5, 0x7fc00000, 0x7fc00001)
+    elif kind == "infinities":
+        bits[:, ::3] = 0x7f800000
+    else:
+        bits[:] = np.where(rng.random((H, n)) < 0.001, bits, 0xff800000)
+    pooled = torch.from_numpy(bits.view(np.int32)).cuda().view(torch.float32).reshape(1, -1)
+    c_max = 500
+    p = S.SpecKVParams(n_layers=1, n_q_heads=H, n_kv_heads=H, head_dim=64, seq_lens=(n,), n_window=1, n_lookahead=1,
+                       pool_k=7, c_max=c_max, dtype=torch.bfloat16, sm_scale=1.0)
+    ws = torch.empty(max(S.select_workspace_bytes(p), 256), dtype=torch.uint8, device="cuda")
+    for workspace in (None, ws):
+        idx = torch.full((1, H * S.total_keep(p)), -7, dtype=torch.int32, device="cuda")
+        S.speckv_select(p, pooled, idx, *(() if workspace is None else (workspace,)))
+        got = idx.cpu().numpy().reshape(H, -1)
+        for g in range(H):
+            assert np.array_equal(got[g], orc.keep_indices(ordered_keys(bits[g, :m]), n, 1, c_max)), g
+
+
+def test_token_selection_from_scores_that_are_all_nan(S):
+    """One NaN key makes every score of a 40000-token prompt NaN: the first tokens are kept, nothing is left unwritten
+    for the expansion to read."""
+    n, top = 40000, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    q = torch.randn(1, 1, 32, 4, 64, generator=gen, device="cuda").bfloat16()
+    k = torch.randn(1, n, 2, 64, generator=gen, device="cuda").bfloat16()
+    k[0, 100, :, 7] = float("nan")
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=32, pool_k=7, c_max=16, sm_scale=0.125)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+    idx, out, count = torch.full_like(ids, -7), torch.full_like(ids, -7), torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.full((S.specpc_workspace_bytes(p, top),), 0x3f, dtype=torch.uint8, device="cuda")
+    S.specpc_select_tokens(p, top, 4, q, k, ids, idx, out, count, ws)
+    want = list(range(top + 4)) + list(range(n - 32, n))
+    assert int(count) == len(want) and idx[:len(want)].tolist() == want and out[:len(want)].tolist() == want
+    assert (idx[len(want):] == -7).all()
