@@ -54,12 +54,13 @@ constexpr int kCsumBuffers = 4;
 // two rows becomes eight products of planes; only v2 w2, below 2^-34 of a term, is left out.  (v1 w2 and v2 w1
 // reach 2^-25 of a term each, half the rounding of an fp32 sum: without them the error of rows with few
 // non-zero channels grew.)  The seven lower products are summed in an accumulator of their own and added to the
-// sum of the leading ones v0 w0 with one fp32 addition: the matrix instruction truncates what it adds
-// beside a much larger number, up to a quarter of a last place, as often as there are chunks.
+// sum of the leading ones v0 w0 with one fp32 addition: the matrix instruction keeps only a few bits below the
+// last place of the largest number it adds, so that lower products summed into the leading ones lose by it.
 // Error of a logit against 64-bit sums, in 2^-24 of its size, rms / largest, fp32 instruction -> here (4096 keys x
 // 32 rows with the given number of non-zero channels at d = 128): 1 channel 0.49 / 1.05 -> 0.49 / 1.05, 2 channels
 // 0.50 / 1.5 -> 0.45 / 1.1, 4 channels 0.61 / 1.9 -> 0.47 / 1.0, 128 channels of one sign 3.0 / 13 -> 0.46 / 0.9,
-// of both signs 2.7 / 11 -> 1.1 / 4.6.  One channel with six products: 0.66 / 2.1.
+// of both signs 2.7 / 11 -> 1.1 / 4.6.  One channel with six products: 0.66 / 2.1; with eight in one accumulator,
+// smallest first: 0.64 / 1.54.
 // The fp32 matrix instruction runs at 1/16 of the bf16 rate (4096 cycles per 32x32 block at d = 128), eight
 // bf16 products take 2048.  Calls measured with it -> here: 4 layers x 16K keys, 32 heads of 128, 128 rows 1092 ->
 // 845 us; 4 layers x 32K keys, 32 heads of 64, 128 rows 1279 -> 874 us; 8 layers x 16K keys, heads of 64, 32 rows
@@ -72,7 +73,7 @@ struct Operand {
   using TL = Tile<2, D>;                                      // LDS layout of one plane
   static constexpr int ALIGN = Tile<elt_bytes(DT), D>::ALIGN;
   // Keys per LDS tile: 32 KiB of keys, except where a row is 128 bytes and a wave has one row block.  The column
-  // sweep of 8 such waves has 101 registers, and with 16 KiB tiles (64 KiB of LDS in all) two workgroups share
+  // sweep of 8 such waves has 101 registers, and with 16 KiB tiles (48 KiB of LDS in all) two workgroups share
   // a CU and one works while the other waits at its tile barrier: prompt-token selection, 16 layers x 64K keys 917 us
   // with 256-key tiles, 874 with 128; 16 layers x 40K, 4 heads x 64 rows 580 and 561 us.  With two row blocks a
   // wave has 151 to 160 registers and one workgroup the CU either way, so that the smaller tile only doubles
