@@ -1,6 +1,7 @@
-// Importance scoring: the kernels between the two sweeps and the host entry that strings the
+// Importance scoring: the kernels that may stand between the two sweeps and the host entry that strings the
 // sweeps together (Sec. 3.1 Eq. 1; Alg. 1 CrossAttention and reduce steps).  The sweeps themselves
 // are in score_sweep.h (compiled in score_rows.hip and score_cols.hip) and score_qs.hip.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -14,13 +15,13 @@ namespace {
 // A block covers 64 rows; its 4 waves split the chunks and merge their partial pairs in LDS.
 constexpr int kMergeRows = 64, kMergeSlices = 4;
 
-// Zeroes A.clear (if any), the work spread over every thread of the grid.
-__device__ inline void clear_scratch(const ScoreArgs &A) {
-  if (A.clear == nullptr) return;
-  const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * blockDim.x;
-  const int64_t id = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int64_t i = id; i < A.clear_words; i += n_threads) A.clear[i] = 0u;
-}
+// Up to this many chunks a sequence, every workgroup of the column sweep merges the pairs of its own rows instead, and
+// converts a caller's normalisers by itself: the kernel is a launch of 3 to 5 us between two sweeps that wait for each other,
+// while the pairs (8 bytes per row and chunk, 1 to 2 us for 32 chunks of 512 rows) arrive beside the first key tile.
+// Calls with the kernel / without: one layer of 4K keys 48.1 / 45.1 us, 32K (29 chunks) 120.3 / 116.7, 128K (32 chunks)
+// 348.6 / 344.2, 4 layers x 60K with a caller's normalisers 267.7 / 262.2, 32 layers x 16K 1113 / 1109.  With more chunks the
+// workgroups' reads (the same pairs again for every chunk) outgrow the launch.
+constexpr int kMergeInSweep = 40;
 
 __device__ inline void merge_pair(float &m, float &l, float m2, float l2) {
   const float mm = fmaxf(m, m2);
@@ -29,7 +30,8 @@ __device__ inline void merge_pair(float &m, float &l, float m2, float l2) {
 }
 
 __global__ __launch_bounds__(kMergeRows * kMergeSlices) void lse_combine_kernel(ScoreArgs A) {
-  clear_scratch(A);
+  clear_scratch(A, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
+                (int64_t)gridDim.x * gridDim.y * blockDim.x);
   __shared__ float2 partial[kMergeSlices][kMergeRows];
   const Dims &d = A.d;
   const int RSB = A.g.RSB;
@@ -67,7 +69,8 @@ __global__ __launch_bounds__(kMergeRows * kMergeSlices) void lse_combine_kernel(
 // Converts caller-supplied natural-log normalisers [L][S][R][Hq] into the padded log2 layout
 // the column-reduction sweep reads.
 __global__ __launch_bounds__(256) void lse_import_kernel(ScoreArgs A) {
-  clear_scratch(A);
+  clear_scratch(A, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
+                (int64_t)gridDim.x * gridDim.y * blockDim.x);
   const Dims &d = A.d;
   const int RSB = A.g.RSB;
   const int unit = blockIdx.x;            // (layer, head, row super-block)
@@ -107,7 +110,7 @@ int64_t score_fail_words(const Plan &pl) { return score_chunk_workgroups(pl.d, p
 bool score_uses_qs(const Plan &pl, int pass) {
   ScoreArgs A;
   A.d = pl.d; A.t = pl.t; A.g = pl.g;
-  A.q = nullptr; A.k = nullptr; A.part = nullptr; A.lse = nullptr; A.planes = nullptr; A.lse_in = nullptr; A.chunk_blocks = 0; A.clear = nullptr; A.clear_words = 0; A.fail = nullptr;
+  A.q = nullptr; A.k = nullptr; A.part = nullptr; A.lse = nullptr; A.planes = nullptr; A.lse_in = nullptr; A.chunk_blocks = 0; A.clear = nullptr; A.clear_words = 0; A.fail = nullptr; A.norm_from = kNormMerged;
   return qs_supported(A, pass);
 }
 
@@ -119,13 +122,22 @@ hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *pa
   A.q = (const char *)q; A.k = (const char *)k;
   A.part = part; A.lse = lse; A.planes = planes; A.lse_in = lse_in; A.chunk_blocks = 0;
   A.clear = clear; A.clear_words = clear != nullptr ? clear_words : 0;
+  A.norm_from = kNormMerged;
+  if (!qs_supported(A, 2)) {
+    int most = 0;                       // chunks of a sequence
+    for (int s = 0; s < A.d.S; ++s) most = std::max(most, A.t.cc[s + 1] - A.t.cc[s]);
+    if (lse_in != nullptr) A.norm_from = kNormCaller;
+    else if (most <= kMergeInSweep) A.norm_from = kNormPairs;
+  }
   A.fail = reinterpret_cast<int32_t *>(part + (int64_t)A.d.L * A.d.Hkv * A.g.RS * A.g.n_chunks * A.g.RSB);
   hipEvent_t *ev = events;
   hipError_t e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   if (A.lse_in == nullptr && (e = launch_row_statistics_sweep(A, st)) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
-  if (A.lse_in == nullptr) {
+  if (A.norm_from != kNormMerged) {
+    // nothing: the column sweep makes its normalisers
+  } else if (A.lse_in == nullptr) {
     hipLaunchKernelGGL(lse_combine_kernel, dim3(A.d.L * A.d.Hkv * A.g.RS * (A.g.RSB / kMergeRows), A.d.S),
                        dim3(kMergeRows * kMergeSlices), 0, st, A);
   } else {

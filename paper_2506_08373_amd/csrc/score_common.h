@@ -15,16 +15,28 @@ struct ScoreArgs {
   const char *q;
   const char *k;
   float2 *part;     // [unit][chunk][RSB] (max2, sum) per row, unit = (layer, head, row super-block)
-  float *lse;       // [layer][head][seq][RS*RSB]
+  int norm_from;    // where the column sweep takes its row normalisers from: kNorm... below
+  float *lse;       // [layer][head][seq][RS*RSB] (kNormMerged)
   const float *lse_in;   // optional caller-supplied natural-log normalisers [L][S][R][Hq]
   float *planes;    // [RS][layer][Hkv*T]
-  uint32_t *clear;  // optional scratch the kernel between the sweeps zeroes (clear_words words)
+  uint32_t *clear;  // optional scratch (clear_words words) that is zeroed on the way: by the kernel between the sweeps
+                    // where there is one, else by the column sweep
   int64_t clear_words;
   int chunk_blocks; // whole-sweep launches: workgroups that run unmasked chunks; the masked tails follow them
   int32_t *fail;    // row-statistics sweep: kFailWords ints per chunk workgroup (see score_sweep.h)
 };
 
+// Row normalisers of the column sweep: merged by a kernel between the sweeps, merged from the partial pairs by every
+// workgroup of the column sweep for its own rows, or the caller's.
+constexpr int kNormMerged = 0, kNormPairs = 1, kNormCaller = 2;
+
 namespace {
+
+// Zeroes A.clear (if any), the work spread over every thread of the grid; id: the thread's number in it.
+__device__ inline void clear_scratch(const ScoreArgs &A, int64_t id, int64_t n_threads) {
+  if (A.clear == nullptr) return;
+  for (int64_t i = id; i < A.clear_words; i += n_threads) A.clear[i] = 0u;
+}
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;

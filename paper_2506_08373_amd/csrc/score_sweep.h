@@ -9,7 +9,7 @@
 //
 //   pass 1  row statistics: per row a pair (reference exponent, sum of 2^(c*S - reference)) over
 //           the keys of one chunk, the reference either the running maximum or fixed per chunk
-//           (see score_body); a small kernel merges the chunks into
+//           (see score_body); a small kernel, or pass 2 itself, merges the chunks into
 //           lse2[row] = log2 sum_j 2^(c*S[row,j]), c = sm_scale*log2(e).
 //   pass 2  column sums: raw[j] = sum_rows 2^(c*S[row,j] - lse2[row]).
 //
@@ -125,6 +125,17 @@ __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3
   plane[0][0] |= least < 2 * kSplitMin - 1 ? 0x7fffu : 0u;
 }
 
+// Adds N (reference, sum) pairs to the pair (top, sum).
+template <int N>
+__device__ __forceinline__ void merge_pairs(float &top, float &sum, const float2 (&in)[N]) {
+  const float before = top;
+#pragma unroll
+  for (int u = 0; u < N; ++u) top = fmaxf(top, in[u].x);
+  sum *= exp2f(before - top);
+#pragma unroll
+  for (int u = 0; u < N; ++u) sum += in[u].y * exp2f(in[u].x - top);
+}
+
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
 //   PASS    1: row statistics, 2: column reduction
 //   RED     (pass 2) 0: sum over the rows of a head, 1: max over the rows of a head;
@@ -210,9 +221,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   const int blocks_per_head = (A.g.PPH == 1 ? A.g.Rp : RSB) / 32;
   const bool paired = PASS == 2 && RED == 1 && !MASKED && MB == 2 && nblk == NW * MB && blocks_per_head % 2 == 0;
   auto block_of = [&](int rb) { return paired ? wv * MB + rb : rb * NW + wv; };
-  if (PASS == 2)   // slots of skipped blocks must read as zero when the tile partials are merged
-    for (int x = tid; x < kCsumBuffers * NW * MB * KT; x += NW * 64) csum[x] = 0.f;
-
   // head and first observation row of each of this wave's 32-row blocks (a block never mixes
   // heads, so one division per block replaces one per row)
   int blk_head[MB], blk_i0[MB];
@@ -316,34 +324,73 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   float mrun[MB], lrun[MB];          // pass 1: lane = one query row per row block
   constexpr bool LSE_LDS = PASS == 2 && normalisers_in_lds<DT, MB>();
   float nlse[LSE_LDS ? 1 : MB][16];  // pass 2: lane = 16 rows per row block
-  float *lds_lse = csum + (size_t)kCsumBuffers * NW * MB * KT + wv * MB * 32;      // ... or in LDS, this wave's blocks
+  float *lds_lse = csum + (size_t)kCsumBuffers * NW * MB * KT;                     // ... or in LDS, [RSB]
   if (PASS == 1) {
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb) { mrun[rb] = kNegBig; lrun[rb] = 0.f; }
   } else {
-    const float *lp = A.lse + (((int64_t)layer * d.Hkv + g) * d.S + s) * ((int64_t)A.g.RS * RSB);
-    auto row_lse = [&](int rb, int r32) {
-      const bool valid = SPECKV_ROW_VALID(rb, r32);
-      const int io = blk_i0[rb] + r32;
-      float v = -lp[rs * RSB + block_of(rb) * 32 + r32];  // the lse buffer covers the padded rows
-      if (d.weight_rows && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
-      return valid ? v : -INFINITY;                       // padded rows contribute 2^-inf = 0
-    };
+    // The normalisers of the workgroup's rows go through LDS, one thread (or RSB_SLICES of them) per row.  Merging
+    // the chunks' pairs here instead of in a kernel between the sweeps saves that launch (see launch_score).
+    constexpr int RSB_SLICES = NW * 64 / RSB, BATCH = 16;
+    float2 *pairs = reinterpret_cast<float2 *>(csum);                                  // [RSB_SLICES][RSB]
+    float *norm = LSE_LDS ? lds_lse : csum + 2 * NW * 64;                             // [RSB]
+    static_assert(RSB_SLICES >= 1 && (size_t)kCsumBuffers * NW * MB * KT >= (size_t)2 * NW * 64 + RSB, "scratch of the merge");
+    const int lr = tid % RSB, slice = tid / RSB;
+    int hh, io;
+    const bool valid = decode_row(d, A.g, rs, lr, &hh, &io);
+    float v = 0.f;                                        // log2 normaliser of row lr
+    if (A.norm_from == kNormPairs) {
+      const float2 *pp = A.part + (int64_t)unit * A.g.n_chunks * RSB + lr;
+      const int c1 = A.t.cc[s + 1];
+      float top = kNegBig, sum = 0.f;
+      for (int c = A.t.cc[s] + slice; c < c1; c += RSB_SLICES * BATCH) {
+        float2 in[BATCH];
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-      if constexpr (LSE_LDS) {
-        if (half == 0) lds_lse[rb * 32 + l32] = row_lse(rb, l32);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) nlse[rb][i] = row_lse(rb, 8 * (i >> 2) + 4 * half + (i & 3));
+        for (int u = 0; u < BATCH; ++u)
+          in[u] = c + u * RSB_SLICES < c1 ? pp[(int64_t)(c + u * RSB_SLICES) * RSB] : make_float2(kNegBig, 0.f);
+        merge_pairs(top, sum, in);
       }
+      if (slice == 0) {                                   // the sequence's masked tail chunk
+        const float2 in[1] = {pp[(int64_t)(A.g.n_fast_chunks + s) * RSB]};
+        merge_pairs(top, sum, in);
+      }
+      if constexpr (RSB_SLICES > 1) {
+        pairs[slice * RSB + lr] = make_float2(top, sum);
+        __syncthreads();
+        if (slice == 0) {
+          float2 in[RSB_SLICES - 1];
+#pragma unroll
+          for (int u = 1; u < RSB_SLICES; ++u) in[u - 1] = pairs[u * RSB + lr];
+          merge_pairs(top, sum, in);
+        }
+      }
+      v = top + log2f(sum);
+    } else if (A.norm_from == kNormCaller) {
+      if (valid) v = A.lse_in[(((int64_t)layer * d.S + s) * d.R + io) * d.Hq + g * d.G + hh] * 1.4426950408889634f;
+    } else {
+      v = A.lse[(((int64_t)layer * d.Hkv + g) * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + lr];
     }
+    if (slice == 0) {
+      v = -v;
+      if (d.weight_rows && valid && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
+      norm[lr] = valid ? v : -INFINITY;                   // padded rows contribute 2^-inf = 0
+    }
+    __syncthreads();
+    if constexpr (!LSE_LDS) {
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) nlse[rb][i] = norm[block_of(rb) * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+      __syncthreads();
+    }
+    // slots of skipped blocks must read as zero when the tile partials are merged
+    for (int x = tid; x < kCsumBuffers * NW * MB * KT; x += NW * 64) csum[x] = 0.f;
   }
   // the negated normalisers of the lane's 16 rows in row block rb
   auto load_lse = [&](int rb, float (&nl)[16]) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      if constexpr (LSE_LDS) nl[i] = lds_lse[rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+      if constexpr (LSE_LDS) nl[i] = lds_lse[block_of(rb) * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
       else nl[i] = nlse[rb][i];
     }
   };
@@ -903,6 +950,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 template <int DT, int D, int MB, int NW, int PASS, int RED, bool TAIL_ONLY>
 __device__ __forceinline__ void score_dispatch(const ScoreArgs &A) {
   const int bid = blockIdx.x;
+  if (PASS == 2 && A.norm_from != kNormMerged)
+    clear_scratch(A, (int64_t)bid * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
   if (TAIL_ONLY) score_body<DT, D, MB, NW, PASS, RED, true>(A, bid);
   else if (bid < A.chunk_blocks) score_body<DT, D, MB, NW, PASS, RED, false>(A, bid);
   else score_body<DT, D, MB, NW, PASS, RED, true>(A, bid - A.chunk_blocks);

@@ -101,7 +101,7 @@ hipError_t launch_compact(const Plan &pl, const void *k, const void *v, const in
 // `lse_in`, when not null, holds natural-log row normalisers [L][S][R][Hq]; the row-statistics
 // sweep is skipped and only the column reduction runs.
 // `clear`, when not null, is scratch of clear_words 32-bit words that the call leaves zeroed (done
-// by the small kernel between the sweeps: the fused calls need zeroed counters for the pooling
+// by the kernel between the sweeps or by the column sweep: the fused calls need zeroed counters for the pooling
 // kernel and must not use a memset, which a captured graph may not contain).
 // ints behind the partial pairs of the row-statistics sweep (one short list per chunk workgroup)
 int64_t score_fail_words(const Plan &pl);
