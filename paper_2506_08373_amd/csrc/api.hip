@@ -23,6 +23,7 @@ constexpr int kSelSplitMinKeys = 1 << 18;            // rows at least this long 
 constexpr int kSelSplitWorkgroups = 512;            // ... when the call has fewer than half this many rows
 constexpr int kSelSplitMaxParts = 64;
 constexpr int kChunkMin = 512;                      // shortest chunk
+constexpr int kShortChunkUnits = 8;                 // ... unless the call has no more (layer, head, super-block) units
 constexpr int kChunkSmallCap = 4096;                // longest chunk that small problems are given
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -170,11 +171,29 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
         if (chunk_wgs(longer) + tails <= kCUs) { kc = longer; break; }
     }
   }
-  g.KC = (int32_t)kc;
-  t.cc[0] = 0;
-  for (int s = 0; s < d.S; ++s) t.cc[s + 1] = t.cc[s] + (t.tail0[s] + g.KC - 1) / g.KC;
-  g.n_fast_chunks = t.cc[d.S];
-  g.n_chunks = g.n_fast_chunks + d.S;
+  auto cut = [&](int64_t kc_) {
+    g.KC = (int32_t)kc_;
+    t.cc[0] = 0;
+    for (int s = 0; s < d.S; ++s) t.cc[s + 1] = t.cc[s] + (t.tail0[s] + g.KC - 1) / g.KC;
+    g.n_fast_chunks = t.cc[d.S];
+    g.n_chunks = g.n_fast_chunks + d.S;
+  };
+  cut(kc);
+  pl->plan_chunk = g.KC;
+  pl->plan_chunks = g.n_fast_chunks;
+  // A call that chunks of kChunkMin keys cannot spread over the CUs is a chain of latencies: set-up, then one tile after the
+  // other.  Its workgroups take as few tiles each as keeps everything in one round of the CUs: one fp32 layer of 1K keys
+  // 56.7 us with 512 keys each, 36.4 with 128 (its sweeps 19.5 and 21.2 us, then 9.8 and 12.1); one layer of 4K 45.1 us
+  // with 512, 38.7 with 256 (13.4 and 14.4, 11.2 and 12.0).  With more units kChunkMin fills the CUs at about 8K keys; there the
+  // cut stays independent of the length, so that a length read on the device gives what the host's would, bit for bit.
+  if (kc == kChunkMin && units <= kShortChunkUnits) {
+    const int tile = rowb <= 128 && g.MB == 1 ? 128 : kt;            // Operand::KT of the scoring kernels
+    for (int64_t piece = tile; piece < kChunkMin; piece += tile) {
+      cut(piece);
+      if (((int64_t)g.n_fast_chunks + d.S) * units <= kCUs) break;
+      cut(kChunkMin);
+    }
+  }
 
   // workspace carve-up
   size_t off = 0;
@@ -282,7 +301,7 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
   if (st != SPECKV_OK) return st;
   if (info == nullptr) return SPECKV_ERR_INVALID_ARG;
   const int rowb = pl.d.D * pl.d.elt;
-  info[0] = pl.g.NW; info[1] = pl.g.MB; info[2] = pl.g.RS; info[3] = pl.g.KC; info[4] = pl.g.n_fast_chunks;
+  info[0] = pl.g.NW; info[1] = pl.g.MB; info[2] = pl.g.RS; info[3] = pl.plan_chunk; info[4] = pl.plan_chunks;
   info[5] = rowb <= 128 ? 256 : rowb <= 256 ? 128 : 64;
   info[6] = pl.sel_parts; info[7] = pl.sel_part_len;
   info[8] = (score_uses_qs(pl, 1) ? 1 : 0) | (score_uses_qs(pl, 2) ? 2 : 0);

@@ -38,3 +38,40 @@ def shape(**kw):
 ], ids=lambda kw: "-".join(str(x) for x in kw.values()))
 def test_row_normalisers_merged_in_the_column_sweep(S, kw):
     parity.check_full_path(S, shape(**kw))
+
+
+# Calls of up to 8 units with chunks shorter than 512 keys: one tile per workgroup, two, three; a last one that is shorter;
+# a live length that leaves whole workgroups without keys; 8 and 9 units; every tile size (64 to 256 keys)
+@pytest.mark.parametrize("kw", [
+    dict(seq_lens=(130,), n_kv_heads=1, n_q_heads=4), dict(seq_lens=(128 * 3 + 15,), n_kv_heads=1, n_q_heads=4),
+    dict(seq_lens=(128 * 3 + 15, 900), dtype="f32", head_dim=64, n_kv_heads=2), dict(seq_lens=(1700,), dtype="f32"),
+    dict(seq_lens=(5200,), n_q_heads=16, n_kv_heads=8), dict(seq_lens=(9000,), n_q_heads=16, n_kv_heads=8, dtype="f16"),
+    dict(seq_lens=(3000,), n_q_heads=18, n_kv_heads=9), dict(seq_lens=(4133,), n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64),
+    dict(seq_lens=(2100,), n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64, head_dim=64),
+], ids=lambda kw: "-".join(str(x) for x in kw.values()))
+@pytest.mark.parametrize("mode", ["online", "fixed"])
+def test_workgroups_of_few_tiles(S, kw, mode, monkeypatch):
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", mode)
+    w = shape(**kw)
+    info = S.plan_info(parity.make_params(S, w))
+    assert info["chunk_keys"] == 512
+    parity.check_full_path(S, w)
+
+
+@pytest.mark.parametrize("n_live", [4000, 1100, 200, 40])
+def test_workgroups_of_few_tiles_with_a_length_on_the_device(S, n_live):
+    w = shape(seq_lens=(4000,), n_q_heads=16, n_kv_heads=8)
+    t = workloads.generate(w)
+    q, k = t["q"].cuda(), t["k"].cuda()
+    n_dev = torch.tensor([n_live], dtype=torch.int32, device="cuda")
+    out = []
+    for n, extra in ((4000, dict(n_in_dev=n_dev)), (n_live, {})):
+        kk = k[:, :n].contiguous()
+        p = S.SpecKVParams.for_tensors(q, kk, seq_lens=(n,), n_window=w.n_window, pool_k=w.pool_k, c_max=w.c_max,
+                                       sm_scale=w.sm_scale, **extra)
+        raw, pooled = (torch.full((1, 8 * n), -1.0, device="cuda") for _ in range(2))
+        S.speckv_score(p, q, kk, pooled, raw, parity.alloc_ws(S, p))
+        out.append((pooled.view(8, n).double().cpu().numpy(), raw.view(8, n).double().cpu().numpy()))
+    for dev, host in zip(*out):
+        parity.assert_scores_close(dev[:, :n_live], host, "live %d" % n_live)
+        assert (dev[:, n_live:] == 0).all()
