@@ -5,8 +5,9 @@
 //    kernel k over the non-window candidates (Alg. 1 pooling step; table: Max, k = 7).
 //  * select: the C largest pooled scores per (layer, sequence, KV head), ties to the
 //    smaller index, ascending, then the window m..n_in-1 (Alg. 1 "Select KVs").
-//    MSD radix select on order-preserving 32-bit keys (digits of 11 + 11 + 10 bits).  One
-//    workgroup per row; every step is deterministic.  The histogram of the first digit comes
+//    MSD radix select on order-preserving 32-bit keys (digits of 11 + 11 + 10 bits; 14 + 11 + 7 where
+//    the pooling kernel has counted the first).  One workgroup per row, or several in fused calls with few
+//    long rows; every step is deterministic.  The histogram of the first digit comes
 //    from the pooling kernel in the fused calls (else from one read of the row); short rows (16K
 //    entries, 32K without the counts) stay in registers, others of up to about 229K entries are
 //    then read once more: entries above the threshold's bin are
@@ -18,6 +19,8 @@
 //    decision kernels per digit), then the same row select with each head's own count.
 //  * expand: widens selected tokens to +-n_neighbor, unites them with the window and
 //    emits the sorted set with the token ids gathered (Sec. 4.2 prompt compression).
+#include <algorithm>
+
 #include "speckv_internal.h"
 
 namespace speckv {
@@ -31,6 +34,18 @@ __device__ __forceinline__ uint32_t ordered_key(float x) {
   const uint32_t u = raw_bits(x);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+
+// The digit the pooling kernel counts for selection: 14 leading bits of the key (sign, exponent, 5 bits of mantissa), in a window
+// of 2048 of their values: scores are sums of probabilities, none negative, none above the 4096 rows of a group.  With the
+// 11 leading bits (2 bits of mantissa) as the digit, a quarter of a row of scores within a factor of four shared the
+// threshold's digit.  Digits 0 and 2047 also hold whatever lies below 2^-51 and from 2^13 - 2^7 on (and NaNs): a threshold there
+// is looked for without the counts.
+constexpr int kWinShift = 18, kWinLow = (int)(0x80000000u >> kWinShift) + ((127 - 51) << 5);
+__device__ __forceinline__ int window_digit(float x) {
+  return min(max((int)(ordered_key(x) >> kWinShift) - kWinLow, 0), 2047);
+}
+__device__ __forceinline__ bool inside_window(uint32_t digit) { return digit - 1u < 2046u; }
+__device__ __forceinline__ uint32_t window_prefix(uint32_t digit) { return (digit + (uint32_t)kWinLow) << kWinShift; }
 
 // ----------------------------------------------------------------------------------
 // reduce + pool
@@ -105,7 +120,7 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
       } else {
         for (int jj = lo + 1; jj <= hi; ++jj) best = fmaxf(best, tile[jj - j0 + half]);
       }
-      if (first_digit != nullptr) atomicAdd(&first_digit[ordered_key(best) >> 21], 1u);   // selection's first digit
+      if (first_digit != nullptr) atomicAdd(&first_digit[window_digit(best)], 1u);   // selection's first digit
     }
     pooled[j] = best;
   }
@@ -113,7 +128,8 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
 
 __global__ __launch_bounds__(kPoolThreads) void reduce_pool_kernel(
     Dims d, SeqTab t, PlaneMerge pm, const float *__restrict__ planes,
-    float *__restrict__ raw, float *__restrict__ pooled, int tiles_per_row, uint32_t *__restrict__ hist0) {
+    float *__restrict__ raw, float *__restrict__ pooled, int tiles_per_row, uint32_t *__restrict__ hist0,
+    uint32_t *__restrict__ arrived) {
   __shared__ float tile[kPoolTile + SPECKV_MAX_POOL_K + 1];
   __shared__ uint32_t first_digit[2048];
   const int unit = blockIdx.x / tiles_per_row;
@@ -122,6 +138,7 @@ __global__ __launch_bounds__(kPoolThreads) void reduce_pool_kernel(
   const int s = (unit / d.Hkv) % d.S;
   const int layer = unit / (d.Hkv * d.S);
   const int n_row = t.cu[s + 1] - t.cu[s];
+  if (arrived != nullptr && j0 == 0 && threadIdx.x == 0) arrived[(int64_t)unit * kPartsWords] = 0u;    // for select_in_parts
   if (j0 >= n_row) return;
   const int n_s = live_len(d, t, s);
   const int64_t base = (int64_t)layer * d.Hkv * d.T + (int64_t)d.Hkv * t.cu[s] + (int64_t)g * n_row;
@@ -213,9 +230,9 @@ constexpr int kHistUnroll = 4;     // independent 128-bit loads in flight per th
 // are leading bits of such keys.
 // The histogram passes work on the raw float bits (fewer operations per element than the ordered
 // key); only the bin index is translated when the bins are read in descending order.
-// Ordered digit D of level `pass` (0, 1, 2) -> digit of the raw bits; `neg`: the number is negative.
-__device__ __forceinline__ int raw_digit(int D, int pass, int nb, bool neg) {
-  if (pass == 0) return D >= 1024 ? D - 1024 : 2047 - D;
+// Ordered digit D (one of nb) -> digit of the raw bits; `leading`: the digit holds the sign; `neg`: the number is negative.
+__device__ __forceinline__ int raw_digit(int D, bool leading, int nb, bool neg) {
+  if (leading) return D >= 1024 ? D - 1024 : 2047 - D;
   return neg ? nb - 1 - D : D;
 }
 // Raw float bits (under `mask`) of the numbers whose ordered key starts with `prefix`.
@@ -314,15 +331,13 @@ __device__ __forceinline__ void histogram_pass(const float *__restrict__ x, int 
   __syncthreads();
 }
 
-// c0, c1: this thread's counts of the entries with digit nb-1-2t and nb-2-2t (ordered digits of
-// level `pass`, t the thread) among the entries that share `prefix`.  Extends `prefix` by the digit
+// c0, c1: this thread's counts of the entries with digit nb-1-2t and nb-2-2t (one of nb ordered digits whose lowest bit is bit
+// `shift` of the key, t the thread) among the entries that share `prefix`.  Extends `prefix` by the digit
 // that holds the remaining-th largest of them, reduces `remaining` to its rank among the entries
 // with that digit and returns how many entries have it.
-__device__ __forceinline__ uint32_t decide_from_counts(SelShared &sh, int pass, uint32_t c0, uint32_t c1,
+__device__ __forceinline__ uint32_t decide_from_counts(SelShared &sh, int shift, int nb, uint32_t c0, uint32_t c1,
                                                        uint32_t &prefix, uint32_t &mask, uint32_t &remaining) {
   const int tid = threadIdx.x;
-  const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;       // digits of 11, 11 and 10 bits
-  const int nb = pass == 2 ? 1024 : 2048;
   const int b0 = nb - 1 - 2 * tid, b1 = nb - 2 - 2 * tid;      // scanning threads in order walks the bins downwards
   uint32_t total;
   const uint32_t above = block_exclusive_scan(c0 + c1, sh.wave_tot[0], &total);
@@ -344,21 +359,20 @@ __device__ __forceinline__ uint32_t decide_from_counts(SelShared &sh, int pass, 
   return in_bin;
 }
 
-// The same after histogram_pass for digit `pass`: the counts come from the LDS histogram.
-__device__ __forceinline__ uint32_t decide_digit(SelShared &sh, int pass, uint32_t &prefix, uint32_t &mask,
+// The same after histogram_pass for that digit: the counts come from the LDS histogram.
+__device__ __forceinline__ uint32_t decide_digit(SelShared &sh, int shift, int nb, uint32_t &prefix, uint32_t &mask,
                                                  uint32_t &remaining) {
   const int tid = threadIdx.x;
-  const int nb = pass == 2 ? 1024 : 2048;
   const int b0 = nb - 1 - 2 * tid, b1 = nb - 2 - 2 * tid;
   const bool neg = (prefix & 0x80000000u) == 0;
-  const int r0 = raw_digit(b0, pass, nb, neg), r1 = raw_digit(b1, pass, nb, neg);
+  const int r0 = raw_digit(b0, shift == 21, nb, neg), r1 = raw_digit(b1, shift == 21, nb, neg);
   uint32_t c0 = 0, c1 = 0;
 #pragma unroll
   for (int cp = 0; cp < kHistCopies; ++cp) {
     if (b0 >= 0) c0 += sh.hist[cp * 2048 + r0];
     if (b1 >= 0) c1 += sh.hist[cp * 2048 + r1];
   }
-  return decide_from_counts(sh, pass, c0, c1, prefix, mask, remaining);
+  return decide_from_counts(sh, shift, nb, c0, c1, prefix, mask, remaining);
 }
 
 // True when keys that start with the `bits` leading bits of `prefix` may belong to infinities or NaNs.
@@ -602,7 +616,16 @@ __device__ __forceinline__ void select_in_registers(const float *__restrict__ x,
     remaining = sh.found[level][1];
     return sh.found[level][0];
   };
+  uint32_t d0 = 0;
+  int low = 7;                                                  // bits of the key below the second digit
+  if (first_digit != nullptr) {
+    d0 = decide(0, b0, b1, c0, c1);
+    if (inside_window(d0)) d0 = window_prefix(d0) >> kWinShift;
+    else first_digit = nullptr;
+  }
   if (first_digit == nullptr) {
+    low = 10;
+    remaining = (uint32_t)count;
     for (int b = tid; b < kHistCopies * kRegStride; b += kSelThreads) sh.first[b] = 0;
     __syncthreads();
     uint32_t *h = sh.first + (tid % kHistCopies) * kRegStride;
@@ -614,35 +637,36 @@ __device__ __forceinline__ void select_in_registers(const float *__restrict__ x,
           if ((uint32_t)(r.j0 + 256 * i + c) < (uint32_t)m) atomicAdd(&h[r.key[4 * i + c] >> 21], 1u);
       }
     __syncthreads();
+    c0 = c1 = 0;
 #pragma unroll
     for (int cp = 0; cp < kHistCopies; ++cp) { c0 += sh.first[cp * kRegStride + b0]; c1 += sh.first[cp * kRegStride + b1]; }
+    d0 = decide(0, b0, b1, c0, c1);                             // (its barriers also order the clearing)
   }
-  const uint32_t d0 = decide(0, b0, b1, c0, c1);                // (its barriers also order the clearing)
   uint32_t *h2 = sh.second + (tid % kRegCopies) * kRegStride, *h3 = sh.third + (tid % kRegCopies) * (1024 + 8);
 #pragma unroll
   for (int i = 0; i < kRegIters; ++i)
     if (i < r.n_it) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        if (r.key[4 * i + c] >> 21 == d0) atomicAdd(&h2[(r.key[4 * i + c] >> 10) & 2047u], 1u);
+        if (r.key[4 * i + c] >> (low + 11) == d0) atomicAdd(&h2[(r.key[4 * i + c] >> low) & 2047u], 1u);
     }
   __syncthreads();
   c0 = c1 = 0;
 #pragma unroll
   for (int cp = 0; cp < kRegCopies; ++cp) { c0 += sh.second[cp * kRegStride + b0]; c1 += sh.second[cp * kRegStride + b1]; }
-  const uint32_t p22 = (d0 << 11) | decide(1, b0, b1, c0, c1);
+  const uint32_t p2 = (d0 << 11) | decide(1, b0, b1, c0, c1);
 #pragma unroll
   for (int i = 0; i < kRegIters; ++i)
     if (i < r.n_it) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        if (r.key[4 * i + c] >> 10 == p22) atomicAdd(&h3[r.key[4 * i + c] & 1023u], 1u);
+        if (r.key[4 * i + c] >> low == p2) atomicAdd(&h3[r.key[4 * i + c] & ((1u << low) - 1u)], 1u);
     }
   __syncthreads();
   c0 = 0;
 #pragma unroll
   for (int cp = 0; cp < kRegCopies; ++cp) c0 += sh.third[cp * (1024 + 8) + 1023 - tid];
-  const uint32_t thr = (p22 << 10) | decide(2, 1023 - tid, 0, c0, 0u);
+  const uint32_t thr = (p2 << low) | decide(2, 1023 - tid, 0, c0, 0u);
   emit_from_registers(r, m, thr, remaining, out, sh.wave_tot[3]);
 }
 
@@ -670,6 +694,7 @@ constexpr int kWaveTileVec = 64 * kSelVec;                       // 128-bit vect
 constexpr int kFastMaxVec = (kFastSlots - 2) * kWaveTileVec * kSelWaves;
 constexpr int kFastRanges = kFastSlots * kSelWaves;
 constexpr int kCandCap = 4096;                                   // candidates the LDS list holds
+constexpr int kRankCap = 64;                                     // candidates ranked by comparing them with each other
 
 struct FastShared {
   uint32_t marks[kFastSlots][kSelThreads + 1];   // per thread and slot: winner bits (low 16) and candidate bits, later
@@ -683,12 +708,14 @@ struct FastShared {
   uint32_t range_sel[kFastRanges + 1];        // selected candidates before each range (wavefront-major)
   uint32_t wave_cnt[kSelWaves];               // winners (low 16 bits) and candidates per wavefront
   uint32_t wave_tot[2][kSelWaves];
-  uint32_t found[2];
+  uint32_t found[3];
+  uint32_t n_equal;
+  alignas(16) uint32_t rank[kRankCap];        // candidates that share the second digit too: the rest of the key, reversed, and the list position
 };
 constexpr size_t kSelLdsBytes = sizeof(FastShared) > sizeof(SelShared) ? sizeof(FastShared) : sizeof(SelShared);
 static_assert(sizeof(RegShared) <= kSelLdsBytes, "one LDS block serves every way of selecting");
 
-// Smallest and largest float whose ordered key starts with the `bits` (11 or 22) leading bits of
+// Smallest and largest float whose ordered key starts with the `bits` (11, 14, 22 or 25) leading bits of
 // `prefix`.  Ranges that hold NaN patterns are cut at the infinities, and a range that would end at
 // -0 ends at the largest negative number instead (zero of either sign has the key of +0).
 __device__ __forceinline__ void prefix_bounds(uint32_t prefix, int bits, float *lo, float *hi) {
@@ -703,7 +730,98 @@ __device__ __forceinline__ void prefix_bounds(uint32_t prefix, int bits, float *
   }
 }
 
-// The threshold's key starts with the `bits` (11: one digit decided, 22: two) leading bits of
+// The list fs.ckey[0..nc) of candidates in index order shares all but the `open` last bits of `prefix` (two digits, 11 + 10 or
+// 11 + 7 bits, or one, 10 or 7): finds the take-th largest of them by those bits and calls chosen(c, pos) for the take
+// largest, ties to the front of the list, pos = 0, 1, ... in list order.  `chosen` may overwrite fs.ckey[0..pos].
+// Begins with a barrier that the list's last writes are ordered by; returns min(take, nc).  hist_is_clear: fs.hist is zero.
+template <typename F>
+__device__ __forceinline__ uint32_t select_candidates(FastShared &fs, int nc, uint32_t prefix, int open, uint32_t take, bool hist_is_clear,
+                                                      F chosen) {
+  const int tid = threadIdx.x;
+  const uint32_t r = min(take, (uint32_t)nc);
+  int buf = 0;
+  if (nc > 0) {
+    const bool two = open > 10;                    // otherwise the second digit is part of the prefix
+    const int low = two ? open - 11 : open;
+    const uint32_t low_mask = (1u << low) - 1u;
+    uint32_t total, d1 = (prefix >> low) & 2047u, r1 = r, in_bin = (uint32_t)nc;
+    if (two) {
+      if (!hist_is_clear) for (int b = tid; b < 2048; b += kSelThreads) fs.hist[b] = 0;
+      __syncthreads();
+      for (int c = tid; c < nc; c += kSelThreads) atomicAdd(&fs.hist[(fs.ckey[c] >> low) & 2047u], 1u);
+      __syncthreads();
+      const int b0 = 2047 - 2 * tid, b1 = 2046 - 2 * tid;
+      const uint32_t c0 = fs.hist[b0], c1 = fs.hist[b1];
+      const uint32_t above = block_exclusive_scan(c0 + c1, fs.wave_tot[buf], &total);
+      buf ^= 1;
+      if (above < r && r <= above + c0) { fs.found[0] = (uint32_t)b0; fs.found[1] = r - above; fs.found[2] = c0; }
+      else if (above + c0 < r && r <= above + c0 + c1) { fs.found[0] = (uint32_t)b1; fs.found[1] = r - above - c0; fs.found[2] = c1; }
+      if (tid == 0) fs.n_equal = 0;
+      if (tid < kRankCap) fs.rank[tid] = ~0u;
+      __syncthreads();
+      d1 = fs.found[0]; r1 = fs.found[1]; in_bin = fs.found[2];
+    }
+    // Usually a handful of candidates shares the second digit as well: each of them counts the ones before it.
+    const bool by_rank = two && in_bin <= (uint32_t)kRankCap;
+    uint32_t thr = d1 << low, need_eq = 0;        // by_rank: every key above the digit, none of the digit's by key
+    if (by_rank) {
+      for (int c = tid; c < nc; c += kSelThreads) {
+        const uint32_t k = fs.ckey[c];
+        if (((k >> low) & 2047u) == d1) {
+          fs.rank[atomicAdd(&fs.n_equal, 1u)] = (low_mask - (k & low_mask)) << 16 | (uint32_t)c;      // ascending: as selected
+        }
+      }
+      __syncthreads();
+      thr |= low_mask;
+    } else {
+      __syncthreads();
+      fs.hist[tid] = 0;                           // 1024 bins, one per thread
+      __syncthreads();
+      for (int c = tid; c < nc; c += kSelThreads) {
+        const uint32_t k = fs.ckey[c];
+        if (((k >> low) & 2047u) == d1) atomicAdd(&fs.hist[k & low_mask], 1u);
+      }
+      __syncthreads();
+      const int b0 = 1023 - tid;
+      const uint32_t c0 = fs.hist[b0];
+      const uint32_t above = block_exclusive_scan(c0, fs.wave_tot[buf], &total);
+      buf ^= 1;
+      if (above < r1 && r1 <= above + c0) { fs.found[0] = (uint32_t)b0; fs.found[1] = r1 - above; }
+      __syncthreads();
+      thr |= fs.found[0];
+      need_eq = fs.found[1];
+    }
+
+    // selected candidates, in list (= index) order (position <= list position, and every key of a round is
+    // read before the round's scan)
+    uint32_t run_sg = 0, run_eq = 0;
+    for (int c0 = 0; c0 < nc; c0 += kSelThreads) {
+      const int c = c0 + tid;
+      const uint32_t open_bits = c < nc ? fs.ckey[c] & ((2048u << low) - 1u) : 0u;
+      bool is_gt = c < nc && open_bits > thr;
+      const bool is_eq = !by_rank && c < nc && open_bits == thr;
+      if (by_rank && c < nc && open_bits >> low == d1) {
+        const uint32_t mine = (low_mask - (open_bits & low_mask)) << 16 | (uint32_t)c;
+        uint32_t before = 0;                       // larger keys of the digit, and equal ones to the front
+#pragma unroll 2
+        for (uint32_t e = 0; e < in_bin; e += 4) {
+          const uint4 v = *reinterpret_cast<const uint4 *>(&fs.rank[e]);        // what lies behind the list is larger
+          before += (v.x < mine) + (v.y < mine) + (v.z < mine) + (v.w < mine);
+        }
+        is_gt = before < r1;
+      }
+      const uint32_t before = block_exclusive_scan((is_gt ? 1u : 0u) | (is_eq ? 1u << 16 : 0u), fs.wave_tot[buf], &total);
+      buf ^= 1;
+      const uint32_t eq_b = run_eq + (before >> 16);
+      if (is_gt || (is_eq && eq_b < need_eq)) chosen(c, run_sg + (before & 0xffffu) + min(eq_b, need_eq));
+      run_sg += total & 0xffffu;
+      run_eq += total >> 16;
+    }
+  }
+  return r;
+}
+
+// The threshold's key starts with the `bits` (11 or 14: one digit decided, 22 or 25: two) leading bits of
 // `prefix`.  Writes the `take` largest of the entries whose key starts the same way plus every
 // larger entry, indices ascending, ties to the lower index (see above).  rs.nv <= kFastMaxVec and
 // at most kCandCap entries share the prefix.
@@ -838,68 +956,14 @@ __device__ __forceinline__ void select_after_prefix(const float *__restrict__ x,
   const int nc = (int)min(c_all, (uint32_t)kCandCap);
   for (int c = tid; c < nc; c += kSelThreads) fs.ckey[c] = ordered_key(x[fs.cidx[c]]);   // read again: cache hits
 
-  // ---- 3. the rest of the threshold: the r-th largest of the nc listed keys, by the digits that
-  // are still open (11 and 10 bits, or the last 10 bits only)
-  const uint32_t r = min(take, (uint32_t)nc);
-  int buf = 0;
-  if (nc > 0) {
-    uint32_t total;
-    if (bits == 11) {
-      for (int b = tid; b < 2048; b += kSelThreads) fs.hist[b] = 0;
-      __syncthreads();
-      for (int c = tid; c < nc; c += kSelThreads) atomicAdd(&fs.hist[(fs.ckey[c] >> 10) & 2047u], 1u);
-      __syncthreads();
-      const int b0 = 2047 - 2 * tid, b1 = 2046 - 2 * tid;
-      const uint32_t c0 = fs.hist[b0], c1 = fs.hist[b1];
-      const uint32_t above = block_exclusive_scan(c0 + c1, fs.wave_tot[buf], &total);
-      buf ^= 1;
-      if (above < r && r <= above + c0) { fs.found[0] = (uint32_t)b0; fs.found[1] = r - above; }
-      else if (above + c0 < r && r <= above + c0 + c1) { fs.found[0] = (uint32_t)b1; fs.found[1] = r - above - c0; }
-    } else if (tid == 0) {
-      fs.found[0] = (prefix >> 10) & 2047u;     // the second digit is part of the prefix
-      fs.found[1] = r;
-    }
-    __syncthreads();
-    const uint32_t d1 = fs.found[0], r1 = fs.found[1];
-    fs.hist[tid] = 0;                           // 1024 bins, one per thread
-    __syncthreads();
-    for (int c = tid; c < nc; c += kSelThreads) {
-      const uint32_t k = fs.ckey[c];
-      if (((k >> 10) & 2047u) == d1) atomicAdd(&fs.hist[k & 1023u], 1u);
-    }
-    __syncthreads();
-    {
-      const int b0 = 1023 - tid;
-      const uint32_t c0 = fs.hist[b0];
-      const uint32_t above = block_exclusive_scan(c0, fs.wave_tot[buf], &total);
-      buf ^= 1;
-      if (above < r1 && r1 <= above + c0) { fs.found[0] = (uint32_t)b0; fs.found[1] = r1 - above; }
-    }
-    __syncthreads();
-    const uint32_t thr21 = (d1 << 10) | fs.found[0], need_eq = fs.found[1];
-
-    // selected candidates, in list (= index) order; their indices overwrite the keys (position <=
-    // list position, and every key of a round is read before the round's scan)
-    uint32_t run_sg = 0, run_eq = 0;
-    for (int c0 = 0; c0 < nc; c0 += kSelThreads) {
-      const int c = c0 + tid;
-      const uint32_t k21 = c < nc ? fs.ckey[c] & 0x1fffffu : 0u;
-      const bool is_gt = c < nc && k21 > thr21, is_eq = c < nc && k21 == thr21;
-      const uint32_t before = block_exclusive_scan((is_gt ? 1u : 0u) | (is_eq ? 1u << 16 : 0u), fs.wave_tot[buf], &total);
-      buf ^= 1;
-      const uint32_t eq_b = run_eq + (before >> 16);
-      if (is_gt || (is_eq && eq_b < need_eq)) {
-        const uint32_t pos = run_sg + (before & 0xffffu) + min(eq_b, need_eq);
-        const int32_t j = fs.cidx[c];
-        const uint32_t gr = fs.cgtb[c];
-        fs.ckey[pos] = (uint32_t)j;
-        out[(gr & 0xffffffu) + pos] = j;
-        atomicAdd(&fs.range_sel[gr >> 24], 1u);
-      }
-      run_sg += total & 0xffffu;
-      run_eq += total >> 16;
-    }
-  }
+  // ---- 3. and the selected candidates
+  select_candidates(fs, nc, prefix, 32 - bits, take, false, [&](int c, uint32_t pos) {
+    const int32_t j = fs.cidx[c];
+    const uint32_t gr = fs.cgtb[c];
+    fs.ckey[pos] = (uint32_t)j;
+    out[(gr & 0xffffffu) + pos] = j;
+    atomicAdd(&fs.range_sel[gr >> 24], 1u);
+  });
   __syncthreads();
   // counts per range -> selected candidates before each range (one wavefront, 4 ranges per lane)
   static_assert(kFastRanges == 256, "four ranges per lane");
@@ -947,7 +1011,7 @@ __device__ __forceinline__ void select_after_prefix(const float *__restrict__ x,
 
 // Writes the `count` (1 <= count <= m) indices of the largest x[0..m) to out, ascending,
 // equal values taken from the low-index end.  lds: kSelLdsBytes of LDS.  first_digit, when not
-// null: the row's histogram of the first digit (2048 counters by ordered digit), already counted.
+// null: how often each value of the row's window_digit occurs (2048 counters), already counted.
 __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int m, int count,
                                                int32_t *__restrict__ out, unsigned char *lds,
                                                const uint32_t *__restrict__ first_digit = nullptr) {
@@ -958,26 +1022,37 @@ __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int 
   SelShared &sh = *reinterpret_cast<SelShared *>(lds);
   const RowSplit rs = split_row(x, m);
   uint32_t prefix = 0, mask = 0, remaining = (uint32_t)count;
-  uint32_t in_bin;
+  uint32_t in_bin = 0;
+  int open = 32;                                // bits of the threshold's key that are not decided
   if (first_digit != nullptr) {
     const int tid = threadIdx.x;
-    in_bin = decide_from_counts(sh, 0, first_digit[2047 - 2 * tid], first_digit[2046 - 2 * tid], prefix, mask, remaining);
-  } else {
-    histogram_pass(x, m, rs, prefix, mask, 21, 2048, sh);
-    in_bin = decide_digit(sh, 0, prefix, mask, remaining);
+    in_bin = decide_from_counts(sh, 0, 2048, first_digit[2047 - 2 * tid], first_digit[2046 - 2 * tid], prefix, mask, remaining);
+    if (inside_window(prefix)) {
+      open = kWinShift;
+      prefix = window_prefix(prefix);
+      mask = ~0u << kWinShift;
+    } else {
+      prefix = mask = 0;
+      remaining = (uint32_t)count;
+    }
   }
-  if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 11)) {
-    select_after_prefix(x, m, rs, prefix, 11, remaining, out, *reinterpret_cast<FastShared *>(lds));
-    return;
+  if (open == 32) {
+    open = 21;
+    histogram_pass(x, m, rs, prefix, mask, open, 2048, sh);
+    in_bin = decide_digit(sh, open, 2048, prefix, mask, remaining);
   }
-  histogram_pass(x, m, rs, prefix, mask, 10, 2048, sh);
-  in_bin = decide_digit(sh, 1, prefix, mask, remaining);
-  if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 22)) {
-    select_after_prefix(x, m, rs, prefix, 22, remaining, out, *reinterpret_cast<FastShared *>(lds));
-    return;
+  for (;;) {
+    if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 32 - open)) {
+      select_after_prefix(x, m, rs, prefix, 32 - open, remaining, out, *reinterpret_cast<FastShared *>(lds));
+      return;
+    }
+    if (open <= 10) break;
+    open -= 11;
+    histogram_pass(x, m, rs, prefix, mask, open, 2048, sh);
+    in_bin = decide_digit(sh, open, 2048, prefix, mask, remaining);
   }
-  histogram_pass(x, m, rs, prefix, mask, 0, 1024, sh);
-  (void)decide_digit(sh, 2, prefix, mask, remaining);
+  histogram_pass(x, m, rs, prefix, mask, 0, 1 << open, sh);
+  (void)decide_digit(sh, 0, 1 << open, prefix, mask, remaining);
   emit_selected(x, m, rs, prefix, remaining, out, sh);
 }
 
@@ -1055,7 +1130,7 @@ __global__ __launch_bounds__(kSelThreads) void msel_hist_kernel(Dims d, SeqTab t
   for (int b = tid; b < 2048; b += kSelThreads) {       // b: ordered digit
     uint32_t c = 0;
     if (b < nb) {
-      const int rd = raw_digit(b, level, nb, neg);
+      const int rd = raw_digit(b, level == 0, nb, neg);
 #pragma unroll
       for (int cp = 0; cp < kHistCopies; ++cp) c += sh.hist[cp * 2048 + rd];
     }
@@ -1134,6 +1209,176 @@ __global__ __launch_bounds__(kSelThreads) void msel_emit_kernel(Dims d, SeqTab t
 }
 
 // ----------------------------------------------------------------------------------
+// few rows, first digit counted: a row ranked by several workgroups in one launch
+// ----------------------------------------------------------------------------------
+// One workgroup reads and classifies a row at what one CU's vector ALU does (9.5 us for 128K entries, and as much again for
+// the positions), so a call with fewer rows than CUs leaves most of them idle.  Here P workgroups share a row.  Every one
+// of them decides the first digit from the row's counters (which the pooling kernel filled), splits its part of the row
+// into winners (entries above the digit) and candidates (entries with it) and leaves both lists, in index order,
+// in memory.  The one that arrives last reads the lists, finds the rest of the threshold among the candidates and
+// places everything.  Nobody waits for another workgroup.
+// The workgroups run on different XCDs, whose L2s are not coherent.  Lists, counts and the arrival counter are therefore
+// written and read by agent-scope atomics only, which go past the L2; a workgroup arrives after a wait for its stores and
+// a barrier, and the last one reads after its own arrival.  Ordering the counter itself (acquire-release) would have every
+// workgroup write back and invalidate its L2: the arrival then takes 4.7 instead of 1 us where 256 workgroups do it.
+// Rows in which more than kCandCap entries share the digit, or more than kPartsMaxCount are to be selected, are
+// ranked by the first of their workgroups alone.
+constexpr int kPartTile = 4 * kSelThreads;        // entries a workgroup classifies per step
+constexpr int kPartsMax = 64;                     // workgroups per row (one wavefront adds their counts)
+constexpr int kPartsMaxCount = 8192;              // winners the LDS list holds
+static_assert(offsetof(FastShared, hist) >= sizeof(SelShared), "the two overlap in LDS");
+static_assert(sizeof(FastShared::marks) >= kPartsMaxCount * sizeof(uint32_t), "LDS of the last workgroup");
+
+__device__ __forceinline__ void store_shared(uint32_t *p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t load_shared(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// x[0..m): the row; first_digit: its 2048 counters; list: scratch for m words; counts: 2 * P words of scratch;
+// arrived: a zeroed counter, of no use afterwards; part_len: a multiple of kPartTile, P * part_len >= m + 3.
+__device__ __forceinline__ void select_in_parts(const float *__restrict__ x, int m, int count, int32_t *__restrict__ out,
+                                                const uint32_t *__restrict__ first_digit, int P, int part, int part_len,
+                                                uint32_t *list, uint32_t *counts, uint32_t *arrived,
+                                                unsigned char *lds) {
+  SelShared &sh = *reinterpret_cast<SelShared *>(lds);
+  FastShared &fs = *reinterpret_cast<FastShared *>(lds);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // parts are cut at 16-byte boundaries: entry j of the row is entry j + shift of the aligned row
+  int shift;
+  (void)row_vectors(x, m, &shift);
+  auto begin_of = [&](int q) { return min(max(q * part_len - shift, 0), m); };
+  const int begin = begin_of(part), end = begin_of(part + 1);
+  auto load4 = [&](int j) {
+    if (j >= 0 && j + 3 < m) return *reinterpret_cast<const float4 *>(x + j);
+    float4 v;
+    v.x = j >= 0 && j < m ? x[j] : 0.f;
+    v.y = j + 1 >= 0 && j + 1 < m ? x[j + 1] : 0.f;
+    v.z = j + 2 >= 0 && j + 2 < m ? x[j + 2] : 0.f;
+    v.w = j + 3 >= 0 && j + 3 < m ? x[j + 3] : 0.f;
+    return v;
+  };
+  float4 next = load4(part * part_len - shift + 4 * tid);    // on its way while the digit is decided
+  for (int b = tid; b < 2048; b += kSelThreads) fs.hist[b] = 0;           // for the last workgroup (lies behind sh)
+  uint32_t prefix = 0, mask = 0, take = (uint32_t)count;
+  const uint32_t n_cand = decide_from_counts(sh, 0, 2048, first_digit[2047 - 2 * tid], first_digit[2046 - 2 * tid], prefix, mask, take);
+  const uint32_t n_win = (uint32_t)count - take;
+  if (!inside_window(prefix) || n_cand > (uint32_t)kCandCap || count > kPartsMaxCount) {
+    if (part == 0) select_top_row(x, m, count, out, lds, first_digit);
+    return;
+  }
+  prefix = window_prefix(prefix);
+  const uint32_t d0 = prefix >> kWinShift;
+  uint32_t run = 0;                                          // winners (low half) and candidates of the part so far
+  for (int j0 = part * part_len - shift, buf = 0; j0 < end; j0 += kPartTile, buf ^= 1) {
+    const int j = j0 + 4 * tid;
+    const uint32_t digit[4] = {ordered_key(next.x) >> kWinShift, ordered_key(next.y) >> kWinShift,
+                               ordered_key(next.z) >> kWinShift, ordered_key(next.w) >> kWinShift};
+    next = load4(j + kPartTile);
+    uint32_t win = 0, cand = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const bool inside = j + c >= begin && j + c < end;
+      win |= inside && digit[c] > d0 ? 1u << c : 0u;
+      cand |= inside && digit[c] == d0 ? 1u << c : 0u;
+    }
+    uint32_t total;
+    const uint32_t before = run + block_exclusive_scan(__popc(win) | (__popc(cand) << 16), sh.wave_tot[buf], &total);
+    uint32_t w_at = before & 0xffffu, c_at = before >> 16;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if ((win >> c) & 1u) store_shared(&list[begin + (int)w_at++], (uint32_t)(j + c));
+      if ((cand >> c) & 1u) store_shared(&list[end - 1 - (int)c_at++], (uint32_t)(j + c));
+    }
+    run += total;
+  }
+  if (tid == 0) {
+    store_shared(&counts[2 * part], run & 0xffffu);
+    store_shared(&counts[2 * part + 1], run >> 16);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // every wavefront's stores are out before the arrival
+  __syncthreads();
+  if (tid == 0) fs.found[0] = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (fs.found[0] != (uint32_t)(P - 1)) return;
+
+  // ---- the last one: lists of all parts into LDS, wavefront w those of the parts w, w + 16, ...
+  uint32_t *winner = &fs.marks[0][0];
+  {
+    // every wavefront adds the parts' counts; the first entries of its first lists are requested along with them
+    const uint32_t nw = lane < P ? load_shared(&counts[2 * lane]) : 0u, nc = lane < P ? load_shared(&counts[2 * lane + 1]) : 0u;
+    constexpr int kAhead = 2;
+    uint32_t w_head[kAhead], c_head[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int q = wv + u * kSelWaves, qb = begin_of(q), qe = begin_of(q + 1);      // an empty range where q >= P
+      w_head[u] = qb + lane < qe ? load_shared(&list[qb + lane]) : 0u;               // (may be no entry: not used then)
+      c_head[u] = qe - 1 - lane >= qb ? load_shared(&list[qe - 1 - lane]) : 0u;
+    }
+    uint32_t all;
+    const uint32_t w_before = wave_exclusive_scan(nw, &all), c_before = wave_exclusive_scan(nc, &all);
+    auto add_candidate = [&](int at, uint32_t j) {
+      fs.cidx[at] = (int32_t)j;
+      fs.ckey[at] = ordered_key(x[j]);
+    };
+#pragma unroll
+    for (int u = 0; u < kPartsMax / kSelWaves; ++u) {
+      const int q = wv + u * kSelWaves;
+      if (q >= P) break;
+      const int n_w = __builtin_amdgcn_readlane((int)nw, q), n_c = __builtin_amdgcn_readlane((int)nc, q);
+      const int w0 = __builtin_amdgcn_readlane((int)w_before, q), c0 = __builtin_amdgcn_readlane((int)c_before, q);
+      const int qb = begin_of(q), qe = begin_of(q + 1);
+      if (u < kAhead) {
+        if (lane < n_w) winner[w0 + lane] = w_head[u < kAhead ? u : 0];
+        if (lane < n_c) add_candidate(c0 + lane, c_head[u < kAhead ? u : 0]);
+      }
+      for (int i = lane + (u < kAhead ? 64 : 0); i < n_w; i += 64) winner[w0 + i] = load_shared(&list[qb + i]);
+      for (int i = lane + (u < kAhead ? 64 : 0); i < n_c; i += 64) add_candidate(c0 + i, load_shared(&list[qe - 1 - i]));
+    }
+  }
+  __syncthreads();
+  auto first_not_below = [](const uint32_t *a, int n, uint32_t v) {       // number of entries of a[0..n) below v
+    int lo = 0, hi = n;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (a[mid] < v) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+  };
+  const int n_sel = (int)select_candidates(fs, (int)n_cand, prefix, kWinShift, take, true, [&](int c, uint32_t pos) {
+    const uint32_t j = (uint32_t)fs.cidx[c];
+    fs.ckey[pos] = j;
+    out[pos + (uint32_t)first_not_below(winner, (int)n_win, j)] = (int32_t)j;
+  });
+  __syncthreads();
+  for (int i = tid; i < (int)n_win; i += kSelThreads) out[i + first_not_below(fs.ckey, n_sel, winner[i])] = (int32_t)winner[i];
+}
+
+// Scratch of select_in_parts for a call's rows: the lists lie over the score planes (a row's list where the row's scores are in
+// the first plane), counts and arrival counters over the partial pairs of the row statistics; both are read no more by then.
+struct PartsArgs {
+  uint32_t *list, *counters;
+  int P, part_len;
+};
+
+__global__ __launch_bounds__(kSelThreads) void select_parts_kernel(Dims d, SeqTab t, const float *__restrict__ pooled,
+                                                                   int32_t *__restrict__ idx,
+                                                                   const uint32_t *__restrict__ hist0, PartsArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char sel_lds[];
+  const int row = blockIdx.x / a.P, part = blockIdx.x - row * a.P;
+  const RowRef r = row_of(d, t, row, pooled, idx);
+  if (part == 0) {
+    for (int x = threadIdx.x; x < d.w; x += kSelThreads) r.out[r.count + x] = r.m + x;   // window, last
+    for (int x = r.count + d.w + threadIdx.x; x < r.n_keep; x += kSelThreads) r.out[x] = -1;   // unused slots
+  }
+  if (r.count > 0)
+    select_in_parts(r.x, r.m, r.count, r.out, hist0 + (int64_t)row * 2048, a.P, part, a.part_len, a.list + (r.x - pooled),
+                    a.counters + (int64_t)row * kPartsWords + 64, a.counters + (int64_t)row * kPartsWords, sel_lds);
+}
+
+// ----------------------------------------------------------------------------------
 // layer budget shared across KV heads
 // ----------------------------------------------------------------------------------
 // The heads' counts follow from one layer-wide threshold: the largest key t for which
@@ -1171,7 +1416,7 @@ __global__ __launch_bounds__(kSelThreads) void ada_hist_kernel(Dims d, SeqTab t,
   for (int b = tid; b < 2048; b += kSelThreads) {       // b: ordered digit
     uint32_t c = 0;
     if (b < nb) {
-      const int r = raw_digit(b, level, nb, neg);
+      const int r = raw_digit(b, level == 0, nb, neg);
 #pragma unroll
       for (int cp = 0; cp < kHistCopies; ++cp) c += sh.hist[cp * 2048 + r];
     }
@@ -1355,8 +1600,31 @@ __global__ __launch_bounds__(kSelThreads) void expand_kernel(
 
 }  // namespace
 
+// How many workgroups share a row of the fused calls' selection: as many as the CUs allow, a part not below 4096 entries,
+// for up to 128 rows (with more there is no CU left over) longer than one workgroup holds in registers.  Selection kernel, one
+// workgroup per row / several: 8 rows of 16K 11.7 / 11.3 us, 20K 20.2 / 11.7, 32K 16.6 / 10.3, 128K 33.8 / 12.6; 32 rows of
+// 32K 20.6 / 10.6, 60K 20.6 / 13.2; 64 rows of 32K 22.9 / 13.7, 128K 51.7 / 28; 128 rows of 32K 28.1 / 19.9, 64K 35.0 / 30.9,
+// 128K 54.3 / 47.2; 8 rows of 64K, 8192 kept 24.4 / 22.8.  Of the 12.6 us, at 8 rows of 128K: first digit 2.2, parts and
+// their stores 2.4, arrival 0.5, lists 2.3, threshold 3.5, the rest of the output 1.5 (a 1024-thread barrier is 0.1 to 0.2).
+constexpr int kPartsMaxRows = 128, kPartsMinKeys = 16384, kPartsWorkgroups = 256;
+SelectParts select_parts_of(const Plan &pl) {
+  const Dims &d = pl.d;
+  const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
+  int max_m = 0, most = 0;
+  for (int s = 0; s < d.S; ++s) {
+    max_m = std::max(max_m, pl.t.cu[s + 1] - pl.t.cu[s] - d.w);
+    most = std::max(most, pl.t.ck[s + 1] - pl.t.ck[s] - d.w);
+  }
+  SelectParts sp = {1, 0};
+  if (rows > kPartsMaxRows || max_m < kPartsMinKeys || most > kPartsMaxCount) return sp;
+  const int64_t want = std::min<int64_t>(kPartsMax, kPartsWorkgroups / rows);
+  sp.part_len = (int)align_up((max_m + 3 + want - 1) / want, kPartTile);
+  sp.P = (max_m + 3 + sp.part_len - 1) / sp.part_len;
+  return sp;
+}
+
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
-                              hipStream_t st, uint32_t *hist0) {
+                              hipStream_t st, uint32_t *hist0, uint32_t *arrived) {
   const Dims &d = pl.d;
   int max_n = 0;
   for (int s = 0; s < d.S; ++s) max_n = max(max_n, pl.t.cu[s + 1] - pl.t.cu[s]);
@@ -1370,7 +1638,7 @@ hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, f
   pm.outer_max = d.reduce_max && d.head_max;
   pm.plane_stride = (int64_t)d.L * d.Hkv * d.T;
   hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)blocks), dim3(kPoolThreads), 0, st, d, pl.t,
-                     pm, planes, raw, pooled, tiles, hist0);
+                     pm, planes, raw, pooled, tiles, hist0, arrived);
   return hipGetLastError();
 }
 
@@ -1402,9 +1670,18 @@ hipError_t launch_pool_row(const float *in, float *out, int32_t n_in, int32_t n_
 }
 
 hipError_t launch_select(const Plan &pl, const float *pooled, int32_t *idx, uint32_t *hist, uint32_t *state,
-                         hipStream_t st, const uint32_t *hist0) {
+                         hipStream_t st, const uint32_t *hist0, uint32_t *list, uint32_t *counters) {
   const Dims &d = pl.d;
   const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
+  const SelectParts sp = select_parts_of(pl);
+  if (sp.P > 1 && hist0 != nullptr && list != nullptr && counters != nullptr) {
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(select_parts_kernel), kSelLdsBytes);
+    if (e != hipSuccess) return e;
+    const PartsArgs a = {list, counters, sp.P, sp.part_len};
+    hipLaunchKernelGGL(select_parts_kernel, dim3((unsigned)(rows * sp.P)), dim3(kSelThreads), kSelLdsBytes, st, d, pl.t,
+                       pooled, idx, hist0, a);
+    return hipGetLastError();
+  }
   if (pl.sel_parts > 1 && hist != nullptr && state != nullptr) {
     const int P = pl.sel_parts;
     const dim3 wide((unsigned)(rows * P)), one((unsigned)rows), block(kSelThreads);

@@ -152,7 +152,7 @@ __host__ __device__ inline bool decode_row(const Dims &d, const ScoreGeom &g, in
 // hist0, when not null: [rows][2048] zeroed counters; the kernel adds the first-digit histogram of
 // every row's pooled scores (the non-window entries), for launch_select.
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
-                              hipStream_t st, uint32_t *hist0 = nullptr);
+                              hipStream_t st, uint32_t *hist0 = nullptr, uint32_t *arrived = nullptr);
 // single output row summing every plane of a one-sequence call (prompt-token selection)
 hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *raw, float *pooled,
                                   hipStream_t st);
@@ -161,9 +161,16 @@ hipError_t launch_pool_row(const float *in, float *out, int32_t n_in, int32_t n_
                            hipStream_t st);
 // hist / state: scratch of the split-row path (off_sel_hist, off_sel_state); with either null, or when
 // the plan does not split rows (sel_parts == 1), every row is ranked by one workgroup.
-// hist0, when not null: the rows' first-digit histograms from launch_reduce_pool (one-workgroup path).
+// hist0, when not null: the rows' first-digit histograms from launch_reduce_pool.  With them, and with list (a word per
+// score, laid out like pooled) and counters (kPartsWords per row: an arrival counter, which launch_reduce_pool zeroes, and from
+// word 64 on 2 * P counts; rows whose counters share a cache line would wait for each other's atomics), several workgroups
+// share a row where select_parts_of says so.
+constexpr int kPartsWords = 256;
+struct SelectParts { int32_t P, part_len; };
+SelectParts select_parts_of(const Plan &pl);
 hipError_t launch_select(const Plan &pl, const float *pooled, int32_t *idx, uint32_t *hist, uint32_t *state,
-                         hipStream_t st, const uint32_t *hist0 = nullptr);
+                         hipStream_t st, const uint32_t *hist0 = nullptr, uint32_t *list = nullptr,
+                         uint32_t *counters = nullptr);
 // Shared layer budget: head offsets from a layer-wide threshold, then per-head selection.
 // hist: L*S*Hkv*2048 uint32, state: L*S*(2 + 3*Hkv) uint32 of scratch.
 hipError_t launch_select_ada(const Plan &pl, int32_t c_floor, const float *pooled, int32_t *idx,

@@ -1,0 +1,98 @@
+"""Selection inside the fused call where several workgroups share a row: the kept indices are the exact ranking of the
+library's own scores (whole numbers, so every comparison is exact), and the cache holds those rows bit for bit."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from . import test_gpu_parity as parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def S():
+    import paper_2506_08373_amd as S
+    S.load_library()
+    return S
+
+
+def ranked(scores, count):
+    """The count best of a row of fp32 scores by their bits (a positive NaN above everything), ties to the lower index."""
+    bits = (scores + np.float32(0)).view(np.uint32)
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000)).astype(np.int64)
+    return np.sort(np.argsort(-key, kind="stable")[:count])
+
+
+def check(S, q, k, lens, n_window, c_max, pool_k=7, n_in_dev=None):
+    L, T, H, d = k.shape
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=lens, n_window=n_window, pool_k=pool_k, c_max=c_max,
+                                   sm_scale=1.0 / math.sqrt(d), n_in_dev=n_in_dev)
+    KT = S.total_keep(p)
+    ws = parity.alloc_ws(S, p)
+    pooled = torch.empty(L, H * T, device="cuda")
+    idx = torch.full((L, H * KT), -7, dtype=torch.int32, device="cuda")
+    k_out = torch.empty(L, H * KT, d, dtype=k.dtype, device="cuda")
+    S.speckv_score(p, q, k, pooled, None, ws)
+    S.speckv_compress(p, q, k, None, idx, k_out, None, ws)
+    sc, ix, kc, ko = pooled.cpu().numpy(), idx.cpu().numpy(), k.cpu(), k_out.cpu()
+    for layer in range(L):
+        t0 = keep0 = 0
+        for n in lens:
+            live = n if n_in_dev is None else int(n_in_dev)
+            m, keep = live - n_window, min(c_max, n - n_window) + n_window
+            for g in range(H):
+                row = sc[layer, H * t0 + g * n:H * t0 + g * n + m]
+                r0 = H * keep0 + g * keep
+                want = np.concatenate([ranked(row, min(c_max, m)), np.arange(m, live)])
+                got = ix[layer, r0:r0 + keep]
+                assert np.array_equal(got[:len(want)], want), (layer, n, g)
+                assert (got[len(want):] == -1).all()
+                rows = kc[layer, t0 + torch.from_numpy(want), g]
+                assert torch.equal(ko[layer, r0:r0 + len(want)].view(torch.int16), rows.view(torch.int16))
+            t0 += n
+            keep0 += keep
+
+
+def tensors(lens, n_layers=1, n_heads=2, rows=32, seed=3, gain=1.0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    q = torch.randn(n_layers, len(lens), rows, 2 * n_heads, 64, generator=g, device="cuda") * gain
+    k = torch.randn(n_layers, sum(lens), n_heads, 64, generator=g, device="cuda")
+    return q.to(torch.bfloat16), k.to(torch.bfloat16)
+
+
+# the shortest rows of the rule and one entry less; parts of one step of 4096 entries and of two, the last one short; rows
+# that start at every alignment (odd lengths); a batch whose shorter rows leave parts empty; 128 rows and one more
+@pytest.mark.parametrize("lens,n_layers,n_heads,c_max", [
+    ((16399,), 1, 2, 300), ((16400,), 1, 2, 300), ((20501,), 1, 3, 1), ((50003,), 1, 8, 2048), ((65551,), 2, 4, 8192),
+    ((65551,), 1, 1, 8193), ((131085,), 1, 2, 1024), ((40001, 700, 17, 30003), 1, 3, 500), ((17001,), 16, 8, 64),
+    ((17001,), 43, 3, 64)])
+def test_rows_shared_by_workgroups(S, lens, n_layers, n_heads, c_max):
+    q, k = tensors(lens, n_layers, n_heads, gain=2.0)
+    check(S, q, k, lens, 16, c_max)
+
+
+@pytest.mark.parametrize("c_max", [1, 4096, 5000])
+def test_many_equal_scores(S, c_max):
+    """All keys alike: the leading digits hold more entries than the candidate list."""
+    q, k = tensors((33001,))
+    check(S, q, torch.zeros_like(k), (33001,), 16, c_max)
+    k[:, ::7] = 0                                         # pooled with a kernel of 7: plateaus of equal scores everywhere
+    check(S, q, k, (33001,), 16, c_max)
+
+
+def test_scores_that_are_no_numbers(S):
+    q, k = tensors((33001,))
+    k[0, 9000, 0, 0] = math.inf                           # logits of both signs: every score of the head is NaN
+    k[0, 20000:20010, 1] = -1e30 * q[0, 0, 0, 2].sign()   # far below every other
+    check(S, q, k, (33001,), 16, 700)
+
+
+@pytest.mark.parametrize("n_live", [60000, 17003, 900, 16])
+def test_a_length_on_the_device(S, n_live):
+    q, k = tensors((60000,))
+    n_dev = torch.tensor([n_live], dtype=torch.int32, device="cuda")
+    check(S, q, k, (60000,), 16, 1500, n_in_dev=n_dev)
