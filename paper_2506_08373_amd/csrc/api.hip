@@ -24,9 +24,23 @@ constexpr int kSelSplitWorkgroups = 512;            // ... when the call has few
 constexpr int kSelSplitMaxParts = 64;
 constexpr int kChunkMin = 512;                      // shortest chunk
 constexpr int kShortChunkUnits = 8;                 // ... unless the call has no more (layer, head, super-block) units
+constexpr int kShortChunks = 20;                    // ... at most so many a sequence: every workgroup of the column sweep merges their pairs
 constexpr int kChunkSmallCap = 4096;                // longest chunk that small problems are given
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+// Lets heads share row blocks, unless a head takes several super-blocks or is made of whole blocks anyway: where rows are summed
+// over all heads, or heads combined by maximum, it does not matter whose rows a block holds.
+// A group of 4 heads with 65 to 72 rows each has 9 row blocks instead of 12, of which waves share the ninth (split_blocks).  Calls
+// with rows padded per head and whole blocks / packed: prompt compression 32K (65 rows) 357 / 294 us, 2 fp32 layers of 8K, 72
+// rows, 236 / 193; one layer of 60K keys, 19 rows a head 90 / 77 us, 37 rows 104 / 83, 84 rows 140 / 124; groups of 7, 36 rows
+// 100 / 72; heads of 64, 90K keys, 37 rows 129 / 81.
+void pack_rows(const Dims &d, ScoreGeom *g) {
+  if (g->PPH != 1 || d.R == g->Rp || d.R < 2) return;
+  g->pitch = d.R;
+  g->pitch_inv = (uint32_t)(((uint64_t)1 << 32) / (uint32_t)g->pitch + 1);
+  g->packed = (d.M + 31) / 32;
+}
 
 // Fills the dimension and per-sequence tables.  Returns SPECKV_OK or the reason.
 speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call, int32_t top_k) {
@@ -108,6 +122,10 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   } else {                        // one head spread over PPH super-blocks
     g.HPS = 1; g.PPH = (g.Rp + g.RSB - 1) / g.RSB; g.RS = d.G * g.PPH;
   }
+  g.pitch = g.Rp;
+  g.packed = 0;
+  if (!d.reduce_max) pack_rows(d, &g);
+  g.pitch_inv = (uint32_t)(((uint64_t)1 << 32) / (uint32_t)g.pitch + 1);
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
   if (units > (int64_t)1 << 24) return SPECKV_ERR_UNSUPPORTED;       // grid sizes stay far below 2^31
   // Keys [0, tail0) of a sequence are complete tiles visible to every observation row
@@ -186,11 +204,15 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   // 56.7 us with 512 keys each, 36.4 with 128 (its sweeps 19.5 and 21.2 us, then 9.8 and 12.1); one layer of 4K 45.1 us
   // with 512, 38.7 with 256 (13.4 and 14.4, 11.2 and 12.0).  With more units kChunkMin fills the CUs at about 8K keys; there the
   // cut stays independent of the length, so that a length read on the device gives what the host's would, bit for bit.
+  // More than 20 chunks a sequence cost the column sweep more in merged pairs than they gain (one layer of 4K keys, 28 heads in
+  // groups of 7: 48.3 us with 256 keys each, 62.5 with 512, 66.0 with 128).
   if (kc == kChunkMin && units <= kShortChunkUnits) {
     const int tile = rowb <= 128 && g.MB == 1 ? 128 : kt;            // Operand::KT of the scoring kernels
     for (int64_t piece = tile; piece < kChunkMin; piece += tile) {
       cut(piece);
-      if (((int64_t)g.n_fast_chunks + d.S) * units <= kCUs) break;
+      int most = 0;
+      for (int s = 0; s < d.S; ++s) most = std::max(most, t.cc[s + 1] - t.cc[s]);
+      if (((int64_t)g.n_fast_chunks + d.S) * units <= kCUs && most <= kShortChunks) break;
       cut(kChunkMin);
     }
   }
@@ -603,6 +625,7 @@ static speckv_status alg2_plan(const speckv_params *p, int32_t l_skip, Plan *pl,
   if (st != SPECKV_OK) return st;
   pl->d.head_max = 1;
   pl->d.weight_rows = 1;
+  pack_rows(pl->d, &pl->g);
   return SPECKV_OK;
 }
 

@@ -110,7 +110,7 @@ int64_t score_fail_words(const Plan &pl) { return score_chunk_workgroups(pl.d, p
 bool score_uses_qs(const Plan &pl, int pass) {
   ScoreArgs A;
   A.d = pl.d; A.t = pl.t; A.g = pl.g;
-  A.q = nullptr; A.k = nullptr; A.part = nullptr; A.lse = nullptr; A.planes = nullptr; A.lse_in = nullptr; A.chunk_blocks = 0; A.clear = nullptr; A.clear_words = 0; A.fail = nullptr; A.norm_from = kNormMerged;
+  A.q = nullptr; A.k = nullptr; A.part = nullptr; A.lse = nullptr; A.planes = nullptr; A.lse_in = nullptr; A.chunk_blocks = 0; A.clear = nullptr; A.clear_words = 0; A.fail = nullptr; A.norm_from = kNormMerged; A.share = 0;
   return qs_supported(A, pass);
 }
 
@@ -122,6 +122,7 @@ hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *pa
   A.q = (const char *)q; A.k = (const char *)k;
   A.part = part; A.lse = lse; A.planes = planes; A.lse_in = lse_in; A.chunk_blocks = 0;
   A.clear = clear; A.clear_words = clear != nullptr ? clear_words : 0;
+  A.share = A.d.reduce_max == 0 || A.d.head_max != 0;        // a head's own maximum is taken over whole blocks
   A.norm_from = kNormMerged;
   if (!qs_supported(A, 2)) {
     int most = 0;                       // chunks of a sequence

@@ -16,6 +16,7 @@ struct ScoreArgs {
   const char *k;
   float2 *part;     // [unit][chunk][RSB] (max2, sum) per row, unit = (layer, head, row super-block)
   int norm_from;    // where the column sweep takes its row normalisers from: kNorm... below
+  int share;        // the key-tile sweeps let waves share row blocks (split_blocks)
   float *lse;       // [layer][head][seq][RS*RSB] (kNormMerged)
   const float *lse_in;   // optional caller-supplied natural-log normalisers [L][S][R][Hq]
   float *planes;    // [RS][layer][Hkv*T]

@@ -124,9 +124,8 @@ __global__ __launch_bounds__(kQsWaves * 64) void score_qs_kernel(ScoreArgs A) {
 
   // row blocks that hold rows, rounded up to an even count (the loop below is unrolled by two);
   // the rows of the padding block are zero and contribute nothing
-  int nblk;
-  if (A.g.PPH == 1) nblk = min(A.g.HPS, d.G - rs * A.g.HPS) * (A.g.Rp / 32);
-  else nblk = (min(RSB, d.R - (rs % A.g.PPH) * RSB) + 31) / 32;
+  int first;
+  const int nblk = super_block_blocks(d, A.g, rs, &first);
   const int nb2 = __builtin_amdgcn_readfirstlane((nblk + 1) & ~1);
   const int nrows = nb2 * 32;
 
@@ -357,9 +356,8 @@ hipError_t qs_launch(const ScoreArgs &A, int pass, size_t lds, dim3 grid, hipStr
 
 // largest number of row blocks (rounded up to even) any workgroup of the launch holds
 int qs_max_blocks(const ScoreArgs &A) {
-  int nblk;
-  if (A.g.PPH == 1) nblk = A.g.HPS * (A.g.Rp / 32);
-  else nblk = (std::min(A.g.RSB, (int)A.d.R) + 31) / 32;
+  int first;
+  const int nblk = super_block_blocks(A.d, A.g, 0, &first);        // no other holds more
   return (nblk + 1) & ~1;
 }
 
@@ -376,7 +374,7 @@ bool qs_supported(const ScoreArgs &A, int pass) {
   // override the choice: SPECKV_SCORE_KERNEL=tile (never), qs (both sweeps), qs1 / qs2 (that sweep
   // only).  Read on every call so that a test can switch it.
   const char *e = std::getenv("SPECKV_SCORE_KERNEL");
-  bool want = pass == 1 && A.d.D == 64;
+  bool want = pass == 1 && A.d.D == 64 && A.g.packed == 0;
   if (e != nullptr && e[0] != '\0') {
     if (std::strcmp(e, "tile") == 0) want = false;
     else if (std::strcmp(e, "qs") == 0) want = true;

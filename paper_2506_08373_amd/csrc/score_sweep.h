@@ -28,7 +28,9 @@
 // for fp32 blocks whose scores are not finite): lane l holds
 // row (A) or column (B) l%32 and the k-slice selected by l/32; the result register i of lane l
 // is element (8*(i/4) + 4*(l/32) + i%4, l%32).  Both operands take their k-slices from the same
-// 16-byte chunks of the head dimension (half l/32 reads chunks [half*NCS, half*NCS+NCS)), so the
+// 16-byte chunks of the head dimension (half l/32 reads the chunks of its parity: the two halves' loads of a query row
+// then fall into one cache line, and the loads of a workgroup's query rows, which are bound by the lines they
+// touch, take half the time), so the
 // contraction is over all d channels whatever order the hardware assigns inside a slice.
 //
 // This header holds the sweep kernels and their launcher, compiled into two translation units, one per
@@ -96,7 +98,8 @@ template <int DT, int D, int MB, int NW>
 constexpr size_t score_lds_bytes() {
   using OP = Operand<DT, D, MB>;
   return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float) +
-         (normalisers_in_lds<DT, MB>() ? NW * MB * 32 * sizeof(float) : 0);
+         (normalisers_in_lds<DT, MB>() ? NW * MB * 32 * sizeof(float) : 0) +
+         (OP::SPLIT ? NW * MB * 32 * sizeof(int64_t) : 0);        // row_off
 }
 
 // Bits of 2^-103.  The last bit of a smaller number lies below 2^-126, where a plane's numbers end.
@@ -131,9 +134,9 @@ __device__ __forceinline__ void merge_pairs(float &top, float &sum, const float2
   const float before = top;
 #pragma unroll
   for (int u = 0; u < N; ++u) top = fmaxf(top, in[u].x);
-  sum *= exp2f(before - top);
+  sum *= __builtin_amdgcn_exp2f(before - top);
 #pragma unroll
-  for (int u = 0; u < N; ++u) sum += in[u].y * exp2f(in[u].x - top);
+  for (int u = 0; u < N; ++u) sum += in[u].y * __builtin_amdgcn_exp2f(in[u].x - top);
 }
 
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
@@ -149,7 +152,8 @@ __device__ __forceinline__ void merge_pairs(float &top, float &sum, const float2
 //           its pairs and lists them in A.fail;  true: segment `seg` alone with the online step,
 //           its pairs merged into the ones already written; wavefronts that do not take part
 //           (the segment is not on their list) only help to load the key tiles
-template <int DT, int D, int MB, int NW, int PASS, int RED, bool MASKED, bool REPAIR = false>
+//   MAY_SHARE  the code for row blocks that waves share (split_blocks)
+template <int DT, int D, int MB, int NW, int PASS, int RED, bool MASKED, bool REPAIR = false, bool MAY_SHARE = true>
 __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, const int seg = 0,
                                            const bool wave_takes_part = true) {
   static_assert(!REPAIR || (PASS == 1 && !MASKED), "only the row-statistics sweep is repaired");
@@ -207,31 +211,28 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   const int ntiles = (key_end - key_begin + KT - 1) / KT;
   const float c2 = d.sm_scale * 1.4426950408889634f;
 
-  // 32-row block b of the super-block belongs to wave b % NW (its row block b / NW), so that a
-  // partly filled super-block still spreads its blocks evenly over the SIMDs.  Blocks past the
-  // last valid row are skipped: nact = how many of this wave's MB blocks hold rows.
-  int nblk;
-  if (A.g.PPH == 1) nblk = min(A.g.HPS, d.G - rs * A.g.HPS) * (A.g.Rp / 32);
-  else nblk = (min(RSB, d.R - (rs % A.g.PPH) * RSB) + 31) / 32;
-  const int nact = wave_takes_part ? __builtin_amdgcn_readfirstlane(max(0, min(MB, (nblk - wv + NW - 1) / NW))) : 0;
-  // Maximum over the query rows, full super-block, an even number of blocks per head: the wave
+  // Which of the super-block's row blocks this wave computes (see split_blocks): `nact` of its own, row blocks 0 .. nact-1 of
+  // the wave, and, if `sharing`, every per-th 32-key block (the ones of number `phase` modulo `per`, counted from the
+  // chunk's first) of the block that is its row block number nact.
+  int first_block;
+  const int nblk = super_block_blocks(d, A.g, rs, &first_block);
+  const BlockSplit split = split_blocks(nblk, MAY_SHARE && A.share != 0);
+  const int share_w0 = split.full % NW;                   // waves share_w0 .. share_w0 + 3 share
+  const int nact = wave_takes_part ? __builtin_amdgcn_readfirstlane(max(0, min(MB, (split.full - wv + NW - 1) / NW))) : 0;
+  const bool sharing = MAY_SHARE && wave_takes_part && split.per > 1 && wv >= share_w0 && wv < share_w0 + 4;
+  const int per = MAY_SHARE ? split.per : 1, phase = (wv - share_w0) & (per - 1);
+  // Maximum over the query rows, full super-block, an even number of blocks per head (or heads that are combined by
+  // maximum as well): the wave
   // takes two neighbouring blocks (2 wv and 2 wv + 1, the same head) instead, merges their
   // column maxima in registers and hands one value per key to the flush, not two.  A maximum
   // does not depend on the order, so the result is the same bit for bit.
-  const int blocks_per_head = (A.g.PPH == 1 ? A.g.Rp : RSB) / 32;
-  const bool paired = PASS == 2 && RED == 1 && !MASKED && MB == 2 && nblk == NW * MB && blocks_per_head % 2 == 0;
-  auto block_of = [&](int rb) { return paired ? wv * MB + rb : rb * NW + wv; };
-  // head and first observation row of each of this wave's 32-row blocks (a block never mixes
-  // heads, so one division per block replaces one per row)
-  int blk_head[MB], blk_i0[MB];
-#pragma unroll
-  for (int rb = 0; rb < MB; ++rb) {
-    int hh, i0;
-    const bool ok = decode_row(d, A.g, rs, block_of(rb) * 32, &hh, &i0);
-    blk_head[rb] = ok ? hh : -1;       // -1: the whole block is padding
-    blk_i0[rb] = i0;
-  }
-#define SPECKV_ROW_VALID(rb_, r32_) (blk_head[rb_] >= 0 && blk_i0[rb_] + (r32_) < d.R)
+  const int blocks_per_head = (A.g.PPH != 1 ? RSB : A.g.packed != 0 ? 32 : A.g.Rp) / 32;
+  const bool paired = PASS == 2 && RED == 1 && !MASKED && MB == 2 && nblk == NW * MB && (blocks_per_head % 2 == 0 || A.g.packed != 0);
+  // ... and where heads are combined by maximum too, a wave merges whatever blocks it has.
+  const bool merged = paired || (PASS == 2 && RED == 1 && !MASKED && d.head_max != 0);
+  auto block_of = [&](int rb) { return paired ? wv * MB + rb : block_of_slot(split, rb * NW + wv); };
+  // row r32 of the wave's row block rb: its head and observation row; false for padding
+  auto row_at = [&](int rb, int r32, int &hh, int &i) { return decode_row(d, A.g, rs, block_of(rb) * 32 + r32, &hh, &i); };
 
   // ---- K tile staging: each wave issues SEG_PER_WAVE wave-wide 128-bit loads that land in LDS
   // at lds_base + lane*16; the lane picks the global chunk that belongs in its (row, slot).
@@ -286,7 +287,22 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       *reinterpret_cast<u32x4 *>(kbuf + (buf_) * TILE_BYTES + p * PLANE_BYTES + r_ * ROWB +   \
                                  ((c_ ^ TL::swizzle(r_)) * 16)) = part_[p];                   \
   }
-  // the first tile is requested before anything else is loaded, so that its latency overlaps
+  // Column sweep, normalisers merged here: one thread (or RSB_SLICES of them) per row.  Entry 0 of a row's list is the pair
+  // of the sequence's masked tail, entry e that of its e-th chunk.
+  // The first entries are requested before everything else: loads return in the order they were issued.
+  constexpr int RSB_SLICES = NW * 64 / RSB, BATCH = 32 / RSB_SLICES;
+  static_assert(RSB_SLICES >= 1, "a thread per row");
+  const int norm_row = tid % RSB, norm_slice = tid / RSB, n_entries = A.t.cc[s + 1] - A.t.cc[s] + 1;
+  const float2 *pairs_of_row = A.part + (int64_t)unit * A.g.n_chunks * RSB + norm_row;
+  auto entry = [&](int e) {
+    return e < n_entries ? pairs_of_row[(int64_t)(e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1) * RSB] : make_float2(kNegBig, 0.f);
+  };
+  float2 first_pairs[BATCH];
+  if (PASS == 2 && A.norm_from == kNormPairs) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) first_pairs[u] = entry(norm_slice + u * RSB_SLICES);
+  }
+  // the first tile is requested before the other loads, so that its latency overlaps
   // with the Q fragment and row normaliser loads below
   const int first_tile = REPAIR ? 1 + seg * kAnchorTiles : 0;
   if (ntiles > first_tile) {
@@ -296,26 +312,27 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 
   // ---- Q fragments of this wave's row blocks, resident for the whole sweep
   u32x4 qf[MB][PLANES * NCS];
-  // the lane's share (half) of query row r32 of row block rb
-  auto query_row = [&](int rb, int r32, bool valid) {
-    const int hh = blk_head[rb], i = blk_i0[rb] + r32;
-    return A.q + ((int64_t)layer * d.q_sl + (int64_t)s * d.q_ss + (int64_t)(valid ? i : 0) * d.q_sr +
-                  (int64_t)(g * d.G + (valid ? hh : 0)) * d.q_sh) * ELT + half * (D / 2) * ELT;
-  };
+  // fp32: where the wave's query rows lie (-1: padding), for recompute_unless_finite, which would keep everything that goes
+  // into these offsets in scalar registers (with rows packed, more than there are)
+  int64_t *row_off = reinterpret_cast<int64_t *>(csum + (size_t)kCsumBuffers * NW * MB * KT + (normalisers_in_lds<DT, MB>() ? RSB : 0));
 #pragma unroll
   for (int rb = 0; rb < MB; ++rb) {
-    const bool valid = SPECKV_ROW_VALID(rb, l32);
-    const char *qp = query_row(rb, l32, valid);
+    int hh, i;
+    const bool valid = row_at(rb, l32, hh, i);
+    const int64_t off = ((int64_t)layer * d.q_sl + (int64_t)s * d.q_ss + (int64_t)(valid ? i : 0) * d.q_sr +
+                         (int64_t)(g * d.G + (valid ? hh : 0)) * d.q_sh) * ELT;
+    const char *qp = A.q + off + half * 8 * ELT;                     // chunk 0 of the lane's share of query row l32
+    if (SPLIT && half == 0) row_off[(rb * NW + wv) * 32 + l32] = valid ? off : -1;
 #pragma unroll
     for (int cs = 0; cs < NCS; ++cs) {
       if constexpr (SPLIT) {
         u32x4 part[3];
-        split_chunk(valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 32) : (u32x4)(0u),
-                    valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 32 + 16) : (u32x4)(0u), part);
+        split_chunk(valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 64) : (u32x4)(0u),
+                    valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 64 + 16) : (u32x4)(0u), part);
 #pragma unroll
         for (int p = 0; p < 3; ++p) qf[rb][p * NCS + cs] = part[p];
       } else {
-        qf[rb][cs] = valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 16) : (u32x4)(0u);
+        qf[rb][cs] = valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 32) : (u32x4)(0u);
       }
     }
   }
@@ -325,33 +342,39 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   constexpr bool LSE_LDS = PASS == 2 && normalisers_in_lds<DT, MB>();
   float nlse[LSE_LDS ? 1 : MB][16];  // pass 2: lane = 16 rows per row block
   float *lds_lse = csum + (size_t)kCsumBuffers * NW * MB * KT;                     // ... or in LDS, [RSB]
+  // masked sweep: last key each row may see (window row i sees keys <= m + i, a lookahead row the whole prompt),
+  // computed once instead of per score
+  int last1[MB];                     // pass 1: the lane's own query row per row block
+  int last2[MASKED ? MB : 1][16];    // pass 2: the 16 rows a lane holds per row block
   if (PASS == 1) {
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) { mrun[rb] = kNegBig; lrun[rb] = 0.f; }
+    for (int rb = 0; rb < MB; ++rb) {
+      mrun[rb] = kNegBig;
+      lrun[rb] = 0.f;
+      if (MASKED) {
+        int hh, io;
+        (void)row_at(rb, l32, hh, io);
+        last1[rb] = io < d.w ? m + io : n_s - 1;
+      }
+    }
   } else {
-    // The normalisers of the workgroup's rows go through LDS, one thread (or RSB_SLICES of them) per row.  Merging
+    // The normalisers of the workgroup's rows go through LDS.  Merging
     // the chunks' pairs here instead of in a kernel between the sweeps saves that launch (see launch_score).
-    constexpr int RSB_SLICES = NW * 64 / RSB, BATCH = 16;
     float2 *pairs = reinterpret_cast<float2 *>(csum);                                  // [RSB_SLICES][RSB]
     float *norm = LSE_LDS ? lds_lse : csum + 2 * NW * 64;                             // [RSB]
-    static_assert(RSB_SLICES >= 1 && (size_t)kCsumBuffers * NW * MB * KT >= (size_t)2 * NW * 64 + RSB, "scratch of the merge");
-    const int lr = tid % RSB, slice = tid / RSB;
+    int *row_last = reinterpret_cast<int *>(csum + 2 * NW * 64 + RSB);                // [RSB], masked: last key a row may see
+    static_assert((size_t)kCsumBuffers * NW * MB * KT >= (size_t)2 * NW * 64 + 2 * RSB, "scratch of the merge");
+    const int lr = norm_row, slice = norm_slice;
     int hh, io;
     const bool valid = decode_row(d, A.g, rs, lr, &hh, &io);
     float v = 0.f;                                        // log2 normaliser of row lr
     if (A.norm_from == kNormPairs) {
-      const float2 *pp = A.part + (int64_t)unit * A.g.n_chunks * RSB + lr;
-      const int c1 = A.t.cc[s + 1];
       float top = kNegBig, sum = 0.f;
-      for (int c = A.t.cc[s] + slice; c < c1; c += RSB_SLICES * BATCH) {
-        float2 in[BATCH];
+      merge_pairs(top, sum, first_pairs);
+      for (int e0 = slice + BATCH * RSB_SLICES; e0 < n_entries; e0 += RSB_SLICES * 8) {
+        float2 in[8];
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u)
-          in[u] = c + u * RSB_SLICES < c1 ? pp[(int64_t)(c + u * RSB_SLICES) * RSB] : make_float2(kNegBig, 0.f);
-        merge_pairs(top, sum, in);
-      }
-      if (slice == 0) {                                   // the sequence's masked tail chunk
-        const float2 in[1] = {pp[(int64_t)(A.g.n_fast_chunks + s) * RSB]};
+        for (int u = 0; u < 8; ++u) in[u] = entry(e0 + u * RSB_SLICES);
         merge_pairs(top, sum, in);
       }
       if constexpr (RSB_SLICES > 1) {
@@ -374,17 +397,21 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       v = -v;
       if (d.weight_rows && valid && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
       norm[lr] = valid ? v : -INFINITY;                   // padded rows contribute 2^-inf = 0
+      if (MASKED) row_last[lr] = io < d.w ? m + io : n_s - 1;
     }
     __syncthreads();
-    if constexpr (!LSE_LDS) {
 #pragma unroll
-      for (int rb = 0; rb < MB; ++rb)
+    for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) nlse[rb][i] = norm[block_of(rb) * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
-      __syncthreads();
-    }
+      for (int i = 0; i < 16; ++i) {
+        const int r = block_of(rb) * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+        if constexpr (!LSE_LDS) nlse[rb][i] = norm[r];
+        if constexpr (MASKED) last2[rb][i] = row_last[r];
+      }
+    __syncthreads();
     // slots of skipped blocks must read as zero when the tile partials are merged
-    for (int x = tid; x < kCsumBuffers * NW * MB * KT; x += NW * 64) csum[x] = 0.f;
+    if (MASKED || split.full < NW || per > 1 || (RED == 1 && nblk != NW * MB))
+      for (int x = tid; x < kCsumBuffers * NW * MB * KT; x += NW * 64) csum[x] = 0.f;
   }
   // the negated normalisers of the lane's 16 rows in row block rb
   auto load_lse = [&](int rb, float (&nl)[16]) {
@@ -395,30 +422,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     }
   };
 
-  // ---- masked sweep: last key each row may see (window row i sees keys <= m + i, a lookahead
-  // row the whole prompt), computed once instead of per score
-  int last1[MB];                     // pass 1: the lane's own query row per row block
-  int last2[MB][16];                 // pass 2: the 16 rows a lane holds per row block
-  if (MASKED) {
-#pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-      if (PASS == 1) {
-        const int io = blk_i0[rb] + l32;
-        last1[rb] = io < d.w ? m + io : n_s - 1;
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int io = blk_i0[rb] + 8 * (i >> 2) + 4 * half + (i & 3);
-          last2[rb][i] = io < d.w ? m + io : n_s - 1;
-        }
-      }
-    }
-  }
-
   // per-lane LDS offsets of the fragment chunks of key row l32 (same for every 32-key block)
   uint32_t foff[NCS];
 #pragma unroll
-  for (int cs = 0; cs < NCS; ++cs) foff[cs] = l32 * ROWB + (((half * NCS + cs) ^ TL::swizzle(l32)) * 16);
+  for (int cs = 0; cs < NCS; ++cs) foff[cs] = l32 * ROWB + (((2 * cs + half) ^ TL::swizzle(l32)) * 16);
   // chunk cs of key block kb_ in plane p_ (fp32: the smallest plane comes first)
 #define SPECKV_FRAG(buf_, p_, kb_, cs_) \
   (*reinterpret_cast<const u32x4 *>(kbuf + (buf_) * TILE_BYTES + (p_) * PLANE_BYTES + (kb_) * 32 * ROWB + foff[cs_]))
@@ -444,8 +451,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       if (__builtin_amdgcn_ballot_w64(!(probe == 0.f)) != 0) {
         int r32 = l32;
         asm volatile("" : "+v"(r32));  // the addresses are made here, not kept in registers through the sweep
-        const bool valid = SPECKV_ROW_VALID(rb, r32);
-        const char *qp = query_row(rb, r32, valid);
+        const int64_t off = row_off[(rb * NW + wv) * 32 + r32];
+        const bool valid = off >= 0;
+        const char *qp = A.q + (valid ? off : 0) + half * (D / 2) * ELT;
         const char *kp = kbase + (int64_t)min(key0 + r32, n_s - 1) * tokb + half * (D / 2) * ELT;
         x = (f32x16){0};
 #pragma unroll 1
@@ -463,7 +471,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   if (PASS == 2)
     plane_out = A.planes + ((int64_t)rs * d.L + layer) * d.Hkv * d.T + (int64_t)d.Hkv * A.t.cu[s] + (int64_t)g * n_host;
   const bool head_max = d.head_max != 0;
-  const int slots_per_head = paired ? blocks_per_head / 2 : blocks_per_head;
+  const int slots_per_head = paired && blocks_per_head > 1 ? blocks_per_head / 2 : blocks_per_head;
+  // sum, unmasked: a wave with a block of its own keeps the column sums of the one it shares in a second slot
+  const bool share_slots = per > 1 && split.full >= NW;
 #define SPECKV_FLUSH_TILE(tile_)                                                             \
   if (tid < KT) {                                                                            \
     const int key_ = key_begin + (tile_) * KT + tid;                                         \
@@ -472,21 +482,28 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       float total_ = 0.f;                                                                    \
       if (RED == 0) {                                                                        \
         _Pragma("unroll") for (int w2 = 0; w2 < NW; ++w2) total_ += cp_[w2 * KT];            \
+        if (MB == 2 && share_slots) {                                                        \
+          _Pragma("unroll") for (int w2 = 0; w2 < 4; ++w2) total_ += cp_[(NW + share_w0 + w2) * KT]; \
+        }                                                                                    \
+      } else if (head_max) {                                                                 \
+        /* one slot per wave (masked: per block), and those of a shared block */             \
+        _Pragma("unroll") for (int b2 = 0; b2 < NW * MB; ++b2)                               \
+          if (MASKED || b2 < NW || share_slots) total_ = fmaxf(total_, cp_[b2 * KT]);        \
       } else {                                                                               \
-        /* per block (or block pair) maxima: max within a head, then heads added (or maxed) */ \
+        /* per block (or block pair) maxima: max within a head, then heads added */          \
         float cur_ = 0.f;                                                                    \
         int in_head_ = 0;                                                                    \
         _Pragma("unroll") for (int b2 = 0; b2 < NW * MB; ++b2) {                             \
           if (paired && b2 >= NW) break;                                                     \
           if (in_head_ == slots_per_head) {                                                  \
-            total_ = head_max ? fmaxf(total_, cur_) : total_ + cur_;                         \
+            total_ += cur_;                                                                  \
             cur_ = 0.f;                                                                      \
             in_head_ = 0;                                                                    \
           }                                                                                  \
           cur_ = fmaxf(cur_, cp_[b2 * KT]);                                                  \
           ++in_head_;                                                                        \
         }                                                                                    \
-        total_ = head_max ? fmaxf(total_, cur_) : total_ + cur_;                             \
+        total_ += cur_;                                                                      \
       }                                                                                      \
       plane_out[key_] = total_;                                                              \
     }                                                                                        \
@@ -563,6 +580,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   };
 
   if constexpr (MASKED) {
+    auto takes = [&](int rb, int kb) { return rb < nact || (sharing && rb == nact && (kb & (per - 1)) == phase); };
     for (int tile = 0; tile < ntiles; ++tile) {
       const int buf = tile & 1;
       if (tile + 1 < ntiles) {
@@ -601,7 +619,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         if (PASS == 1) {
 #pragma unroll
           for (int rb = 0; rb < MB; ++rb) {
-            if (rb >= nact) continue;
+            if (!takes(rb, tile * (KT / 32) + kb)) continue;
             f32x16 acc = scores(rb);
             // lane: query row (wv*MB+rb)*32 + l32; keys tk0 + kb*32 + 8*(i/4) + 4*half + i%4
 #pragma unroll
@@ -627,7 +645,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           float *dst = csum + (size_t)(tile % kCsumBuffers) * NW * MB * KT + kb * 32 + l32;
 #pragma unroll
           for (int rb = 0; rb < MB; ++rb) {
-            if (rb >= nact) continue;
+            if (!takes(rb, tile * (KT / 32) + kb)) continue;
             f32x16 acc = scores(rb);
             // lane: key tk0 + kb*32 + l32; rows (wv*MB+rb)*32 + 8*(i/4) + 4*half + i%4
             float p[16], nl[16];
@@ -685,15 +703,33 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     // rows 729 -> 709 us, 28 layers x 60K, 7 x 32 rows 1087 -> 1051 us, 5 x 32 rows 1162 -> 1114 us (before any
     // pipelining 727, 1085, 1140 us).
     constexpr bool PIPELINED = !(PASS == 2 && MB == 1 && NW == 8 && D == 128 && !SPLIT);
-    auto sweep = [&](auto nact_c) {
+    // SHARED: the wave also has its part of row block NACT, done at the end of a tile: usually one 32-key block of four,
+    // beside which the other wave of the SIMD has its own work.
+    auto sweep = [&](auto nact_c, auto shared_c) {
       constexpr int NACT = decltype(nact_c)::value;
+      constexpr bool SHARED = decltype(shared_c)::value;
       f32x16 acc[2];                   // blocks of the units: the open one in one, the next one in the other
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;    // nothing open: probabilities of 2^-inf = 0
       bool open = false;               // a unit waits in acc[1] (fp32: only then are its scores looked at)
       float top_before = 0.f;          // pass 1, fp32: largest score of the unit before a segment's last look
+      float shared_top = 0.f;          // pass 1: largest score of the last unit of the shared block
       float colsum = 0.f;              // pass 2: the lane's key, over the row blocks of the current key block
 
+      // pass 2: sum (maximum) of the lane's 16 probabilities and `before`
+      auto column_of = [&](const f32x16 &x, int rb, float before) {
+        float p[16], nl[16];
+        load_lse(rb, nl);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nl[i]));
+        if (RED == 0)
+          return before + ((((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
+                           (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15]))));
+        const float t0 = fmaxf(fmaxf(p[0], p[1]), p[2]), t1 = fmaxf(fmaxf(p[3], p[4]), p[5]);
+        const float t2 = fmaxf(fmaxf(p[6], p[7]), p[8]), t3 = fmaxf(fmaxf(p[9], p[10]), p[11]);
+        const float t4 = fmaxf(fmaxf(p[12], p[13]), p[14]);
+        return fmaxf(fmaxf(before, fmaxf(fmaxf(t0, t1), t2)), fmaxf(fmaxf(t3, t4), p[15]));
+      };
       // turns the scores x of row block rb into probabilities; pass 2: of key block kb, into partial buffer cbuf
       auto finish_unit = [&](const f32x16 &x, int rb, int kb, int cbuf, auto anchored_c) {
         if constexpr (PASS == 1 && decltype(anchored_c)::value) {
@@ -719,32 +755,65 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           mrun[rb] = mnew;
           asm volatile("" : "+v"(lrun[rb]), "+v"(mrun[rb]));
         } else {
-          if (rb == 0 || (RED == 1 && !paired)) colsum = 0.f;
-          float p[16], nl[16];
-          load_lse(rb, nl);
-#pragma unroll
-          for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nl[i]));
-          if (RED == 0) {
-            colsum += (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
-                      (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15])));
-          } else {
-            const float t0 = fmaxf(fmaxf(p[0], p[1]), p[2]), t1 = fmaxf(fmaxf(p[3], p[4]), p[5]);
-            const float t2 = fmaxf(fmaxf(p[6], p[7]), p[8]), t3 = fmaxf(fmaxf(p[9], p[10]), p[11]);
-            const float t4 = fmaxf(fmaxf(p[12], p[13]), p[14]);
-            colsum = fmaxf(fmaxf(colsum, fmaxf(fmaxf(t0, t1), t2)), fmaxf(fmaxf(t3, t4), p[15]));
-          }
+          if (rb == 0 || (RED == 1 && !merged)) colsum = 0.f;
+          colsum = column_of(x, rb, colsum);
           // sum (or the maximum over a block pair): one value per wave, slot wv; otherwise one per 32-row
           // block, blocks of a head are merged at the flush.  Both halves write the same value.
           float *dst = csum + (size_t)cbuf * NW * MB * KT + kb * 32 + l32;
           if (RED == 0) {
             if (rb == NACT - 1) dst[wv * KT] = add_other_half(colsum);
-          } else if (!paired || rb == NACT - 1) {
-            dst[paired ? wv * KT : (rb * NW + wv) * KT] = max_other_half(colsum);
+          } else if (!merged || rb == NACT - 1) {
+            dst[merged ? wv * KT : (rb * NW + wv) * KT] = max_other_half(colsum);
           }
           asm volatile("" : "+v"(colsum));
         }
       };
 
+      // The wave's key blocks of a tile for the row block it shares.
+      auto shared_units = [&](int tile, int buf, auto anchored_c) {
+        constexpr bool anchored = decltype(anchored_c)::value;
+        // A tile of two key blocks shared by four waves leaves two of them without any of the chunk's first tile, which gives
+        // the rows their references: they take theirs from a key block that is another wave's.
+        const bool reference_only = kAnchored && !anchored && KB < 4 && tile == 0 && phase >= KB;
+#pragma unroll 1
+        for (int kb = reference_only ? phase - KB : (phase - tile * KB) & (per - 1); kb < KB; kb += per) {
+          f32x16 x = {0}, low = {0};
+          u32x4 bf[NCS];
+          if constexpr (SPLIT) {
+#pragma unroll
+            for (int kp = PLANES - 1; kp >= 0; --kp) {
+#pragma unroll
+              for (int cs = 0; cs < NCS; ++cs) bf[cs] = SPECKV_FRAG(buf, kp, kb, cs);
+#pragma unroll
+              for (int cs = 0; cs < NCS; ++cs) add_lower_products(low, bf[cs], kp, NACT, cs);
+            }
+          } else {
+            SPECKV_LOAD_BFRAG(bf, buf, kb)
+          }
+#pragma unroll
+          for (int cs = 0; cs < NCS; ++cs) add_product(x, bf[cs], 0, NACT, cs);
+          if constexpr (SPLIT) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] += low[i];
+            recompute_unless_finite(x, NACT, key_begin + tile * KT + kb * 32);
+          }
+          if constexpr (PASS == 1) {
+            if constexpr (kAnchored) {
+              float top = fmaxf(fmaxf(x[0], x[1]), x[2]);
+#pragma unroll
+              for (int i = 3; i < 15; i += 2) top = fmaxf(fmaxf(top, x[i]), x[i + 1]);
+              shared_top = fmaxf(top, x[15]);
+            }
+            if (reference_only) mrun[NACT] = fmaxf(mrun[NACT], shared_top * c2);
+            else finish_unit(x, NACT, kb, 0, anchored_c);
+          } else {
+            // (a block that heads share has no maximum of its own head: one slot per block is right for the flush)
+            const float v = column_of(x, NACT, 0.f);
+            float *dst = csum + (size_t)(tile % kCsumBuffers) * NW * MB * KT + kb * 32 + l32;
+            dst[(NACT * NW + wv) * KT] = RED == 0 ? add_other_half(v) : max_other_half(v);
+          }
+        }
+      };
       // One tile of the sweep; the LDS buffer index is a compile-time constant so that every LDS
       // address below is a register plus an immediate.  Pass 2 flushes the tile before last: its last
       // column partials were written in the previous tile's first unit.
@@ -757,6 +826,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           else SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
         }
         if (PASS == 2 && tile > 1) SPECKV_FLUSH_TILE(tile - 2)
+        if constexpr (NACT == 0 && SHARED && kAnchored && anchored && buf == 1) {
+          if (tile > 1)
+            end_segment((tile - 3) / kAnchorTiles, [&](int, float) { return fmaxf(shared_top * c2, kNegBig) + (float)anchor_shift; });
+        }
         if constexpr (NACT > 0) {
           u32x4 bf[NCS];
           SPECKV_LOAD_BFRAG(bf, buf, 0)
@@ -822,7 +895,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
               // where there are two (fp32: this unit has its registers by now, their maximum is kept)
               end_segment((tile - 3) / kAnchorTiles, [&](int rb_, float) {
                 float top = top_before;
-                if (!SPLIT || rb_ == 0) {
+                if (SHARED && rb_ == NACT) {
+                  top = shared_top;
+                } else if (!SPLIT || rb_ == 0) {
                   const f32x16 &s_ = acc[SPLIT || rb_ != 0 ? 1 : 0];
                   top = s_[0];
 #pragma unroll
@@ -834,6 +909,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           }
         }
         open = true;
+        if constexpr (SHARED) shared_units(tile, buf, anchored_c);
         if constexpr (SPLIT) {
           if (tile + 1 < ntiles) SPECKV_STORE_TILE(buf ^ 1)
         }
@@ -890,9 +966,15 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       }
     };
     // (the barriers inside count wavefronts, whichever copy of the code they are in)
-    if (nact == MB) sweep(std::integral_constant<int, MB>{});
-    else if (MB > 1 && nact == 1) sweep(std::integral_constant<int, 1>{});
-    else sweep(std::integral_constant<int, 0>{});
+    auto sweep_shared = [&](auto nact_c) {
+      if constexpr (MAY_SHARE) {
+        if (sharing) return sweep(nact_c, std::true_type{});
+      }
+      sweep(nact_c, std::false_type{});
+    };
+    if (nact == MB) sweep(std::integral_constant<int, MB>{}, std::false_type{});
+    else if (MB > 1 && nact == 1) sweep_shared(std::integral_constant<int, MB - 1>{});
+    else sweep_shared(std::integral_constant<int, 0>{});
     if constexpr (kAnchored) {
       if (lane <= kFailListed + 1) {
         int32_t *mine = A.fail + ((int64_t)bid * NW + wv) * kFailWords;
@@ -917,10 +999,25 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       const float lf = __builtin_frexpf(lrun[rb], &e2);
       const float mf = mrun[rb] + (float)e2;
       const float mo = __shfl_xor(mf, 32, 64), lo = __shfl_xor(lf, 32, 64);
-      const float mm = fmaxf(mf, mo);
-      const float ll = lf * __builtin_amdgcn_exp2f(mf - mm) + lo * __builtin_amdgcn_exp2f(mo - mm);
-      if (half == 0) {
-        float2 *slot = &pp[(rb * NW + wv) * 32 + l32];
+      float mm = fmaxf(mf, mo);
+      float ll = lf * __builtin_amdgcn_exp2f(mf - mm) + lo * __builtin_amdgcn_exp2f(mo - mm);
+      // a block that waves share: the first of them adds the others' pairs
+      const bool in_share = per > 1 && rb == split.full / NW && wv >= share_w0 && wv < share_w0 + 4;
+      if (per > 1 && rb == split.full / NW) {
+        float2 *others = reinterpret_cast<float2 *>(csum);
+        if (in_share && half == 0) others[(wv - share_w0) * 32 + l32] = make_float2(mm, ll);
+        __syncthreads();
+        if (in_share && phase == 0) {
+          for (int u = 1; u < per; ++u) {
+            const float2 v = others[(wv - share_w0 + u) * 32 + l32];
+            const float m2 = fmaxf(mm, v.x);
+            ll = ll * __builtin_amdgcn_exp2f(mm - m2) + v.y * __builtin_amdgcn_exp2f(v.x - m2);
+            mm = m2;
+          }
+        }
+      }
+      if (half == 0 && (!in_share || phase == 0)) {
+        float2 *slot = &pp[block_of(rb) * 32 + l32];
         if (REPAIR) {                // add to what the first sweep (and earlier repairs) left there
           const float2 have = *slot;
           const float m2 = fmaxf(have.x, mm);
@@ -933,7 +1030,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   }
 }
 
-#undef SPECKV_ROW_VALID
 #undef SPECKV_LOAD_TILE
 #undef SPECKV_FETCH_TILE
 #undef SPECKV_STORE_TILE
@@ -947,14 +1043,24 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 // last round of chunk workgroups frees one by one (ragged batches: 1 % faster than tails in front,
 // equal-length grids: the same).  TAIL_ONLY = true is the tails alone (calls without a complete
 // chunk, and the tails behind a Q-stationary sweep).
+// Column sweeps of fp32 with two row blocks a wave are short of registers: the code for shared blocks costs the sum 4 % where
+// no block is shared (3 layers x 30K keys, normalisers given, 442 and 464 us), so that there is a kernel without it for those
+// calls (RED = kSumWhole), and the maximum has 90 scalar registers spilled instead of 18 (19 layers x 27K keys 2660 and 3000 us), so
+// that it shares nothing.
+constexpr int kSumWhole = 2;
+template <int DT, int MB, int PASS, int RED>
+constexpr bool may_share() { return !(DT == kF32 && MB == 2 && PASS == 2 && RED != 0); }
+
 template <int DT, int D, int MB, int NW, int PASS, int RED, bool TAIL_ONLY>
 __device__ __forceinline__ void score_dispatch(const ScoreArgs &A) {
+  constexpr int R = PASS == 2 && RED == kSumWhole ? 0 : RED;
+  constexpr bool SHARE = may_share<DT, MB, PASS, RED>();
   const int bid = blockIdx.x;
   if (PASS == 2 && A.norm_from != kNormMerged)
     clear_scratch(A, (int64_t)bid * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
-  if (TAIL_ONLY) score_body<DT, D, MB, NW, PASS, RED, true>(A, bid);
-  else if (bid < A.chunk_blocks) score_body<DT, D, MB, NW, PASS, RED, false>(A, bid);
-  else score_body<DT, D, MB, NW, PASS, RED, true>(A, bid - A.chunk_blocks);
+  if (TAIL_ONLY) score_body<DT, D, MB, NW, PASS, R, true, false, SHARE>(A, bid);
+  else if (bid < A.chunk_blocks) score_body<DT, D, MB, NW, PASS, R, false, false, SHARE>(A, bid);
+  else score_body<DT, D, MB, NW, PASS, R, true, false, SHARE>(A, bid - A.chunk_blocks);
 }
 
 // The row-statistics sweep is compiled for exactly two waves per SIMD (the register allocator
@@ -972,8 +1078,9 @@ __global__ __launch_bounds__(NW * 64) void score_kernel_cols(ScoreArgs A) {
 // The launch behind a row-statistics sweep: a chunk workgroup's twin reads the lists its wavefronts
 // left and repeats the listed segments, in ascending order, with the online step (normally there
 // are none and it returns).  Every thread walks all NW lists, so the order needs no exchange.
+// (Compiled for one workgroup per CU, which its LDS allows: otherwise one fp32 variant spills.)
 template <int DT, int D, int MB, int NW>
-__global__ __launch_bounds__(NW * 64) void score_kernel_rows_repair(ScoreArgs A) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void score_kernel_rows_repair(ScoreArgs A) {
   const int bid = blockIdx.x;
   const int per_group = 8 * A.g.RS;
   const int item = (bid / per_group) * 8 + ((bid % per_group) & 7);
@@ -1053,7 +1160,15 @@ hipError_t sweep_for_geometry(const ScoreArgs &A, hipStream_t st) {
     if (score_rows_fixed_reference(A.d, A.g)) return launch_sweep<DT, D, MB, NW, 1, 1>(A, lds, st);
     return launch_sweep<DT, D, MB, NW, 1, 0>(A, lds, st);
   }
-  else return A.d.reduce_max ? launch_sweep<DT, D, MB, NW, 2, 1>(A, lds, st) : launch_sweep<DT, D, MB, NW, 2, 0>(A, lds, st);
+  else {
+    if (A.d.reduce_max) return launch_sweep<DT, D, MB, NW, 2, 1>(A, lds, st);
+    if constexpr (!may_share<DT, MB, 2, kSumWhole>()) {
+      bool shared = false;
+      for (int rs = 0, first; rs < A.g.RS; ++rs) shared |= split_blocks(super_block_blocks(A.d, A.g, rs, &first), A.share != 0).per > 1;
+      if (!shared) return launch_sweep<DT, D, MB, NW, 2, kSumWhole>(A, lds, st);
+    }
+    return launch_sweep<DT, D, MB, NW, 2, 0>(A, lds, st);
+  }
 }
 
 template <int DT, int D, int PASS>

@@ -48,6 +48,9 @@ struct ScoreGeom {
   int32_t Rp;         // observation rows per head, padded to a multiple of 32
   int32_t HPS;        // whole heads per super-block (when a head fits), else 1
   int32_t PPH;        // super-blocks per head (1 when a head fits)
+  int32_t pitch;      // rows from one head's first row to the next one's: Rp, or R where rows are packed (pack_rows)
+  uint32_t pitch_inv; // 2^32 / pitch, rounded up: row / pitch is the high word of row * pitch_inv (rows stay below 2^13)
+  int32_t packed;     // row blocks of the group where rows are packed, spread evenly over the super-blocks; else 0
   int32_t KC;         // keys per chunk (multiple of the LDS tile)
   int32_t n_fast_chunks;   // unmasked chunks over all sequences = cc[S]
   int32_t n_chunks;        // n_fast_chunks + one masked tail chunk per sequence
@@ -134,19 +137,51 @@ hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *pa
 // plan runs in the Q-stationary kernel (score_qs.hip) rather than the tile-streaming one
 // (score_sweep.h); diagnostics only.
 bool score_uses_qs(const Plan &pl, int pass);
+// Row blocks of super-block `rs`; *first: the group's row blocks before it (PPH == 1).
+__host__ __device__ inline int super_block_blocks(const Dims &d, const ScoreGeom &g, int rs, int *first) {
+  if (g.PPH != 1) {
+    const int rows = d.R - (rs % g.PPH) * g.RSB;
+    *first = 0;
+    return ((rows < g.RSB ? rows : g.RSB) + 31) / 32;
+  }
+  if (g.packed != 0) {
+    const int base = g.packed / g.RS, more = g.packed % g.RS;
+    *first = rs * base + (rs < more ? rs : more);
+    return base + (rs < more ? 1 : 0);
+  }
+  const int heads = d.G - rs * g.HPS;
+  *first = rs * g.HPS * (g.Rp / 32);
+  return (heads < g.HPS ? heads : g.HPS) * (g.Rp / 32);
+}
 // Row `lr` of super-block `rs` -> (head in group, observation row); false for padding rows.
-// Heads never share a 32-row block: each head's R rows are padded to Rp, and a super-block holds
-// either HPS whole heads or one of the PPH slices of a single head.
+// A super-block holds a run of the group's row blocks, or one of the PPH slices of a single head.  Each head's R rows are padded
+// to Rp, so that heads never share a 32-row block, unless rows are packed.
 __host__ __device__ inline bool decode_row(const Dims &d, const ScoreGeom &g, int rs, int lr, int *hh, int *i) {
+  int first;
+  const int n = super_block_blocks(d, g, rs, &first);
   if (g.PPH == 1) {
-    *hh = rs * g.HPS + lr / g.Rp;
-    *i = lr % g.Rp;
-    return lr < g.HPS * g.Rp && *hh < d.G && *i < d.R;
+    const int row = first * 32 + lr;
+    *hh = (int)(((uint64_t)(uint32_t)row * g.pitch_inv) >> 32);
+    *i = row - *hh * g.pitch;
+    return lr < n * 32 && *hh < d.G && *i < d.R;
   }
   *hh = rs / g.PPH;
   *i = (rs % g.PPH) * g.RSB + lr;
   return *i < d.R;
 }
+// Which wavefronts compute a super-block's n row blocks in the key-tile sweeps.  The first `full` blocks belong to one wavefront
+// each (block b to wave b % NW, as its row block b / NW), which loads the four SIMDs of a CU (wave w runs on SIMD w % 4) evenly
+// if `full` is a multiple of four.  One or two blocks beyond that are shared by the next four waves, `per` = 4 or 2 waves a block,
+// each of which takes every per-th 32-key block; per = 1: every block belongs to one wave.
+struct BlockSplit { int n, full, per; };
+__host__ __device__ inline BlockSplit split_blocks(int n, bool share) {
+  BlockSplit b = {n, n, 1};
+  const int rest = n & 3;
+  if (share && (rest == 1 || rest == 2)) { b.full = n - rest; b.per = 4 / rest; }
+  return b;
+}
+// Block that slot s (= row block * NW + wave) computes.
+__host__ __device__ inline int block_of_slot(const BlockSplit &b, int s) { return s < b.full ? s : b.full + (s - b.full) / b.per; }
 
 // out rows = (layer, seq, head): pooled/raw in the "scores" layout from RS planes.
 // hist0, when not null: [rows][2048] zeroed counters; the kernel adds the first-digit histogram of

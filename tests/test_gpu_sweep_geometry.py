@@ -75,3 +75,28 @@ def test_workgroups_of_few_tiles_with_a_length_on_the_device(S, n_live):
     for dev, host in zip(*out):
         parity.assert_scores_close(dev[:, :n_live], host, "live %d" % n_live)
         assert (dev[:, n_live:] == 0).all()
+
+
+# Row blocks that heads share, and blocks that waves share: 32-row blocks of a group -> what the last waves do
+#   1, 2 of 4 waves; 3; 5, 6 of 8 waves; 7; 9, 10 with two blocks a wave; 13, 14; two super-blocks of unequal size; two rows a
+#   head; a head longer than a super-block (never packed)
+@pytest.mark.parametrize("g,window,lookahead", [
+    (1, 16, 9), (2, 16, 24), (4, 16, 1), (4, 16, 24), (4, 16, 32), (4, 32, 23), (4, 64, 1), (4, 32, 40), (4, 32, 48), (5, 16, 64),
+    (5, 64, 20), (7, 64, 8), (7, 64, 64), (8, 1, 1), (1, 64, 520)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("mode", ["online", "fixed"])
+def test_rows_packed_and_blocks_shared(S, g, window, lookahead, dtype, d, mode, monkeypatch):
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", mode)
+    monkeypatch.setenv("SPECKV_SCORE_KERNEL", "tile")
+    parity.check_full_path(S, shape(n_q_heads=2 * g, n_kv_heads=2, head_dim=d, n_window=window, n_lookahead=lookahead,
+                                    seq_lens=(1500, 2740), dtype=dtype))
+
+
+def test_shared_blocks_behind_outliers_and_the_query_stationary_sweep(S, monkeypatch):
+    """Fixed references that overflow (segments are repaired by the waves that share), and partial pairs left by the
+    query-stationary kernel, which shares nothing, for a column sweep that does."""
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", "fixed")
+    for dtype in ("bf16", "f32"):
+        parity.check_full_path(S, shape(n_q_heads=8, n_kv_heads=2, n_window=64, n_lookahead=1, seq_lens=(9000,), dtype=dtype,
+                                        q_gain=8.0, n_planted=8))
+    parity.check_full_path(S, shape(n_q_heads=8, n_kv_heads=2, head_dim=64, n_window=64, n_lookahead=1, seq_lens=(5000,)))
