@@ -581,9 +581,19 @@ static speckv_status select_tokens_impl(const speckv_params *p, int32_t top_k, i
   hipError_t e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part),
                               reinterpret_cast<float *>(ws + pl.off_lse), planes, hs, ev);
   if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_reduce_pool_all(pl, planes, nullptr, pooled, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  // a long row is ranked by several workgroups: its pooling is a pass of its own, which counts the first digit (scratch over
+  // the partial pairs and the planes, which are read no more)
+  uint32_t *scratch = reinterpret_cast<uint32_t *>(ws + pl.off_part);
+  const SelectParts sp = row_parts_of(m, count, pl.off_lse - pl.off_part);
+  if (sp.P > 1) {
+    float *merged = reinterpret_cast<float *>(ws + pl.off_pooled2);
+    if ((e = launch_reduce_pool_all(pl, planes, merged, 1, scratch, 2048, hs)) != hipSuccess ||
+        (e = launch_pool_row(pl, merged, pooled, pl.d.pool_k, scratch, scratch + 2048, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  } else if ((e = launch_reduce_pool_all(pl, planes, pooled, pl.d.pool_k, nullptr, 0, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
   if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_select_row(pooled, m, count, sel, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  e = sp.P > 1 ? launch_select_row_parts(pooled, m, count, sel, sp, reinterpret_cast<uint32_t *>(planes), scratch, hs)
+               : launch_select_row(pooled, m, count, sel, hs);
+  if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
   if (ev && hipEventRecord(ev[5], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
   if ((e = launch_expand(sel, count, n_in, pl.d.w, n_neighbor, token_ids, idx_out, ids_out, count_out, hs)) != hipSuccess)
     return SPECKV_ERR_RUNTIME;
@@ -664,9 +674,15 @@ speckv_status specpc_compress_prompt(const speckv_params *p, int32_t l_skip, int
   hipError_t e = launch_score(pl, q0, k0, reinterpret_cast<float2 *>(ws + pl.off_part),
                               reinterpret_cast<float *>(ws + pl.off_lse), planes, hs);
   if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_reduce_pool_all(pl, planes, nullptr, smooth, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_pool_row(smooth, spread, n_in, d.w, n_neighbor, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_select_row(spread, m, count, sel, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  uint32_t *scratch = reinterpret_cast<uint32_t *>(ws + pl.off_part);        // see select_tokens_impl
+  const SelectParts sp = row_parts_of(m, count, pl.off_lse - pl.off_part);
+  if ((e = launch_reduce_pool_all(pl, planes, smooth, d.pool_k, scratch, sp.P > 1 ? 2048 : 0, hs)) != hipSuccess)
+    return SPECKV_ERR_RUNTIME;
+  if ((e = launch_pool_row(pl, smooth, spread, n_neighbor, sp.P > 1 ? scratch : nullptr, sp.P > 1 ? scratch + 2048 : nullptr, hs)) !=
+      hipSuccess) return SPECKV_ERR_RUNTIME;
+  e = sp.P > 1 ? launch_select_row_parts(spread, m, count, sel, sp, reinterpret_cast<uint32_t *>(planes), scratch, hs)
+               : launch_select_row(spread, m, count, sel, hs);
+  if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
   return from_hip(launch_expand(sel, count, n_in, d.w, 0, token_ids, idx_out, ids_out, count_out, hs));
 }
 

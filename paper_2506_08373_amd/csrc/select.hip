@@ -105,6 +105,32 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
     tile[x] = acc;
   }
   __syncthreads();
+  // A wide maximum in place: after pass p an entry holds the maximum of 2^p entries from its own on, and a window is two
+  // of those.  Entries outside [0, m) become NaN, which fmaxf passes over.  (Kernel of 64: one row of 12K scores 14.0 us
+  // with a read per entry of the window, one of 60K 8.7 with this.)
+  const bool wide = !pool_avg && pool_k >= 16 && raw == nullptr;
+  int run = 1;
+  if (wide) {
+    for (; 2 * run <= pool_k; run *= 2) {
+      float v[kPerThread];
+#pragma unroll
+      for (int u = 0; u < kPerThread; ++u) {
+        const int x = threadIdx.x + u * kPoolThreads, jj = j0 - half + x;
+        v[u] = x < span ? tile[x] : __builtin_nanf("");
+        if (run == 1 && (jj < 0 || jj >= m)) v[u] = __builtin_nanf("");
+        float w = x + run < span ? tile[x + run] : __builtin_nanf("");
+        if (run == 1 && (jj + 1 < 0 || jj + 1 >= m)) w = __builtin_nanf("");
+        v[u] = fmaxf(v[u], w);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kPerThread; ++u) {
+        const int x = threadIdx.x + u * kPoolThreads;
+        if (x < span) tile[x] = v[u];
+      }
+      __syncthreads();
+    }
+  }
   for (int x = threadIdx.x; x < kPoolTile; x += kPoolThreads) {
     const int j = j0 + x;
     if (j >= n_row) break;                                  // entries past the live length read as zero
@@ -114,7 +140,9 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
     if (j < m) {
       const int lo = max(0, j - half), hi = min(m - 1, j + after);
       best = tile[lo - j0 + half];
-      if (pool_avg) {
+      if (wide) {
+        best = fmaxf(tile[x], tile[x + pool_k - run]);    // the whole window j - half .. j + after
+      } else if (pool_avg) {
         for (int jj = lo + 1; jj <= hi; ++jj) best += tile[jj - j0 + half];
         best /= (float)pool_k;                            // zeros outside [0, m) count in the divisor
       } else {
@@ -165,7 +193,9 @@ constexpr int kAllTile = 64, kAllSlices = 4;
 
 __global__ __launch_bounds__(kAllTile * kAllSlices) void reduce_pool_all_kernel(
     int n_in, int n_window, int pool_k, int pool_avg, PlaneMerge pm, const float *__restrict__ planes,
-    float *__restrict__ raw, float *__restrict__ pooled) {
+    float *__restrict__ raw, float *__restrict__ pooled, uint32_t *__restrict__ clear, int clear_words) {
+  const int id = blockIdx.x * (kAllTile * kAllSlices) + threadIdx.x;       // (at least as many threads as words: see launch)
+  if (id < clear_words) clear[id] = 0u;
   __shared__ float part[kAllSlices][kAllTile + SPECKV_MAX_POOL_K + 1];
   const int j0 = blockIdx.x * kAllTile;
   if (j0 >= n_in) return;
@@ -1363,6 +1393,14 @@ struct PartsArgs {
   int P, part_len;
 };
 
+// the same for a single row (prompt-token selection)
+__global__ __launch_bounds__(kSelThreads) void select_row_parts_kernel(const float *__restrict__ row, int m, int count,
+                                                                       int32_t *__restrict__ sel,
+                                                                       const uint32_t *__restrict__ hist0, PartsArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char sel_lds[];
+  select_in_parts(row, m, count, sel, hist0, a.P, blockIdx.x, a.part_len, a.list, a.counters + 64, a.counters, sel_lds);
+}
+
 __global__ __launch_bounds__(kSelThreads) void select_parts_kernel(Dims d, SeqTab t, const float *__restrict__ pooled,
                                                                    int32_t *__restrict__ idx,
                                                                    const uint32_t *__restrict__ hist0, PartsArgs a) {
@@ -1555,43 +1593,74 @@ __global__ __launch_bounds__(kSelThreads) void select_ada_kernel(Dims d, SeqTab 
 }
 
 // ----------------------------------------------------------------------------------
-// neighbour expansion (single workgroup)
+// neighbour expansion
 // ----------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelThreads) void expand_kernel(
-    const int32_t *__restrict__ sel, int count, int n_in, int n_window, int nb,
+// `sel` is ascending, so interval r = [t_r - nb, t_r + nb] only has to be trimmed against the end of interval r-1 to make
+// the union duplicate-free.  A workgroup takes `per` intervals, adds up what the ones before them leave (two cached
+// reads per interval) and writes one output per thread.  One workgroup for everything wrote an interval per thread, 17
+// scattered words each: 4096 tokens +- 8 23.1 us, here 7.1 (2048 tokens without neighbours 4.7 and 5.4).
+constexpr int kExpThreads = 256, kExpMin = 64, kExpWorkgroups = 256;
+
+__global__ __launch_bounds__(kExpThreads) void expand_kernel(
+    const int32_t *__restrict__ sel, int count, int per, int n_in, int n_window, int nb,
     const int32_t *__restrict__ token_ids, int32_t *__restrict__ idx_out,
     int32_t *__restrict__ ids_out, int32_t *__restrict__ count_out) {
-  __shared__ uint32_t wave_tot[2][kSelWaves];
-  const int tid = threadIdx.x;
-  uint32_t written = 0;
-  int buf = 0;
-  // `sel` is ascending, so interval r = [t_r - nb, t_r + nb] only has to be trimmed
-  // against the end of interval r-1 to make the union duplicate-free.
-  for (int r0 = 0; r0 < count; r0 += kSelThreads, buf ^= 1) {
-    const int r = r0 + tid;
-    int start = 0, fresh = 0;
-    if (r < count) {
-      const int tok = sel[r];
-      const int lo = max(0, tok - nb), hi = min(n_in - 1, tok + nb);
-      const int prev_hi = r > 0 ? min(n_in - 1, sel[r - 1] + nb) : -1;
-      start = max(lo, prev_hi + 1);
-      fresh = max(0, hi - start + 1);
+  __shared__ uint32_t wave_tot[2][kExpThreads / 64];
+  __shared__ int first[kExpThreads], at[kExpThreads + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto trimmed = [&](int r, int &start) {
+    const int tok = sel[r];
+    const int lo = max(0, tok - nb), hi = min(n_in - 1, tok + nb);
+    const int prev_hi = r > 0 ? min(n_in - 1, sel[r - 1] + nb) : -1;
+    start = max(lo, prev_hi + 1);
+    return max(0, hi - start + 1);
+  };
+  // exclusive prefix sum over the workgroup in thread order
+  auto scan = [&](uint32_t v, uint32_t *tot, uint32_t &total) {
+    const uint32_t inc = wave_inclusive_scan(v);
+    if (lane == 63) tot[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w2 = 0; w2 < kExpThreads / 64; ++w2) {
+      if (w2 < wave) before += tot[w2];
+      total += tot[w2];
     }
+    return before + inc - v;
+  };
+  const int r0 = blockIdx.x * per, r1 = min(count, r0 + per);
+  uint32_t mine = 0, written;
+  int start;
+#pragma unroll 8
+  for (int r = tid; r < r0; r += kExpThreads) mine += (uint32_t)trimmed(r, start);
+  (void)scan(mine, wave_tot[0], written);
+  for (int q0 = r0, buf = 1; q0 < r1; q0 += kExpThreads, buf ^= 1) {
+    const int fresh = q0 + tid < r1 ? trimmed(q0 + tid, start) : 0;
     uint32_t total;
-    uint32_t pos = written + block_exclusive_scan((uint32_t)fresh, wave_tot[buf], &total);
-    // with `sel` ascending and complete neither limit is ever met; no other `sel` may write outside the outputs
-    pos = min(pos, (uint32_t)n_in);
-    fresh = min(fresh, n_in - (int)pos);
-    for (int e = 0; e < fresh; ++e) {
-      idx_out[pos + e] = start + e;
-      ids_out[pos + e] = token_ids[start + e];
+    at[tid] = (int)scan((uint32_t)fresh, wave_tot[buf], total);
+    first[tid] = start;
+    __syncthreads();
+    // with `sel` ascending and complete the limit is never met; no other `sel` may write outside the outputs
+    const int room = n_in - (int)min(written, (uint32_t)n_in);
+    for (int o = tid; o < min((int)total, room); o += kExpThreads) {
+      int lo = 0, hi = kExpThreads;               // the last interval that begins at or before o (empty ones begin where the next does)
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (at[mid] <= o) lo = mid; else hi = mid;
+      }
+      const int j = first[lo] + (o - at[lo]);
+      idx_out[written + (uint32_t)o] = j;
+      ids_out[written + (uint32_t)o] = token_ids[j];
     }
     written = min(written + total, (uint32_t)n_in);
+    __syncthreads();
   }
+  if (blockIdx.x != gridDim.x - 1) return;
   const int m = n_in - n_window;
   const int last_hi = count > 0 ? min(n_in - 1, sel[count - 1] + nb) : -1;
   const int wstart = max(max(m, last_hi + 1), (int)written);       // the last: holds anyway (see above)
-  for (int j = wstart + tid; j < n_in; j += kSelThreads) {
+  for (int j = wstart + tid; j < n_in; j += kExpThreads) {
     idx_out[written + (j - wstart)] = j;
     ids_out[written + (j - wstart)] = token_ids[j];
   }
@@ -1642,11 +1711,12 @@ hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, f
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *raw, float *pooled,
-                                  hipStream_t st) {
+hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *pooled, int32_t pool_k, uint32_t *clear,
+                                  int32_t clear_words, hipStream_t st) {
   const Dims &d = pl.d;
   const int n_in = (int)d.T;
   const int tiles = (n_in + kAllTile - 1) / kAllTile;
+  if (clear_words > tiles * kAllTile * kAllSlices) return hipErrorInvalidValue;
   // every plane (row super-block, layer, head) merges with one op: all sums, or all maxima
   PlaneMerge pm;
   pm.n_inner = 1;
@@ -1655,17 +1725,49 @@ hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *ra
   pm.outer_max = d.reduce_max && d.head_max;
   pm.plane_stride = n_in;
   hipLaunchKernelGGL(reduce_pool_all_kernel, dim3(tiles), dim3(kAllTile * kAllSlices), 0, st, n_in, d.w,
-                     d.pool_k, d.pool_avg, pm, planes, raw, pooled);
+                     pool_k, d.pool_avg, pm, planes, (float *)nullptr, pooled, clear, clear_words);
   return hipGetLastError();
 }
 
-hipError_t launch_pool_row(const float *in, float *out, int32_t n_in, int32_t n_window, int32_t pool_k,
+hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t pool_k, uint32_t *hist0, uint32_t *arrived,
                            hipStream_t st) {
-  const int tiles = (n_in + kAllTile - 1) / kAllTile;
+  if (hist0 == nullptr) {
+    const int n_in = (int)pl.d.T;
+    PlaneMerge one;
+    one.n_inner = 1; one.n_outer = 1; one.inner_max = 0; one.outer_max = 0; one.plane_stride = n_in;
+    hipLaunchKernelGGL(reduce_pool_all_kernel, dim3((n_in + kAllTile - 1) / kAllTile), dim3(kAllTile * kAllSlices), 0, st, n_in,
+                       pl.d.w, pool_k, 0, one, in, (float *)nullptr, out, (uint32_t *)nullptr, 0);
+    return hipGetLastError();
+  }
+  Dims d = pl.d;                      // the row as the only row of a call
+  d.L = d.Hkv = 1;
+  d.pool_k = pool_k;
+  d.pool_avg = 0;
   PlaneMerge pm;
-  pm.n_inner = 1; pm.n_outer = 1; pm.inner_max = 0; pm.outer_max = 0; pm.plane_stride = n_in;
-  hipLaunchKernelGGL(reduce_pool_all_kernel, dim3(tiles), dim3(kAllTile * kAllSlices), 0, st, n_in, n_window,
-                     pool_k, 0, pm, in, (float *)nullptr, out);
+  pm.n_inner = 1; pm.n_outer = 1; pm.inner_max = 0; pm.outer_max = 0; pm.plane_stride = 0;
+  const int tiles = ((int)d.T + kPoolTile - 1) / kPoolTile;
+  hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)tiles), dim3(kPoolThreads), 0, st, d, pl.t, pm, in, (float *)nullptr, out,
+                     tiles, hist0, arrived);
+  return hipGetLastError();
+}
+
+// Several workgroups rank the row of a prompt-token call when it is too long for one workgroup's registers; the counters of the
+// first digit need a pooling pass with whole tiles (launch_pool_row) and 9 KiB.  Pooling and selection, 65472 candidates, 4096 kept:
+// 14.2 + 41.1 us with one workgroup, 7.8 + 8.0 + 14.8 with 16; 16936 candidates 4.8 + 13.4 and 4.7 + 5.5 + 15.4.
+SelectParts row_parts_of(int32_t m, int32_t count, size_t scratch_bytes) {
+  SelectParts sp = {1, 0};
+  if (m <= 4 * kRegMaxVec - 4 || count < 1 || count > kPartsMaxCount || scratch_bytes < kRowScratchWords * sizeof(uint32_t)) return sp;
+  sp.part_len = (int)align_up((m + 3 + kPartsMax - 1) / kPartsMax, kPartTile);
+  sp.P = (m + 3 + sp.part_len - 1) / sp.part_len;
+  return sp;
+}
+
+hipError_t launch_select_row_parts(const float *row, int32_t m, int32_t count, int32_t *sel, const SelectParts &sp,
+                                   uint32_t *list, uint32_t *scratch, hipStream_t st) {
+  const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(select_row_parts_kernel), kSelLdsBytes);
+  if (e != hipSuccess) return e;
+  const PartsArgs a = {list, scratch + 2048, sp.P, sp.part_len};
+  hipLaunchKernelGGL(select_row_parts_kernel, dim3(sp.P), dim3(kSelThreads), kSelLdsBytes, st, row, m, count, sel, scratch, a);
   return hipGetLastError();
 }
 
@@ -1727,8 +1829,10 @@ hipError_t launch_select_row(const float *pooled_row, int32_t m, int32_t count, 
 hipError_t launch_expand(const int32_t *sel, int32_t count, int32_t n_in, int32_t n_window,
                          int32_t n_neighbor, const int32_t *token_ids, int32_t *idx_out,
                          int32_t *ids_out, int32_t *count_out, hipStream_t st) {
-  hipLaunchKernelGGL(expand_kernel, dim3(1), dim3(kSelThreads), 0, st, sel, count, n_in, n_window,
-                     n_neighbor, token_ids, idx_out, ids_out, count_out);
+  const int per = std::max(kExpMin, (int)align_up((count + kExpWorkgroups - 1) / kExpWorkgroups, kExpMin));
+  const int groups = std::max(1, (count + per - 1) / per);
+  hipLaunchKernelGGL(expand_kernel, dim3(groups), dim3(kExpThreads), 0, st, sel, count, per, n_in, n_window,
+                     std::min(n_neighbor, n_in), token_ids, idx_out, ids_out, count_out);
   return hipGetLastError();
 }
 

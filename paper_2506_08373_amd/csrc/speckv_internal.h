@@ -188,14 +188,13 @@ __host__ __device__ inline int block_of_slot(const BlockSplit &b, int s) { retur
 // every row's pooled scores (the non-window entries), for launch_select.
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
                               hipStream_t st, uint32_t *hist0 = nullptr, uint32_t *arrived = nullptr);
-// single output row summing every plane of a one-sequence call (prompt-token selection)
-hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *raw, float *pooled,
-                                  hipStream_t st);
-// max-pool (kernel pool_k, clipped to [0, n_in - n_window)) of one row of n_in scores
-hipError_t launch_pool_row(const float *in, float *out, int32_t n_in, int32_t n_window, int32_t pool_k,
+// single output row merging every plane of a one-sequence call (prompt-token selection), pooled with pool_k (1: not at
+// all); leaves clear[0..clear_words) zeroed
+hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *pooled, int32_t pool_k, uint32_t *clear,
+                                  int32_t clear_words, hipStream_t st);
+// max-pool (kernel pool_k, clipped to [0, n_in - n_window)) of one row of n_in scores; hist0, arrived: see launch_reduce_pool
+hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t pool_k, uint32_t *hist0, uint32_t *arrived,
                            hipStream_t st);
-// hist / state: scratch of the split-row path (off_sel_hist, off_sel_state); with either null, or when
-// the plan does not split rows (sel_parts == 1), every row is ranked by one workgroup.
 // hist0, when not null: the rows' first-digit histograms from launch_reduce_pool.  With them, and with list (a word per
 // score, laid out like pooled) and counters (kPartsWords per row: an arrival counter, which launch_reduce_pool zeroes, and from
 // word 64 on 2 * P counts; rows whose counters share a cache line would wait for each other's atomics), several workgroups
@@ -212,6 +211,12 @@ hipError_t launch_select_ada(const Plan &pl, int32_t c_floor, const float *poole
                              int32_t *head_off, uint32_t *hist, uint32_t *state, hipStream_t st);
 hipError_t launch_compact_ada(const Plan &pl, const void *k, const void *v, const int32_t *idx,
                               const int32_t *head_off, void *k_out, void *v_out, hipStream_t st);
+// The same by several workgroups (row_parts_of: P > 1).  scratch: kRowScratchWords words, the row's first-digit histogram from
+// launch_pool_row and the arrival counter it zeroed; list: a word per score.
+constexpr int kRowScratchWords = 2048 + kPartsWords;
+SelectParts row_parts_of(int32_t m, int32_t count, size_t scratch_bytes);
+hipError_t launch_select_row_parts(const float *row, int32_t m, int32_t count, int32_t *sel, const SelectParts &sp,
+                                   uint32_t *list, uint32_t *scratch, hipStream_t st);
 hipError_t launch_select_row(const float *pooled_row, int32_t m, int32_t count, int32_t *sel,
                              hipStream_t st);
 hipError_t launch_expand(const int32_t *sel, int32_t count, int32_t n_in, int32_t n_window,

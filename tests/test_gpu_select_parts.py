@@ -96,3 +96,60 @@ def test_a_length_on_the_device(S, n_live):
     q, k = tensors((60000,))
     n_dev = torch.tensor([n_live], dtype=torch.int32, device="cuda")
     check(S, q, k, (60000,), 16, 1500, n_in_dev=n_dev)
+
+
+# one row of a prompt-token call: ranked by one workgroup up to 32K candidates and above 8192 kept, by several otherwise; the
+# expansion with fewer intervals than a workgroup takes, with many workgroups, with none, with intervals that all overlap
+@pytest.mark.parametrize("n,top_k,n_neighbor", [
+    (3000, 1, 3), (32783, 700, 8), (32784, 700, 8), (20003, 0, 4), (20003, 4096, 1), (40005, 8192, 2), (40005, 8193, 30),
+    (70001, 20000, 1), (20003, 20003, 5), (20003, 3, 2**31 - 1)])
+def test_prompt_tokens_and_their_neighbours(S, n, top_k, n_neighbor):
+    w = 16
+    q, k = tensors((n,), 2, 2, gain=2.0)
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=(n,), n_window=w, pool_k=7, c_max=1, sm_scale=0.125)
+    ids = torch.randint(0, 1 << 20, (n,), dtype=torch.int32, device="cuda")
+    ws = torch.empty(S.specpc_workspace_bytes(p, top_k), dtype=torch.uint8, device="cuda")
+
+    def run(nb):
+        idx, out = (torch.full((n,), -5, dtype=torch.int32, device="cuda") for _ in range(2))
+        count = torch.zeros(1, dtype=torch.int32, device="cuda")
+        S.specpc_select_tokens(p, top_k, nb, q, k, ids, idx, out, count, ws)
+        c = int(count)
+        assert torch.equal(out[:c], ids[idx[:c].long()]) and bool((idx[c:] == -5).all())
+        return idx[:c].cpu().numpy()
+
+    m = n - w
+    kept = run(0)
+    assert kept[-w:].tolist() == list(range(m, n))
+    # the scores again in 64 bits
+    score = torch.zeros(n, dtype=torch.float64, device="cuda")
+    last = torch.cat([m + torch.arange(w), torch.full((q.shape[2] - w,), n - 1)]).cuda()
+    hidden = torch.arange(n, device="cuda")[None, :] > last[:, None]
+    for layer in range(2):
+        for h in range(4):
+            logits = (q[layer, 0, :, h].double() @ k[layer, :, h // 2].double().t()) * 0.125
+            score += torch.softmax(logits.masked_fill(hidden, -math.inf), dim=1).sum(0)
+    pooled = torch.nn.functional.max_pool1d(score[None, None, :m], 7, 1, 3)[0, 0].cpu().numpy()
+    parity.assert_indices_valid(kept, pooled, n, w, top_k, "tokens")
+    want = np.zeros(n, bool)
+    for t in kept[:len(kept) - w].tolist():
+        want[max(0, t - n_neighbor):t + n_neighbor + 1] = True
+    want[m:] = True
+    assert np.array_equal(run(n_neighbor), np.nonzero(want)[0])
+
+
+@pytest.mark.parametrize("pool_k", [15, 16, 17, 31, 32, 63, 64, 100, 255])
+@pytest.mark.parametrize("n", [40005, 300])
+def test_wide_maximum_pooling(S, n, pool_k):
+    """Fused calls pool without handing the raw scores out; speckv_score with raw does it entry by entry."""
+    q, k = tensors((n,), gain=2.0)
+    w = 16
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=(n,), n_window=w, pool_k=pool_k, c_max=5, sm_scale=0.125)
+    ws = parity.alloc_ws(S, p)
+    raw, pooled, alone = (torch.empty(1, 2 * n, device="cuda") for _ in range(3))
+    S.speckv_score(p, q, k, pooled, raw, ws)
+    S.speckv_score(p, q, k, alone, None, ws)
+    assert torch.equal(pooled, alone)
+    x = raw.view(2, n)[:, :n - w]
+    padded = torch.nn.functional.pad(x, (pool_k // 2, (pool_k - 1) // 2), value=-1.0)
+    assert torch.equal(pooled.view(2, n)[:, :n - w], padded.unfold(1, pool_k, 1).amax(-1))
