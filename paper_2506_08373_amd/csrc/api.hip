@@ -435,18 +435,24 @@ static speckv_status compress_impl(const speckv_params *p, const void *q, const 
   float *pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
   // the pooling kernel also counts the first selection digit of every row (counters zeroed by the
   // kernel between the sweeps), so that selection starts at its second read of the pooled scores
-  uint32_t *hist0 = pl.hist0_words > 0 ? reinterpret_cast<uint32_t *>(ws + pl.off_hist0) : nullptr;
+  const bool short_rows = pool_select_fused(pl);
+  uint32_t *hist0 = pl.hist0_words > 0 && !short_rows ? reinterpret_cast<uint32_t *>(ws + pl.off_hist0) : nullptr;
   hipError_t e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part),
                               reinterpret_cast<float *>(ws + pl.off_lse), planes, hs, ev, lse_in, hist0, pl.hist0_words);
   if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
-  // once pooled, the planes and the partial pairs are scratch for the selection (a row's tail alone has 128 pairs, 1 KiB, and its
-  // counters take as much)
-  uint32_t *counters = reinterpret_cast<uint32_t *>(ws + pl.off_part);
-  if ((e = launch_reduce_pool(pl, planes, nullptr, pooled, hs, hist0, counters)) != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_select(pl, pooled, idx, reinterpret_cast<uint32_t *>(ws + pl.off_sel_hist),
-                         reinterpret_cast<uint32_t *>(ws + pl.off_sel_state), hs, hist0,
-                         reinterpret_cast<uint32_t *>(planes), counters)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (short_rows) {
+    if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+    if ((e = launch_pool_select(pl, planes, idx, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  } else {
+    // once pooled, the planes and the partial pairs are scratch for the selection (a row's tail alone has 128 pairs, 1 KiB, and
+    // its counters take as much)
+    uint32_t *counters = reinterpret_cast<uint32_t *>(ws + pl.off_part);
+    if ((e = launch_reduce_pool(pl, planes, nullptr, pooled, hs, hist0, counters)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+    if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+    if ((e = launch_select(pl, pooled, idx, reinterpret_cast<uint32_t *>(ws + pl.off_sel_hist),
+                           reinterpret_cast<uint32_t *>(ws + pl.off_sel_state), hs, hist0,
+                           reinterpret_cast<uint32_t *>(planes), counters)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  }
   if (ev && hipEventRecord(ev[5], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
   if ((e = launch_compact(pl, k, v, idx, k_out, v_out, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
   if (ev && hipEventRecord(ev[6], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;

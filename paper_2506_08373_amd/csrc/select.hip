@@ -616,17 +616,17 @@ __device__ __forceinline__ void emit_from_registers(const RegRow &r, int m, uint
   }
 }
 
-// select_top_row for a row that fits registers.  Entries outside the row have the smallest key of all, so they
+// select_top_row for a row that registers hold (load(r) fills them).  Entries outside the row have the smallest key of all, so they
 // never change the rank of one inside (they may be counted beside a key of 0 in the lowest bins, behind it).
-__device__ __forceinline__ void select_in_registers(const float *__restrict__ x, int m, int count,
-                                                    int32_t *__restrict__ out, RegShared &sh,
+template <typename F>
+__device__ __forceinline__ void select_in_registers(F load, int m, int count, int32_t *__restrict__ out, RegShared &sh,
                                                     const uint32_t *__restrict__ first_digit) {
   const int tid = threadIdx.x;
   const int b0 = 2047 - 2 * tid, b1 = 2046 - 2 * tid;           // threads in order walk the bins downwards
   uint32_t c0 = 0, c1 = 0;
   if (first_digit != nullptr) { c0 = first_digit[b0]; c1 = first_digit[b1]; }
   RegRow r;
-  load_row(x, m, r);
+  load(r);
   for (int b = tid; b < kRegCopies * kRegStride; b += kSelThreads) sh.second[b] = 0;
   for (int b = tid; b < kRegCopies * (1024 + 8); b += kSelThreads) sh.third[b] = 0;
   uint32_t remaining = (uint32_t)count;
@@ -1046,7 +1046,7 @@ __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int 
                                                int32_t *__restrict__ out, unsigned char *lds,
                                                const uint32_t *__restrict__ first_digit = nullptr) {
   if (row_in_registers(x, m, first_digit != nullptr)) {
-    select_in_registers(x, m, count, out, *reinterpret_cast<RegShared *>(lds), first_digit);
+    select_in_registers([&](RegRow &r) { load_row(x, m, r); }, m, count, out, *reinterpret_cast<RegShared *>(lds), first_digit);
     return;
   }
   SelShared &sh = *reinterpret_cast<SelShared *>(lds);
@@ -1104,6 +1104,78 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(Dims d, SeqTab t,
   for (int x = threadIdx.x; x < d.w; x += kSelThreads) out[count + x] = m + x;   // window, last
   for (int x = count + d.w + threadIdx.x; x < n_keep; x += kSelThreads) out[x] = -1;   // unused slots
   if (count > 0) select_top_row(row, m, count, out, sel_lds, hist0 != nullptr ? hist0 + (int64_t)unit * 2048 : nullptr);
+}
+
+// Pooling and selection of short rows in one launch: the row's workgroup merges the planes into LDS (reduce_pool_tile's sums,
+// in its order) and pools the entries it then holds in registers.  The pooled scores of a fused call are nobody else's, so they
+// are not written.  Bound by latencies; what it saves is a launch between two kernels that wait for each other.
+// Pooling + selection kernels -> here: 2 rows of 1K 5.0 + 7.6 -> 9.3 us, 8 rows of 4K 5.3 + 9.4 -> 11.8; calls: one fp32 layer of
+// 1K keys 36.5 -> 33.0, one layer of 4K 38.7 -> 36.0.  With more entries the row's one workgroup is the limit.
+constexpr int kFusedMax = 8192, kFusedMaxPool = 16;        // entries of a row, pooling kernel
+static_assert(kFusedMax <= kHistCopies * kRegStride && kFusedMax <= 4 * kRegMaxVec, "the row lies over RegShared::first");
+
+__global__ __launch_bounds__(kSelThreads) void pool_select_kernel(Dims d, SeqTab t, PlaneMerge pm, const float *__restrict__ planes,
+                                                                  int32_t *__restrict__ idx) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char sel_lds[];
+  RegShared &sh = *reinterpret_cast<RegShared *>(sel_lds);
+  float *row = reinterpret_cast<float *>(sh.first);
+  const int tid = threadIdx.x;
+  const int unit = blockIdx.x;
+  const int g = unit % d.Hkv;
+  const int s = (unit / d.Hkv) % d.S;
+  const int layer = unit / (d.Hkv * d.S);
+  const int n_row = t.cu[s + 1] - t.cu[s];
+  const int m = live_len(d, t, s) - d.w;
+  const int n_keep = t.ck[s + 1] - t.ck[s];
+  const int count = min(n_keep - d.w, m);
+  const float *in = planes + (int64_t)layer * d.Hkv * d.T + (int64_t)d.Hkv * t.cu[s] + (int64_t)g * n_row;
+  int32_t *out = idx + (int64_t)layer * d.Hkv * d.KT + (int64_t)d.Hkv * t.ck[s] + (int64_t)g * n_keep;
+  constexpr int kPer = kFusedMax / kSelThreads;
+  float r0[kPer], r1[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {                          // every load is issued before the first is used
+    const int j = tid + u * kSelThreads;
+    r0[u] = j < m ? in[j] : 0.f;
+    r1[u] = j < m && pm.n_outer == 2 ? in[j + pm.plane_stride] : 0.f;
+  }
+  for (int x = tid; x < d.w; x += kSelThreads) out[count + x] = m + x;   // window, last
+  for (int x = count + d.w + tid; x < n_keep; x += kSelThreads) out[x] = -1;   // unused slots
+  if (count <= 0) return;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int j = tid + u * kSelThreads;
+    const float a0 = pm.inner_max ? fmaxf(0.f, r0[u]) : r0[u], a1 = pm.inner_max ? fmaxf(0.f, r1[u]) : r1[u];
+    if (j < m) row[j] = pm.outer_max ? fmaxf(fmaxf(0.f, a0), a1) : 0.f + a0 + a1;
+  }
+  __syncthreads();
+  const int half = d.pool_k / 2, after = (d.pool_k - 1) / 2;
+  auto load = [&](RegRow &r) {
+    r.n_it = ((m + 3) / 4 + kSelThreads - 1) / kSelThreads;
+    r.j0 = 4 * ((tid >> 6) * r.n_it * 64 + (tid & 63));
+#pragma unroll
+    for (int i = 0; i < kRegIters; ++i) {
+      if (i >= kFusedMax / (4 * kSelThreads) || i >= r.n_it) continue;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int j = r.j0 + 256 * i + c;
+        uint32_t key = 0u;
+        if (j < m) {
+          const int lo = max(0, j - half), hi = min(m - 1, j + after);
+          float best = row[lo];
+          if (d.pool_avg) {
+            for (int jj = lo + 1; jj <= hi; ++jj) best += row[jj];
+            best /= (float)d.pool_k;                        // zeros outside [0, m) count in the divisor
+          } else {
+            for (int jj = lo + 1; jj <= hi; ++jj) best = fmaxf(best, row[jj]);
+          }
+          key = ordered_key(best);
+        }
+        r.key[4 * i + c] = key;
+      }
+    }
+    __syncthreads();                                        // the row's LDS is the first digit's counters from here on
+  };
+  select_in_registers(load, m, count, out, sh, nullptr);
 }
 
 __global__ __launch_bounds__(kSelThreads) void select_row_kernel(const float *__restrict__ row,
@@ -1692,6 +1764,32 @@ SelectParts select_parts_of(const Plan &pl) {
   return sp;
 }
 
+// planes of one head (PPH slices) merge like the rows of a head; heads merge by sum or max
+static PlaneMerge merge_of(const Plan &pl) {
+  const Dims &d = pl.d;
+  PlaneMerge pm;
+  pm.n_inner = pl.g.PPH;
+  pm.n_outer = pl.g.RS / pl.g.PPH;
+  pm.inner_max = d.reduce_max;
+  pm.outer_max = d.reduce_max && d.head_max;
+  pm.plane_stride = (int64_t)d.L * d.Hkv * d.T;
+  return pm;
+}
+
+bool pool_select_fused(const Plan &pl) {
+  int max_n = 0;
+  for (int s = 0; s < pl.d.S; ++s) max_n = std::max(max_n, pl.t.cu[s + 1] - pl.t.cu[s]);
+  return max_n <= kFusedMax && pl.d.pool_k <= kFusedMaxPool && pl.g.PPH == 1 && pl.g.RS <= 2 && pl.sel_parts == 1;
+}
+
+hipError_t launch_pool_select(const Plan &pl, const float *planes, int32_t *idx, hipStream_t st) {
+  const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(pool_select_kernel), sizeof(RegShared));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pool_select_kernel, dim3((unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv)), dim3(kSelThreads), sizeof(RegShared),
+                     st, pl.d, pl.t, merge_of(pl), planes, idx);
+  return hipGetLastError();
+}
+
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
                               hipStream_t st, uint32_t *hist0, uint32_t *arrived) {
   const Dims &d = pl.d;
@@ -1699,13 +1797,7 @@ hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, f
   for (int s = 0; s < d.S; ++s) max_n = max(max_n, pl.t.cu[s + 1] - pl.t.cu[s]);
   const int tiles = (max_n + kPoolTile - 1) / kPoolTile;
   const int64_t blocks = (int64_t)d.L * d.S * d.Hkv * tiles;
-  // planes of one head (PPH slices) merge like the rows of a head; heads merge by sum or max
-  PlaneMerge pm;
-  pm.n_inner = pl.g.PPH;
-  pm.n_outer = pl.g.RS / pl.g.PPH;
-  pm.inner_max = d.reduce_max;
-  pm.outer_max = d.reduce_max && d.head_max;
-  pm.plane_stride = (int64_t)d.L * d.Hkv * d.T;
+  const PlaneMerge pm = merge_of(pl);
   hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)blocks), dim3(kPoolThreads), 0, st, d, pl.t,
                      pm, planes, raw, pooled, tiles, hist0, arrived);
   return hipGetLastError();

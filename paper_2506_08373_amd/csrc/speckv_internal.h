@@ -188,6 +188,9 @@ __host__ __device__ inline int block_of_slot(const BlockSplit &b, int s) { retur
 // every row's pooled scores (the non-window entries), for launch_select.
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
                               hipStream_t st, uint32_t *hist0 = nullptr, uint32_t *arrived = nullptr);
+// Pooling and selection of a fused call's short rows in one launch, where pool_select_fused says so.
+bool pool_select_fused(const Plan &pl);
+hipError_t launch_pool_select(const Plan &pl, const float *planes, int32_t *idx, hipStream_t st);
 // single output row merging every plane of a one-sequence call (prompt-token selection), pooled with pool_k (1: not at
 // all); leaves clear[0..clear_words) zeroed
 hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *pooled, int32_t pool_k, uint32_t *clear,

@@ -153,3 +153,17 @@ def test_wide_maximum_pooling(S, n, pool_k):
     x = raw.view(2, n)[:, :n - w]
     padded = torch.nn.functional.pad(x, (pool_k // 2, (pool_k - 1) // 2), value=-1.0)
     assert torch.equal(pooled.view(2, n)[:, :n - w], padded.unfold(1, pool_k, 1).amax(-1))
+
+
+# Rows of up to 8192 entries with a pooling kernel of up to 16: pooled and ranked in one launch; both sides of both limits,
+# one and two planes, one vector to a full row, every entry kept, equal scores, a batch
+@pytest.mark.parametrize("lens,rows,c_max,pool_k", [
+    ((17,), 32, 5, 7), ((21,), 32, 100, 7), ((300,), 32, 7, 1), ((4113,), 32, 4000, 16), ((4113,), 32, 900, 17),
+    ((8192,), 32, 2048, 6), ((8193,), 32, 2048, 7), ((5001, 19, 1234, 8192), 32, 300, 7), ((3001,), 320, 700, 7)])
+def test_short_rows_pooled_and_ranked_in_one_launch(S, lens, rows, c_max, pool_k):
+    q, k = tensors(lens, 2, 3, rows=rows, gain=2.0)
+    check(S, q, k, lens, 16, c_max, pool_k)
+    check(S, q, torch.zeros_like(k), lens, 16, c_max, pool_k)
+    if len(lens) == 1:
+        for n_live in (lens[0] - 1, 17, 16, 1):
+            check(S, q, k, lens, 16, c_max, pool_k, n_in_dev=torch.tensor([max(n_live, 16)], dtype=torch.int32, device="cuda"))
