@@ -1534,11 +1534,18 @@ __global__ __launch_bounds__(kSelThreads) void ada_hist_kernel(Dims d, SeqTab t,
   }
 }
 
+// A chain of latencies in one workgroup: a lane's 32 counters are requested together, the suffix sums of up to kAdaLdsHeads heads
+// stay in LDS (with more they go back to the histogram's memory), and what the last level's serial part reads is in LDS.
+// Calls of 8 layers x 32K tokens, 8 heads, three levels: 11.3 us a level with all of it in memory, 7.4 here.
+constexpr int kAdaLdsHeads = 16;
+template <bool IN_LDS>
 __global__ __launch_bounds__(kSelThreads) void ada_decide_kernel(Dims d, SeqTab t, int c_floor, int level,
                                                                  uint32_t *__restrict__ state,
                                                                  uint32_t *__restrict__ hist,
                                                                  int32_t *__restrict__ head_off) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char sel_lds[];
   __shared__ uint32_t wave_tot[kSelWaves];
+  __shared__ uint32_t head_gt[SPECKV_MAX_ADA_HEADS], head_eq[SPECKV_MAX_ADA_HEADS];     // keys above and equal to the prefix
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ls = blockIdx.x;
   const int s = ls % d.S;
@@ -1548,19 +1555,24 @@ __global__ __launch_bounds__(kSelThreads) void ada_decide_kernel(Dims d, SeqTab 
   const int f = min(c_floor, C);
   const unsigned long long need = (unsigned long long)H * (unsigned)(C - f);
   uint32_t *hs = hist + (int64_t)ls * H * 2048;
+  uint32_t *sums = IN_LDS ? reinterpret_cast<uint32_t *>(sel_lds) : hs;       // [H][2048]
   uint32_t *st = state + (int64_t)ls * kAdaStateWords(H);
   const int shift = ada_shift(level), nb = ada_bins(level);
 
   // (i) each head's histogram becomes inclusive suffix sums (keys with this digit or a larger one)
   const int per = nb / 64;
   for (int h = wave; h < H; h += kSelWaves) {
-    uint32_t *hh = hs + (int64_t)h * 2048 + lane * per;
+    const uint32_t *hh = hs + (int64_t)h * 2048 + lane * per;
+    uint32_t *out = sums + (int64_t)h * 2048 + lane * per;
     uint32_t v[32];
+#pragma unroll
+    for (int i = 0; i < 32; i += 4) {            // (every load before the first is used)
+      const uint4 q = i < per ? *reinterpret_cast<const uint4 *>(hh + i) : make_uint4(0u, 0u, 0u, 0u);
+      v[i] = q.x; v[i + 1] = q.y; v[i + 2] = q.z; v[i + 3] = q.w;
+    }
     uint32_t sum = 0;
 #pragma unroll
-    for (int i = 31; i >= 0; --i) {
-      if (i < per) { sum += hh[i]; v[i] = sum; }
-    }
+    for (int i = 31; i >= 0; --i) { sum += v[i]; v[i] = sum; }
     uint32_t run = sum;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -1569,9 +1581,11 @@ __global__ __launch_bounds__(kSelThreads) void ada_decide_kernel(Dims d, SeqTab 
     }
     const uint32_t higher = run - sum;
 #pragma unroll
-    for (int i = 0; i < 32; ++i)
-      if (i < per) hh[i] = v[i] + higher;
+    for (int i = 0; i < 32; i += 4)
+      if (i < per)
+        *reinterpret_cast<uint4 *>(out + i) = make_uint4(v[i] + higher, v[i + 1] + higher, v[i + 2] + higher, v[i + 3] + higher);
   }
+  if (tid < H) head_gt[tid] = level == 0 ? 0u : st[2 + tid];
   __syncthreads();
 
   // (ii) F at the digits nb-1-2t and nb-2-2t; F does not grow with the digit, so the digits
@@ -1579,10 +1593,11 @@ __global__ __launch_bounds__(kSelThreads) void ada_decide_kernel(Dims d, SeqTab 
   const int b0 = nb - 1 - 2 * tid, b1 = nb - 2 - 2 * tid;
   unsigned long long F0 = 0, F1 = 0;
   if (b0 >= 0) {
+#pragma unroll 8
     for (int h = 0; h < H; ++h) {
-      const uint32_t above = level == 0 ? 0u : st[2 + h];
-      const uint32_t c0 = above + hs[(int64_t)h * 2048 + b0];
-      const uint32_t c1 = b1 >= 0 ? above + hs[(int64_t)h * 2048 + b1] : 0u;
+      const uint32_t above = head_gt[h];
+      const uint32_t c0 = above + sums[(int64_t)h * 2048 + b0];
+      const uint32_t c1 = b1 >= 0 ? above + sums[(int64_t)h * 2048 + b1] : 0u;
       F0 += c0 > (uint32_t)f ? c0 - (uint32_t)f : 0u;
       F1 += c1 > (uint32_t)f ? c1 - (uint32_t)f : 0u;
     }
@@ -1594,10 +1609,11 @@ __global__ __launch_bounds__(kSelThreads) void ada_decide_kernel(Dims d, SeqTab 
 
   // (iii) per head: keys above the extended prefix, and keys equal to it
   if (tid < H) {
-    const uint32_t ge = hs[(int64_t)tid * 2048 + digit];
-    const uint32_t gt = digit + 1 < nb ? hs[(int64_t)tid * 2048 + digit + 1] : 0u;
-    st[2 + tid] = (level == 0 ? 0u : st[2 + tid]) + gt;
-    st[2 + H + tid] = ge - gt;
+    const uint32_t ge = sums[(int64_t)tid * 2048 + digit];
+    const uint32_t gt = digit + 1 < nb ? sums[(int64_t)tid * 2048 + digit + 1] : 0u;
+    const uint32_t above = head_gt[tid] + gt;
+    st[2 + tid] = head_gt[tid] = above;
+    st[2 + H + tid] = head_eq[tid] = ge - gt;
   }
   if (tid == 0) st[0] = (level == 0 ? 0u : st[0]) | ((uint32_t)digit << shift);
   if (level < 2) return;
@@ -1607,13 +1623,13 @@ __global__ __launch_bounds__(kSelThreads) void ada_decide_kernel(Dims d, SeqTab 
   if (tid == 0) {
     long long open = (long long)need;
     for (int h = 0; h < H; ++h) {
-      const long long gt = st[2 + h];
+      const long long gt = head_gt[h];
       open -= gt > f ? gt - f : 0;
     }
     int32_t *ho = head_off + (int64_t)ls * (H + 1);
     int off = 0;
     for (int h = 0; h < H; ++h) {
-      const long long gt = st[2 + h], eq = st[2 + H + h];
+      const long long gt = head_gt[h], eq = head_eq[h];
       long long avail = gt + eq - f < eq ? gt + eq - f : eq;
       if (avail < 0) avail = 0;
       const long long take = avail < open ? avail : open;
@@ -1900,8 +1916,16 @@ hipError_t launch_select_ada(const Plan &pl, int32_t c_floor, const float *poole
   for (int level = 0; level < 3; ++level) {
     hipLaunchKernelGGL(ada_hist_kernel, dim3(pairs * d.Hkv), dim3(kSelThreads), 0, st, d, pl.t, pooled,
                        level, state, hist);
-    hipLaunchKernelGGL(ada_decide_kernel, dim3(pairs), dim3(kSelThreads), 0, st, d, pl.t, c_floor, level,
-                       state, hist, head_off);
+    if (d.Hkv <= kAdaLdsHeads) {
+      const size_t lds = (size_t)d.Hkv * 2048 * sizeof(uint32_t);
+      const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(ada_decide_kernel<true>), lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(ada_decide_kernel<true>, dim3(pairs), dim3(kSelThreads), lds, st, d, pl.t, c_floor, level,
+                         state, hist, head_off);
+    } else {
+      hipLaunchKernelGGL(ada_decide_kernel<false>, dim3(pairs), dim3(kSelThreads), 0, st, d, pl.t, c_floor, level,
+                         state, hist, head_off);
+    }
   }
   const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(select_ada_kernel), kSelLdsBytes);
   if (e != hipSuccess) return e;

@@ -167,3 +167,26 @@ def test_short_rows_pooled_and_ranked_in_one_launch(S, lens, rows, c_max, pool_k
     if len(lens) == 1:
         for n_live in (lens[0] - 1, 17, 16, 1):
             check(S, q, k, lens, 16, c_max, pool_k, n_in_dev=torch.tensor([max(n_live, 16)], dtype=torch.int32, device="cuda"))
+
+
+# the most heads whose sums stay in LDS, one more, and the most there may be
+@pytest.mark.parametrize("H,lens,c_floor", [(16, (5003, 40), 11), (17, (5003, 40), 11), (128, (1200,), 0), (1, (9001,), 60)])
+def test_shared_budget_around_the_heads_held_in_lds(S, H, lens, c_floor):
+    n_window, c_max = 8, 100
+    w = workloads.SpecKVWorkload(name="ada_heads", n_layers=1, n_q_heads=H, n_kv_heads=H, head_dim=64, seq_lens=lens, n_window=n_window,
+                                 n_lookahead=1, pool_k=7, c_max=c_max, dtype="bf16", sm_scale=1.0)
+    p = parity.make_params(S, w)
+    rng = np.random.default_rng(H)
+    base = rng.integers(-20, 400, size=(1, H * w.total_tokens)).astype(np.float32) / 400
+    for s in range(len(lens)):
+        parity.split_scores(w, base, 0, s)[...] *= np.float32(2) ** rng.integers(-2, 3, size=(H, 1))
+    idx = torch.full((1, H * S.total_keep(p)), -1, dtype=torch.int32, device="cuda")
+    head_off = torch.full((1, len(lens), H + 1), -1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(S.ada_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.speckv_select_ada(p, c_floor, torch.from_numpy(base).cuda(), idx, head_off, ws)
+    got, off = idx.cpu().numpy(), head_off.cpu().numpy()
+    for s, n in enumerate(lens):
+        rows = parity.split_scores(w, base, 0, s)[:, :n - n_window].astype(np.float64)
+        want = parity.orc.ada_keep_indices(rows, n, n_window, c_max, c_floor)
+        assert off[0, s].tolist() == np.concatenate([[0], np.cumsum([len(x) for x in want])]).tolist()
+        assert parity.ada_block(w, got, 0, s, c_max).tolist() == np.concatenate(want).tolist()
