@@ -5,8 +5,8 @@
 //    kernel k over the non-window candidates (Alg. 1 pooling step; table: Max, k = 7).
 //  * select: the C largest pooled scores per (layer, sequence, KV head), ties to the
 //    smaller index, ascending, then the window m..n_in-1 (Alg. 1 "Select KVs").
-//    MSD radix select on order-preserving 32-bit keys (digits of 11 + 11 + 10 bits; 14 + 11 + 7 where
-//    the pooling kernel has counted the first).  One workgroup per row, or several in fused calls with few
+//    MSD radix select on order-preserving 32-bit keys (digits of 11 + 11 + 10 bits; where
+//    the pooling kernel has counted the first also 14 + 11 + 7, see first_digit.h).  One workgroup per row, or several in fused calls with few
 //    long rows; every step is deterministic.  The histogram of the first digit comes
 //    from the pooling kernel in the fused calls (else from one read of the row); short rows (16K
 //    entries, 32K without the counts) stay in registers, others of up to about 229K entries are
@@ -21,6 +21,7 @@
 //    emits the sorted set with the token ids gathered (Sec. 4.2 prompt compression).
 #include <algorithm>
 
+#include "first_digit.h"
 #include "speckv_internal.h"
 
 namespace speckv {
@@ -34,18 +35,6 @@ __device__ __forceinline__ uint32_t ordered_key(float x) {
   const uint32_t u = raw_bits(x);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-
-// The digit the pooling kernel counts for selection: 14 leading bits of the key (sign, exponent, 5 bits of mantissa), in a window
-// of 2048 of their values: scores are sums of probabilities, none negative, none above the 4096 rows of a group.  With the
-// 11 leading bits (2 bits of mantissa) as the digit, a quarter of a row of scores within a factor of four shared the
-// threshold's digit.  Digits 0 and 2047 also hold whatever lies below 2^-51 and from 2^13 - 2^7 on (and NaNs): a threshold there
-// is looked for without the counts.
-constexpr int kWinShift = 18, kWinLow = (int)(0x80000000u >> kWinShift) + ((127 - 51) << 5);
-__device__ __forceinline__ int window_digit(float x) {
-  return min(max((int)(ordered_key(x) >> kWinShift) - kWinLow, 0), 2047);
-}
-__device__ __forceinline__ bool inside_window(uint32_t digit) { return digit - 1u < 2046u; }
-__device__ __forceinline__ uint32_t window_prefix(uint32_t digit) { return (digit + (uint32_t)kWinLow) << kWinShift; }
 
 // ----------------------------------------------------------------------------------
 // reduce + pool
@@ -148,7 +137,7 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
       } else {
         for (int jj = lo + 1; jj <= hi; ++jj) best = fmaxf(best, tile[jj - j0 + half]);
       }
-      if (first_digit != nullptr) atomicAdd(&first_digit[window_digit(best)], 1u);   // selection's first digit
+      if (first_digit != nullptr) atomicAdd(&first_digit[first_digit_of(ordered_key(best))], 1u);   // selection's first digit
     }
     pooled[j] = best;
   }
@@ -650,8 +639,10 @@ __device__ __forceinline__ void select_in_registers(F load, int m, int count, in
   int low = 7;                                                  // bits of the key below the second digit
   if (first_digit != nullptr) {
     d0 = decide(0, b0, b1, c0, c1);
-    if (inside_window(d0)) d0 = window_prefix(d0) >> kWinShift;
-    else first_digit = nullptr;
+    int open;
+    d0 = key_prefix_of(d0, &open);
+    if (open == 32) first_digit = nullptr;
+    else { d0 >>= open; low = open - 11; }
   }
   if (first_digit == nullptr) {
     low = 10;
@@ -1039,9 +1030,30 @@ __device__ __forceinline__ void select_after_prefix(const float *__restrict__ x,
   if (has_tail) emit_winners(kFastSlots - 1);
 }
 
+// The rest of a selection in which all but the last `open` bits (21 or 10, 18 or 7; mask: the others) of the threshold's key are
+// known to be `prefix`, which in_bin entries share, of which the `remaining` largest are wanted.
+__device__ __forceinline__ void select_below_prefix(const float *__restrict__ x, int m, RowSplit rs, uint32_t prefix, uint32_t mask,
+                                                    int open, uint32_t remaining, uint32_t in_bin, int32_t *__restrict__ out,
+                                                    unsigned char *lds) {
+  SelShared &sh = *reinterpret_cast<SelShared *>(lds);
+  for (;;) {
+    if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 32 - open)) {
+      select_after_prefix(x, m, rs, prefix, 32 - open, remaining, out, *reinterpret_cast<FastShared *>(lds));
+      return;
+    }
+    if (open <= 10) break;
+    open -= 11;
+    histogram_pass(x, m, rs, prefix, mask, open, 2048, sh);
+    in_bin = decide_digit(sh, open, 2048, prefix, mask, remaining);
+  }
+  histogram_pass(x, m, rs, prefix, mask, 0, 1 << open, sh);
+  (void)decide_digit(sh, 0, 1 << open, prefix, mask, remaining);
+  emit_selected(x, m, rs, prefix, remaining, out, sh);
+}
+
 // Writes the `count` (1 <= count <= m) indices of the largest x[0..m) to out, ascending,
 // equal values taken from the low-index end.  lds: kSelLdsBytes of LDS.  first_digit, when not
-// null: how often each value of the row's window_digit occurs (2048 counters), already counted.
+// null: how often each first digit of the row occurs (2048 counters, first_digit.h), already counted.
 __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int m, int count,
                                                int32_t *__restrict__ out, unsigned char *lds,
                                                const uint32_t *__restrict__ first_digit = nullptr) {
@@ -1057,33 +1069,17 @@ __device__ __forceinline__ void select_top_row(const float *__restrict__ x, int 
   if (first_digit != nullptr) {
     const int tid = threadIdx.x;
     in_bin = decide_from_counts(sh, 0, 2048, first_digit[2047 - 2 * tid], first_digit[2046 - 2 * tid], prefix, mask, remaining);
-    if (inside_window(prefix)) {
-      open = kWinShift;
-      prefix = window_prefix(prefix);
-      mask = ~0u << kWinShift;
-    } else {
-      prefix = mask = 0;
-      remaining = (uint32_t)count;
-    }
+    prefix = key_prefix_of(prefix, &open);
+    mask = ~0u << (open & 31);
   }
   if (open == 32) {
+    prefix = mask = 0;
+    remaining = (uint32_t)count;
     open = 21;
     histogram_pass(x, m, rs, prefix, mask, open, 2048, sh);
     in_bin = decide_digit(sh, open, 2048, prefix, mask, remaining);
   }
-  for (;;) {
-    if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 32 - open)) {
-      select_after_prefix(x, m, rs, prefix, 32 - open, remaining, out, *reinterpret_cast<FastShared *>(lds));
-      return;
-    }
-    if (open <= 10) break;
-    open -= 11;
-    histogram_pass(x, m, rs, prefix, mask, open, 2048, sh);
-    in_bin = decide_digit(sh, open, 2048, prefix, mask, remaining);
-  }
-  histogram_pass(x, m, rs, prefix, mask, 0, 1 << open, sh);
-  (void)decide_digit(sh, 0, 1 << open, prefix, mask, remaining);
-  emit_selected(x, m, rs, prefix, remaining, out, sh);
+  select_below_prefix(x, m, rs, prefix, mask, open, remaining, in_bin, out, lds);
 }
 
 __global__ __launch_bounds__(kSelThreads) void select_kernel(Dims d, SeqTab t,
@@ -1367,17 +1363,20 @@ __device__ __forceinline__ void select_in_parts(const float *__restrict__ x, int
   uint32_t prefix = 0, mask = 0, take = (uint32_t)count;
   const uint32_t n_cand = decide_from_counts(sh, 0, 2048, first_digit[2047 - 2 * tid], first_digit[2046 - 2 * tid], prefix, mask, take);
   const uint32_t n_win = (uint32_t)count - take;
-  if (!inside_window(prefix) || n_cand > (uint32_t)kCandCap || count > kPartsMaxCount) {
-    if (part == 0) select_top_row(x, m, count, out, lds, first_digit);
+  int open;
+  prefix = key_prefix_of(prefix, &open);
+  if (open == 32 || n_cand > (uint32_t)kCandCap || count > kPartsMaxCount) {
+    if (part != 0) return;
+    if (open == 32) select_top_row(x, m, count, out, lds);
+    else select_below_prefix(x, m, split_row(x, m), prefix, ~0u << open, open, take, n_cand, out, lds);
     return;
   }
-  prefix = window_prefix(prefix);
-  const uint32_t d0 = prefix >> kWinShift;
+  const uint32_t d0 = prefix >> open;
   uint32_t run = 0;                                          // winners (low half) and candidates of the part so far
   for (int j0 = part * part_len - shift, buf = 0; j0 < end; j0 += kPartTile, buf ^= 1) {
     const int j = j0 + 4 * tid;
-    const uint32_t digit[4] = {ordered_key(next.x) >> kWinShift, ordered_key(next.y) >> kWinShift,
-                               ordered_key(next.z) >> kWinShift, ordered_key(next.w) >> kWinShift};
+    const uint32_t digit[4] = {ordered_key(next.x) >> open, ordered_key(next.y) >> open,
+                               ordered_key(next.z) >> open, ordered_key(next.w) >> open};
     next = load4(j + kPartTile);
     uint32_t win = 0, cand = 0;
 #pragma unroll
@@ -1449,7 +1448,7 @@ __device__ __forceinline__ void select_in_parts(const float *__restrict__ x, int
     }
     return lo;
   };
-  const int n_sel = (int)select_candidates(fs, (int)n_cand, prefix, kWinShift, take, true, [&](int c, uint32_t pos) {
+  const int n_sel = (int)select_candidates(fs, (int)n_cand, prefix, open, take, true, [&](int c, uint32_t pos) {
     const uint32_t j = (uint32_t)fs.cidx[c];
     fs.ckey[pos] = j;
     out[pos + (uint32_t)first_not_below(winner, (int)n_win, j)] = (int32_t)j;

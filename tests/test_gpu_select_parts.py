@@ -91,6 +91,16 @@ def test_scores_that_are_no_numbers(S):
     check(S, q, k, (33001,), 16, 700)
 
 
+# One query row whose logits spread over hundreds of nats, as an attention sink makes them: the threshold lies around 2^-30, 2^-75
+# or among scores that underflowed.  Rows shared by workgroups (8, 128 of them) and not (129, 256; short ones in registers)
+@pytest.mark.parametrize("n,n_layers,n_heads", [(16400, 1, 8), (70003, 1, 2), (17001, 16, 8), (17001, 43, 3), (40003, 32, 8),
+                                                (9001, 32, 8), (9001, 1, 2)])
+@pytest.mark.parametrize("gain", [10.0, 25.0, 60.0])
+def test_peaked_rows(S, n, n_layers, n_heads, gain):
+    q, k = tensors((n,), n_layers, n_heads, rows=1, gain=gain)
+    check(S, q, k, (n,), 1, n // 60)
+
+
 @pytest.mark.parametrize("n_live", [60000, 17003, 900, 16])
 def test_a_length_on_the_device(S, n_live):
     q, k = tensors((60000,))
