@@ -199,6 +199,7 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   cut(kc);
   pl->plan_chunk = g.KC;
   pl->plan_chunks = g.n_fast_chunks;
+  int64_t room_chunks = g.n_fast_chunks;        // unmasked chunks the workspace has room for
   // A call that chunks of kChunkMin keys cannot spread over the CUs is a chain of latencies: set-up, then one tile after the
   // other.  Its workgroups take as few tiles each as keeps everything in one round of the CUs: one fp32 layer of 1K keys
   // 56.7 us with 512 keys each, 36.4 with 128 (its sweeps 19.5 and 21.2 us, then 9.8 and 12.1); one layer of 4K 45.1 us
@@ -208,6 +209,11 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   // groups of 7: 48.3 us with 256 keys each, 62.5 with 512, 66.0 with 128).
   if (kc == kChunkMin && units <= kShortChunkUnits) {
     const int tile = rowb <= 128 && g.MB == 1 ? 128 : kt;            // Operand::KT of the scoring kernels
+    // A shorter prompt may have more chunks than this one, and a workspace that is large enough for a prompt is so for every
+    // shorter one: there is room for the most chunks that the rule below gives at any length up to this one.
+    int64_t most_pieces = 0;
+    for (int s = 0; s < d.S; ++s) most_pieces += std::min(kShortChunks, (t.tail0[s] + tile - 1) / tile);
+    room_chunks = std::max(room_chunks, std::min(most_pieces, (int64_t)kCUs / units - d.S));
     for (int64_t piece = tile; piece < kChunkMin; piece += tile) {
       cut(piece);
       int most = 0;
@@ -222,7 +228,8 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
   // partial pairs of the row-statistics sweep, and behind them the segments its chunk workgroups
   // leave for the repair launch (score_fail_words ints)
-  pl->off_part = take((size_t)units * g.n_chunks * g.RSB * sizeof(float2) + (size_t)score_fail_words(*pl) * sizeof(int32_t));
+  pl->off_part = take((size_t)units * (room_chunks + d.S) * g.RSB * sizeof(float2) +
+                      (size_t)score_fail_words(d, g, room_chunks) * sizeof(int32_t));
   pl->off_lse = take((size_t)d.L * d.Hkv * d.S * g.RS * g.RSB * sizeof(float));
   pl->off_planes = take((size_t)g.RS * d.L * d.Hkv * d.T * sizeof(float));
   pl->off_pooled = take(one_row_per_call ? (size_t)d.T * sizeof(float) : (size_t)d.L * d.Hkv * d.T * sizeof(float));

@@ -105,7 +105,9 @@ hipError_t allow_dynamic_lds(const void *kernel, size_t bytes) {
   return e;
 }
 
-int64_t score_fail_words(const Plan &pl) { return score_chunk_workgroups(pl.d, pl.g) * kFailWaves * kFailWords; }
+int64_t score_fail_words(const Dims &d, const ScoreGeom &g, int64_t n_fast_chunks) {
+  return score_chunk_workgroups(d, g, n_fast_chunks) * kFailWaves * kFailWords;
+}
 
 bool score_uses_qs(const Plan &pl, int pass) {
   ScoreArgs A;

@@ -108,11 +108,11 @@ hipError_t launch_compact(const Plan &pl, const void *k, const void *v, const in
 // by the kernel between the sweeps or by the column sweep: the fused calls need zeroed counters for the pooling
 // kernel and must not use a memset, which a captured graph may not contain).
 // ints behind the partial pairs of the row-statistics sweep (one short list per chunk workgroup)
-int64_t score_fail_words(const Plan &pl);
+int64_t score_fail_words(const Dims &d, const ScoreGeom &g, int64_t n_fast_chunks);
 // Workgroups of one scoring sweep: chunk workgroups ((layer, head, chunk) items rounded up to a
 // multiple of 8, times the row super-blocks) plus one masked tail per (unit, sequence).
-inline int64_t score_chunk_workgroups(const Dims &d, const ScoreGeom &g) {
-  return ((int64_t)g.n_fast_chunks * d.L * d.Hkv + 7) / 8 * 8 * g.RS;
+inline int64_t score_chunk_workgroups(const Dims &d, const ScoreGeom &g, int64_t n_fast_chunks) {
+  return (n_fast_chunks * d.L * d.Hkv + 7) / 8 * 8 * g.RS;
 }
 // True when the key-tile row-statistics sweep sums against fixed reference exponents and a repair
 // launch follows it.  That pays when the sweep runs for several rounds of workgroups; in a
@@ -128,7 +128,7 @@ inline bool score_rows_fixed_reference(const Dims &d, const ScoreGeom &g) {
   const char *e = std::getenv("SPECKV_ROW_STATISTICS");
   if (e != nullptr && std::strcmp(e, "fixed") == 0) return true;
   if (e != nullptr && std::strcmp(e, "online") == 0) return false;
-  return score_chunk_workgroups(d, g) + (int64_t)d.L * d.Hkv * g.RS * d.S > 2 * 256;
+  return score_chunk_workgroups(d, g, g.n_fast_chunks) + (int64_t)d.L * d.Hkv * g.RS * d.S > 2 * 256;
 }
 hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *part, float *lse,
                         float *planes, hipStream_t st, hipEvent_t *events = nullptr,

@@ -274,6 +274,29 @@ def test_plan_invariants_over_random_shapes(lib):
         assert S.workspace_bytes(p) > 0
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("units", range(1, 9))
+def test_workspace_of_a_prompt_suffices_for_every_shorter_one(lib, units, d, dtype):
+    """Calls of few (layer, head, super-block) units cut short prompts into shorter chunks than longer ones.  Up to 512 keys
+    for every workgroup of the first round; beyond, chunks grow with the prompt."""
+    for G, rows in ((4, 32), (4, 128), (1, 600)):
+        def need(*lens):
+            p = S.SpecKVParams(n_layers=1, n_q_heads=G * units, n_kv_heads=units, head_dim=d, seq_lens=lens, n_window=16,
+                               n_lookahead=rows - 16, pool_k=7, c_max=64, sm_scale=0.1, dtype=dtype)
+            info = S.plan_info(p)
+            return S.workspace_bytes(p), S.ada_workspace_bytes(p), info["row_super_blocks"] * units
+        for lens in ([(n,) for n in range(16, 15900, 61)],
+                     [(n, 700, 3000) for n in range(16, 9000, 97)] + [(9000, n, 3000) for n in range(700, 1900, 61)]):
+            before = (0, 0)
+            for ls in lens:
+                *now, n_units = need(*ls)
+                if n_units > 8:
+                    break
+                assert now[0] >= before[0] and now[1] >= before[1], (ls, now, before)
+                before = now
+
+
 def test_plain_c_caller(lib, repo_root, tmp_path):
     """The header and the library from a C99 program (host-side entry points only)."""
     import shutil
