@@ -151,8 +151,8 @@ size_t speckv_workspace_bytes(const speckv_params *p);
 /* Launch plan the host derives for these parameters, for diagnostics and tests (no GPU needed):
  * info[0] waves per scoring workgroup, [1] 32-row blocks per wave, [2] row super-blocks per KV group,
  * [3] keys per chunk of the scoring sweeps, [4] unmasked chunks over all sequences, [5] keys per tile
- * (chunks and masked tails start at multiples of it; a tile may pass through LDS in two halves; calls too
- * small to fill the GPU give a workgroup less than a chunk), [6]
+ * (masked tails start at multiples of it, and chunks too, or at multiples of half of it in calls too small
+ * to fill the GPU: a tile may pass through LDS in two halves), [6]
  * parts a row is split into for selection (1: one workgroup per row), [7] keys per such part, [8]
  * kernels of the unmasked scoring sweeps: bit 0 set when the row-statistics sweep, bit 1
  * when the column-reduction sweep keeps the query rows stationary in LDS (clear: key tiles streamed

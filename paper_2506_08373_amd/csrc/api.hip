@@ -197,8 +197,6 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
     g.n_chunks = g.n_fast_chunks + d.S;
   };
   cut(kc);
-  pl->plan_chunk = g.KC;
-  pl->plan_chunks = g.n_fast_chunks;
   int64_t room_chunks = g.n_fast_chunks;        // unmasked chunks the workspace has room for
   // A call that chunks of kChunkMin keys cannot spread over the CUs is a chain of latencies: set-up, then one tile after the
   // other.  Its workgroups take as few tiles each as keeps everything in one round of the CUs: one fp32 layer of 1K keys
@@ -330,7 +328,7 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
   if (st != SPECKV_OK) return st;
   if (info == nullptr) return SPECKV_ERR_INVALID_ARG;
   const int rowb = pl.d.D * pl.d.elt;
-  info[0] = pl.g.NW; info[1] = pl.g.MB; info[2] = pl.g.RS; info[3] = pl.plan_chunk; info[4] = pl.plan_chunks;
+  info[0] = pl.g.NW; info[1] = pl.g.MB; info[2] = pl.g.RS; info[3] = pl.g.KC; info[4] = pl.g.n_fast_chunks;
   info[5] = rowb <= 128 ? 256 : rowb <= 256 ? 128 : 64;
   info[6] = pl.sel_parts; info[7] = pl.sel_part_len;
   info[8] = (score_uses_qs(pl, 1) ? 1 : 0) | (score_uses_qs(pl, 2) ? 2 : 0);

@@ -60,7 +60,6 @@ struct Plan {
   Dims d;
   SeqTab t;
   ScoreGeom g;
-  int32_t plan_chunk, plan_chunks;   // keys per chunk, chunks; g has shorter ones where a small call cuts them further
   // workspace carve-up (byte offsets, 256-aligned)
   size_t off_part, off_lse, off_planes, off_pooled, off_pooled2, off_sel, total;
   size_t off_ada_hist, off_ada_state, total_ada;   // extra scratch of the shared-budget selection

@@ -214,6 +214,21 @@ def test_plan_of_the_benchmark_configurations(lib):
     assert c5["q_stationary"] & 1 and c5["fixed_reference_rows"] == 0 and tiny["fixed_reference_rows"] == 0
 
 
+def test_plan_of_small_calls(lib):
+    """Up to 8 units: as few tiles a workgroup as keeps a prompt to 20 chunks and the call to one round of the CUs."""
+    def plan(units, n, rows, dtype=torch.bfloat16, d=128, G=4):
+        info = S.plan_info(S.SpecKVParams(n_layers=1, n_q_heads=G * units, n_kv_heads=units, head_dim=d, seq_lens=[n], n_window=16,
+                                          n_lookahead=rows - 16, pool_k=7, c_max=64, sm_scale=0.1, dtype=dtype))
+        return info["chunk_keys"], info["n_chunks"]
+    assert plan(2, 1024, 32, torch.float32, 64) == (128, 7)
+    assert plan(8, 4133, 55) == (256, 16)
+    assert plan(8, 2560 + 15, 55) == (128, 20) and plan(8, 2560 + 128 + 15, 55) == (256, 11)
+    assert plan(8, 7680 + 15, 55) == (384, 20) and plan(8, 7680 + 128 + 15, 55) == (512, 16)
+    assert plan(1, 1280 + 15, 55, torch.float32) == (64, 20) and plan(1, 1280 + 64 + 15, 55, torch.float32) == (128, 11)
+    assert plan(8, 2560 + 15, 30, d=64) == (128, 20) and plan(8, 2560 + 15, 128, d=64) == (256, 10)     # tiles of half a row length in LDS
+    assert plan(9, 4133, 55) == (512, 8)
+
+
 def test_row_statistics_mode_follows_the_environment(lib, monkeypatch):
     import workloads
     w = workloads.llama8b_layer(n_in=32768, n_layers=1)
@@ -256,7 +271,13 @@ def test_plan_invariants_over_random_shapes(lib):
         assert st == 0
         info = S.plan_info(p)
         tile, kc = info["tile_keys"], info["chunk_keys"]
-        assert kc % tile == 0 and kc >= 512
+        # chunks are whole tiles; below 512 keys, in small calls only, whole tiles as they pass through LDS
+        units = L * Hkv * info["row_super_blocks"]
+        if kc < 512:
+            lds_tile = 128 if tile == 256 and info["blocks_per_wave"] == 1 else tile
+            assert units <= 8 and kc % lds_tile == 0 and (info["n_chunks"] + n_seqs) * units <= 256
+        else:
+            assert kc % tile == 0
         rows_per_wg = info["waves"] * info["blocks_per_wave"] * 32
         rp = (w_ + a_ + 31) // 32 * 32
         assert info["row_super_blocks"] * rows_per_wg >= G * min(rp, rows_per_wg) or rp > rows_per_wg

@@ -42,19 +42,24 @@ def test_row_normalisers_merged_in_the_column_sweep(S, kw):
 
 # Calls of up to 8 units with chunks shorter than 512 keys: one tile per workgroup, two, three; a last one that is shorter;
 # a live length that leaves whole workgroups without keys; 8 and 9 units; every tile size (64 to 256 keys)
-@pytest.mark.parametrize("kw", [
-    dict(seq_lens=(130,), n_kv_heads=1, n_q_heads=4), dict(seq_lens=(128 * 3 + 15,), n_kv_heads=1, n_q_heads=4),
-    dict(seq_lens=(128 * 3 + 15, 900), dtype="f32", head_dim=64, n_kv_heads=2), dict(seq_lens=(1700,), dtype="f32"),
-    dict(seq_lens=(5200,), n_q_heads=16, n_kv_heads=8), dict(seq_lens=(9000,), n_q_heads=16, n_kv_heads=8, dtype="f16"),
-    dict(seq_lens=(3000,), n_q_heads=18, n_kv_heads=9), dict(seq_lens=(4133,), n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64),
-    dict(seq_lens=(2100,), n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64, head_dim=64),
-], ids=lambda kw: "-".join(str(x) for x in kw.values()))
+@pytest.mark.parametrize("keys,chunks,kw", [
+    (128, 0, dict(seq_lens=(130,), n_kv_heads=1, n_q_heads=4)),
+    (128, 3, dict(seq_lens=(128 * 3 + 15,), n_kv_heads=1, n_q_heads=4)),
+    (128, 9, dict(seq_lens=(128 * 3 + 15, 900), dtype="f32", head_dim=64, n_kv_heads=2)),
+    (128, 13, dict(seq_lens=(1700,), dtype="f32")),
+    (64, 14, dict(seq_lens=(920,), dtype="f32")),
+    (256, 20, dict(seq_lens=(5200,), n_q_heads=16, n_kv_heads=8)),
+    (512, 18, dict(seq_lens=(9000,), n_q_heads=16, n_kv_heads=8, dtype="f16")),
+    (512, 6, dict(seq_lens=(3000,), n_q_heads=18, n_kv_heads=9)),
+    (256, 16, dict(seq_lens=(4133,), n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64)),
+    (256, 7, dict(seq_lens=(2100,), n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64, head_dim=64)),
+], ids=lambda kw: "-".join(str(x) for x in kw.values()) if isinstance(kw, dict) else str(kw))
 @pytest.mark.parametrize("mode", ["online", "fixed"])
-def test_workgroups_of_few_tiles(S, kw, mode, monkeypatch):
+def test_workgroups_of_few_tiles(S, keys, chunks, kw, mode, monkeypatch):
     monkeypatch.setenv("SPECKV_ROW_STATISTICS", mode)
     w = shape(**kw)
     info = S.plan_info(parity.make_params(S, w))
-    assert info["chunk_keys"] == 512
+    assert (info["chunk_keys"], info["n_chunks"]) == (keys, chunks)
     parity.check_full_path(S, w)
 
 
