@@ -11,9 +11,9 @@
 namespace speckv {
 namespace {
 
-// Merges the per-chunk (max2, sum) pairs of each row into lse2 = max2 + log2(sum).
-// A block covers 64 rows; its 4 waves split the chunks and merge their partial pairs in LDS.
-constexpr int kMergeRows = 64, kMergeSlices = 4;
+// Merges the per-chunk (max2, sum) pairs of each row into lse2 = max2 + log2(sum), in the order of merge_pairs.
+// A block covers 64 rows.
+constexpr int kMergeRows = 64;
 
 // Up to this many chunks a sequence, every workgroup of the column sweep merges the pairs of its own rows instead, and
 // converts a caller's normalisers by itself: the kernel is a launch of 3 to 5 us between two sweeps that wait for each other,
@@ -23,16 +23,11 @@ constexpr int kMergeRows = 64, kMergeSlices = 4;
 // workgroups' reads (the same pairs again for every chunk) outgrow the launch.
 constexpr int kMergeInSweep = 40;
 
-__device__ inline void merge_pair(float &m, float &l, float m2, float l2) {
-  const float mm = fmaxf(m, m2);
-  l = l * exp2f(m - mm) + l2 * exp2f(m2 - mm);
-  m = mm;
-}
-
-__global__ __launch_bounds__(kMergeRows * kMergeSlices) void lse_combine_kernel(ScoreArgs A) {
+template <int SLICES>
+__global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreArgs A) {
   clear_scratch(A, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
                 (int64_t)gridDim.x * gridDim.y * blockDim.x);
-  __shared__ float2 partial[kMergeSlices][kMergeRows];
+  __shared__ float2 partial[SLICES][kMergeRows];
   const Dims &d = A.d;
   const int RSB = A.g.RSB;
   const int blocks_per_unit = RSB / kMergeRows;
@@ -42,28 +37,34 @@ __global__ __launch_bounds__(kMergeRows * kMergeSlices) void lse_combine_kernel(
   const int s = blockIdx.y;
   const int rs = unit % A.g.RS;
   const int lh = unit / A.g.RS;                       // layer * Hkv + head
-  const int c0 = A.t.cc[s], c1 = A.t.cc[s + 1];
+  const int n_entries = A.t.cc[s + 1] - A.t.cc[s] + 1;
   const float2 *pp = A.part + ((int64_t)unit * A.g.n_chunks) * RSB + r;
-  float mm = kNegBig, ll = 0.f;
-#pragma unroll 4
-  for (int c = c0 + slice; c < c1; c += kMergeSlices) {
-    const float2 v = pp[(int64_t)c * RSB];
-    merge_pair(mm, ll, v.x, v.y);
-  }
-  if (slice == 0) {                                   // the sequence's masked tail chunk
-    const float2 v = pp[(int64_t)(A.g.n_fast_chunks + s) * RSB];
-    merge_pair(mm, ll, v.x, v.y);
-  }
-  partial[slice][threadIdx.x % kMergeRows] = make_float2(mm, ll);
-  __syncthreads();
-  if (slice == 0) {
+  float top = kNegBig, sum = 0.f;
+  constexpr int BATCH = kMergeFirst / SLICES;         // entries requested together
+  for (int e0 = slice; e0 < n_entries; e0 += BATCH * SLICES) {
+    float2 in[BATCH];
 #pragma unroll
-    for (int k2 = 1; k2 < kMergeSlices; ++k2) {
-      const float2 v = partial[k2][threadIdx.x];
-      merge_pair(mm, ll, v.x, v.y);
+    for (int u = 0; u < BATCH; ++u) {
+      const int e = e0 + u * SLICES;
+      in[u] = e < n_entries ? pp[(int64_t)(e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1) * RSB] : make_float2(kNegBig, 0.f);
     }
-    A.lse[((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r] = mm + log2f(ll);
+    if (e0 == slice) {
+      merge_pairs(top, sum, in);
+    } else {
+#pragma unroll
+      for (int u = 0; u < BATCH; u += kMergeNext) merge_pairs<kMergeNext>(top, sum, in + u);
+    }
   }
+  if constexpr (SLICES > 1) {
+    partial[slice][threadIdx.x % kMergeRows] = make_float2(top, sum);
+    __syncthreads();
+    if (slice != 0) return;
+    float2 in[SLICES - 1];
+#pragma unroll
+    for (int u = 1; u < SLICES; ++u) in[u - 1] = partial[u][threadIdx.x];
+    merge_pairs(top, sum, in);
+  }
+  A.lse[((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r] = top + log2f(sum);
 }
 
 // Converts caller-supplied natural-log normalisers [L][S][R][Hq] into the padded log2 layout
@@ -141,8 +142,9 @@ hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *pa
   if (A.norm_from != kNormMerged) {
     // nothing: the column sweep makes its normalisers
   } else if (A.lse_in == nullptr) {
-    hipLaunchKernelGGL(lse_combine_kernel, dim3(A.d.L * A.d.Hkv * A.g.RS * (A.g.RSB / kMergeRows), A.d.S),
-                       dim3(kMergeRows * kMergeSlices), 0, st, A);
+    const dim3 blocks(A.d.L * A.d.Hkv * A.g.RS * (A.g.RSB / kMergeRows), A.d.S);
+    if (merge_slices(A.g.MB) == 1) hipLaunchKernelGGL(lse_combine_kernel<1>, blocks, dim3(kMergeRows), 0, st, A);
+    else hipLaunchKernelGGL(lse_combine_kernel<2>, blocks, dim3(kMergeRows * 2), 0, st, A);
   } else {
     hipLaunchKernelGGL(lse_import_kernel, dim3(A.d.L * A.d.Hkv * A.g.RS, A.d.S), dim3(256), 0, st, A);
   }

@@ -39,6 +39,27 @@ __device__ inline void clear_scratch(const ScoreArgs &A, int64_t id, int64_t n_t
   for (int64_t i = id; i < A.clear_words; i += n_threads) A.clear[i] = 0u;
 }
 
+// The pairs of a row are merged in one order, wherever that is done: a length that is read on the device may come with the
+// chunks, and so the place, of a longer prompt, and gives the bits that the same length on the host gives.  merge_slices
+// threads per row take every such entry of the row's list: the first kMergeFirst entries together, then kMergeNext each.  The first
+// thread adds the others' pairs.  Entry 0 is the pair of the sequence's masked tail, entry e that of its e-th chunk; entries
+// of empty chunks, (kNegBig, 0), change nothing.
+constexpr int merge_slices(int MB) { return 2 / MB; }
+constexpr int kMergeFirst = 32, kMergeNext = 8;
+
+// Adds N (reference, sum) pairs to the pair (top, sum).  (Fused by hand: every copy rounds alike.)
+template <int N>
+__device__ __forceinline__ void merge_pairs(float &top, float &sum, const float2 *in) {
+  const float before = top;
+#pragma unroll
+  for (int u = 0; u < N; ++u) top = fmaxf(top, in[u].x);
+  sum *= __builtin_amdgcn_exp2f(before - top);
+#pragma unroll
+  for (int u = 0; u < N; ++u) sum = __builtin_fmaf(in[u].y, __builtin_amdgcn_exp2f(in[u].x - top), sum);
+}
+template <int N>
+__device__ __forceinline__ void merge_pairs(float &top, float &sum, const float2 (&in)[N]) { merge_pairs<N>(top, sum, &in[0]); }
+
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;

@@ -128,17 +128,6 @@ __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3
   plane[0][0] |= least < 2 * kSplitMin - 1 ? 0x7fffu : 0u;
 }
 
-// Adds N (reference, sum) pairs to the pair (top, sum).
-template <int N>
-__device__ __forceinline__ void merge_pairs(float &top, float &sum, const float2 (&in)[N]) {
-  const float before = top;
-#pragma unroll
-  for (int u = 0; u < N; ++u) top = fmaxf(top, in[u].x);
-  sum *= __builtin_amdgcn_exp2f(before - top);
-#pragma unroll
-  for (int u = 0; u < N; ++u) sum += in[u].y * __builtin_amdgcn_exp2f(in[u].x - top);
-}
-
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
 //   PASS    1: row statistics, 2: column reduction
 //   RED     (pass 2) 0: sum over the rows of a head, 1: max over the rows of a head;
@@ -287,11 +276,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       *reinterpret_cast<u32x4 *>(kbuf + (buf_) * TILE_BYTES + p * PLANE_BYTES + r_ * ROWB +   \
                                  ((c_ ^ TL::swizzle(r_)) * 16)) = part_[p];                   \
   }
-  // Column sweep, normalisers merged here: one thread (or RSB_SLICES of them) per row.  Entry 0 of a row's list is the pair
-  // of the sequence's masked tail, entry e that of its e-th chunk.
+  // Column sweep, normalisers merged here (in the order of merge_pairs): one thread (or RSB_SLICES of them) per row.
   // The first entries are requested before everything else: loads return in the order they were issued.
-  constexpr int RSB_SLICES = NW * 64 / RSB, BATCH = 32 / RSB_SLICES;
-  static_assert(RSB_SLICES >= 1, "a thread per row");
+  constexpr int RSB_SLICES = NW * 64 / RSB, BATCH = kMergeFirst / RSB_SLICES;
+  static_assert(RSB_SLICES == merge_slices(MB), "threads per row");
   const int norm_row = tid % RSB, norm_slice = tid / RSB, n_entries = A.t.cc[s + 1] - A.t.cc[s] + 1;
   const float2 *pairs_of_row = A.part + (int64_t)unit * A.g.n_chunks * RSB + norm_row;
   auto entry = [&](int e) {
@@ -371,10 +359,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     if (A.norm_from == kNormPairs) {
       float top = kNegBig, sum = 0.f;
       merge_pairs(top, sum, first_pairs);
-      for (int e0 = slice + BATCH * RSB_SLICES; e0 < n_entries; e0 += RSB_SLICES * 8) {
-        float2 in[8];
+      for (int e0 = slice + BATCH * RSB_SLICES; e0 < n_entries; e0 += RSB_SLICES * kMergeNext) {
+        float2 in[kMergeNext];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) in[u] = entry(e0 + u * RSB_SLICES);
+        for (int u = 0; u < kMergeNext; ++u) in[u] = entry(e0 + u * RSB_SLICES);
         merge_pairs(top, sum, in);
       }
       if constexpr (RSB_SLICES > 1) {

@@ -82,6 +82,43 @@ def test_workgroups_of_few_tiles_with_a_length_on_the_device(S, n_live):
         assert (dev[:, n_live:] == 0).all()
 
 
+# The host length is a bound then: it may call for other chunks than the live length, and for another place where the
+# chunks' pairs are merged (up to 40 chunks the column sweep, with one or two threads per row).  Scores have the same bits.
+LENGTHS = [
+    ("merge", 30000, (30000, 15000, 10200), dict(n_q_heads=16, n_kv_heads=4, n_window=64, n_lookahead=64)),
+    ("merge-two-threads", 60000, (41000, 20000, 12000), dict(n_q_heads=4, n_kv_heads=2, n_window=16, n_lookahead=39)),
+    ("merge-f32", 30000, (17000,), dict(n_q_heads=8, n_kv_heads=4, dtype="f32", n_window=64, n_lookahead=64)),
+    ("merge-64", 60000, (18000,), dict(n_q_heads=8, n_kv_heads=2, head_dim=64, n_window=64, n_lookahead=64)),
+]
+
+
+@pytest.mark.parametrize("bound,lives,kw", [x[1:] for x in LENGTHS], ids=[x[0] for x in LENGTHS])
+def test_a_length_on_the_device_gives_the_bits_of_a_host_length(S, bound, lives, kw):
+    w = shape(seq_lens=(bound,), q_gain=2.0, **kw)
+    t = workloads.generate(w)
+    q, k = t["q"].cuda(), t["k"].cuda()
+    H = w.n_kv_heads
+
+    def scores(kk, n, **extra):
+        p = S.SpecKVParams.for_tensors(q, kk, seq_lens=(n,), n_window=w.n_window, pool_k=w.pool_k, c_max=w.c_max,
+                                       sm_scale=w.sm_scale, **extra)
+        raw, pooled = (torch.full((1, H * n), -1.0, device="cuda") for _ in range(2))
+        idx = torch.full((1, H * S.total_keep(p)), -7, dtype=torch.int32, device="cuda")
+        k_out = torch.empty((1, H * S.total_keep(p), w.head_dim), dtype=kk.dtype, device="cuda")
+        ws = parity.alloc_ws(S, p)
+        S.speckv_score(p, q, kk, pooled, raw, ws)
+        S.speckv_compress(p, q, kk, None, idx, k_out, None, ws)
+        return raw.view(H, n), pooled.view(H, n), idx.view(H, -1)
+
+    for live in lives:
+        raw, pooled, idx = scores(k, bound, n_in_dev=torch.tensor([live], dtype=torch.int32, device="cuda"))
+        raw_h, pooled_h, idx_h = scores(k[:, :live].contiguous(), live)
+        assert torch.equal(raw[:, :live], raw_h) and torch.equal(pooled[:, :live], pooled_h), live
+        assert bool((raw[:, live:] == 0).all()) and bool((pooled[:, live:] == 0).all())
+        keep = idx_h.shape[1]
+        assert torch.equal(idx[:, :keep], idx_h) and bool((idx[:, keep:] == -1).all())
+
+
 # Row blocks that heads share, and blocks that waves share: 32-row blocks of a group -> what the last waves do
 #   1, 2 of 4 waves; 3; 5, 6 of 8 waves; 7; 9, 10 with two blocks a wave; 13, 14; two super-blocks of unequal size; two rows a
 #   head; a head longer than a super-block (never packed)
