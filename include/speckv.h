@@ -126,6 +126,9 @@ typedef struct {
                           m' = n' - n_window: scores at j >= n' are written as 0, idx holds
                           min(c_max, m') candidates, the window m'..n'-1 and then -1 up to the
                           host-sized row; compaction writes zero rows for the -1 entries.
+                          Scores equal those of a call with n' on the host up to rounding (its sums
+                          may be cut up otherwise), and bit for bit where the bound is short enough
+                          for one round of 512-key chunks on the GPU (16K keys of one 8-head layer).
                           With per-head budgets head_off[Hkv] = Hkv * (min(c_max, m') + n_window)
                           and the rows behind it hold -1 / zeros.
                           Supported by speckv_score(_lse), speckv_select(_ada), speckv_compact(_ada)
@@ -150,7 +153,8 @@ size_t speckv_workspace_bytes(const speckv_params *p);
 
 /* Launch plan the host derives for these parameters, for diagnostics and tests (no GPU needed):
  * info[0] waves per scoring workgroup, [1] 32-row blocks per wave, [2] row super-blocks per KV group,
- * [3] keys per chunk of the scoring sweeps, [4] unmasked chunks over all sequences, [5] keys per tile
+ * [3] keys per chunk of the scoring sweeps, [4] unmasked chunks over all sequences (with n_in_dev: for the
+ * host's length, and the most that any shorter length has), [5] keys per tile
  * (masked tails start at multiples of it, and chunks too, or at multiples of half of it in calls too small
  * to fill the GPU: a tile may pass through LDS in two halves), [6]
  * parts a row is split into for selection (1: one workgroup per row), [7] keys per such part, [8]

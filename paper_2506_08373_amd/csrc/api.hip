@@ -23,8 +23,7 @@ constexpr int kSelSplitMinKeys = 1 << 18;            // rows at least this long 
 constexpr int kSelSplitWorkgroups = 512;            // ... when the call has fewer than half this many rows
 constexpr int kSelSplitMaxParts = 64;
 constexpr int kChunkMin = 512;                      // shortest chunk
-constexpr int kShortChunkUnits = 8;                 // ... unless the call has no more (layer, head, super-block) units
-constexpr int kShortChunks = 20;                    // ... at most so many a sequence: every workgroup of the column sweep merges their pairs
+constexpr int kShortChunkUnits = 8;                 // ... unless the call has no more (layer, head, super-block) units: short_chunk
 constexpr int kChunkSmallCap = 4096;                // longest chunk that small problems are given
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -202,7 +201,7 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   // other.  Its workgroups take as few tiles each as keeps everything in one round of the CUs: one fp32 layer of 1K keys
   // 56.7 us with 512 keys each, 36.4 with 128 (its sweeps 19.5 and 21.2 us, then 9.8 and 12.1); one layer of 4K 45.1 us
   // with 512, 38.7 with 256 (13.4 and 14.4, 11.2 and 12.0).  With more units kChunkMin fills the CUs at about 8K keys; there the
-  // cut stays independent of the length, so that a length read on the device gives what the host's would, bit for bit.
+  // cut stays independent of the length.
   // More than 20 chunks a sequence cost the column sweep more in merged pairs than they gain (one layer of 4K keys, 28 heads in
   // groups of 7: 48.3 us with 256 keys each, 62.5 with 512, 66.0 with 128).
   if (kc == kChunkMin && units <= kShortChunkUnits) {
@@ -212,12 +211,20 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
     int64_t most_pieces = 0;
     for (int s = 0; s < d.S; ++s) most_pieces += std::min(kShortChunks, (t.tail0[s] + tile - 1) / tile);
     room_chunks = std::max(room_chunks, std::min(most_pieces, (int64_t)kCUs / units - d.S));
+    static_assert((kShortChunks + 1) * kShortChunkUnits <= kCUs, "short_chunk: one prompt's chunks and tails are one round");
     for (int64_t piece = tile; piece < kChunkMin; piece += tile) {
       cut(piece);
       int most = 0;
       for (int s = 0; s < d.S; ++s) most = std::max(most, t.cc[s + 1] - t.cc[s]);
       if (((int64_t)g.n_fast_chunks + d.S) * units <= kCUs && most <= kShortChunks) break;
       cut(kChunkMin);
+    }
+    // A length that is read on the device is cut as it would be here, by the kernels; the grid has the workgroups for any.
+    if (d.n_dev != nullptr) {
+      g.short_tile = tile;
+      g.KC = kChunkMin;
+      t.cc[1] = g.n_fast_chunks = (int32_t)room_chunks;
+      g.n_chunks = g.n_fast_chunks + 1;
     }
   }
 
@@ -328,7 +335,7 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
   if (st != SPECKV_OK) return st;
   if (info == nullptr) return SPECKV_ERR_INVALID_ARG;
   const int rowb = pl.d.D * pl.d.elt;
-  info[0] = pl.g.NW; info[1] = pl.g.MB; info[2] = pl.g.RS; info[3] = pl.g.KC; info[4] = pl.g.n_fast_chunks;
+  info[0] = pl.g.NW; info[1] = pl.g.MB; info[2] = pl.g.RS; info[3] = chunk_keys(pl.g, pl.t.tail0[0]); info[4] = pl.g.n_fast_chunks;
   info[5] = rowb <= 128 ? 256 : rowb <= 256 ? 128 : 64;
   info[6] = pl.sel_parts; info[7] = pl.sel_part_len;
   info[8] = (score_uses_qs(pl, 1) ? 1 : 0) | (score_uses_qs(pl, 2) ? 2 : 0);

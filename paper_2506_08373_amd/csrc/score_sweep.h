@@ -190,8 +190,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     key_begin = tail0;
     key_end = n_s;
   } else {
-    key_begin = (chunk - A.t.cc[s]) * A.g.KC;
-    key_end = min(tail0, key_begin + A.g.KC);             // a chunk past a shorter live prompt is empty
+    const int kc = chunk_keys(A.g, tail0);
+    key_begin = (chunk - A.t.cc[s]) * kc;
+    key_end = min(tail0, key_begin + kc);                 // a chunk past a shorter live prompt is empty
   }
   const int rs = unit % A.g.RS;
   const int g = (unit / A.g.RS) % d.Hkv;

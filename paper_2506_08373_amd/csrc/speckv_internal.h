@@ -52,6 +52,7 @@ struct ScoreGeom {
   uint32_t pitch_inv; // 2^32 / pitch, rounded up: row / pitch is the high word of row * pitch_inv (rows stay below 2^13)
   int32_t packed;     // row blocks of the group where rows are packed, spread evenly over the super-blocks; else 0
   int32_t KC;         // keys per chunk (multiple of the LDS tile)
+  int32_t short_tile; // when not 0: chunks have fewer keys if the length that is read on the device says so (chunk_keys)
   int32_t n_fast_chunks;   // unmasked chunks over all sequences = cc[S]
   int32_t n_chunks;        // n_fast_chunks + one masked tail chunk per sequence
 };
@@ -71,6 +72,19 @@ struct Plan {
   size_t off_hist0;
   int64_t hist0_words;
 };
+
+// Keys per chunk of a prompt with `keys` unmasked keys in a call that longer chunks would not spread over the CUs (see
+// build_plan): as few tiles as make at most kShortChunks chunks, and not more than `longest`.
+constexpr int kShortChunks = 20;
+inline __host__ __device__ int short_chunk(int keys, int tile, int longest) {
+  int c = tile;
+  while (c < longest && keys > c * kShortChunks) c += tile;
+  return c < longest ? c : longest;
+}
+// Keys per chunk, given the first key of the masked tail as the kernels see it.
+inline __host__ __device__ int chunk_keys(const ScoreGeom &g, int tail0) {
+  return g.short_tile == 0 ? g.KC : short_chunk(tail0, g.short_tile, g.KC);
+}
 
 inline __host__ __device__ int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 

@@ -227,6 +227,16 @@ def test_plan_of_small_calls(lib):
     assert plan(1, 1280 + 15, 55, torch.float32) == (64, 20) and plan(1, 1280 + 64 + 15, 55, torch.float32) == (128, 11)
     assert plan(8, 2560 + 15, 30, d=64) == (128, 20) and plan(8, 2560 + 15, 128, d=64) == (256, 10)     # tiles of half a row length in LDS
     assert plan(9, 4133, 55) == (512, 8)
+    # a length on the device: the kernels cut it; the grid has room for the most chunks of any length up to the bound
+    for units, bound in ((8, 7000), (2, 1000), (1, 60000)):
+        most = max(plan(units, n, 55)[1] for n in list(range(16, bound, 53)) + [bound])
+        p = S.SpecKVParams(n_layers=1, n_q_heads=4 * units, n_kv_heads=units, head_dim=128, seq_lens=[bound], n_window=16,
+                           n_lookahead=39, pool_k=7, c_max=64, sm_scale=0.1, dtype=torch.bfloat16)
+        need = S.workspace_bytes(p)
+        p.c.n_in_dev = 1024
+        info = S.plan_info(p)
+        assert info["chunk_keys"] == plan(units, bound, 55)[0] and info["n_chunks"] == most
+        assert S.workspace_bytes(p) == need
 
 
 def test_row_statistics_mode_follows_the_environment(lib, monkeypatch):

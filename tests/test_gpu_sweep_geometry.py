@@ -85,6 +85,13 @@ def test_workgroups_of_few_tiles_with_a_length_on_the_device(S, n_live):
 # The host length is a bound then: it may call for other chunks than the live length, and for another place where the
 # chunks' pairs are merged (up to 40 chunks the column sweep, with one or two threads per row).  Scores have the same bits.
 LENGTHS = [
+    ("short", 7000, (7000, 4097, 2600, 700, 64), dict(n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64)),
+    ("short-shared-rows", 14000, (8000, 4133, 900), dict(n_q_heads=32, n_kv_heads=8, n_window=32, n_lookahead=23)),
+    ("short-64", 9000, (8000, 4097, 2600, 1100), dict(n_q_heads=32, n_kv_heads=8, head_dim=64, n_window=64, n_lookahead=64)),
+    ("short-64-one-block", 9000, (4097, 2600, 300), dict(n_q_heads=32, n_kv_heads=8, head_dim=64, n_window=16, n_lookahead=4)),
+    ("short-f32", 3000, (2600, 1500, 1024, 300), dict(n_q_heads=8, n_kv_heads=2, head_dim=64, dtype="f32")),
+    ("short-f32-128", 6000, (5000, 1300, 200), dict(n_q_heads=8, n_kv_heads=2, dtype="f32")),
+    ("short-gqa7", 9000, (6000, 3000, 600), dict(n_q_heads=28, n_kv_heads=4, n_window=64, n_lookahead=64)),
     ("merge", 30000, (30000, 15000, 10200), dict(n_q_heads=16, n_kv_heads=4, n_window=64, n_lookahead=64)),
     ("merge-two-threads", 60000, (41000, 20000, 12000), dict(n_q_heads=4, n_kv_heads=2, n_window=16, n_lookahead=39)),
     ("merge-f32", 30000, (17000,), dict(n_q_heads=8, n_kv_heads=4, dtype="f32", n_window=64, n_lookahead=64)),
