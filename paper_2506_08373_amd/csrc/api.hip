@@ -39,10 +39,12 @@ void pack_rows(const Dims &d, ScoreGeom *g) {
   g->pitch = d.R;
   g->pitch_inv = (uint32_t)(((uint64_t)1 << 32) / (uint32_t)g->pitch + 1);
   g->packed = (d.M + 31) / 32;
+  g->RS = std::min(g->RS, g->packed);           // (many heads of few rows: no super-block without any)
 }
 
-// Fills the dimension and per-sequence tables.  Returns SPECKV_OK or the reason.
-speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call, int32_t top_k) {
+// Fills the dimension and per-sequence tables.  Returns SPECKV_OK or the reason.  alg2: heads are combined by maximum and
+// window rows weighted (Alg. 2).
+speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call, int32_t top_k, bool alg2 = false) {
   if (p == nullptr) return SPECKV_ERR_INVALID_ARG;
   std::memset(pl, 0, sizeof(*pl));
   Dims &d = pl->d;
@@ -64,7 +66,7 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   d.w = p->n_window; d.a = p->n_lookahead; d.R = d.w + d.a;
   d.pool_k = p->pool_k; d.c_max = p->c_max; d.sm_scale = p->sm_scale;
   d.reduce_max = p->reduce_op == SPECKV_REDUCE_MAX; d.pool_avg = p->pool_op == SPECKV_POOL_AVG;
-  d.head_max = 0; d.weight_rows = 0;
+  d.head_max = d.weight_rows = alg2;
   if ((int64_t)d.G * d.R > SPECKV_MAX_GROUP_ROWS) return SPECKV_ERR_UNSUPPORTED;
   d.M = d.G * d.R;
   d.q_sl = p->q_stride_layer; d.q_ss = p->q_stride_seq; d.q_sr = p->q_stride_row; d.q_sh = p->q_stride_head;
@@ -123,7 +125,7 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   }
   g.pitch = g.Rp;
   g.packed = 0;
-  if (!d.reduce_max) pack_rows(d, &g);
+  if (!d.reduce_max || d.head_max) pack_rows(d, &g);
   g.pitch_inv = (uint32_t)(((uint64_t)1 << 32) / (uint32_t)g.pitch + 1);
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
   if (units > (int64_t)1 << 24) return SPECKV_ERR_UNSUPPORTED;       // grid sizes stay far below 2^31
@@ -649,12 +651,7 @@ static speckv_status alg2_plan(const speckv_params *p, int32_t l_skip, Plan *pl,
   eff->reduce_op = SPECKV_REDUCE_MAX;
   eff->pool_op = SPECKV_POOL_AVG;
   const int32_t m_cap = p->c_max < 0 ? 0 : p->c_max;
-  speckv_status st = build_plan(eff, pl, true, m_cap);
-  if (st != SPECKV_OK) return st;
-  pl->d.head_max = 1;
-  pl->d.weight_rows = 1;
-  pack_rows(pl->d, &pl->g);
-  return SPECKV_OK;
+  return build_plan(eff, pl, true, m_cap, true);
 }
 
 size_t specpc_compress_workspace_bytes(const speckv_params *p, int32_t l_skip) {

@@ -239,6 +239,20 @@ def test_plan_of_small_calls(lib):
         assert S.workspace_bytes(p) == need
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.float32, 128)])
+def test_every_super_block_has_rows(lib, dtype, d):
+    """Many heads of few rows: what heads padded to whole row blocks need is more than what they need packed."""
+    for G in range(1, 129):
+        for rows in (2, 3, 7, 17, 31, 33, 40, 65):
+            if G * rows > 4096:
+                continue
+            info = S.plan_info(S.SpecKVParams(n_layers=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, seq_lens=[3000], n_window=1,
+                                              n_lookahead=rows - 1, pool_k=7, c_max=64, sm_scale=0.1, dtype=dtype))
+            blocks, rows_per_wg = -(-G * rows // 32), info["waves"] * info["blocks_per_wave"] * 32
+            if -(-rows // 32) * 32 <= rows_per_wg:
+                assert info["row_super_blocks"] <= blocks <= info["row_super_blocks"] * rows_per_wg // 32, (G, rows)
+
+
 def test_row_statistics_mode_follows_the_environment(lib, monkeypatch):
     import workloads
     w = workloads.llama8b_layer(n_in=32768, n_layers=1)
@@ -290,7 +304,11 @@ def test_plan_invariants_over_random_shapes(lib):
             assert kc % tile == 0
         rows_per_wg = info["waves"] * info["blocks_per_wave"] * 32
         rp = (w_ + a_ + 31) // 32 * 32
-        assert info["row_super_blocks"] * rows_per_wg >= G * min(rp, rows_per_wg) or rp > rows_per_wg
+        if rp > rows_per_wg or (w_ + a_) % 32 == 0 or w_ + a_ == 1:
+            assert info["row_super_blocks"] * rows_per_wg >= G * min(rp, rows_per_wg) or rp > rows_per_wg
+        else:       # heads share row blocks: room for all of them, and no super-block without any
+            assert info["row_super_blocks"] * rows_per_wg >= G * (w_ + a_)
+            assert info["row_super_blocks"] <= -(-G * (w_ + a_) // 32)
         # the unmasked chunks cover exactly the whole tiles visible to every row
         want_chunks = 0
         for n in lens:

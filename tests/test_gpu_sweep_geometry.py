@@ -141,6 +141,16 @@ def test_rows_packed_and_blocks_shared(S, g, window, lookahead, dtype, d, mode, 
                                     seq_lens=(1500, 2740), dtype=dtype))
 
 
+# Groups of many heads with few rows each: fewer row blocks than heads padded to whole blocks would take super-blocks
+@pytest.mark.parametrize("g,rows,dtype,d", [(9, 2, "f32", 128), (17, 2, "f32", 128), (17, 2, "bf16", 128), (40, 3, "bf16", 64),
+                                            (64, 2, "f16", 128), (33, 17, "f32", 64)])
+@pytest.mark.parametrize("mode", ["online", "fixed"])
+def test_many_heads_of_few_rows(S, g, rows, dtype, d, mode, monkeypatch):
+    monkeypatch.setenv("SPECKV_ROW_STATISTICS", mode)
+    parity.check_full_path(S, shape(n_q_heads=2 * g, n_kv_heads=2, head_dim=d, n_window=1, n_lookahead=rows - 1,
+                                    seq_lens=(1500, 740), dtype=dtype))
+
+
 def test_shared_blocks_behind_outliers_and_the_query_stationary_sweep(S, monkeypatch):
     """Fixed references that overflow (segments are repaired by the waves that share), and partial pairs left by the
     query-stationary kernel, which shares nothing, for a column sweep that does."""
