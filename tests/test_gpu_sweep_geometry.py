@@ -151,6 +151,30 @@ def test_many_heads_of_few_rows(S, g, rows, dtype, d, mode, monkeypatch):
                                     seq_lens=(1500, 740), dtype=dtype))
 
 
+# The same with heads combined by maximum (Alg. 2): 1, 2, 5, 6, 9, 10, 13, 14 packed blocks; 16, taken in pairs; two super-blocks
+# of unequal size; heads made of whole blocks; a head longer than a super-block; super-blocks that heads of two rows do not need.
+# (fp32: the row statistics share blocks, the column maxima of two blocks a wave do not.)  Pools of one: every score is compared.
+@pytest.mark.parametrize("g,window,lookahead", [
+    (1, 16, 9), (2, 16, 24), (8, 16, 4), (4, 16, 32), (4, 64, 1), (4, 32, 48), (5, 16, 64), (5, 64, 20), (7, 64, 9), (7, 64, 20), (4, 64, 64),
+    (1, 64, 520), (17, 1, 1)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 64), ("f32", 128), ("f32", 64)])
+def test_heads_combined_by_maximum(S, g, window, lookahead, dtype, d):
+    n, budget = 2740, 400
+    w = shape(n_layers=2, n_q_heads=2 * g, n_kv_heads=2, head_dim=d, n_window=window, n_lookahead=lookahead, seq_lens=(n,),
+              dtype=dtype, pool_k=1, c_max=budget)
+    t = workloads.generate(w)
+    ids = workloads.generate_token_ids(w)
+    ref = parity.orc.specpc_compress_prompt(workloads.to_float64(t["q"][:, 0]), workloads.to_float64(t["k"]), ids.numpy(), window,
+                                            1, 1, budget, 0, w.sm_scale)
+    p = parity.make_params(S, w)
+    ws = torch.empty(S.specpc_compress_workspace_bytes(p, 0), dtype=torch.uint8, device="cuda")
+    idx, out = (torch.full((budget + window,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    count = torch.zeros(1, dtype=torch.int32, device="cuda")
+    S.specpc_compress_prompt(p, 0, 1, t["q"].cuda(), t["k"].cuda(), ids.cuda(), idx, out, count, ws)
+    assert int(count) == budget + window and torch.equal(out.cpu(), ids[idx.cpu().long()])
+    parity.assert_indices_valid(idx.cpu().numpy().astype("int64"), ref["pooled"], n, window, budget, "alg2")
+
+
 def test_shared_blocks_behind_outliers_and_the_query_stationary_sweep(S, monkeypatch):
     """Fixed references that overflow (segments are repaired by the waves that share), and partial pairs left by the
     query-stationary kernel, which shares nothing, for a column sweep that does."""
