@@ -64,6 +64,13 @@ def _hip_runtime() -> ctypes.CDLL:
     return hip
 
 
+# Stages that hold no kernel in some calls: their time is then that of two event records.
+FOLDED_STAGES = {
+    "lse_merge": "no kernel where a sequence has at most 40 chunks: pass 2 merges the row statistics (its time includes that)",
+    "pool": "no kernel for sequences of up to 8192 tokens: one launch pools and selects (the time of select)",
+}
+
+
 def _traffic_from_profile(stage: str, tag: str):
     """HBM bytes per launch from the committed rocprofv3 --pmc summary of this workload, if any."""
     path = os.path.join(ROOT, "profiles", "pmc_traffic_%s.txt" % tag)
@@ -300,6 +307,8 @@ def main() -> int:
             compact_bytes = 2.0 * 2.0 * H * KT * d * elt * L + 4.0 * H * KT * L   # K,V read + write, indices
             entry.update(bound="hbm", achieved=round(compact_bytes / (ms * 1e-3) / 1e9, 1), peak=PEAK_HBM_GBS,
                          unit="GB/s", kernel="compact_kernel<true>")
+        elif name in FOLDED_STAGES:
+            entry["note"] = FOLDED_STAGES[name]
         if "achieved" in entry:
             entry["frac"] = round(entry["achieved"] / entry["peak"], 4)
         kernels[name] = entry

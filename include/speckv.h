@@ -237,7 +237,10 @@ speckv_status speckv_compress_lse(const speckv_params *p, const void *q, const v
  * records them on `stream` around its kernels and does not synchronise:
  *   [0] start  [1] after scoring pass 1 (row statistics)  [2] after the row-statistics merge
  *   [3] after scoring pass 2 (column sums)  [4] after pooling  [5] after selection
- *   [6] after compaction.  Same results as speckv_compress (Alg. 1 loop body). */
+ *   [6] after compaction.  Same results as speckv_compress (Alg. 1 loop body).
+ * Two stages may hold no kernel, their work is then part of the next one: [1]-[2] where the workgroups of
+ * pass 2 merge the statistics of their rows (up to 40 chunks a sequence), [3]-[4] where one launch pools
+ * and selects (no sequence above 8192 tokens, pool_k up to 16, groups of one or two row super-blocks). */
 #define SPECKV_N_STAGE_EVENTS 7
 speckv_status speckv_compress_events(const speckv_params *p, const void *q, const void *k,
                                      const void *v, int32_t *idx, void *k_out, void *v_out,

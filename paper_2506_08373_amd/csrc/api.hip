@@ -202,8 +202,10 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   // A call that chunks of kChunkMin keys cannot spread over the CUs is a chain of latencies: set-up, then one tile after the
   // other.  Its workgroups take as few tiles each as keeps everything in one round of the CUs: one fp32 layer of 1K keys
   // 56.7 us with 512 keys each, 36.4 with 128 (its sweeps 19.5 and 21.2 us, then 9.8 and 12.1); one layer of 4K 45.1 us
-  // with 512, 38.7 with 256 (13.4 and 14.4, 11.2 and 12.0).  With more units kChunkMin fills the CUs at about 8K keys; there the
-  // cut stays independent of the length.
+  // with 512, 38.7 with 256 (13.4 and 14.4, 11.2 and 12.0).  Up to 8 units any length's chunks (20 at most) and tails are one round
+  // of the CUs, which is what lets kernels cut by a length that only they know (short_chunk).  That is why the line lies here, not
+  // that there is nothing to gain beyond: 16 units, 128 rows a head, 1K keys 53.6 us with 512 keys each, 39.7 with 128; 2K 54.5
+  // and 42.4; 4K 61.6 and 55.1; from 6K on level.
   // More than 20 chunks a sequence cost the column sweep more in merged pairs than they gain (one layer of 4K keys, 28 heads in
   // groups of 7: 48.3 us with 256 keys each, 62.5 with 512, 66.0 with 128).
   if (kc == kChunkMin && units <= kShortChunkUnits) {

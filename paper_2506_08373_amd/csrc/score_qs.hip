@@ -1,7 +1,7 @@
 // Scoring sweeps with the query rows stationary in LDS (Sec. 3.1 Eq. 1; Alg. 1 CrossAttention
 // and reduce steps; App. C.2 for the GQA group).  An alternative to the tile-streaming kernel of
 // score_sweep.h for the unmasked chunks of large groups: by default it runs the row-statistics sweep at
-// d = 64; SPECKV_SCORE_KERNEL=qs selects it for every sweep it supports.
+// d = 64 of groups whose heads do not share row blocks; SPECKV_SCORE_KERNEL=qs selects it for every sweep it supports.
 //
 // Same mathematics (pass 1: per-row (reference, sum of exp2) over a chunk of keys; pass 2:
 // per-key sum over the rows of 2^(c*S - lse2)), different dataflow:
@@ -365,7 +365,8 @@ int qs_max_blocks(const ScoreArgs &A) {
 }  // namespace
 
 bool qs_supported(const ScoreArgs &A, int pass) {
-  // Default: only the row-statistics sweep at d = 64, where the vector pipe is the limit.  The line was drawn
+  // Default: only the row-statistics sweep at d = 64, where the vector pipe is the limit, of rows that are not packed (this kernel
+  // shares no blocks between waves: 65 rows in the list below).  The line was drawn
   // when the tile-streaming kernel searched every block's maximum there, and no longer lies where the two cross.
   // Scoring with 4 query heads per KV head, us with this kernel for the row statistics / with the tile-streaming kernel
   // for both sweeps (with this kernel for both): 64 rows per head, 16 layers x 64K keys 849-888 / 860 (906), 16 x 32K

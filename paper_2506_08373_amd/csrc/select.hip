@@ -1106,7 +1106,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(Dims d, SeqTab t,
 // in its order) and pools the entries it then holds in registers.  The pooled scores of a fused call are nobody else's, so they
 // are not written.  Bound by latencies; what it saves is a launch between two kernels that wait for each other.
 // Pooling + selection kernels -> here: 2 rows of 1K 5.0 + 7.6 -> 9.3 us, 8 rows of 4K 5.3 + 9.4 -> 11.8; calls: one fp32 layer of
-// 1K keys 36.5 -> 33.0, one layer of 4K 38.7 -> 36.0.  With more entries the row's one workgroup is the limit.
+// 1K keys 36.5 -> 33.0, one layer of 4K 38.7 -> 36.0.  With more entries the row's one workgroup is the limit.  More rows than CUs
+// are no limit: calls with one query row, 1K entries a row, 256 rows 48 -> 43, 2048 rows 228 -> 224; 4K, 1024 rows 298 -> 284; 8.1K,
+// 256 rows 130 -> 120, 2048 rows 1065 -> 1032.
 constexpr int kFusedMax = 8192, kFusedMaxPool = 16;        // entries of a row, pooling kernel
 static_assert(kFusedMax <= kHistCopies * kRegStride && kFusedMax <= 4 * kRegMaxVec, "the row lies over RegShared::first");
 
@@ -1319,6 +1321,7 @@ __global__ __launch_bounds__(kSelThreads) void msel_emit_kernel(Dims d, SeqTab t
 // written and read by agent-scope atomics only, which go past the L2; a workgroup arrives after a wait for its stores and
 // a barrier, and the last one reads after its own arrival.  Ordering the counter itself (acquire-release) would have every
 // workgroup write back and invalidate its L2: the arrival then takes 4.7 instead of 1 us where 256 workgroups do it.
+// The order thus rests on the wait and on every shared word going past the L2: a plain store or load among them would be a race.
 // Rows in which more than kCandCap entries share the digit, or more than kPartsMaxCount are to be selected, are
 // ranked by the first of their workgroups alone.
 constexpr int kPartTile = 4 * kSelThreads;        // entries a workgroup classifies per step
