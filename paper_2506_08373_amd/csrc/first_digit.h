@@ -15,8 +15,9 @@ namespace speckv {
 // With 2 bits of mantissa everywhere a quarter of a row of scores within a factor of four shares the threshold's digit; with 5 bits
 // everywhere there are digits for 64 powers of two only, and rows whose threshold lies outside them had to be counted again: one
 // query row of logits with a standard deviation of 40, calls with 2 bits everywhere / 5 bits down to 2^-51 / these digits: 8 rows of
-// 128K keys 111.2 / 141.5 / 75.9 us, 2 rows of 200K 81.6 / 154.0 / 53.8, 256 rows of 128K 2231 / 2276 / 2223; one row of ordinary
-// logits, 256 rows of 128K, 2085 / 2079 / 2081 (pooling and selection 105 + 54 / 121 + 46 / 123 + 47).
+// 128K keys 111.2 / 141.5 / 75.9 us, 2 rows of 200K 81.6 / 154.0 / 53.8, 256 rows of 128K 2231 / 2276 / 2223.  Pooling and selection
+// of 256 rows of 128K ordinary scores: one query row 105 + 54 / 118 + 46 / 119 + 47 us; 512 rows 174 + 64 / 131 + 58 / 131 + 59, but
+// with heavy hitters among the keys 122 + 50 / 147 + 47 / 150 + 46 (a tile's counters then have more entries to add to the row's).
 constexpr uint32_t kFineKey = 0x80000000u | ((127u - 40u) << 23), kTopKey = 0x80000000u | ((127u + 13u) << 23);
 constexpr int kCoarseBase = (int)(0x80000000u >> 21) - 1;
 constexpr int kFineDigit = (int)(kFineKey >> 21) - kCoarseBase;
@@ -25,9 +26,10 @@ constexpr int kTopDigit = (int)(kTopKey >> 18) - kFineBase;
 static_assert(kFineDigit == 349 && kTopDigit == 2045, "the digits above");
 
 __host__ __device__ inline int first_digit_of(uint32_t key) {
+  // below kFineKey the coarse digit is the larger of the two, from there on the fine one
   const int coarse = (int)(key >> 21) - kCoarseBase, fine = (int)(key >> 18) - kFineBase;
-  if (fine >= kFineDigit) return fine < kTopDigit ? fine : kTopDigit;
-  return coarse > 0 ? coarse : 0;
+  const int top = fine < kTopDigit ? fine : kTopDigit, low = coarse > 0 ? coarse : 0;
+  return low > top ? low : top;
 }
 
 // What digit D says of the keys it stands for: all but their last `open` bits, which are zero in the result.  open = 32: nothing.
