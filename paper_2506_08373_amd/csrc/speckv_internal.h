@@ -106,6 +106,9 @@ __device__ inline int live_tail0(const Dims &d, const SeqTab &t, int s, int n, i
   return visible / kt * kt;
 }
 
+// Keys per chunk as the kernels see it (a length on the host has been cut there).
+__device__ inline int live_chunk(const Dims &d, const ScoreGeom &g, int tail0) { return d.n_dev == nullptr ? g.KC : chunk_keys(g, tail0); }
+
 // Raises a kernel's dynamic LDS limit; the runtime call is made once per (device, kernel, size)
 // and remembered (score.hip).
 hipError_t allow_dynamic_lds(const void *kernel, size_t bytes);
