@@ -225,7 +225,7 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
     }
     // A length that is read on the device is cut as it would be here, by the kernels; the grid has the workgroups for any.
     if (d.n_dev != nullptr) {
-      g.short_tile = tile;
+      g.short_log = __builtin_ctz((unsigned)tile);
       g.KC = kChunkMin;
       t.cc[1] = g.n_fast_chunks = (int32_t)room_chunks;
       g.n_chunks = g.n_fast_chunks + 1;

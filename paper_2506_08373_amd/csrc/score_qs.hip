@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kQsWaves * 64) void score_qs_kernel(ScoreArgs A) {
   while (s + 1 < d.S && A.t.cc[s + 1] <= chunk) ++s;
   const int n_host = A.t.cu[s + 1] - A.t.cu[s];          // row stride of the score layouts
   const int n_live = live_len(d, A.t, s);                 // tokens that exist (device-side count honoured)
-  const int tail0 = live_tail0(d, A.t, s, n_live, TL::ALIGN), kc = live_chunk(d, A.g, tail0);
+  const int tail0 = live_tail0(d, A.t, s, n_live, TL::ALIGN), kc = chunk_keys(A.g, tail0);
   const int key_begin = (chunk - A.t.cc[s]) * kc;
   const int key_end = min(tail0, key_begin + kc);
   const int rs = unit % A.g.RS;

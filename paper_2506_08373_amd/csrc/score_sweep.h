@@ -190,7 +190,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     key_begin = tail0;
     key_end = n_s;
   } else {
-    const int kc = live_chunk(d, A.g, tail0);
+    const int kc = chunk_keys(A.g, tail0);
     key_begin = (chunk - A.t.cc[s]) * kc;
     key_end = min(tail0, key_begin + kc);                 // a chunk past a shorter live prompt is empty
   }

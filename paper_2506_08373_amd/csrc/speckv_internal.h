@@ -52,7 +52,7 @@ struct ScoreGeom {
   uint32_t pitch_inv; // 2^32 / pitch, rounded up: row / pitch is the high word of row * pitch_inv (rows stay below 2^13)
   int32_t packed;     // row blocks of the group where rows are packed, spread evenly over the super-blocks; else 0
   int32_t KC;         // keys per chunk (multiple of the LDS tile)
-  int32_t short_tile; // when not 0: chunks have fewer keys if the length that is read on the device says so (chunk_keys)
+  int32_t short_log;  // when not 0: chunks have fewer keys if the length that is read on the device says so; log2 of a tile's keys (chunk_keys)
   int32_t n_fast_chunks;   // unmasked chunks over all sequences = cc[S]
   int32_t n_chunks;        // n_fast_chunks + one masked tail chunk per sequence
 };
@@ -76,14 +76,16 @@ struct Plan {
 // Keys per chunk of a prompt with `keys` unmasked keys in a call that longer chunks would not spread over the CUs (see
 // build_plan): as few tiles as make at most kShortChunks chunks, and not more than `longest`.
 constexpr int kShortChunks = 20;
-inline __host__ __device__ int short_chunk(int keys, int tile, int longest) {
-  int c = tile;
-  while (c < longest && keys > c * kShortChunks) c += tile;
+inline __host__ __device__ int short_chunk(uint32_t keys, int tile_log, int longest) {
+  const int tiles = (int)(((keys >> tile_log) + kShortChunks - 1) / (uint32_t)kShortChunks);
+  const int c = (tiles > 1 ? tiles : 1) << tile_log;
   return c < longest ? c : longest;
 }
-// Keys per chunk, given the first key of the masked tail as the kernels see it.
+// Keys per chunk, given the first key of the masked tail as the kernels see it (straight code: a branch here, never taken, cost
+// the sweeps of small calls 1 %).
 inline __host__ __device__ int chunk_keys(const ScoreGeom &g, int tail0) {
-  return g.short_tile == 0 ? g.KC : short_chunk(tail0, g.short_tile, g.KC);
+  const int c = short_chunk((uint32_t)tail0, g.short_log, g.KC);
+  return g.short_log == 0 ? g.KC : c;
 }
 
 inline __host__ __device__ int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
@@ -105,9 +107,6 @@ __device__ inline int live_tail0(const Dims &d, const SeqTab &t, int s, int n, i
   const int visible = n - d.w + 1 < n ? n - d.w + 1 : n;
   return visible / kt * kt;
 }
-
-// Keys per chunk as the kernels see it (a length on the host has been cut there).
-__device__ inline int live_chunk(const Dims &d, const ScoreGeom &g, int tail0) { return d.n_dev == nullptr ? g.KC : chunk_keys(g, tail0); }
 
 // Raises a kernel's dynamic LDS limit; the runtime call is made once per (device, kernel, size)
 // and remembered (score.hip).
