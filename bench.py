@@ -307,7 +307,7 @@ def main() -> int:
             compact_bytes = 2.0 * 2.0 * H * KT * d * elt * L + 4.0 * H * KT * L   # K,V read + write, indices
             entry.update(bound="hbm", achieved=round(compact_bytes / (ms * 1e-3) / 1e9, 1), peak=PEAK_HBM_GBS,
                          unit="GB/s", kernel="compact_kernel<true>")
-        elif name in FOLDED_STAGES:
+        elif name in FOLDED_STAGES and not (specpc and name == "pool"):
             entry["note"] = FOLDED_STAGES[name]
         if "achieved" in entry:
             entry["frac"] = round(entry["achieved"] / entry["peak"], 4)

@@ -24,11 +24,12 @@ int main() {
       seen[D] = 1;
       int open;
       const uint32_t prefix = key_prefix_of((uint32_t)D, &open);
-      // a positive number below 2^13 is described by its digit, by at least as many bits as 2 of mantissa make
-      if (key >= 0x80000000u && key < (0x80000000u | (140u << 23))) {
+      // a positive number, infinity or NaN is described by its digit, by at least as many bits as 2 of mantissa make
+      if (key >= 0x80000000u) {
         if (open != 21 && open != 18) { std::printf("key %08x: %d bits open\n", key, open); return 1; }
         if (prefix >> open != key >> open || prefix << (32 - open) != 0) { std::printf("key %08x: prefix %08x\n", key, prefix); return 1; }
-        if (key >= (0x80000000u | (87u << 23)) && open != 18) { std::printf("key %08x: coarse\n", key); return 1; }
+        const bool usual = key >= (0x80000000u | (98u << 23)) && key < (0x80000000u | (134u << 23));     // 2^-29 to 2^7
+        if (usual != (open == 18)) { std::printf("key %08x: %d bits open\n", key, open); return 1; }
       } else if (open != 32) { std::printf("key %08x: %d bits open\n", key, open); return 1; }
     }
   }
@@ -36,7 +37,7 @@ int main() {
   for (uint32_t D = 0; D < 2048; ++D) {
     int open;
     const uint32_t prefix = key_prefix_of(D, &open);
-    if (open == 32) { if (D > 0 && D < (uint32_t)kTopDigit) return 1; continue; }
+    if (open == 32) { if (D > 0 && D <= (uint32_t)kLastDigit) return 1; continue; }
     if (!seen[D] || first_digit_of(prefix) != (int)D || first_digit_of(prefix + ((1u << open) - 1u)) != (int)D) { std::printf("digit %u\n", D); return 1; }
   }
   std::printf("digits ok\n");

@@ -101,6 +101,25 @@ def test_peaked_rows(S, n, n_layers, n_heads, gain):
     check(S, q, k, (n,), 1, n // 60)
 
 
+# Normalisers from the caller that are too small: scores far above what probabilities sum to, some or all of them infinite
+@pytest.mark.parametrize("n,n_layers", [(33001, 1), (17001, 65), (9001, 17)])
+@pytest.mark.parametrize("lse", [-20.0, -60.0, -84.0])
+def test_scores_of_any_size(S, n, n_layers, lse):
+    q, k = tensors((n,), n_layers)
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=(n,), n_window=16, pool_k=7, c_max=400, sm_scale=0.125)
+    norm = torch.full((n_layers, 1, 32, 4), lse, device="cuda")
+    pooled = torch.empty(n_layers, 2 * n, device="cuda")
+    idx = torch.empty(n_layers, 2 * 416, dtype=torch.int32, device="cuda")
+    k_out = torch.empty(n_layers, 2 * 416, 64, dtype=k.dtype, device="cuda")
+    ws = parity.alloc_ws(S, p)
+    S.speckv_score_lse(p, q, k, norm, pooled, None, ws)
+    S.speckv_compress_lse(p, q, k, None, norm, idx, k_out, None, ws)
+    scores, got = pooled.view(n_layers, 2, n).cpu().numpy(), idx.view(n_layers, 2, 416).cpu().numpy()
+    for layer in range(n_layers):
+        for h in range(2):
+            assert np.array_equal(got[layer, h, :400], ranked(scores[layer, h, :n - 16], 400)), (layer, h)
+
+
 @pytest.mark.parametrize("n_live", [60000, 17003, 900, 16])
 def test_a_length_on_the_device(S, n_live):
     q, k = tensors((60000,))
