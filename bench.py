@@ -91,6 +91,8 @@ def _scoring_kernel_symbol(S, p, w, stage: str) -> str:
     red = info["reduce_max"] if npass == 2 else info["fixed_reference_rows"]
     if info["q_stationary"] & npass:
         return "score_qs_kernel<%d, %d, %d, %d>" % (dt, w.head_dim, npass, red)
+    if w.dtype == "f32":
+        red += 2        # groups of whole row blocks (the fp32 workload's): the sweeps without the code for shared ones
     fn = "score_kernel_rows" if (npass == 1 and info["waves"] == 8) else "score_kernel_cols"
     return "%s<%d, %d, %d, %d, %d, %d, false>" % (fn, dt, w.head_dim, info["blocks_per_wave"], info["waves"],
                                                   npass, red)

@@ -1032,18 +1032,25 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 // last round of chunk workgroups frees one by one (ragged batches: 1 % faster than tails in front,
 // equal-length grids: the same).  TAIL_ONLY = true is the tails alone (calls without a complete
 // chunk, and the tails behind a Q-stationary sweep).
-// Column sweeps of fp32 with two row blocks a wave are short of registers: the code for shared blocks costs the sum 4 % where
-// no block is shared (3 layers x 30K keys, normalisers given, 442 and 464 us), so that there is a kernel without it for those
-// calls (RED = kSumWhole), and the maximum has 90 scalar registers spilled instead of 18 (19 layers x 27K keys 2660 and 3000 us), so
-// that it shares nothing.
-constexpr int kSumWhole = 2;
-template <int DT, int MB, int PASS, int RED>
-constexpr bool may_share() { return !(DT == kF32 && MB == 2 && PASS == 2 && RED != 0); }
+// RED + kWhole: a sweep of fp32 without the code for row blocks that waves share, which costs the fp32 sweeps where no block is shared
+// (sweeps with it / without: maximum, 8 heads of 400K keys, d = 128, 2 row blocks a group 710 / 643 us; sum, d = 64, 8 blocks, column sums 434 /
+// 432, row statistics 444 / 429; two blocks a wave, 12 and 9 in two super-blocks, 1241 / 1149).  The 16-bit sweeps are level and have
+// one kernel for both.  With blocks shared, calls of 2 fp32 layers x 30K keys take (with the code / all blocks whole): 1 row block a group
+// 95 / 145 us, 5 blocks 172 / 204, 9 blocks in two super-blocks of d = 128 537 / 667, 9 and 13 blocks with two a wave 266 / 285 and 346 / 391.
+// A super-block that shares beside a fuller one that does not gains nothing: 8 and 6 blocks 749 / 717.
+// The maximum of two blocks a wave never shares: it would have 90 scalar registers spilled instead of 18 (19 layers x 27K keys 2660 and 3000 us).
+constexpr int kWhole = 2;
+template <int DT, int MB, int PASS>
+bool shares_blocks(const ScoreArgs &A) {
+  if (DT == kF32 && MB == 2 && PASS == 2 && A.d.reduce_max) return false;
+  int first;
+  return split_blocks(super_block_blocks(A.d, A.g, 0, &first), A.share != 0).per > 1;        // no super-block is fuller than the first
+}
 
 template <int DT, int D, int MB, int NW, int PASS, int RED, bool TAIL_ONLY>
 __device__ __forceinline__ void score_dispatch(const ScoreArgs &A) {
-  constexpr int R = PASS == 2 && RED == kSumWhole ? 0 : RED;
-  constexpr bool SHARE = may_share<DT, MB, PASS, RED>();
+  constexpr int R = RED & 1;
+  constexpr bool SHARE = RED < kWhole;
   const int bid = blockIdx.x;
   if (PASS == 2 && A.norm_from != kNormMerged)
     clear_scratch(A, (int64_t)bid * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
@@ -1127,7 +1134,7 @@ hipError_t launch_sweep(const ScoreArgs &A0, size_t lds, hipStream_t st) {
       hipError_t e;
       if constexpr (NW == 8) e = launch_one(score_kernel_rows<DT, D, MB, NW, PASS, RED, false>, A, grid, block, lds, st);
       else e = launch_one(score_kernel_cols<DT, D, MB, NW, PASS, RED, false>, A, grid, block, lds, st);
-      if (e != hipSuccess || RED == 0) return e;
+      if (e != hipSuccess || (RED & 1) == 0) return e;
       return launch_one(score_kernel_rows_repair<DT, D, MB, NW>, A, dim3((unsigned)chunk_wgs), block, lds, st);
     } else {
       return launch_one(score_kernel_cols<DT, D, MB, NW, PASS, RED, false>, A, grid, block, lds, st);
@@ -1137,7 +1144,7 @@ hipError_t launch_sweep(const ScoreArgs &A0, size_t lds, hipStream_t st) {
     const hipError_t e = launch_qs_sweep(A, PASS, st);
     if (e != hipSuccess) return e;
   }
-  return launch_one(score_kernel_cols<DT, D, MB, NW, PASS, RED, true>, A, dim3((unsigned)tails), block, lds, st);
+  return launch_one(score_kernel_cols<DT, D, MB, NW, PASS, RED & 1, true>, A, dim3((unsigned)tails), block, lds, st);
 }
 
 // Sweep PASS (1 row statistics, 2 column reduction) for the number type, head dimension and
@@ -1145,19 +1152,18 @@ hipError_t launch_sweep(const ScoreArgs &A0, size_t lds, hipStream_t st) {
 template <int DT, int D, int MB, int NW, int PASS>
 hipError_t sweep_for_geometry(const ScoreArgs &A, hipStream_t st) {
   const size_t lds = score_lds_bytes<DT, D, MB, NW>();
-  if constexpr (PASS == 1) {
-    if (score_rows_fixed_reference(A.d, A.g)) return launch_sweep<DT, D, MB, NW, 1, 1>(A, lds, st);
-    return launch_sweep<DT, D, MB, NW, 1, 0>(A, lds, st);
-  }
-  else {
-    if (A.d.reduce_max) return launch_sweep<DT, D, MB, NW, 2, 1>(A, lds, st);
-    if constexpr (!may_share<DT, MB, 2, kSumWhole>()) {
-      bool shared = false;
-      for (int rs = 0, first; rs < A.g.RS; ++rs) shared |= split_blocks(super_block_blocks(A.d, A.g, rs, &first), A.share != 0).per > 1;
-      if (!shared) return launch_sweep<DT, D, MB, NW, 2, kSumWhole>(A, lds, st);
+  const bool red = PASS == 1 ? score_rows_fixed_reference(A.d, A.g) : A.d.reduce_max != 0;
+  if constexpr (DT == kF32) {
+    if (!shares_blocks<DT, MB, PASS>(A)) {
+      ScoreArgs whole = A;                       // (the masked tails and the repair launch read it)
+      whole.share = 0;
+      return red ? launch_sweep<DT, D, MB, NW, PASS, 1 + kWhole>(whole, lds, st) : launch_sweep<DT, D, MB, NW, PASS, kWhole>(whole, lds, st);
     }
-    return launch_sweep<DT, D, MB, NW, 2, 0>(A, lds, st);
   }
+  if constexpr (!(DT == kF32 && MB == 2 && PASS == 2)) {
+    if (red) return launch_sweep<DT, D, MB, NW, PASS, 1>(A, lds, st);
+  }
+  return launch_sweep<DT, D, MB, NW, PASS, 0>(A, lds, st);
 }
 
 template <int DT, int D, int PASS>
