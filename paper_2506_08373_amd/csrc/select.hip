@@ -1032,12 +1032,16 @@ __device__ __forceinline__ void select_after_prefix(const float *__restrict__ x,
 
 // The rest of a selection in which all but the last `open` bits (21 or 10, 18 or 7; mask: the others) of the threshold's key are
 // known to be `prefix`, which in_bin entries share, of which the `remaining` largest are wanted.
+// While another digit may be decided first, the list is only taken if it is short for the row: 1000 candidates cost about 4 us, as
+// each is listed, ranked and searched for, a digit's read of the row 1.5 us and 0.07 per 1K entries.  16000 of 61K kept, 3000 to 4000
+// candidates: call 71 us with the list, 60 with the digit first.
 __device__ __forceinline__ void select_below_prefix(const float *__restrict__ x, int m, RowSplit rs, uint32_t prefix, uint32_t mask,
                                                     int open, uint32_t remaining, uint32_t in_bin, int32_t *__restrict__ out,
                                                     unsigned char *lds) {
   SelShared &sh = *reinterpret_cast<SelShared *>(lds);
   for (;;) {
-    if (rs.nv <= kFastMaxVec && in_bin <= (uint32_t)kCandCap && !beyond_floats(prefix, 32 - open)) {
+    const uint32_t list_max = open > 10 ? min((uint32_t)kCandCap, 512u + (uint32_t)m / 64u) : (uint32_t)kCandCap;
+    if (rs.nv <= kFastMaxVec && in_bin <= list_max && !beyond_floats(prefix, 32 - open)) {
       select_after_prefix(x, m, rs, prefix, 32 - open, remaining, out, *reinterpret_cast<FastShared *>(lds));
       return;
     }
@@ -1765,7 +1769,10 @@ __global__ __launch_bounds__(kExpThreads) void expand_kernel(
 // 32K 20.6 / 10.6, 60K 20.6 / 13.2; 64 rows of 32K 22.9 / 13.7, 128K 51.7 / 28; 128 rows of 32K 28.1 / 19.9, 64K 35.0 / 30.9,
 // 128K 54.3 / 47.2; 8 rows of 64K, 8192 kept 24.4 / 22.8.  Of the 12.6 us, at 8 rows of 128K: first digit 2.2, parts and
 // their stores 2.4, arrival 0.5, lists 2.3, threshold 3.5, the rest of the output 1.5 (a 1024-thread barrier is 0.1 to 0.2).
-constexpr int kPartsMaxRows = 128, kPartsMinKeys = 16384, kPartsWorkgroups = 256;
+// Above a fifth of the row kept, what the last workgroup does alone (lists of all that is kept) outweighs the reads that are shared:
+// calls with one workgroup per row / several, 2 rows, 8000 kept of 19K 45.6 / 53.7 us, of 33K 47.9 / 53.2, of 61K 57.7 / 55.6; 4096 of 19K
+// 44.1 / 43.2.
+constexpr int kPartsMaxRows = 128, kPartsMinKeys = 16384, kPartsWorkgroups = 256, kPartsMaxShare = 5;
 SelectParts select_parts_of(const Plan &pl) {
   const Dims &d = pl.d;
   const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
@@ -1775,7 +1782,7 @@ SelectParts select_parts_of(const Plan &pl) {
     most = std::max(most, pl.t.ck[s + 1] - pl.t.ck[s] - d.w);
   }
   SelectParts sp = {1, 0};
-  if (rows > kPartsMaxRows || max_m < kPartsMinKeys || most > kPartsMaxCount) return sp;
+  if (rows > kPartsMaxRows || max_m < kPartsMinKeys || most > kPartsMaxCount || most > max_m / kPartsMaxShare) return sp;
   const int64_t want = std::min<int64_t>(kPartsMax, kPartsWorkgroups / rows);
   sp.part_len = (int)align_up((max_m + 3 + want - 1) / want, kPartTile);
   sp.P = (max_m + 3 + sp.part_len - 1) / sp.part_len;

@@ -64,12 +64,14 @@ def tensors(lens, n_layers=1, n_heads=2, rows=32, seed=3, gain=1.0):
     return q.to(torch.bfloat16), k.to(torch.bfloat16)
 
 
+# a fifth of the row kept and one more; thousands of candidates with the threshold's first digit, ranked by one workgroup;
 # the shortest rows of the rule and one entry less; parts of one step of 4096 entries and of two, the last one short; rows
 # that start at every alignment (odd lengths); a batch whose shorter rows leave parts empty; 128 rows and one more
 @pytest.mark.parametrize("lens,n_layers,n_heads,c_max", [
     ((16399,), 1, 2, 300), ((16400,), 1, 2, 300), ((20501,), 1, 3, 1), ((50003,), 1, 8, 2048), ((65551,), 2, 4, 8192),
     ((65551,), 1, 1, 8193), ((131085,), 1, 2, 1024), ((40001, 700, 17, 30003), 1, 3, 500), ((17001,), 16, 8, 64),
-    ((17001,), 43, 3, 64)])
+    ((17001,), 43, 3, 64), ((33001,), 1, 3, 6597), ((33001,), 1, 3, 6598), ((61001,), 1, 2, 9000), ((61001,), 1, 2, 16000),
+    ((33001,), 1, 2, 16000), ((131085,), 1, 1, 30000)])
 def test_rows_shared_by_workgroups(S, lens, n_layers, n_heads, c_max):
     q, k = tensors(lens, n_layers, n_heads, gain=2.0)
     check(S, q, k, lens, 16, c_max)
