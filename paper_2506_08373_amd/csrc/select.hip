@@ -1034,13 +1034,13 @@ __device__ __forceinline__ void select_after_prefix(const float *__restrict__ x,
 // known to be `prefix`, which in_bin entries share, of which the `remaining` largest are wanted.
 // While another digit may be decided first, the list is only taken if it is short for the row: 1000 candidates cost about 4 us, as
 // each is listed, ranked and searched for, a digit's read of the row 1.5 us and 0.07 per 1K entries.  16000 of 61K kept, 3000 to 4000
-// candidates: call 71 us with the list, 60 with the digit first.
+// candidates: call 71 us with the list, 60 with the digit first; 9000 of 128K, about 2000 candidates 90 and 82.
 __device__ __forceinline__ void select_below_prefix(const float *__restrict__ x, int m, RowSplit rs, uint32_t prefix, uint32_t mask,
                                                     int open, uint32_t remaining, uint32_t in_bin, int32_t *__restrict__ out,
                                                     unsigned char *lds) {
   SelShared &sh = *reinterpret_cast<SelShared *>(lds);
   for (;;) {
-    const uint32_t list_max = open > 10 ? min((uint32_t)kCandCap, 512u + (uint32_t)m / 64u) : (uint32_t)kCandCap;
+    const uint32_t list_max = open > 10 ? min((uint32_t)kCandCap, 512u + (uint32_t)m / 128u) : (uint32_t)kCandCap;
     if (rs.nv <= kFastMaxVec && in_bin <= list_max && !beyond_floats(prefix, 32 - open)) {
       select_after_prefix(x, m, rs, prefix, 32 - open, remaining, out, *reinterpret_cast<FastShared *>(lds));
       return;
