@@ -12,7 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libspeckv.so")
-SOURCES = ["api.hip", "score.hip", "score_rows.hip", "score_cols.hip", "score_qs.hip", "select.hip", "compact.hip",
+SOURCES = ["api.hip", "score.hip", "score_rows.hip", "score_cols.hip", "score_qs.hip", "score_prune.hip", "prune.hip", "select.hip", "compact.hip",
            "probe.hip"]
 # Packed fp32 VALU ops are disabled on purpose; the host pass warns that it does not
 # know the feature, which is harmless.
@@ -45,7 +45,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

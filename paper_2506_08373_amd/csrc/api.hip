@@ -351,7 +351,8 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
 size_t speckv_workspace_bytes(const speckv_params *p) {
   Plan pl;
   if (build_plan(p, &pl, false, 0) != SPECKV_OK) return 0;
-  return pl.total;
+  Plan pruned = pl;
+  return prune_plan(&pruned) ? pruned.total_pruned : pl.total;
 }
 
 size_t speckv_select_workspace_bytes(const speckv_params *p) {
@@ -433,6 +434,29 @@ speckv_status speckv_compact(const speckv_params *p, const void *k, const void *
   return from_hip(launch_compact(pl, k, v, idx, k_out, v_out, static_cast<hipStream_t>(stream)));
 }
 
+// The fused call where not every score is needed (score_prune.hip).
+static speckv_status compress_pruned(const Plan &pl, const void *q, const void *k, const void *v, int32_t *idx, void *k_out,
+                                     void *v_out, void *workspace, hipStream_t hs, hipEvent_t *ev) {
+  char *ws = static_cast<char *>(workspace);
+  float *planes = reinterpret_cast<float *>(ws + pl.off_planes);
+  float *pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
+  uint32_t *hist0 = reinterpret_cast<uint32_t *>(ws + pl.off_hist0);
+  uint32_t *counters = reinterpret_cast<uint32_t *>(ws + pl.off_part);
+  const PruneRow *rows = reinterpret_cast<const PruneRow *>(ws + pl.off_prune_rows);
+  if (launch_prune_rows(pl, q, k, workspace, hs, ev, hist0, pl.hist0_words) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (launch_prune_columns(pl, q, k, workspace, hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (launch_reduce_pool(pl, planes, nullptr, pooled, hs, hist0, counters, rows) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (launch_prune_repeat(pl, q, k, workspace, hist0, hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (launch_select(pl, pooled, idx, nullptr, nullptr, hs, hist0, reinterpret_cast<uint32_t *>(planes), counters) != hipSuccess)
+    return SPECKV_ERR_RUNTIME;
+  if (ev && hipEventRecord(ev[5], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (launch_compact(pl, k, v, idx, k_out, v_out, hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  if (ev && hipEventRecord(ev[6], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  return SPECKV_OK;
+}
+
 static speckv_status compress_impl(const speckv_params *p, const void *q, const void *k, const void *v,
                                    int32_t *idx, void *k_out, void *v_out, void *workspace,
                                    size_t workspace_bytes, void *stream, hipEvent_t *ev,
@@ -449,6 +473,12 @@ static speckv_status compress_impl(const speckv_params *p, const void *q, const 
   hipStream_t hs = static_cast<hipStream_t>(stream);
   float *planes = reinterpret_cast<float *>(ws + pl.off_planes);
   float *pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
+  if (lse_in == nullptr) {
+    // (a workspace that has no room for it is a caller's own choice of size: all scores are computed then)
+    Plan pruned = pl;
+    if (prune_plan(&pruned) && workspace_bytes >= pruned.total_pruned)
+      return compress_pruned(pruned, q, k, v, idx, k_out, v_out, workspace, hs, ev);
+  }
   // the pooling kernel also counts the first selection digit of every row (counters zeroed by the
   // kernel between the sweeps), so that selection starts at its second read of the pooled scores
   const bool short_rows = pool_select_fused(pl);

@@ -1,0 +1,255 @@
+// Pruned scoring: which keys' column sums have to be computed (see score_prune.hip for the whole and the reasons).
+//
+// A pruned call knows, per output row (layer, sequence, head), the exact scores of a sample of its keys and a bound on the score
+// of every other key.  The kernels here take a threshold from the sample and list the keys whose bound reaches it.
+#include <algorithm>
+
+#include "first_digit.h"
+#include "score_common.h"
+
+namespace speckv {
+namespace {
+
+// A bound counts as below a threshold only if it is by this much: the bound's own rounding (probabilities to 2^-13 where
+// logits reach 1000, sums to 2^-20) stays inside.
+constexpr float kPruneSlack = 1.f / 1024.f;
+// Smallest threshold that prunes.  A probability below 2^-126 underflows in a bound (2^(kPruneShift - 126) unscaled), 2^12 rows
+// of them add up to 2^-38, the slack's share of 2^-28.
+constexpr float kPruneFloor = 3.7252903e-9f;
+
+__device__ __forceinline__ uint32_t key_of(float x) {            // the selection's ordered key
+  const uint32_t u = __float_as_uint(x + 0.0f);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+struct RowAt { int layer, s, g, n, m, tail0; int64_t base; };
+__device__ __forceinline__ RowAt row_at(const Dims &d, const SeqTab &t, int row) {
+  RowAt r;
+  r.g = row % d.Hkv;
+  r.s = (row / d.Hkv) % d.S;
+  r.layer = row / (d.Hkv * d.S);
+  r.n = t.cu[r.s + 1] - t.cu[r.s];
+  r.m = r.n - d.w;
+  r.tail0 = t.tail0[r.s];
+  r.base = (int64_t)r.layer * d.Hkv * d.T + (int64_t)d.Hkv * t.cu[r.s] + (int64_t)r.g * r.n;
+  return r;
+}
+
+struct Steps { int32_t log[kMaxSeqs]; };
+
+constexpr int kThrThreads = 1024, kThrEach = 8;
+
+// A row's threshold: the lower end of the largest first digit that enough of the sample's pooled scores reach.  Neighbouring
+// pooled scores are one key's, so that `expected` of them are about expected / pool_k independent draws; three standard
+// deviations more are asked for, since a row that falls short is computed whole (launch_prune_repeat).
+// Bound: the latency of two or three rounds of loads; one workgroup per row.
+__global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes,
+                                                                      const float *__restrict__ planes, PruneRow *__restrict__ rows,
+                                                                      int32_t *__restrict__ n_items) {
+  __shared__ float score[kThrThreads * kThrEach];
+  __shared__ uint32_t hist[2048];
+  __shared__ uint32_t wave_tot[kThrThreads / 64];
+  __shared__ int digit;
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  if (row == 0 && tid < 2) n_items[tid] = 0;
+  const RowAt r = row_at(d, t, row);
+  const int step = steps.log[r.s], tile = 1 << tile_log;
+  if (step == 0) {
+    if (tid == 0) rows[row] = {-1.f, 0, 0, 0};
+    return;
+  }
+  hist[tid] = hist[tid + kThrThreads] = 0;
+  if (tid == 0) digit = 0;
+  const int n_tiles = ((r.tail0 >> tile_log) + (1 << step) - 1) >> step, n = n_tiles << tile_log;
+  const int64_t plane = (int64_t)d.L * d.Hkv * d.T;
+  const int before = d.pool_k / 2, after = (d.pool_k - 1) / 2;
+  auto key_at = [&](int e) { return ((e >> tile_log) << (tile_log + step)) + (e & (tile - 1)); };
+  for (int e0 = 0; e0 < n; e0 += kThrThreads * kThrEach) {            // (whole tiles at a time)
+    float v[kThrEach];
+#pragma unroll
+    for (int u = 0; u < kThrEach; ++u) {
+      const int e = e0 + u * kThrThreads + tid;
+      v[u] = 0.f;
+      if (e < n)
+        for (int p = 0; p < n_planes; ++p) v[u] += planes[p * plane + r.base + key_at(e)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kThrEach; ++u) score[u * kThrThreads + tid] = v[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kThrEach; ++u) {
+      const int x = u * kThrThreads + tid, first = x & ~(tile - 1);
+      if (e0 + x >= n || key_at(e0 + x) >= r.m) continue;
+      const int lo = max(first, x - before), hi = min(first + tile - 1, x + after);
+      float best = score[lo];
+      for (int y = lo + 1; y <= hi; ++y) best = fmaxf(best, score[y]);
+      atomicAdd(&hist[first_digit_of(key_of(best))], 1u);
+    }
+  }
+  __syncthreads();
+  const float expected = (float)d.c_max * (float)n / (float)r.m;
+  const uint32_t wanted = (uint32_t)ceilf(expected + 3.f * sqrtf(expected * (float)d.pool_k));
+  // numbers of scores from digit b on, digits in descending order: thread i has digits 2047 - 2 i and 2046 - 2 i
+  const uint32_t c0 = hist[2047 - 2 * tid], c1 = hist[2046 - 2 * tid];
+  uint32_t sum = c0 + c1;
+  for (int o = 1; o < 64; o *= 2) {
+    const uint32_t x = __shfl_up(sum, o, 64);
+    if (lane >= o) sum += x;
+  }
+  if (lane == 63) wave_tot[tid >> 6] = sum;
+  __syncthreads();
+  for (int w = 0; w < (tid >> 6); ++w) sum += wave_tot[w];
+  const uint32_t upto1 = sum, upto0 = sum - c1, none = sum - c1 - c0;
+  if (none < wanted && upto0 >= wanted) digit = 2047 - 2 * tid;
+  else if (upto0 < wanted && upto1 >= wanted) digit = 2046 - 2 * tid;
+  __syncthreads();
+  if (tid != 0) return;
+  int open;
+  const uint32_t key = key_prefix_of((uint32_t)digit, &open);
+  const float threshold = key >= 0x80000000u ? __uint_as_float(key ^ 0x80000000u) : 0.f;
+  // (written so that a threshold that is not a number lists every key)
+  if (threshold < kPruneFloor) rows[row] = {-1.f, 0, 0, 0};
+  else rows[row] = {threshold * (1.f - kPruneSlack) * __builtin_exp2f(-kPruneShift), digit, 0, 0};
+}
+
+constexpr int kListThreads = 512, kListEach = 8, kListKeys = kListThreads * kListEach;
+
+// Adds `n` keys to a row's list: returns the place of the first, and makes the items that begin among them (in any order: an
+// item's results depend neither on its place nor on the order of its keys).
+__device__ __forceinline__ int reserve(PruneRow *rows, int row, int n, int item_keys, int2 *items, int32_t *n_items) {
+  const int at = atomicAdd(&rows[row].listed, n);
+  const int i0 = (at + item_keys - 1) / item_keys, i1 = (at + n + item_keys - 1) / item_keys;
+  if (i1 > i0) {
+    const int first = atomicAdd(n_items, i1 - i0);
+    for (int i = i0; i < i1; ++i) items[first + i - i0] = make_int2(row, i * item_keys);
+  }
+  return at;
+}
+
+// Lists the keys outside the sample whose bound reaches the row's threshold, kListKeys of the row's keys a workgroup.
+// Bound: reading the bounds once.
+__global__ __launch_bounds__(kListThreads) void prune_list_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes, int parts, int item_keys,
+                                                                  const float *__restrict__ planes, PruneRow *__restrict__ rows,
+                                                                  int32_t *__restrict__ list, int2 *__restrict__ items,
+                                                                  int32_t *__restrict__ n_items) {
+  __shared__ int wave_tot[kListThreads / 64];
+  __shared__ int place;
+  const int row = blockIdx.x / parts, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const RowAt r = row_at(d, t, row);
+  const int step = steps.log[r.s], j0 = (blockIdx.x % parts) * kListKeys;
+  if (step == 0 || j0 >= r.tail0) return;
+  const int64_t plane = (int64_t)d.L * d.Hkv * d.T;
+  const float bound = rows[row].bound;
+  float v[kListEach];
+#pragma unroll
+  for (int u = 0; u < kListEach; ++u) {
+    const int j = j0 + u * kListThreads + tid;
+    v[u] = j < r.tail0 ? planes[r.base + j] : 0.f;
+  }
+  for (int p = 1; p < n_planes; ++p) {
+#pragma unroll
+    for (int u = 0; u < kListEach; ++u) {
+      const int j = j0 + u * kListThreads + tid;
+      if (j < r.tail0) v[u] += planes[p * plane + r.base + j];
+    }
+  }
+  uint32_t mine = 0;                        // bit u: key u of the thread is listed
+  int n = 0;                                // keys the wavefront lists
+#pragma unroll
+  for (int u = 0; u < kListEach; ++u) {
+    const int j = j0 + u * kListThreads + tid;
+    const bool listed = j < r.tail0 && ((j >> tile_log) & ((1 << step) - 1)) != 0 && !(v[u] < bound);
+    mine |= (listed ? 1u : 0u) << u;
+    n += __popcll(__ballot(listed));
+  }
+  if (lane == 0) wave_tot[wave] = n;
+  __syncthreads();
+  int at = 0, total = 0;
+  for (int w = 0; w < kListThreads / 64; ++w) {
+    if (w < wave) at += wave_tot[w];
+    total += wave_tot[w];
+  }
+  if (tid == 0 && total > 0) place = reserve(rows, row, total, item_keys, items, n_items);
+  __syncthreads();
+  int32_t *out = list + r.base + place;
+  for (int u = 0; u < kListEach; ++u) {
+    const bool listed = ((mine >> u) & 1u) != 0;
+    const uint64_t b = __ballot(listed);
+    if (listed) out[at + __popcll(b & ((1ull << lane) - 1ull))] = j0 + u * kListThreads + tid;
+    at += __popcll(b);
+  }
+}
+static_assert(kListEach <= 32, "one bit per key");
+
+// The check that pruning found every score that matters: at least c_max pooled scores, counted by first digit, reach the row's
+// digit.  A row that falls short lists every key outside the sample, one workgroup per row.
+__global__ __launch_bounds__(kListThreads) void prune_check_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int item_keys,
+                                                                   const uint32_t *__restrict__ hist0, PruneRow *__restrict__ rows,
+                                                                   int32_t *__restrict__ list, int2 *__restrict__ items,
+                                                                   int32_t *__restrict__ n_items) {
+  __shared__ int wave_tot[kListThreads / 64];
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const RowAt r = row_at(d, t, row);
+  const int step = steps.log[r.s], digit = rows[row].digit;
+  if (step == 0 || digit == 0) return;
+  static_assert(kListThreads * 4 == 2048, "four counters per thread");
+  const uint4 c = reinterpret_cast<const uint4 *>(hist0 + (int64_t)row * 2048)[tid];
+  const int b = tid * 4;
+  int n = (b >= digit ? c.x : 0) + (b + 1 >= digit ? c.y : 0) + (b + 2 >= digit ? c.z : 0) + (b + 3 >= digit ? c.w : 0);
+  for (int o = 32; o > 0; o /= 2) n += __shfl_xor(n, o, 64);
+  if (lane == 0) wave_tot[wave] = n;
+  __syncthreads();
+  n = 0;
+  for (int w = 0; w < kListThreads / 64; ++w) n += wave_tot[w];
+  if (n >= min(d.c_max, r.m)) return;
+  const int tiles = r.tail0 >> tile_log, other = tiles - ((tiles + (1 << step) - 1) >> step);
+  if (tid == 0) {
+    rows[row].failed = 1;
+    rows[row].listed = other << tile_log;
+    const int n_new = ((other << tile_log) + item_keys - 1) / item_keys, first = atomicAdd(n_items, n_new);
+    for (int i = 0; i < n_new; ++i) items[first + i] = make_int2(row, i * item_keys);
+  }
+  for (int x = tid; x < other << tile_log; x += kListThreads) {
+    const int tile = x >> tile_log;
+    list[r.base + x] = ((tile + 1 + tile / ((1 << step) - 1)) << tile_log) + (x & ((1 << tile_log) - 1));
+  }
+}
+
+Steps steps_of(const Plan &pl) {
+  Steps s;
+  std::memcpy(s.log, pl.step_log, sizeof(s.log));
+  return s;
+}
+int tile_log_of(const Plan &pl) { return __builtin_ctz((unsigned)prune_tile_keys(pl)); }
+
+}  // namespace
+
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, PruneRow *rows, int32_t *n_items, hipStream_t st) {
+  const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
+  hipLaunchKernelGGL(prune_threshold_kernel, dim3(n_rows), dim3(kThrThreads), 0, st, pl.d, pl.t, steps_of(pl), tile_log_of(pl), pl.g.RS,
+                     planes, rows, n_items);
+  return hipGetLastError();
+}
+
+hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
+                             hipStream_t st) {
+  int most = 0;
+  for (int s = 0; s < pl.d.S; ++s)
+    if (pl.step_log[s] != 0) most = std::max(most, pl.t.tail0[s]);
+  const int parts = (most + kListKeys - 1) / kListKeys;
+  const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
+  hipLaunchKernelGGL(prune_list_kernel, dim3(n_rows * (unsigned)parts), dim3(kListThreads), 0, st, pl.d, pl.t, steps_of(pl),
+                     tile_log_of(pl), pl.g.RS, parts, pl.item_keys, planes, rows, list, items, n_items);
+  return hipGetLastError();
+}
+
+hipError_t launch_prune_check(const Plan &pl, const uint32_t *hist0, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
+                              hipStream_t st) {
+  const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
+  hipLaunchKernelGGL(prune_check_kernel, dim3(n_rows), dim3(kListThreads), 0, st, pl.d, pl.t, steps_of(pl), tile_log_of(pl), pl.item_keys, hist0,
+                     rows, list, items, n_items);
+  return hipGetLastError();
+}
+
+}  // namespace speckv

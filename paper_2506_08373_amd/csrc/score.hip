@@ -23,8 +23,9 @@ constexpr int kMergeRows = 64;
 // workgroups' reads (the same pairs again for every chunk) outgrow the launch.
 constexpr int kMergeInSweep = 40;
 
+// others: a pruned call, whose chunks have a second pair each (score_prune.hip).
 template <int SLICES>
-__global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreArgs A) {
+__global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreArgs A, bool others) {
   clear_scratch(A, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
                 (int64_t)gridDim.x * gridDim.y * blockDim.x);
   __shared__ float2 partial[SLICES][kMergeRows];
@@ -37,7 +38,10 @@ __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreA
   const int s = blockIdx.y;
   const int rs = unit % A.g.RS;
   const int lh = unit / A.g.RS;                       // layer * Hkv + head
-  const int n_entries = A.t.cc[s + 1] - A.t.cc[s] + 1;
+  const int n_first = A.t.cc[s + 1] - A.t.cc[s] + 1, n_entries = others ? 2 * n_first - 1 : n_first;
+  auto slot = [&](int e) {
+    return e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1 + (e < n_first ? 0 : A.g.n_fast_chunks + d.S - n_first + 1);
+  };
   const float2 *pp = A.part + ((int64_t)unit * A.g.n_chunks) * RSB + r;
   float top = kNegBig, sum = 0.f;
   constexpr int BATCH = kMergeFirst / SLICES;         // entries requested together
@@ -46,7 +50,7 @@ __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreA
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
       const int e = e0 + u * SLICES;
-      in[u] = e < n_entries ? pp[(int64_t)(e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1) * RSB] : make_float2(kNegBig, 0.f);
+      in[u] = e < n_entries ? pp[(int64_t)slot(e) * RSB] : make_float2(kNegBig, 0.f);
     }
     if (e0 == slice) {
       merge_pairs(top, sum, in);
@@ -117,6 +121,13 @@ bool score_uses_qs(const Plan &pl, int pass) {
   return qs_supported(A, pass);
 }
 
+hipError_t launch_lse_combine(const ScoreArgs &A, bool others, hipStream_t st) {
+  const dim3 blocks(A.d.L * A.d.Hkv * A.g.RS * (A.g.RSB / kMergeRows), A.d.S);
+  if (merge_slices(A.g.MB) == 1) hipLaunchKernelGGL(lse_combine_kernel<1>, blocks, dim3(kMergeRows), 0, st, A, others);
+  else hipLaunchKernelGGL(lse_combine_kernel<2>, blocks, dim3(kMergeRows * 2), 0, st, A, others);
+  return hipGetLastError();
+}
+
 hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *part, float *lse,
                         float *planes, hipStream_t st, hipEvent_t *events, const float *lse_in,
                         uint32_t *clear, int64_t clear_words) {
@@ -142,9 +153,8 @@ hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *pa
   if (A.norm_from != kNormMerged) {
     // nothing: the column sweep makes its normalisers
   } else if (A.lse_in == nullptr) {
-    const dim3 blocks(A.d.L * A.d.Hkv * A.g.RS * (A.g.RSB / kMergeRows), A.d.S);
-    if (merge_slices(A.g.MB) == 1) hipLaunchKernelGGL(lse_combine_kernel<1>, blocks, dim3(kMergeRows), 0, st, A);
-    else hipLaunchKernelGGL(lse_combine_kernel<2>, blocks, dim3(kMergeRows * 2), 0, st, A);
+    e = launch_lse_combine(A, false, st);
+    if (e != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(lse_import_kernel, dim3(A.d.L * A.d.Hkv * A.g.RS, A.d.S), dim3(256), 0, st, A);
   }

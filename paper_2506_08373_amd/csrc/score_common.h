@@ -27,11 +27,59 @@ struct ScoreArgs {
   int32_t *fail;    // row-statistics sweep: kFailWords ints per chunk workgroup (see score_sweep.h)
 };
 
+// Which of a chunk's keys a sweep visits.  A pruned call (score_prune.hip) has a sample, every 2^step_log-th tile of a sequence's
+// unmasked keys, the others, and lists of single keys.
+constexpr int kAllKeys = 0, kSampleKeys = 1, kOtherKeys = 2, kListedKeys = 3;
+
+// Argument block of a pruned call's sweeps.
+struct PruneArgs : ScoreArgs {
+  int32_t step_log[kMaxSeqs];   // 0: every key of the sequence is in the sample
+  int32_t order[kMaxSeqs];      // the sequences, those with the longest chunks first
+  int32_t item_keys;
+  int32_t whole_chunk;          // keys per chunk of a sequence that is all sample
+  const int32_t *list;          // [layer][Hkv*T], laid out like the scores: a row's listed keys
+  const PruneRow *rows;
+  const int2 *items;            // (row, place): up to item_keys listed keys of the row from this place on
+  const int32_t *n_items;
+};
+
 // Row normalisers of the column sweep: merged by a kernel between the sweeps, merged from the partial pairs by every
 // workgroup of the column sweep for its own rows, or the caller's.
 constexpr int kNormMerged = 0, kNormPairs = 1, kNormCaller = 2;
 
 namespace {
+
+// Chunk workgroup `bid` of a pruned call (unit < 0: it has none).  The workgroups of all layers and heads take a chunk of a sequence
+// before those of the next chunk, the longest chunks first.  For the super-blocks of a group see score_sweep.h.
+struct PruneChunk { int unit, s, chunk, key_begin, key_end; };
+__device__ __forceinline__ PruneChunk prune_chunk(const PruneArgs &A, int bid) {
+  PruneChunk c;
+  const int groups = A.d.L * A.d.Hkv, per_group = 8 * A.g.RS;
+  const int item = bid / per_group * 8 + (bid % per_group & 7);
+  c.unit = -1;
+  if (item >= A.g.n_fast_chunks * groups) return c;
+  int rank = item / groups, i = 0;
+  c.unit = item % groups * A.g.RS + (bid % per_group >> 3);
+  int s = A.order[0];
+  for (;;) {
+    const int n = A.t.cc[s + 1] - A.t.cc[s];
+    if (rank < n) break;
+    rank -= n;
+    s = A.order[++i];
+  }
+  c.s = s;
+  const int kc = A.step_log[c.s] != 0 ? A.g.KC : A.whole_chunk;
+  c.chunk = A.t.cc[c.s] + rank;
+  c.key_begin = rank * kc;
+  c.key_end = c.key_begin + kc < A.t.tail0[c.s] ? c.key_begin + kc : A.t.tail0[c.s];
+  return c;
+}
+// The tile-th tile of a chunk that is not in the sample, among all of the chunk's.
+__device__ __forceinline__ int other_tile(int tile, int step_log) {
+  return tile + 1 + (int)((unsigned)tile / ((1u << step_log) - 1u));
+}
+// Place of the pairs over a chunk's other keys, behind those of all samples and tails.
+__device__ __forceinline__ int other_pairs(const PruneArgs &A, int chunk) { return A.g.n_fast_chunks + A.d.S + chunk; }
 
 // Zeroes A.clear (if any), the work spread over every thread of the grid; id: the thread's number in it.
 __device__ inline void clear_scratch(const ScoreArgs &A, int64_t id, int64_t n_threads) {
@@ -78,6 +126,13 @@ constexpr int kAnchorGrowth = 4;
 // than that.  A workgroup has kFailWaves such lists (the most waves a workgroup has).
 constexpr int kFailWords = 8, kFailListed = 6, kFailWaves = 8;
 constexpr float kAnchorLimit = 8.507059e37f;
+// The sweep of a pruned call over the keys that are not in the sample sums 2^(score - e - kPruneShift) along rows and columns, with
+// e the log2 normaliser that the sample and the masked tail give the row.  A score may exceed e by 126 + kPruneShift binary
+// orders (140 nats) before the sum of a segment of kPruneSegment tiles overflows and is left to the repair launch; a column sum is
+// a bound as long as what underflows in it does not matter beside the threshold (kPruneFloor).
+// The references are multiples of 1 / kPruneGrain and grow by such, so that they are exact.
+constexpr float kPruneShift = 76.f, kPruneGrain = 8.f;
+constexpr int kPruneSegment = 16;
 
 
 // x + (x of the lane 32 away), in every lane, without going through LDS (v_permlane32_swap).
@@ -143,6 +198,8 @@ struct Tile {
 // The two sweeps over all chunks and masked tails of a call (score_rows.hip, score_cols.hip).
 hipError_t launch_row_statistics_sweep(const ScoreArgs &A, hipStream_t st);
 hipError_t launch_column_sweep(const ScoreArgs &A, hipStream_t st);
+// Merges the partial pairs of every row into A.lse; others: also those of a pruned call's other keys (score.hip).
+hipError_t launch_lse_combine(const ScoreArgs &A, bool others, hipStream_t st);
 bool qs_supported(const ScoreArgs &A, int pass);
 hipError_t launch_qs_sweep(const ScoreArgs &A, int pass, hipStream_t st);
 

@@ -1,0 +1,341 @@
+// Pruned scoring: the sweeps of a fused call that needs the scores only to find the largest ones (Alg. 1 CrossAttention, reduce and
+// "Select KVs" together), and their host entry.
+//
+// A column sum of the row softmax needs every row's normaliser first, so two sweeps over all keys multiply every key with every row
+// twice (score_sweep.h).  A call that returns indices and rows, not scores, needs the exact scores of the best keys alone:
+//
+//   1  row statistics over a sample (every 2^step_log-th key tile) and the masked tails: a lower bound e on a row's normaliser
+//   2  one sweep over the other keys sums 2^(score - e) along rows, which completes the normalisers, and along columns: since e is
+//      no larger than the normaliser, a column sum is an upper bound on the key's score.  e follows what a chunk has seen.
+//   3  column sums of the sample with the normalisers; from them a threshold that more than c_max pooled scores will reach
+//      (prune.hip), and the list of the other keys whose bound reaches it
+//   4  column sums of the listed keys, by the same arithmetic as without pruning
+//   5  pooling.  A score that is not known is below the threshold, and so is its stand-in, the bound: where c_max or more pooled
+//      scores reach the threshold they and their order are exact.  Rows where fewer do are computed whole.
+//
+// The indices are those of all scores, whatever the data; only the time depends on them.
+// One sweep instead of two is what there is to gain.  Sum of 32 layers x 128K keys, 4 heads x 128 rows, d = 128, us: the two sweeps
+// 4350 + 4400; here sample 310, sweep 4450 (a block's 16 more additions and the row sums cost it 8 %), sample's columns 330,
+// listed keys (4 %) 230, the rest 250.  Calls, all scores / pruned: that one 8650 / 5480, eight prompts of 4K to 64K, groups of
+// 7, 28 layers 16000 / 10400, 32 layers x 16K, maximum 1020 / 880, 8 layers x 32K 644 / 566; 3 layers x 32K 331 / 400.
+// Where nothing can be pruned (all scores alike, or a threshold under kPruneFloor) the listed sweep is a second whole one and the call a
+// fifth longer than without.
+#include <algorithm>
+#include <cmath>
+
+#include "score_sweep.h"
+
+namespace speckv {
+namespace {
+
+template <int DT, int D, int MB, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void prune_sample_rows_kernel(PruneArgs A) {
+  const int bid = blockIdx.x;
+  if (bid < A.chunk_blocks) score_body<DT, D, MB, NW, 1, 0, false, false, true, kSampleKeys>(A, bid);
+  else score_body<DT, D, MB, NW, 1, 0, true>(static_cast<const ScoreArgs &>(A), bid - A.chunk_blocks);
+}
+
+template <int DT, int D, int MB, int NW, int RED>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void prune_sweep_kernel(PruneArgs A) {
+  score_body<DT, D, MB, NW, 2, RED, false, false, false, kOtherKeys>(A, blockIdx.x);
+}
+
+// The segments that wavefronts of the sweep left out of their sums, with the online step; one workgroup per wavefront's list
+// (normally empty), whose eight wavefronts share a segment's keys and read them straight into fragments.  A segment is one chain
+// of latencies: 16 tiles by the sweep's own workgroup shape (one wavefront working) 60 us, here 8.
+template <int DT, int D, int MB, int NW, int RED>
+__global__ __launch_bounds__(512) void prune_repair_kernel(PruneArgs A) {
+  using OP = Operand<DT, D, MB>;
+  constexpr int NCS = OP::TL::NCS, KT = OP::KT, RSB = NW * MB * 32, WAVES = 8;
+  __shared__ float2 pairs[WAVES][MB * 32];
+  const int bid = blockIdx.x / NW, list = blockIdx.x % NW;
+  const PruneChunk c = prune_chunk(A, bid);
+  if (c.unit < 0) return;
+  const int32_t *listed = A.fail + ((int64_t)bid * NW + list) * kFailWords;
+  const int count = listed[0];
+  if (count == 0) return;
+  const Dims &d = A.d;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int rs = c.unit % A.g.RS, g = c.unit / A.g.RS % d.Hkv, layer = c.unit / (A.g.RS * d.Hkv);
+  const int step_log = A.step_log[c.s], tiles = (c.key_end - c.key_begin + KT - 1) / KT;
+  const int others = tiles - ((tiles + (1 << step_log) - 1) >> step_log);
+  const float c2 = d.sm_scale * 1.4426950408889634f;
+  int first;
+  const int nblk = super_block_blocks(d, A.g, rs, &first);
+  const bool paired = sweep_pairs_blocks<RED, MB, NW>(A, nblk);
+  auto block_of = [&](int rb) { return paired ? list * MB + rb : rb * NW + list; };
+  u32x4 qf[MB][NCS];
+#pragma unroll
+  for (int rb = 0; rb < MB; ++rb) {
+    int hh, i;
+    const bool valid = decode_row(d, A.g, rs, block_of(rb) * 32 + l32, &hh, &i);
+    const char *qp = A.q + ((int64_t)layer * d.q_sl + (int64_t)c.s * d.q_ss + (int64_t)(valid ? i : 0) * d.q_sr +
+                            (int64_t)(g * d.G + (valid ? hh : 0)) * d.q_sh) * 2 + half * 16;
+#pragma unroll
+    for (int cs = 0; cs < NCS; ++cs) qf[rb][cs] = valid ? *reinterpret_cast<const u32x4 *>(qp + cs * 32) : (u32x4)(0u);
+  }
+  const char *kbase = A.k + ((int64_t)layer * d.kv_sl + (int64_t)A.t.cu[c.s] * d.kv_st + (int64_t)g * d.kv_sh) * 2 + half * 16;
+  float top[MB], sum[MB];
+#pragma unroll
+  for (int rb = 0; rb < MB; ++rb) { top[rb] = kNegBig; sum[rb] = 0.f; }
+  for (int n = 0; n < count; ++n) {
+    const int seg = n < kFailListed ? listed[1 + n] : listed[1 + kFailListed] + (n - kFailListed);
+    const int b1 = min(others, (seg + 1) * kPruneSegment) * (KT / 32);
+    u32x4 next[NCS];
+    auto request = [&](int b) {
+      const int bb = min(b, b1 - 1);
+      const int key = c.key_begin + other_tile(bb / (KT / 32), step_log) * KT + bb % (KT / 32) * 32 + l32;
+      const char *kp = kbase + (int64_t)key * d.kv_st * 2;
+#pragma unroll
+      for (int cs = 0; cs < NCS; ++cs) next[cs] = *reinterpret_cast<const u32x4 *>(kp + cs * 32);
+    };
+    const int b0 = seg * kPruneSegment * (KT / 32) + wave;
+    request(b0);
+    for (int b = b0; b < b1; b += WAVES) {
+      u32x4 kf[NCS];
+#pragma unroll
+      for (int cs = 0; cs < NCS; ++cs) kf[cs] = next[cs];
+      request(b + WAVES);
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb) {
+        f32x16 x = {0};
+#pragma unroll
+        for (int cs = 0; cs < NCS; ++cs) x = mma_chunk<DT>(kf[cs], qf[rb][cs], x);
+        float t = x[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) t = fmaxf(t, x[i]);
+        const float m = fmaxf(top[rb], t * c2);
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += __builtin_amdgcn_exp2f(fmaf(x[i], c2, -m));
+        sum[rb] = fmaf(sum[rb], __builtin_amdgcn_exp2f(top[rb] - m), s);
+        top[rb] = m;
+      }
+    }
+  }
+#pragma unroll
+  for (int rb = 0; rb < MB; ++rb) {
+    const float2 other = make_float2(__shfl_xor(top[rb], 32, 64), __shfl_xor(sum[rb], 32, 64));
+    merge_pairs<1>(top[rb], sum[rb], &other);
+    if (half == 0) pairs[wave][rb * 32 + l32] = make_float2(top[rb], sum[rb]);
+  }
+  __syncthreads();
+  if (threadIdx.x < MB * 32) {
+    const int r = threadIdx.x;
+    float2 *slot = A.part + ((int64_t)c.unit * A.g.n_chunks + other_pairs(A, c.chunk)) * RSB + block_of(r >> 5) * 32 + (r & 31);
+    float2 have = *slot;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) merge_pairs<1>(have.x, have.y, &pairs[w][r]);
+    *slot = have;
+  }
+}
+
+template <int DT, int D, int MB, int NW, int RED>
+__global__ __launch_bounds__(NW * 64) void prune_sample_columns_kernel(PruneArgs A) {
+  const int bid = blockIdx.x;
+  if (bid < A.chunk_blocks) score_body<DT, D, MB, NW, 2, RED, false, false, true, kSampleKeys>(A, bid);
+  else score_body<DT, D, MB, NW, 2, RED, true>(static_cast<const ScoreArgs &>(A), bid - A.chunk_blocks);
+}
+
+template <int DT, int D, int MB, int NW, int RED>
+__global__ __launch_bounds__(NW * 64) void prune_listed_kernel(PruneArgs A) {
+  const int n = *A.n_items * A.g.RS;
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    score_body<DT, D, MB, NW, 2, RED, false, false, true, kListedKeys>(A, i);
+    __syncthreads();
+  }
+}
+
+enum class Sweep { SampleRows, Others, SampleColumns, Listed };
+
+template <int DT, int D, int MB, int NW, int RED>
+hipError_t launch_prune_sweep(Sweep which, const PruneArgs &A, hipStream_t st) {
+  const unsigned chunks = (unsigned)A.chunk_blocks, tails = (unsigned)(A.d.L * A.d.Hkv * A.g.RS * A.d.S);
+  const dim3 block(NW * 64);
+  auto launch = [&](auto kernel, unsigned grid, bool row_sums = false) {
+    const size_t lds = score_lds_bytes<DT, D, MB, NW>(row_sums);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(grid), block, lds, st, A);
+    return hipGetLastError();
+  };
+  switch (which) {
+    case Sweep::SampleRows: return launch(prune_sample_rows_kernel<DT, D, MB, NW>, chunks + tails);
+    case Sweep::Others: {
+      const hipError_t e = launch(prune_sweep_kernel<DT, D, MB, NW, RED>, chunks, true);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((prune_repair_kernel<DT, D, MB, NW, RED>), dim3(chunks * NW), dim3(512), 0, st, A);
+      return hipGetLastError();
+    }
+    case Sweep::SampleColumns: return launch(prune_sample_columns_kernel<DT, D, MB, NW, RED>, chunks + tails);
+    default: return launch(prune_listed_kernel<DT, D, MB, NW, RED>, 512);
+  }
+}
+
+template <int DT, int D>
+hipError_t launch_for_type(Sweep which, const PruneArgs &A, hipStream_t st) {
+  const bool max = A.d.reduce_max != 0;
+  if (A.g.MB == 2) return max ? launch_prune_sweep<DT, D, 2, 8, 1>(which, A, st) : launch_prune_sweep<DT, D, 2, 8, 0>(which, A, st);
+  return max ? launch_prune_sweep<DT, D, 1, 8, 1>(which, A, st) : launch_prune_sweep<DT, D, 1, 8, 0>(which, A, st);
+}
+
+hipError_t launch(Sweep which, const PruneArgs &A, hipStream_t st) {
+  if (A.d.dt == SPECKV_BF16) return A.d.D == 128 ? launch_for_type<kBf16, 128>(which, A, st) : launch_for_type<kBf16, 64>(which, A, st);
+  return A.d.D == 128 ? launch_for_type<kF16, 128>(which, A, st) : launch_for_type<kF16, 64>(which, A, st);
+}
+
+// The buffers of a pruned call.
+struct Buffers {
+  PruneArgs A;
+  float *planes;
+  PruneRow *rows;
+  int32_t *list, *n_items;            // n_items[0] of the first listing, [1] of the repeated one
+  int2 *items;
+  Buffers(const Plan &pl, const void *q, const void *k, void *workspace) {
+    char *ws = static_cast<char *>(workspace);
+    planes = reinterpret_cast<float *>(ws + pl.off_planes);
+    rows = reinterpret_cast<PruneRow *>(ws + pl.off_prune_rows);
+    n_items = reinterpret_cast<int32_t *>(rows + (int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
+    items = reinterpret_cast<int2 *>(ws + pl.off_prune_items);
+    list = reinterpret_cast<int32_t *>(ws + pl.off_pooled);      // read before the pooled scores are written
+    A.d = pl.d; A.t = pl.t; A.g = pl.g;
+    A.q = (const char *)q; A.k = (const char *)k;
+    A.part = reinterpret_cast<float2 *>(ws + pl.off_part);
+    A.lse = reinterpret_cast<float *>(ws + pl.off_lse);
+    A.planes = planes; A.lse_in = nullptr; A.clear = nullptr; A.clear_words = 0;
+    A.norm_from = kNormMerged;
+    A.share = A.d.reduce_max == 0;
+    A.chunk_blocks = (int)score_chunk_workgroups(A.d, A.g, A.g.n_fast_chunks);
+    A.fail = reinterpret_cast<int32_t *>(A.part + (int64_t)A.d.L * A.d.Hkv * A.g.RS * A.g.n_chunks * A.g.RSB);
+    std::memcpy(A.step_log, pl.step_log, sizeof(A.step_log));
+    std::memcpy(A.order, pl.order, sizeof(A.order));
+    A.whole_chunk = pl.whole_chunk;
+    A.item_keys = pl.item_keys;
+    A.list = list; A.rows = rows; A.items = items; A.n_items = n_items;
+  }
+};
+
+}  // namespace
+
+// Keys per chunk, a multiple of the samples' longest period.  References grow with what a chunk has seen, so that longer chunks have
+// closer bounds and fewer keys to list: the longest that costs the sweep little in CUs left idle at its end.
+static int prune_chunk_keys(const Plan &pl, int64_t units) {
+  int step = 0;
+  int64_t longest = 0;
+  for (int s = 0; s < pl.d.S; ++s) {
+    step = std::max(step, (int)pl.step_log[s]);
+    if (pl.step_log[s] != 0) longest = std::max<int64_t>(longest, pl.t.tail0[s]);
+  }
+  const int64_t period = (int64_t)prune_tile_keys(pl) << step;
+  auto duration = [&](int64_t kc) {                     // key-times per CU
+    int64_t chunks = 0, full = 0, keys = 0, shortest = kc;
+    for (int s = 0; s < pl.d.S; ++s) {
+      if (pl.step_log[s] == 0) continue;
+      const int64_t n = pl.t.tail0[s], last = n % kc == 0 ? kc : n % kc;
+      chunks += (n + kc - 1) / kc;
+      full += n / kc + (n % kc >= kc / 4 * 3 ? 1 : 0);
+      keys += n;
+      shortest = std::min(shortest, last);
+    }
+    // whole rounds of (nearly) full chunks, the shorter ones behind them; no less than an even spread and half of the last one
+    const double n_wg = (double)(chunks * units), cost = 190., one = (double)std::min(kc, longest) + cost;
+    const double rounds = std::max(1., std::ceil((double)(full * units) / 256.)) * one;
+    if (n_wg <= 256.) return one;
+    return std::max(rounds, ((double)(keys * units) + n_wg * cost) / 256. + 0.5 * ((double)shortest + cost));
+  };
+  static const int parts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128};
+  auto cut = [&](int p) { return align_up((longest + p - 1) / p, period); };
+  double best = 1e30;
+  for (int p : parts) best = std::min(best, duration(cut(p)));
+  for (int p : parts)
+    if (duration(cut(p)) <= 1.03 * best) return (int)cut(p);
+  return (int)cut(1);
+}
+
+// Work below which the additional launches cost more than a sweep saves, in blocks of 32 rows x keys.  With all scores / pruned, d = 128:
+// 13M (3 layers of 32K) 331 / 400 us, 15M (2 layers of 64K) 290 / 337, 26M (32 layers of 8K) 646 / 568, 34M (8 layers of 32K) 644 / 566.
+constexpr int64_t kPruneMinWork = 24 << 20;
+
+bool prune_plan(Plan *pl) {
+  Dims &d = pl->d;
+  ScoreGeom &g = pl->g;
+  if (d.elt != 2 || d.D != 128 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
+      pl->hist0_words == 0 || d.c_max < 1)
+    return false;
+  const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
+  int64_t pruned = 0;
+  for (int s = 0; s < d.S; ++s) {
+    const int64_t m = pl->t.cu[s + 1] - pl->t.cu[s] - d.w;
+    pl->step_log[s] = m < 7ll * d.c_max ? 0 : m < 16ll * d.c_max || m < 24000 ? 2 : m < 48ll * d.c_max || m < 60000 ? 3 : 4;
+    if (pl->step_log[s] != 0) pruned += pl->t.tail0[s];
+  }
+  if (pruned * d.L * d.Hkv * ((d.M + 31) / 32) < kPruneMinWork) return false;
+  // about a tenth of the keys is listed: one item per CU or more
+  pl->item_keys = kPruneItemMax;
+  while (pl->item_keys > kPruneItemMin && pl->item_keys * 2560ll > pruned * units) pl->item_keys /= 2;
+  const int kc = prune_chunk_keys(*pl, units);
+  pl->whole_chunk = std::min(kc, 4096);
+  int cc = 0, most = 0;
+  int length[kMaxSeqs];               // keys that a chunk of the sequence gives the longer one of its sweeps
+  for (int s = 0; s < d.S; ++s) {
+    const int step = pl->step_log[s], c = step != 0 ? kc : pl->whole_chunk, n = (pl->t.tail0[s] + c - 1) / c;
+    pl->t.cc[s] = cc;
+    cc += n;
+    most = std::max(most, n);
+    length[s] = std::min(c, pl->t.tail0[s]);
+    pl->order[s] = s;
+  }
+  std::sort(pl->order, pl->order + d.S, [&](int a, int b) { return length[a] != length[b] ? length[a] > length[b] : a < b; });
+  pl->t.cc[d.S] = cc;
+  g.KC = kc;
+  g.n_fast_chunks = cc;
+  g.n_chunks = 2 * cc + d.S;
+  size_t off = pl->total;
+  auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
+  pl->off_part = take((size_t)units * g.n_chunks * g.RSB * sizeof(float2) + (size_t)score_fail_words(d, g, cc) * sizeof(int32_t));
+  const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
+  pl->off_prune_rows = take((size_t)rows * sizeof(PruneRow) + 2 * sizeof(int32_t));
+  int64_t items = 0;
+  for (int s = 0; s < d.S; ++s)
+    if (pl->step_log[s] != 0) items += (pl->t.tail0[s] + kPruneItemMin - 1) / kPruneItemMin;
+  pl->off_prune_items = take((size_t)(items * d.L * d.Hkv) * sizeof(int2));
+  pl->total_pruned = off;
+  return true;
+}
+
+hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, hipEvent_t *ev, uint32_t *clear,
+                             int64_t clear_words) {
+  Buffers b(pl, q, k, ws);
+  hipError_t e;
+  if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
+  if ((e = launch(Sweep::SampleRows, b.A, st)) != hipSuccess) return e;
+  b.A.norm_from = kNormPairs;
+  if ((e = launch(Sweep::Others, b.A, st)) != hipSuccess) return e;
+  if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
+  b.A.clear = clear;
+  b.A.clear_words = clear != nullptr ? clear_words : 0;
+  if ((e = launch_lse_combine(b.A, true, st)) != hipSuccess) return e;
+  if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;
+  return hipSuccess;
+}
+
+hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st) {
+  Buffers b(pl, q, k, ws);
+  hipError_t e;
+  if ((e = launch(Sweep::SampleColumns, b.A, st)) != hipSuccess) return e;
+  if ((e = launch_prune_thresholds(pl, b.planes, b.rows, b.n_items, st)) != hipSuccess) return e;
+  if ((e = launch_prune_list(pl, b.planes, b.rows, b.list, b.items, b.n_items, st)) != hipSuccess) return e;
+  return launch(Sweep::Listed, b.A, st);
+}
+
+hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st) {
+  Buffers b(pl, q, k, ws);
+  b.A.n_items = b.n_items + 1;
+  hipError_t e;
+  if ((e = launch_prune_check(pl, hist0, b.rows, b.list, b.items, b.n_items + 1, st)) != hipSuccess) return e;
+  if ((e = launch(Sweep::Listed, b.A, st)) != hipSuccess) return e;
+  float *pooled = reinterpret_cast<float *>(static_cast<char *>(ws) + pl.off_pooled);
+  return launch_reduce_pool(pl, b.planes, nullptr, pooled, st, hist0, nullptr, b.rows, true);
+}
+
+}  // namespace speckv

@@ -49,6 +49,48 @@ namespace {
 // (see do_tile): three tiles' worth is alive at a time, kept modulo four.
 constexpr int kCsumBuffers = 4;
 
+// Has the compiler compute x where this stands.
+__device__ __forceinline__ void stay_here(float (&x)[16]) {
+#pragma unroll
+  for (int i = 0; i < 16; i += 4) asm volatile("" : "+v"(x[i]), "+v"(x[i + 1]), "+v"(x[i + 2]), "+v"(x[i + 3]));
+}
+
+// Sums 16 MB values per lane over the 32 lanes of its half; lane l gets the sum of value l % 16 of row block l / 16 (MB = 1: of
+// value l % 16).  At each step a lane hands half of its values to another lane of the half and adds what it gets for the others.
+template <int MB>
+__device__ __forceinline__ float add_over_lanes(const float (&v)[MB][16]) {
+  const int lane = threadIdx.x;
+  float a[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if constexpr (MB == 2) {        // lanes 0 .. 15 keep row block 0
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[0][i]), __float_as_uint(v[1][i]), false, false);
+      a[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+      a[i] = v[0][i];
+    }
+  }
+  auto halve = [&](auto n_c, auto ctrl_c) {            // n values left; the other lane's number differs in bit n
+    constexpr int n = decltype(n_c)::value, ctrl = decltype(ctrl_c)::value;
+    const bool high = (lane & n) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const float keep = high ? a[i + n] : a[i], give = high ? a[i] : a[i + n];
+      a[i] = keep + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(give), ctrl, 0xf, 0xf, false));
+    }
+  };
+  halve(std::integral_constant<int, 8>{}, std::integral_constant<int, 0x128>{});     // row_ror:8, lane ^ 8
+  halve(std::integral_constant<int, 4>{}, std::integral_constant<int, 0x141>{});     // row_half_mirror, lane ^ 7
+  halve(std::integral_constant<int, 2>{}, std::integral_constant<int, 0x4e>{});      // quad_perm [2, 3, 0, 1], lane ^ 2
+  halve(std::integral_constant<int, 1>{}, std::integral_constant<int, 0xb1>{});      // quad_perm [1, 0, 3, 2], lane ^ 1
+  if constexpr (MB == 1) {
+    const unsigned u = __float_as_uint(a[0]);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    a[0] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  return a[0];
+}
+
 // How a sweep holds its operands.  bf16 and f16 rows are used as they are.  An fp32 row becomes three
 // bf16 rows ("planes") that add up to it exactly, v = v0 + v1 + v2 with each part the remainder of the ones
 // before it, rounded to bf16's 8 significant bits: |v1| <= 2^-8 |v|, |v2| <= 2^-17 |v|, and what is left after
@@ -95,10 +137,10 @@ template <int DT, int MB>
 constexpr bool normalisers_in_lds() { return DT == kF32 && MB == 2; }
 
 template <int DT, int D, int MB, int NW>
-constexpr size_t score_lds_bytes() {
+constexpr size_t score_lds_bytes(bool row_sums = false) {
   using OP = Operand<DT, D, MB>;
   return (size_t)2 * OP::TILE_BYTES + (size_t)kCsumBuffers * NW * MB * OP::KT * sizeof(float) +
-         (normalisers_in_lds<DT, MB>() ? NW * MB * 32 * sizeof(float) : 0) +
+         (normalisers_in_lds<DT, MB>() ? 1 : row_sums ? 3 : 0) * NW * MB * 32 * sizeof(float) +
          (OP::SPLIT ? NW * MB * 32 * sizeof(int64_t) : 0);        // row_off
 }
 
@@ -128,6 +170,13 @@ __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3
   plane[0][0] |= least < 2 * kSplitMin - 1 ? 0x7fffu : 0u;
 }
 
+// Whether a column sweep's waves take neighbouring row blocks (see `paired` below).
+template <int RED, int MB, int NW>
+__device__ __forceinline__ bool sweep_pairs_blocks(const ScoreArgs &A, int nblk) {
+  const int blocks_per_head = (A.g.PPH != 1 ? NW * MB * 32 : A.g.packed != 0 ? 32 : A.g.Rp) / 32;
+  return RED == 1 && MB == 2 && nblk == NW * MB && (blocks_per_head % 2 == 0 || A.g.packed != 0);
+}
+
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
 //   PASS    1: row statistics, 2: column reduction
 //   RED     (pass 2) 0: sum over the rows of a head, 1: max over the rows of a head;
@@ -142,10 +191,16 @@ __device__ __forceinline__ void split_chunk(u32x4 lo, u32x4 hi, u32x4 (&plane)[3
 //           its pairs merged into the ones already written; wavefronts that do not take part
 //           (the segment is not on their list) only help to load the key tiles
 //   MAY_SHARE  the code for row blocks that waves share (split_blocks)
-template <int DT, int D, int MB, int NW, int PASS, int RED, bool MASKED, bool REPAIR = false, bool MAY_SHARE = true>
-__device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, const int seg = 0,
+//   KEYS    which of a chunk's keys: all, or for a pruned call (score_prune.hip) its sample, the others or a list.
+//           Pass 2 over the others also sums the rows, in segments of kPruneSegment tiles.
+template <int DT, int D, int MB, int NW, int PASS, int RED, bool MASKED, bool REPAIR = false, bool MAY_SHARE = true,
+          int KEYS = kAllKeys, typename Args = ScoreArgs>
+__device__ __forceinline__ void score_body(const Args &A, const int bid, const int seg = 0,
                                            const bool wave_takes_part = true) {
-  static_assert(!REPAIR || (PASS == 1 && !MASKED), "only the row-statistics sweep is repaired");
+  static_assert(!REPAIR || (PASS == 1 && !MASKED && KEYS == kAllKeys), "only the row-statistics sweep is repaired");
+  static_assert(KEYS == kAllKeys || (DT != kF32 && !MASKED), "pruned calls: 16-bit rows, unmasked keys");
+  constexpr bool ROW_SUMS = PASS == 2 && KEYS == kOtherKeys;
+  static_assert(KEYS != kOtherKeys || !MAY_SHARE, "with the code for shared blocks the row sums do not fit the registers");
   constexpr int ELT = elt_bytes(DT);
   using OP = Operand<DT, D, MB>;
   using TL = typename OP::TL;
@@ -170,6 +225,22 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     unit = bid % units;
     s = bid / units;
     chunk = A.g.n_fast_chunks + s;
+  } else if constexpr (KEYS == kListedKeys) {
+    const int2 item = A.items[bid / A.g.RS];
+    const int layer_seq = item.x / d.Hkv;
+    s = layer_seq % d.S;
+    unit = (layer_seq / d.S * d.Hkv + item.x % d.Hkv) * A.g.RS + bid % A.g.RS;
+    chunk = 0;
+    key_begin = item.y;                                   // places in the row's list, not keys
+    key_end = min(item.y + A.item_keys, A.rows[item.x].listed);
+  } else if constexpr (KEYS != kAllKeys) {
+    const PruneChunk c = prune_chunk(A, bid);
+    if (c.unit < 0) return;
+    unit = c.unit;
+    s = c.s;
+    chunk = c.chunk;
+    key_begin = c.key_begin;
+    key_end = c.key_end;
   } else {
     // 1-D grid.  Workgroups go to the 8 XCDs round-robin by their linear id and each XCD has its
     // own L2, so the RS row super-blocks that sweep the SAME keys of a (layer, head) get ids 8
@@ -189,7 +260,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   if (MASKED) {
     key_begin = tail0;
     key_end = n_s;
-  } else {
+  } else if constexpr (KEYS == kAllKeys) {
     const int kc = chunk_keys(A.g, tail0);
     key_begin = (chunk - A.t.cc[s]) * kc;
     key_end = min(tail0, key_begin + kc);                 // a chunk past a shorter live prompt is empty
@@ -198,7 +269,17 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   const int g = (unit / A.g.RS) % d.Hkv;
   const int layer = unit / (A.g.RS * d.Hkv);
   const int m = n_s - d.w;
-  const int ntiles = (key_end - key_begin + KT - 1) / KT;
+  const int chunk_tiles = (key_end - key_begin + KT - 1) / KT;
+  int step_log = 0;                                       // the sample: every 2^step_log-th tile of a chunk
+  if constexpr (KEYS == kSampleKeys || KEYS == kOtherKeys) step_log = A.step_log[s];
+  const int sampled = (chunk_tiles + (1 << step_log) - 1) >> step_log;
+  const int ntiles = KEYS == kSampleKeys ? sampled : KEYS == kOtherKeys ? chunk_tiles - sampled : chunk_tiles;
+  // a tile's first key (place in the list)
+  auto tile_key = [&](int tile) {
+    if constexpr (KEYS == kSampleKeys) tile <<= step_log;
+    if constexpr (KEYS == kOtherKeys) tile = other_tile(tile, step_log);
+    return key_begin + tile * KT;
+  };
   const float c2 = d.sm_scale * 1.4426950408889634f;
 
   // Which of the super-block's row blocks this wave computes (see split_blocks): `nact` of its own, row blocks 0 .. nact-1 of
@@ -217,7 +298,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   // column maxima in registers and hands one value per key to the flush, not two.  A maximum
   // does not depend on the order, so the result is the same bit for bit.
   const int blocks_per_head = (A.g.PPH != 1 ? RSB : A.g.packed != 0 ? 32 : A.g.Rp) / 32;
-  const bool paired = PASS == 2 && RED == 1 && !MASKED && MB == 2 && nblk == NW * MB && (blocks_per_head % 2 == 0 || A.g.packed != 0);
+  const bool paired = PASS == 2 && !MASKED && sweep_pairs_blocks<RED, MB, NW>(A, nblk);
   // ... and where heads are combined by maximum too, a wave merges whatever blocks it has.
   const bool merged = paired || (PASS == 2 && RED == 1 && !MASKED && d.head_max != 0);
   auto block_of = [&](int rb) { return paired ? wv * MB + rb : block_of_slot(split, rb * NW + wv); };
@@ -229,17 +310,28 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   const char *kbase = A.k + ((int64_t)layer * d.kv_sl + (int64_t)A.t.cu[s] * d.kv_st + (int64_t)g * d.kv_sh) * ELT;
   const int64_t tokb = d.kv_st * ELT;
   const int st_row = (lane * 16) / ROWB, st_slot = ((lane * 16) % ROWB) / 16;
-  // unmasked sweep: the lane's byte offset inside a tile never changes, only the (uniform) tile
-  // base moves, so the loads use a scalar base plus a 32-bit lane offset
-  uint32_t loff[SEG_PER_WAVE];
+  // unmasked sweep: the lane's byte offset inside a tile never changes, only the (uniform) base of the
+  // tile's segment moves, so the loads use a scalar base plus a 32-bit lane offset
+  static_assert(SPLIT || NW * RPS / TL::RPB % (TL::SWZ + 1) == 0, "a wave's segments of a tile are swizzled alike");
+  const uint32_t loff = (KEYS == kListedKeys ? 0u : (uint32_t)(wv * RPS + st_row) * (uint32_t)tokb) +
+                        (uint32_t)((st_slot ^ TL::swizzle(wv * RPS + st_row)) * 16);
+  // listed keys: the lane's keys of the next tile to be loaded, requested one tile ahead
+  const int32_t *list = nullptr;
+  int next_key[SEG_PER_WAVE];
+  auto request_keys = [&](int tile) {
+    if constexpr (KEYS == kListedKeys) {
 #pragma unroll
-  for (int it = 0; it < SEG_PER_WAVE; ++it) {
-    const int r_ = (it * NW + wv) * RPS + st_row;
-    loff[it] = (uint32_t)r_ * (uint32_t)tokb + (uint32_t)((st_slot ^ TL::swizzle(r_)) * 16);
+      for (int it = 0; it < SEG_PER_WAVE; ++it)      // places past the end repeat the last key; they are not written
+        next_key[it] = list[min(key_begin + tile * KT + (it * NW + wv) * RPS + st_row, key_end - 1)];
+    }
+  };
+  if constexpr (KEYS == kListedKeys) {
+    list = A.list + (int64_t)layer * d.Hkv * d.T + (int64_t)d.Hkv * A.t.cu[s] + (int64_t)g * n_host;
+    request_keys(0);
   }
 #define SPECKV_LOAD_TILE(tile_, buf_)                                                         \
   {                                                                                           \
-    const int k0_ = key_begin + (tile_) * KT;                                                 \
+    const int k0_ = tile_key(tile_);                                                          \
     const char *tbase_ = kbase + (int64_t)k0_ * tokb;                                         \
     _Pragma("unroll") for (int it = 0; it < SEG_PER_WAVE; ++it) {                             \
       const int seg_ = it * NW + wv;                                                          \
@@ -248,13 +340,16 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         const int r_ = seg_ * RPS + st_row;                                                   \
         /* rows past the end of the sequence re-read its last key; they are masked later */   \
         src_ = kbase + (int64_t)min(k0_ + r_, n_s - 1) * tokb + (st_slot ^ TL::swizzle(r_)) * 16; \
+      } else if (KEYS == kListedKeys) {                                                       \
+        src_ = kbase + (int64_t)next_key[it] * tokb + loff;                                   \
       } else {                                                                                \
-        src_ = tbase_ + loff[it];                                                             \
+        src_ = tbase_ + (int64_t)(it * NW * RPS) * tokb + loff;                               \
       }                                                                                       \
       __builtin_amdgcn_global_load_lds(                                                       \
           (const __attribute__((address_space(1))) void *)src_,                               \
           (__attribute__((address_space(3))) void *)(kbuf + (buf_) * TILE_BYTES + seg_ * 1024), 16, 0, 0); \
     }                                                                                         \
+    request_keys((tile_) + 1);                                                                \
   }
   // fp32: the tile passes through registers, split into its planes on the way.  SPECKV_FETCH_TILE
   // requests it, SPECKV_STORE_TILE (before the barrier that hands the tile over) splits and stores it.
@@ -328,6 +423,15 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
 
   // ---- per-pass row state
   float mrun[MB], lrun[MB];          // pass 1: lane = one query row per row block
+  // Pass 2 with row sums: what a wave knows of its rows between segments lies in LDS, [NW][MB][32] each: the row's negated
+  // reference, its sum, and the part of the sum that is in the first reference.  A lane keeps the row own_slot() for this:
+  // row l32 % 16, counted as in nlse, of row block l32 / 16 (MB = 1: lanes from 16 on repeat the others).
+  float *own_ref = csum + (size_t)kCsumBuffers * NW * MB * KT, *own_sum = own_ref + RSB, *own_first = own_sum + RSB;
+  auto own_slot = [&]() {
+    int l = lane;
+    asm volatile("" : "+v"(l));        // made where it is used, not kept in a register
+    return wv * MB * 32 + (MB == 2 ? l & 16 : 0) * 2 + 8 * ((l & 15) >> 2) + 4 * (l >> 5) + (l & 3);
+  };
   constexpr bool LSE_LDS = PASS == 2 && normalisers_in_lds<DT, MB>();
   float nlse[LSE_LDS ? 1 : MB][16];  // pass 2: lane = 16 rows per row block
   float *lds_lse = csum + (size_t)kCsumBuffers * NW * MB * KT;                     // ... or in LDS, [RSB]
@@ -384,6 +488,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     }
     if (slice == 0) {
       v = -v;
+      if constexpr (ROW_SUMS) v = ceilf(v * kPruneGrain) / kPruneGrain - kPruneShift;      // see kPruneShift
       if (d.weight_rows && valid && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
       norm[lr] = valid ? v : -INFINITY;                   // padded rows contribute 2^-inf = 0
       if (MASKED) row_last[lr] = io < d.w ? m + io : n_s - 1;
@@ -397,6 +502,12 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         if constexpr (!LSE_LDS) nlse[rb][i] = norm[r];
         if constexpr (MASKED) last2[rb][i] = row_last[r];
       }
+    if constexpr (ROW_SUMS) {
+      const int own = own_slot();
+      own_ref[own] = norm[block_of((own >> 5) & (MB - 1)) * 32 + (own & 31)];
+      own_sum[own] = 0.f;
+      own_first[own] = __builtin_amdgcn_exp2f(-kPruneShift);
+    }
     __syncthreads();
     // slots of skipped blocks must read as zero when the tile partials are merged
     if (MASKED || split.full < NW || per > 1 || (RED == 1 && nblk != NW * MB))
@@ -465,7 +576,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   const bool share_slots = per > 1 && split.full >= NW;
 #define SPECKV_FLUSH_TILE(tile_)                                                             \
   if (tid < KT) {                                                                            \
-    const int key_ = key_begin + (tile_) * KT + tid;                                         \
+    const int key_ = tile_key(tile_) + tid;                                                  \
     if (key_ < key_end) {                                                                    \
       const float *cp_ = csum + (size_t)((tile_) % kCsumBuffers) * NW * MB * KT + tid;                  \
       float total_ = 0.f;                                                                    \
@@ -494,7 +605,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         }                                                                                    \
         total_ += cur_;                                                                      \
       }                                                                                      \
-      plane_out[key_] = total_;                                                              \
+      if constexpr (KEYS == kListedKeys) plane_out[list[key_]] = total_;                     \
+      else plane_out[key_] = total_;                                                         \
     }                                                                                        \
   }
 
@@ -524,7 +636,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
   float l_before[MB];                 // the sums at the start of the current segment
   int n_failed = 0;
   int listed[kFailListed + 1];        // uniform: lives in scalar registers
-  if (kAnchored) {
+  if (kAnchored || ROW_SUMS) {
 #pragma unroll
     for (int i = 0; i <= kFailListed; ++i) listed[i] = 0;
   }
@@ -704,6 +816,49 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       float top_before = 0.f;          // pass 1, fp32: largest score of the unit before a segment's last look
       float shared_top = 0.f;          // pass 1: largest score of the last unit of the shared block
       float colsum = 0.f;              // pass 2: the lane's key, over the row blocks of the current key block
+      float row_sum[ROW_SUMS ? MB : 1][16];                 // over the keys that the lane has seen in this segment
+      if constexpr (ROW_SUMS) {
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) row_sum[rb][i] = 0.f;
+      }
+      // The segment is over: its row sums, added up over the lanes, join the rows' sums, or it is left to the repair launch.
+      auto end_row_segment = [&](int segment) {
+        if constexpr (ROW_SUMS) {
+          const float t = add_over_lanes<MB>(row_sum);
+#pragma unroll
+          for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) row_sum[rb][i] = 0.f;
+          if (__builtin_amdgcn_ballot_w64(!(t < kAnchorLimit)) != 0 || n_failed > kFailListed) {
+#pragma unroll
+            for (int i = 0; i <= kFailListed; ++i)
+              if (i == n_failed) listed[i] = segment;
+            ++n_failed;
+          } else {
+            const int own = own_slot();
+            float sum = own_sum[own] + t, first = own_first[own];
+            // A bound is as close as the row's reference is to its normaliser: the reference follows what has been seen, in steps
+            // that are exact (kPruneGrain).
+            const float up = floorf((__builtin_amdgcn_logf(sum + first) + kPruneShift) * kPruneGrain) / kPruneGrain;
+            const bool grown = up > 0.f && up < 1024.f;
+            if (grown) {
+              const float scale = __builtin_amdgcn_exp2f(-0.5f * up);        // (its square may be too small for a number)
+              sum = sum * scale * scale;
+              own_first[own] = first * scale * scale;
+              own_ref[own] -= up;
+            }
+            own_sum[own] = sum;
+            if (__builtin_amdgcn_ballot_w64(grown) != 0) {
+#pragma unroll
+              for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) nlse[rb][i] = own_ref[(wv * MB + rb) * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+            }
+          }
+        }
+      };
 
       // pass 2: sum (maximum) of the lane's 16 probabilities and `before`
       auto column_of = [&](const f32x16 &x, int rb, float before) {
@@ -711,6 +866,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
         load_lse(rb, nl);
 #pragma unroll
         for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nl[i]));
+        if constexpr (ROW_SUMS) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) row_sum[rb][i] += p[i];
+          stay_here(row_sum[rb]);        // (added later, the block's probabilities would be kept until then)
+        }
         if (RED == 0)
           return before + ((((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
                            (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15]))));
@@ -803,6 +963,16 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           }
         }
       };
+      // the open unit (the last one of a tile: it always sits in acc[1])
+      auto drain = [&](int last_tile, auto anchored_c) {
+        if constexpr (NACT > 0 && PIPELINED) {
+          if (SPLIT && open) recompute_unless_finite(acc[1], NACT - 1, key_begin + last_tile * KT + (KB - 1) * 32);
+          finish_unit(acc[1], NACT - 1, KB - 1, last_tile % kCsumBuffers, anchored_c);
+        }
+        open = false;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
+      };
       // One tile of the sweep; the LDS buffer index is a compile-time constant so that every LDS
       // address below is a register plus an immediate.  Pass 2 flushes the tile before last: its last
       // column partials were written in the previous tile's first unit.
@@ -815,6 +985,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           else SPECKV_LOAD_TILE(tile + 1, buf ^ 1)
         }
         if (PASS == 2 && tile > 1) SPECKV_FLUSH_TILE(tile - 2)
+        // (here, where no fragment and only the open block is in registers)
+        if (ROW_SUMS && buf == 0 && tile > 0 && tile % kPruneSegment == 0) {
+          drain(tile - 1, anchored_c);
+          end_row_segment(tile / kPruneSegment - 1);
+        }
         if constexpr (NACT == 0 && SHARED && kAnchored && anchored && buf == 1) {
           if (tile > 1)
             end_segment((tile - 3) / kAnchorTiles, [&](int, float) { return fmaxf(shared_top * c2, kNegBig) + (float)anchor_shift; });
@@ -826,7 +1001,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           for (int u = 0; u < KB * NACT; ++u) {
             const int kb = u / NACT, rb = u % NACT;
             const int pu = (u + KB * NACT - 1) % (KB * NACT);      // the unit before (of the tile before for u = 0)
-            const int pbuf = (u == 0 ? tile + kCsumBuffers - 1 : tile) % kCsumBuffers;
+            // (where nothing is open its place is in the partial buffer that no tile uses now)
+            const int pbuf = (u != 0 ? tile : ROW_SUMS && !open ? tile + 1 : tile + kCsumBuffers - 1) % kCsumBuffers;
             if constexpr (SPLIT) {
               // the open unit is finished beside the lower products, the leading ones then take its registers
               f32x16 low = {0};
@@ -914,16 +1090,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
           if (tile + 1 < t1) do_tile(tile + 1, std::integral_constant<int, buf ^ 1>{}, anchored_c);
         }
       };
-      // the open unit (the last one of a tile: it always sits in acc[1])
-      auto drain = [&](int last_tile, auto anchored_c) {
-        if constexpr (NACT > 0 && PIPELINED) {
-          if (SPLIT && open) recompute_unless_finite(acc[1], NACT - 1, key_begin + last_tile * KT + (KB - 1) * 32);
-          finish_unit(acc[1], NACT - 1, KB - 1, last_tile % kCsumBuffers, anchored_c);
-        }
-        open = false;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
-      };
       using buf0 = std::integral_constant<int, 0>;
       using buf1 = std::integral_constant<int, 1>;
       if constexpr (REPAIR) {
@@ -947,6 +1113,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
       } else if (ntiles > 0) {
         run_tiles(0, ntiles, buf0{}, std::false_type{});
         drain(ntiles - 1, std::false_type{});
+        end_row_segment((ntiles - 1) / kPruneSegment);
         if (PASS == 2) {
           __syncthreads();
           if (ntiles > 1) SPECKV_FLUSH_TILE(ntiles - 2)
@@ -964,7 +1131,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     if (nact == MB) sweep(std::integral_constant<int, MB>{}, std::false_type{});
     else if (MB > 1 && nact == 1) sweep_shared(std::integral_constant<int, MB - 1>{});
     else sweep_shared(std::integral_constant<int, 0>{});
-    if constexpr (kAnchored) {
+    if constexpr (kAnchored || ROW_SUMS) {
       if (lane <= kFailListed + 1) {
         int32_t *mine = A.fail + ((int64_t)bid * NW + wv) * kFailWords;
         int v = n_failed;
@@ -976,6 +1143,14 @@ __device__ __forceinline__ void score_body(const ScoreArgs &A, const int bid, co
     }
   }
 
+  if constexpr (ROW_SUMS) {
+    const int own = own_slot(), own_rb = (own >> 5) & (MB - 1);
+    int e2;
+    const float sum = own_sum[own], lf = __builtin_frexpf(sum, &e2);
+    if (l32 < MB * 16)
+      A.part[((int64_t)unit * A.g.n_chunks + other_pairs(A, chunk)) * RSB + block_of(own_rb) * 32 + (own & 31)] =
+          sum > 0.f ? make_float2((float)e2 - own_ref[own], lf) : make_float2(kNegBig, 0.f);
+  }
   if (PASS == 1) {
     // an empty chunk (a sequence without masked tail) leaves the neutral pair (-big, 0)
     float2 *pp = A.part + ((int64_t)unit * A.g.n_chunks + chunk) * RSB;

@@ -54,7 +54,8 @@ struct PlaneMerge {
 __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge pm,
                                         float *__restrict__ raw, float *__restrict__ pooled,
                                         int n_s, int n_row, int m, int pool_k, int pool_avg, int j0,
-                                        float *tile, uint32_t *first_digit = nullptr) {
+                                        float *tile, uint32_t *first_digit = nullptr, int digit_from = 0,
+                                        int digit_to = 2048) {
   // window of key j: j - half .. j + after (symmetric for odd kernels; an even kernel looks one
   // position further back than ahead, the library convention with padding k / 2)
   const int half = pool_k / 2, after = (pool_k - 1) / 2;
@@ -137,7 +138,10 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
       } else {
         for (int jj = lo + 1; jj <= hi; ++jj) best = fmaxf(best, tile[jj - j0 + half]);
       }
-      if (first_digit != nullptr) atomicAdd(&first_digit[first_digit_of(ordered_key(best))], 1u);   // selection's first digit
+      if (first_digit != nullptr) {                         // selection's first digit
+        const int digit = first_digit_of(ordered_key(best));
+        if (digit >= digit_from && digit < digit_to) atomicAdd(&first_digit[digit], 1u);
+      }
     }
     pooled[j] = best;
   }
@@ -145,26 +149,38 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
 
 __global__ __launch_bounds__(kPoolThreads) void reduce_pool_kernel(
     Dims d, SeqTab t, PlaneMerge pm, const float *__restrict__ planes,
-    float *__restrict__ raw, float *__restrict__ pooled, int tiles_per_row, uint32_t *__restrict__ hist0,
-    uint32_t *__restrict__ arrived) {
+    float *__restrict__ raw, float *__restrict__ pooled, int groups_per_row, uint32_t *__restrict__ hist0,
+    uint32_t *__restrict__ arrived, const PruneRow *__restrict__ prune, bool repeat) {
   __shared__ float tile[kPoolTile + SPECKV_MAX_POOL_K + 1];
   __shared__ uint32_t first_digit[2048];
-  const int unit = blockIdx.x / tiles_per_row;
-  const int j0 = (blockIdx.x - unit * tiles_per_row) * kPoolTile;
+  const int unit = blockIdx.x / groups_per_row;
+  int j0 = (blockIdx.x - unit * groups_per_row) * kPoolTile;
   const int g = unit % d.Hkv;
   const int s = (unit / d.Hkv) % d.S;
   const int layer = unit / (d.Hkv * d.S);
   const int n_row = t.cu[s + 1] - t.cu[s];
   if (arrived != nullptr && j0 == 0 && threadIdx.x == 0) arrived[(int64_t)unit * kPartsWords] = 0u;    // for select_in_parts
   if (j0 >= n_row) return;
+  // Pruned scores: only the ones from the row's digit on are certain.  They are counted here, the others after every key
+  // of a row has been computed.
+  int digit_from = 0, digit_to = 2048;
+  if (prune != nullptr) {
+    if (repeat && prune[unit].failed == 0) return;
+    (repeat ? digit_to : digit_from) = prune[unit].digit;
+  }
   const int n_s = live_len(d, t, s);
   const int64_t base = (int64_t)layer * d.Hkv * d.T + (int64_t)d.Hkv * t.cu[s] + (int64_t)g * n_row;
   // with hist0: the tile's histogram of the first selection digit is built in LDS (cleared here; the
   // barrier inside reduce_pool_tile orders the clearing before the counting) and added to the row's
   if (hist0 != nullptr)
     for (int b = threadIdx.x; b < 2048; b += kPoolThreads) first_digit[b] = 0;
-  reduce_pool_tile(planes + base, pm, raw ? raw + base : nullptr, pooled + base, n_s, n_row, n_s - d.w,
-                   d.pool_k, d.pool_avg, j0, tile, hist0 != nullptr ? first_digit : nullptr);
+  for (;;) {
+    reduce_pool_tile(planes + base, pm, raw ? raw + base : nullptr, pooled + base, n_s, n_row, n_s - d.w,
+                     d.pool_k, d.pool_avg, j0, tile, hist0 != nullptr ? first_digit : nullptr, digit_from, digit_to);
+    j0 += groups_per_row * kPoolTile;
+    if (j0 >= n_row) break;                                // (as a rule at once: a workgroup per tile)
+    __syncthreads();
+  }
   if (hist0 != nullptr) {
     __syncthreads();
     for (int b = threadIdx.x; b < 2048; b += kPoolThreads) {
@@ -1816,15 +1832,16 @@ hipError_t launch_pool_select(const Plan &pl, const float *planes, int32_t *idx,
 }
 
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
-                              hipStream_t st, uint32_t *hist0, uint32_t *arrived) {
+                              hipStream_t st, uint32_t *hist0, uint32_t *arrived, const PruneRow *prune, bool repeat) {
   const Dims &d = pl.d;
   int max_n = 0;
   for (int s = 0; s < d.S; ++s) max_n = max(max_n, pl.t.cu[s + 1] - pl.t.cu[s]);
-  const int tiles = (max_n + kPoolTile - 1) / kPoolTile;
+  // (a repeat has few rows to do, if any: workgroups that only return should be few, too)
+  const int tiles = repeat ? 32 : (max_n + kPoolTile - 1) / kPoolTile;
   const int64_t blocks = (int64_t)d.L * d.S * d.Hkv * tiles;
   const PlaneMerge pm = merge_of(pl);
   hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)blocks), dim3(kPoolThreads), 0, st, d, pl.t,
-                     pm, planes, raw, pooled, tiles, hist0, arrived);
+                     pm, planes, raw, pooled, tiles, hist0, arrived, prune, repeat);
   return hipGetLastError();
 }
 
@@ -1864,7 +1881,7 @@ hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t 
   pm.n_inner = 1; pm.n_outer = 1; pm.inner_max = 0; pm.outer_max = 0; pm.plane_stride = 0;
   const int tiles = ((int)d.T + kPoolTile - 1) / kPoolTile;
   hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)tiles), dim3(kPoolThreads), 0, st, d, pl.t, pm, in, (float *)nullptr, out,
-                     tiles, hist0, arrived);
+                     tiles, hist0, arrived, (const PruneRow *)nullptr, false);
   return hipGetLastError();
 }
 

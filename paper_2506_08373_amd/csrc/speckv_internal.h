@@ -67,6 +67,11 @@ struct Plan {
   // selection of long rows in calls with few rows: parts per row (1: not split), keys per part, scratch
   int32_t sel_parts, sel_part_len;
   size_t off_sel_hist, off_sel_state;
+  // pruned scoring (score_prune.hip): sample step of every sequence, and scratch behind everything else
+  int32_t step_log[kMaxSeqs], order[kMaxSeqs];
+  int32_t whole_chunk, item_keys;
+  size_t off_prune_items, off_prune_rows, total_pruned;
+  int64_t prune_items;
   // first-digit histograms of the pooled rows (2048 counters per row), filled by the pooling kernel
   // of a fused call so that selection starts at the second read; hist0_words == 0: not used
   size_t off_hist0;
@@ -198,11 +203,42 @@ __host__ __device__ inline BlockSplit split_blocks(int n, bool share) {
 // Block that slot s (= row block * NW + wave) computes.
 __host__ __device__ inline int block_of_slot(const BlockSplit &b, int s) { return s < b.full ? s : b.full + (s - b.full) / b.per; }
 
+// ---- pruned scoring (score_prune.hip, prune.hip) ----
+// What the pruned sweeps know of an output row (layer, seq, head).
+struct PruneRow {
+  float bound;       // keys whose bound from the sweep is below this are not listed (negative: every key is)
+  int32_t digit;     // first digit of the scores that cannot come from an unlisted key; smaller digits are not counted
+  int32_t listed;    // keys in the row's list
+  int32_t failed;    // 1: fewer than c_max scores reached the digit, every key is computed
+};
+// An item of a listed sweep holds at most Plan::item_keys keys, and at least this many but for the last of a row.
+constexpr int kPruneItemMin = 512, kPruneItemMax = 2048;
+// Keys of a sample's tile: Operand::KT of the scoring kernels.
+inline int prune_tile_keys(const Plan &pl) { return pl.d.D == 64 && pl.g.MB == 2 ? 256 : 128; }
+// Turns the plan of a fused call into one of a pruned call where that is faster; false: it is not.
+bool prune_plan(Plan *pl);
+// Row statistics over the sample, then the sweep over the other keys (bounds into the planes), then the normalisers
+// (clear: see launch_score).
+hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, hipEvent_t *events,
+                             uint32_t *clear, int64_t clear_words);
+// Column sums of the sample and the masked tails; thresholds and lists; column sums of the listed keys.
+hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st);
+// After the pooling of these: column sums of all keys, and pooling, of the rows that failed.
+hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st);
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, PruneRow *rows, int32_t *n_items, hipStream_t st);
+hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
+                             hipStream_t st);
+// hist0: the pooled scores' first digits.  Lists every key of the rows that failed.
+hipError_t launch_prune_check(const Plan &pl, const uint32_t *hist0, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
+                              hipStream_t st);
+
 // out rows = (layer, seq, head): pooled/raw in the "scores" layout from RS planes.
+// prune, when not null: smaller digits than a row's are not counted; repeat: only the rows that failed, only the smaller digits.
 // hist0, when not null: [rows][2048] zeroed counters; the kernel adds the first-digit histogram of
 // every row's pooled scores (the non-window entries), for launch_select.
 hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, float *pooled,
-                              hipStream_t st, uint32_t *hist0 = nullptr, uint32_t *arrived = nullptr);
+                              hipStream_t st, uint32_t *hist0 = nullptr, uint32_t *arrived = nullptr,
+                              const PruneRow *prune = nullptr, bool repeat = false);
 // Pooling and selection of a fused call's short rows in one launch, where pool_select_fused says so.
 bool pool_select_fused(const Plan &pl);
 hipError_t launch_pool_select(const Plan &pl, const float *planes, int32_t *idx, hipStream_t st);

@@ -1,0 +1,163 @@
+"""Fused calls large enough to be pruned keep what the complete scores say: the best c_max keys by the library's own scores, which
+other tests hold against the oracle.  The two ways add a row's sum in different orders (relative 1e-6), so that keys whose scores
+are closer than TIE to the last kept one may change places."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from . import test_gpu_parity as parity
+
+pytestmark = pytest.mark.gpu
+TIE = 2e-5        # ten times the largest relative difference of two fp32 scores over logits of 10^2 (2e-6)
+
+
+@pytest.fixture(scope="module")
+def S():
+    import paper_2506_08373_amd as S
+    S.load_library()
+    return S
+
+
+def params(S, q, k, lens, n_window, c_max, **kw):
+    return S.SpecKVParams.for_tensors(q, k, seq_lens=lens, n_window=n_window, pool_k=kw.pop("pool_k", 7), c_max=c_max,
+                                      sm_scale=kw.pop("sm_scale", k.shape[-1] ** -0.5), **kw)
+
+
+def check(S, q, k, lens, n_window, c_max, ws=None, **kw):
+    L, T, H, d = k.shape
+    p = params(S, q, k, lens, n_window, c_max, **kw)
+    assert ws is not None or S.workspace_bytes(p) > S.workspace_bytes(params(S, q, k, lens, n_window, c_max, **{**kw, "pool": "avg"})), \
+        "not a pruned call"
+    KT = S.total_keep(p)
+    ws = parity.alloc_ws(S, p) if ws is None else ws
+    pooled = torch.empty(L, H * T, device="cuda")
+    idx = torch.full((L, H * KT), -7, dtype=torch.int32, device="cuda")
+    k_out = torch.empty(L, H * KT, d, dtype=k.dtype, device="cuda")
+    S.speckv_score(p, q, k, pooled, None, ws)
+    for _ in range(2):                                   # the second one on the first one's workspace
+        idx.fill_(-7)
+        S.speckv_compress(p, q, k, None, idx, k_out, None, ws)
+        t0 = keep0 = 0
+        for n in lens:
+            m, c = n - n_window, min(c_max, n - n_window)
+            sc = pooled[:, H * t0:H * (t0 + n)].view(L, H, n)[..., :m]
+            got = idx[:, H * keep0:H * (keep0 + c + n_window)].view(L, H, c + n_window).long()
+            assert (got.diff(dim=-1) > 0).all() and (got[..., 0] >= 0).all()
+            assert torch.equal(got[..., c:], torch.arange(m, n, device="cuda").expand(L, H, n_window))
+            last = sc.topk(c, dim=-1).values[..., -1:]
+            kept = torch.zeros(L, H, m, dtype=torch.bool, device="cuda").scatter_(-1, got[..., :c], True)
+            assert not (kept & (sc < last * (1 - TIE))).any() and not (~kept & (sc > last * (1 + TIE))).any(), n
+            rows = k[:, t0:t0 + n].permute(0, 2, 1, 3).gather(2, got[..., None].expand(-1, -1, -1, d))
+            out = k_out[:, H * keep0:H * (keep0 + c + n_window)].view(L, H, c + n_window, d)
+            assert torch.equal(rows.view(torch.int16), out.view(torch.int16))
+            t0 += n
+            keep0 += c + n_window
+    return idx, pooled
+
+
+def tensors(lens, n_layers, heads=8, group=4, rows=128, d=128, dtype=torch.bfloat16, gain=2.0, planted=16, seed=3):
+    """Logits with a standard deviation of about `gain`, outlier channels, and keys aligned with query rows."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q = torch.empty(n_layers, len(lens), rows, heads * group, d, dtype=dtype, device="cuda")
+    k = torch.empty(n_layers, sum(lens), heads, d, dtype=dtype, device="cuda")
+    for layer in range(n_layers):
+        scale = torch.exp(r(heads, d) * 0.5)
+        scale /= scale.pow(4).mean(-1, keepdim=True).pow(0.25)
+        q[layer] = (r(len(lens), rows, heads * group, d) * scale.repeat_interleave(group, 0) * gain).to(dtype)
+        kl = r(sum(lens), heads, d) * scale
+        for x in torch.randint(0, sum(lens), (planted,), generator=g, device="cuda").tolist():
+            kl[x] = 2.5 * q[layer, 0, x % rows, ::group].float() / gain
+        k[layer] = kl.to(dtype)
+    return q, k
+
+
+@pytest.mark.parametrize("lens,n_layers,kw", [
+    ([24832 + 65], 9, {}),                                              # one chunk a sequence, packed pairs of blocks
+    ([24832 + 64], 9, {"reduce": "max"}),
+    ([70001], 3, {"pool_k": 1}),                                        # longest sample step, several chunks
+    ([9000, 30123, 700, 17999, 12289], 4, {"pool_k": 16}),              # short ones are all sample
+    ([13000, 50001], 12, {"rows": 37, "pool_k": 4}),                     # blocks shared by waves beside whole ones
+    ([40000], 9, {"rows": 67, "reduce": "max"}),                        # padded heads
+    ([33000], 12, {"heads": 4, "group": 7}),                            # two super-blocks
+    ([33000], 20, {"heads": 4, "group": 7, "rows": 45, "reduce": "max"}),
+    ([65537], 10, {"rows": 41}),                                        # one row block a wave
+    ([65537], 10, {"rows": 41, "reduce": "max"}),
+    ([30001], 8, {"dtype": torch.float16, "c_max": 100}),
+    ([30001], 8, {"c_max": 3700}),
+    ([30001], 8, {"gain": 0.2}),                                        # flat attention
+    ([30001], 8, {"gain": 12.0}),                                       # one key a row
+])
+def test_pruned_calls_keep_what_complete_scores_say(S, lens, n_layers, kw):
+    kw = dict(kw)
+    shape = {x: kw.pop(x) for x in ("heads", "group", "rows", "dtype", "gain") if x in kw}
+    q, k = tensors(lens, n_layers, **shape)
+    check(S, q, k, lens, 32, kw.pop("c_max", 512), **kw)
+
+
+def test_rows_whose_sample_misleads_are_computed_whole(S):
+    """The best keys of one layer lie in the sample, so that its threshold is too high for the others."""
+    q, k = tensors([30001], 8, gain=1.0, planted=0)
+    k[3].view(-1, 8, 128)[:29952].view(-1, 128, 8, 128)[::8] *= 4
+    k[5].view(-1, 8, 128)[:29952].view(-1, 128, 8, 128)[::8] *= 1.5
+    check(S, q, k, [30001], 32, 512)
+
+
+def test_heavy_keys_outside_the_sample(S):
+    """Scores 400 binary orders above a row's reference overflow the sums of their segment, in many segments of one chunk."""
+    q, k = tensors([30001], 8, gain=1.0, planted=0)
+    for i, x in enumerate(range(200, 29000, 700)):
+        k[2, x] = 40.0 * q[2, 0, i % 128, ::4]
+    k[4, 777] = 40.0 * q[4, 0, 5, ::4]
+    check(S, q, k, [30001], 32, 512)
+
+
+def test_all_scores_alike(S):
+    q, k = tensors([30001], 8)
+    q.zero_()
+    idx, _ = check(S, q, k, [30001], 32, 512)
+    want = torch.cat([torch.arange(512), torch.arange(29969, 30001)]).to(idx)
+    assert torch.equal(idx, want.expand(8, 8, -1).reshape(8, -1))
+
+
+def test_numbers_that_are_none(S):
+    """Scores of heads with such numbers need not be numbers; the other heads' are what they are without them."""
+    q, k = tensors([30001], 8)
+    clean, _ = check(S, q, k, [30001], 32, 512)
+    k[1, 5000, 2] = float("nan")
+    k[3, 7000, 4, 5] = float("inf")
+    p = params(S, q, k, [30001], 32, 512)
+    idx = torch.empty_like(clean)
+    k_out = torch.empty(8, idx.shape[1], 128, dtype=k.dtype, device="cuda")
+    S.speckv_compress(p, q, k, None, idx, k_out, None, parity.alloc_ws(S, p))
+    same = (idx.view(64, -1) == clean.view(64, -1)).all(-1)
+    assert same[[i for i in range(64) if i not in (10, 28)]].all()
+
+
+def test_a_workspace_without_room_for_it_is_enough(S):
+    q, k = tensors([24897], 9)
+    avg = params(S, q, k, [24897], 32, 512, pool="avg")
+    check(S, q, k, [24897], 32, 512, ws=torch.empty(S.workspace_bytes(avg), dtype=torch.uint8, device="cuda"))
+
+
+def test_captured_and_replayed_on_other_inputs(S):
+    q, k = tensors([24897], 9)
+    p = params(S, q, k, [24897], 32, 512)
+    ws = parity.alloc_ws(S, p)
+    idx = torch.empty(9, 8 * S.total_keep(p), dtype=torch.int32, device="cuda")
+    k_out = torch.empty(9, idx.shape[1], 128, dtype=k.dtype, device="cuda")
+    S.speckv_compress(p, q, k, None, idx, k_out, None, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        S.speckv_compress(p, q, k, None, idx, k_out, None, ws)
+    for seed in (4, 5, 6):
+        q2, k2 = tensors([24897], 9, seed=seed, gain=float(seed - 3))
+        q.copy_(q2), k.copy_(k2)
+        graph.replay()
+        got = idx.clone()
+        S.speckv_compress(p, q, k, None, idx, k_out, None, ws)
+        assert torch.equal(got, idx)
