@@ -37,6 +37,42 @@ __device__ __forceinline__ RowAt row_at(const Dims &d, const SeqTab &t, int row)
 
 struct Steps { int32_t log[kMaxSeqs]; };
 
+// First references of the rows.  What the sample and the masked tail add up to, S + T, is a lower bound on a row's normaliser,
+// but of a row that attends to many keys alike only the sample's share, and the bounds on scores are larger by as much.  The rest of
+// such a row is expected from its sample, (ratio - 1) S with ratio = keys / keys in the sample, less four standard deviations,
+// ratio sqrt(sum of squared terms): nothing is left of it where a few keys make up the row.  A reference that turns out above its
+// normaliser makes the bounds too small by as much, which prune_threshold_kernel allows for.
+// Keys listed of 32K with logits of standard deviation 1, a sample of 1/8: 84 % with S + T, 18 % with this; 2: 25 and 6 %; 3 to 8: level.
+constexpr float kSampleDeviations = 4.f;
+constexpr int kRefThreads = 256;
+__global__ __launch_bounds__(kRefThreads) void prune_reference_kernel(PruneArgs A, int tile_keys) {
+  const Dims &d = A.d;
+  const int RSB = A.g.RSB, s = blockIdx.y;
+  const int unit_row = blockIdx.x * kRefThreads + threadIdx.x, unit = unit_row / RSB, r = unit_row % RSB;
+  if (unit >= d.L * d.Hkv * A.g.RS) return;
+  const int first = A.t.cc[s], n = A.t.cc[s + 1] - first;
+  const float2 *pairs = A.part + (int64_t)unit * A.g.n_chunks * RSB + r;
+  const float *squares = A.squares + (int64_t)unit * A.g.n_fast_chunks * RSB + r;
+  const float2 tail = pairs[(int64_t)(A.g.n_fast_chunks + s) * RSB];
+  float top = tail.x, sum = 0.f, square = 0.f;             // of the sample
+  for (int e = 0; e < n; ++e) {
+    const float2 p = pairs[(int64_t)(first + e) * RSB];
+    const float m = fmaxf(top, p.x), f1 = __builtin_amdgcn_exp2f(top - m), f2 = __builtin_amdgcn_exp2f(p.x - m);
+    sum = sum * f1 + p.y * f2;
+    square = square * f1 * f1 + squares[(int64_t)(first + e) * RSB] * f2 * f2;
+    top = m;
+  }
+  const float seen = sum + tail.y * __builtin_amdgcn_exp2f(tail.x - top);
+  const int step = prune_step(A.chunk_of[s]), tiles = A.t.tail0[s] / tile_keys, sampled = (tiles + (1 << step) - 1) >> step;
+  const float ratio = sampled > 0 ? (float)tiles / (float)sampled : 1.f;
+  const float rest = (ratio - 1.f) * sum - kSampleDeviations * ratio * sqrtf(square);
+  const float all = seen + (rest > 0.f ? rest : 0.f);
+  const int rs = unit % A.g.RS, lh = unit / A.g.RS;
+  const int64_t at = ((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r;
+  A.lse[at] = top + log2f(all);
+  A.row_extra[at] = seen / all;
+}
+
 constexpr int kThrThreads = 1024, kThrEach = 8;
 
 // A row's threshold: the lower end of the largest first digit that enough of the sample's pooled scores reach.  Neighbouring
@@ -44,12 +80,14 @@ constexpr int kThrThreads = 1024, kThrEach = 8;
 // deviations more are asked for, since a row that falls short is computed whole (launch_prune_repeat).
 // Bound: the latency of two or three rounds of loads; one workgroup per row.
 __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes,
-                                                                      const float *__restrict__ planes, PruneRow *__restrict__ rows,
-                                                                      int32_t *__restrict__ n_items) {
+                                                                      const float *__restrict__ planes,
+                                                                      const float *__restrict__ row_extra, int group_rows,
+                                                                      PruneRow *__restrict__ rows, int32_t *__restrict__ n_items) {
   __shared__ float score[kThrThreads * kThrEach];
   __shared__ uint32_t hist[2048];
   __shared__ uint32_t wave_tot[kThrThreads / 64];
   __shared__ int digit;
+  __shared__ float excess[kThrThreads / 64];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   if (row == 0 && tid < 2) n_items[tid] = 0;
   const RowAt r = row_at(d, t, row);
@@ -88,6 +126,12 @@ __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, Se
     }
   }
   __syncthreads();
+  // how far the largest reference of the group's rows is above its normaliser
+  float over = 0.f;
+  for (int x = tid; x < group_rows; x += kThrThreads)
+    over = fmaxf(over, row_extra[(((int64_t)r.layer * d.Hkv + r.g) * d.S + r.s) * group_rows + x]);
+  for (int o = 32; o > 0; o /= 2) over = fmaxf(over, __shfl_xor(over, o, 64));
+  if (lane == 0) excess[tid >> 6] = over;
   const float expected = (float)d.c_max * (float)n / (float)r.m;
   const uint32_t wanted = (uint32_t)ceilf(expected + 3.f * sqrtf(expected * (float)d.pool_k));
   // numbers of scores from digit b on, digits in descending order: thread i has digits 2047 - 2 i and 2046 - 2 i
@@ -108,9 +152,11 @@ __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, Se
   int open;
   const uint32_t key = key_prefix_of((uint32_t)digit, &open);
   const float threshold = key >= 0x80000000u ? __uint_as_float(key ^ 0x80000000u) : 0.f;
+  for (int w = 0; w < kThrThreads / 64; ++w) over = fmaxf(over, excess[w]);
   // (written so that a threshold that is not a number lists every key)
-  if (threshold < kPruneFloor) rows[row] = {-1.f, 0, 0, 0};
-  else rows[row] = {threshold * (1.f - kPruneSlack) * __builtin_exp2f(-kPruneShift), digit, 0, 0};
+  const float bound = threshold * __builtin_exp2f(-over);
+  if (bound < kPruneFloor) rows[row] = {-1.f, 0, 0, 0};
+  else rows[row] = {bound * (1.f - kPruneSlack) * __builtin_exp2f(-kPruneShift), digit, 0, 0};
 }
 
 constexpr int kListThreads = 512, kListEach = 8, kListKeys = kListThreads * kListEach;
@@ -218,17 +264,23 @@ __global__ __launch_bounds__(kListThreads) void prune_check_kernel(Dims d, SeqTa
 
 Steps steps_of(const Plan &pl) {
   Steps s;
-  std::memcpy(s.log, pl.step_log, sizeof(s.log));
+  for (int i = 0; i < pl.d.S; ++i) s.log[i] = prune_step(pl.chunk_of[i]);
   return s;
 }
 int tile_log_of(const Plan &pl) { return __builtin_ctz((unsigned)prune_tile_keys(pl)); }
 
 }  // namespace
 
-hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, PruneRow *rows, int32_t *n_items, hipStream_t st) {
+hipError_t launch_prune_references(const PruneArgs &A, int tile_keys, hipStream_t st) {
+  const int rows = A.d.L * A.d.Hkv * A.g.RS * A.g.RSB;
+  hipLaunchKernelGGL(prune_reference_kernel, dim3((rows + kRefThreads - 1) / kRefThreads, A.d.S), dim3(kRefThreads), 0, st, A, tile_keys);
+  return hipGetLastError();
+}
+
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st) {
   const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
   hipLaunchKernelGGL(prune_threshold_kernel, dim3(n_rows), dim3(kThrThreads), 0, st, pl.d, pl.t, steps_of(pl), tile_log_of(pl), pl.g.RS,
-                     planes, rows, n_items);
+                     planes, row_extra, pl.g.RS * pl.g.RSB, rows, n_items);
   return hipGetLastError();
 }
 
@@ -236,7 +288,7 @@ hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows
                              hipStream_t st) {
   int most = 0;
   for (int s = 0; s < pl.d.S; ++s)
-    if (pl.step_log[s] != 0) most = std::max(most, pl.t.tail0[s]);
+    if (prune_step(pl.chunk_of[s]) != 0) most = std::max(most, pl.t.tail0[s]);
   const int parts = (most + kListKeys - 1) / kListKeys;
   const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
   hipLaunchKernelGGL(prune_list_kernel, dim3(n_rows * (unsigned)parts), dim3(kListThreads), 0, st, pl.d, pl.t, steps_of(pl),

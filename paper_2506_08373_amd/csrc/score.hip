@@ -23,9 +23,9 @@ constexpr int kMergeRows = 64;
 // workgroups' reads (the same pairs again for every chunk) outgrow the launch.
 constexpr int kMergeInSweep = 40;
 
-// others: a pruned call, whose chunks have a second pair each (score_prune.hip).
+// row_extra: of a pruned call, whose chunks have a second pair each and whose first references stand in A.lse (score_prune.hip).
 template <int SLICES>
-__global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreArgs A, bool others) {
+__global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreArgs A, float *row_extra) {
   clear_scratch(A, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
                 (int64_t)gridDim.x * gridDim.y * blockDim.x);
   __shared__ float2 partial[SLICES][kMergeRows];
@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreA
   const int s = blockIdx.y;
   const int rs = unit % A.g.RS;
   const int lh = unit / A.g.RS;                       // layer * Hkv + head
-  const int n_first = A.t.cc[s + 1] - A.t.cc[s] + 1, n_entries = others ? 2 * n_first - 1 : n_first;
+  const int n_first = A.t.cc[s + 1] - A.t.cc[s] + 1, n_entries = row_extra != nullptr ? 2 * n_first - 1 : n_first;
   auto slot = [&](int e) {
     return e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1 + (e < n_first ? 0 : A.g.n_fast_chunks + d.S - n_first + 1);
   };
@@ -68,7 +68,13 @@ __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreA
     for (int u = 1; u < SLICES; ++u) in[u - 1] = partial[u][threadIdx.x];
     merge_pairs(top, sum, in);
   }
-  A.lse[((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r] = top + log2f(sum);
+  const int64_t at = ((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r;
+  const float lse = top + log2f(sum);
+  if (row_extra != nullptr) {
+    int hh, i;
+    row_extra[at] = decode_row(d, A.g, rs, r, &hh, &i) ? A.lse[at] - lse : -INFINITY;
+  }
+  A.lse[at] = lse;
 }
 
 // Converts caller-supplied natural-log normalisers [L][S][R][Hq] into the padded log2 layout
@@ -121,10 +127,10 @@ bool score_uses_qs(const Plan &pl, int pass) {
   return qs_supported(A, pass);
 }
 
-hipError_t launch_lse_combine(const ScoreArgs &A, bool others, hipStream_t st) {
+hipError_t launch_lse_combine(const ScoreArgs &A, float *row_extra, hipStream_t st) {
   const dim3 blocks(A.d.L * A.d.Hkv * A.g.RS * (A.g.RSB / kMergeRows), A.d.S);
-  if (merge_slices(A.g.MB) == 1) hipLaunchKernelGGL(lse_combine_kernel<1>, blocks, dim3(kMergeRows), 0, st, A, others);
-  else hipLaunchKernelGGL(lse_combine_kernel<2>, blocks, dim3(kMergeRows * 2), 0, st, A, others);
+  if (merge_slices(A.g.MB) == 1) hipLaunchKernelGGL(lse_combine_kernel<1>, blocks, dim3(kMergeRows), 0, st, A, row_extra);
+  else hipLaunchKernelGGL(lse_combine_kernel<2>, blocks, dim3(kMergeRows * 2), 0, st, A, row_extra);
   return hipGetLastError();
 }
 
@@ -153,7 +159,7 @@ hipError_t launch_score(const Plan &pl, const void *q, const void *k, float2 *pa
   if (A.norm_from != kNormMerged) {
     // nothing: the column sweep makes its normalisers
   } else if (A.lse_in == nullptr) {
-    e = launch_lse_combine(A, false, st);
+    e = launch_lse_combine(A, nullptr, st);
     if (e != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(lse_import_kernel, dim3(A.d.L * A.d.Hkv * A.g.RS, A.d.S), dim3(256), 0, st, A);

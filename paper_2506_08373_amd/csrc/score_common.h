@@ -33,10 +33,12 @@ constexpr int kAllKeys = 0, kSampleKeys = 1, kOtherKeys = 2, kListedKeys = 3;
 
 // Argument block of a pruned call's sweeps.
 struct PruneArgs : ScoreArgs {
-  int32_t step_log[kMaxSeqs];   // 0: every key of the sequence is in the sample
+  int32_t chunk_of[kMaxSeqs];   // keys per chunk of the sequence + step_log (prune_step); step_log 0: every key is in the sample
   int32_t order[kMaxSeqs];      // the sequences, those with the longest chunks first
   int32_t item_keys;
-  int32_t whole_chunk;          // keys per chunk of a sequence that is all sample
+  float *squares;               // [unit][chunk][RSB]: sums of the squared terms of the samples' pairs
+  float *row_extra;             // laid out like lse: what a row's sample and tail are of its first reference, later log2(first reference /
+                                // normaliser)
   const int32_t *list;          // [layer][Hkv*T], laid out like the scores: a row's listed keys
   const PruneRow *rows;
   const int2 *items;            // (row, place): up to item_keys listed keys of the row from this place on
@@ -68,7 +70,7 @@ __device__ __forceinline__ PruneChunk prune_chunk(const PruneArgs &A, int bid) {
     s = A.order[++i];
   }
   c.s = s;
-  const int kc = A.step_log[c.s] != 0 ? A.g.KC : A.whole_chunk;
+  const int kc = A.chunk_of[c.s] - prune_step(A.chunk_of[c.s]);
   c.chunk = A.t.cc[c.s] + rank;
   c.key_begin = rank * kc;
   c.key_end = c.key_begin + kc < A.t.tail0[c.s] ? c.key_begin + kc : A.t.tail0[c.s];
@@ -132,7 +134,8 @@ constexpr float kAnchorLimit = 8.507059e37f;
 // a bound as long as what underflows in it does not matter beside the threshold (kPruneFloor).
 // The references are multiples of 1 / kPruneGrain and grow by such, so that they are exact.
 constexpr float kPruneShift = 76.f, kPruneGrain = 8.f;
-constexpr int kPruneSegment = 16;
+// Segments that wavefronts leave out are listed as kFailWords says, but with the row blocks from bit kFailBlocks on.
+constexpr int kPruneSegment = 8, kFailBlocks = 28;
 
 
 // x + (x of the lane 32 away), in every lane, without going through LDS (v_permlane32_swap).
@@ -198,8 +201,10 @@ struct Tile {
 // The two sweeps over all chunks and masked tails of a call (score_rows.hip, score_cols.hip).
 hipError_t launch_row_statistics_sweep(const ScoreArgs &A, hipStream_t st);
 hipError_t launch_column_sweep(const ScoreArgs &A, hipStream_t st);
-// Merges the partial pairs of every row into A.lse; others: also those of a pruned call's other keys (score.hip).
-hipError_t launch_lse_combine(const ScoreArgs &A, bool others, hipStream_t st);
+// Merges the partial pairs of every row into A.lse; row_extra: not null in a pruned call, whose other keys have pairs, too (score.hip).
+hipError_t launch_lse_combine(const ScoreArgs &A, float *row_extra, hipStream_t st);
+// First references of a pruned call, into A.lse and A.row_extra (prune.hip).
+hipError_t launch_prune_references(const PruneArgs &A, int tile_keys, hipStream_t st);
 bool qs_supported(const ScoreArgs &A, int pass);
 hipError_t launch_qs_sweep(const ScoreArgs &A, int pass, hipStream_t st);
 

@@ -4,8 +4,9 @@
 // A column sum of the row softmax needs every row's normaliser first, so two sweeps over all keys multiply every key with every row
 // twice (score_sweep.h).  A call that returns indices and rows, not scores, needs the exact scores of the best keys alone:
 //
-//   1  row statistics over a sample (every 2^step_log-th key tile) and the masked tails: a lower bound e on a row's normaliser
-//   2  one sweep over the other keys sums 2^(score - e) along rows, which completes the normalisers, and along columns: since e is
+//   1  row statistics over a sample (every 2^step_log-th key tile) and the masked tails, and from them a cautious estimate e of a row's
+//      normaliser (prune_reference_kernel)
+//   2  one sweep over the other keys sums 2^(score - e) along rows, which completes the normalisers, and along columns: as far as e is
 //      no larger than the normaliser, a column sum is an upper bound on the key's score.  e follows what a chunk has seen.
 //   3  column sums of the sample with the normalisers; from them a threshold that more than c_max pooled scores will reach
 //      (prune.hip), and the list of the other keys whose bound reaches it
@@ -15,13 +16,15 @@
 //
 // The indices are those of all scores, whatever the data; only the time depends on them.
 // One sweep instead of two is what there is to gain.  Sum of 32 layers x 128K keys, 4 heads x 128 rows, d = 128, us: the two sweeps
-// 4350 + 4400; here sample 310, sweep 4450 (a block's 16 more additions and the row sums cost it 8 %), sample's columns 330,
-// listed keys (4 %) 230, the rest 250.  Calls, all scores / pruned: that one 8650 / 5480, eight prompts of 4K to 64K, groups of
-// 7, 28 layers 16000 / 10400, 32 layers x 16K, maximum 1020 / 880, 8 layers x 32K 644 / 566; 3 layers x 32K 331 / 400.
+// 4350 + 4400; here sample 330, sweep 4500 (a block's 16 more additions and the row sums cost it 8 %), sample's columns 310,
+// listed keys (4 %) 250, the rest 200.  Calls, all scores / pruned: that one 8690 / 5560, eight prompts of 4K to 64K, groups of
+// 7, 28 layers 15990 / 10550, 32 layers x 16K, maximum 1010 / 870, 8 layers x 32K 644 / 550; d = 64: 31 layers x 31K 1511 / 1017, 32 layers x
+// 43K, 2 heads, flat attention 492 / 395.
 // Where nothing can be pruned (all scores alike, or a threshold under kPruneFloor) the listed sweep is a second whole one and the call a
 // fifth longer than without.
 #include <algorithm>
-#include <cmath>
+#include <utility>
+#include <vector>
 
 #include "score_sweep.h"
 
@@ -42,7 +45,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 // The segments that wavefronts of the sweep left out of their sums, with the online step; one workgroup per wavefront's list
 // (normally empty), whose eight wavefronts share a segment's keys and read them straight into fragments.  A segment is one chain
-// of latencies: 16 tiles by the sweep's own workgroup shape (one wavefront working) 60 us, here 8.
+// of latencies: 8 tiles by the sweep's own workgroup shape (one wavefront working) take 30 us.
 template <int DT, int D, int MB, int NW, int RED>
 __global__ __launch_bounds__(512) void prune_repair_kernel(PruneArgs A) {
   using OP = Operand<DT, D, MB>;
@@ -57,7 +60,7 @@ __global__ __launch_bounds__(512) void prune_repair_kernel(PruneArgs A) {
   const Dims &d = A.d;
   const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int rs = c.unit % A.g.RS, g = c.unit / A.g.RS % d.Hkv, layer = c.unit / (A.g.RS * d.Hkv);
-  const int step_log = A.step_log[c.s], tiles = (c.key_end - c.key_begin + KT - 1) / KT;
+  const int step_log = prune_step(A.chunk_of[c.s]), tiles = (c.key_end - c.key_begin + KT - 1) / KT;
   const int others = tiles - ((tiles + (1 << step_log) - 1) >> step_log);
   const float c2 = d.sm_scale * 1.4426950408889634f;
   int first;
@@ -79,7 +82,8 @@ __global__ __launch_bounds__(512) void prune_repair_kernel(PruneArgs A) {
 #pragma unroll
   for (int rb = 0; rb < MB; ++rb) { top[rb] = kNegBig; sum[rb] = 0.f; }
   for (int n = 0; n < count; ++n) {
-    const int seg = n < kFailListed ? listed[1 + n] : listed[1 + kFailListed] + (n - kFailListed);
+    const int entry = n < kFailListed ? listed[1 + n] : listed[1 + kFailListed] + (n - kFailListed);
+    const int seg = entry & ((1 << kFailBlocks) - 1), blocks = n < kFailListed ? entry >> kFailBlocks : (1 << MB) - 1;
     const int b1 = min(others, (seg + 1) * kPruneSegment) * (KT / 32);
     u32x4 next[NCS];
     auto request = [&](int b) {
@@ -98,6 +102,7 @@ __global__ __launch_bounds__(512) void prune_repair_kernel(PruneArgs A) {
       request(b + WAVES);
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb) {
+        if ((blocks >> rb & 1) == 0) continue;
         f32x16 x = {0};
 #pragma unroll
         for (int cs = 0; cs < NCS; ++cs) x = mma_chunk<DT>(kf[cs], qf[rb][cs], x);
@@ -207,97 +212,129 @@ struct Buffers {
     A.share = A.d.reduce_max == 0;
     A.chunk_blocks = (int)score_chunk_workgroups(A.d, A.g, A.g.n_fast_chunks);
     A.fail = reinterpret_cast<int32_t *>(A.part + (int64_t)A.d.L * A.d.Hkv * A.g.RS * A.g.n_chunks * A.g.RSB);
-    std::memcpy(A.step_log, pl.step_log, sizeof(A.step_log));
+    std::memcpy(A.chunk_of, pl.chunk_of, sizeof(A.chunk_of));
     std::memcpy(A.order, pl.order, sizeof(A.order));
-    A.whole_chunk = pl.whole_chunk;
     A.item_keys = pl.item_keys;
+    A.squares = reinterpret_cast<float *>(ws + pl.off_squares);
+    A.row_extra = reinterpret_cast<float *>(ws + pl.off_row_extra);
     A.list = list; A.rows = rows; A.items = items; A.n_items = n_items;
   }
 };
 
 }  // namespace
 
-// Keys per chunk, a multiple of the samples' longest period.  References grow with what a chunk has seen, so that longer chunks have
-// closer bounds and fewer keys to list: the longest that costs the sweep little in CUs left idle at its end.
-static int prune_chunk_keys(const Plan &pl, int64_t units) {
-  int step = 0;
-  int64_t longest = 0;
-  for (int s = 0; s < pl.d.S; ++s) {
-    step = std::max(step, (int)pl.step_log[s]);
-    if (pl.step_log[s] != 0) longest = std::max<int64_t>(longest, pl.t.tail0[s]);
-  }
-  const int64_t period = (int64_t)prune_tile_keys(pl) << step;
-  auto duration = [&](int64_t kc) {                     // key-times per CU
-    int64_t chunks = 0, full = 0, keys = 0, shortest = kc;
-    for (int s = 0; s < pl.d.S; ++s) {
-      if (pl.step_log[s] == 0) continue;
-      const int64_t n = pl.t.tail0[s], last = n % kc == 0 ? kc : n % kc;
-      chunks += (n + kc - 1) / kc;
-      full += n / kc + (n % kc >= kc / 4 * 3 ? 1 : 0);
-      keys += n;
-      shortest = std::min(shortest, last);
-    }
-    // whole rounds of (nearly) full chunks, the shorter ones behind them; no less than an even spread and half of the last one
-    const double n_wg = (double)(chunks * units), cost = 190., one = (double)std::min(kc, longest) + cost;
-    const double rounds = std::max(1., std::ceil((double)(full * units) / 256.)) * one;
-    if (n_wg <= 256.) return one;
-    return std::max(rounds, ((double)(keys * units) + n_wg * cost) / 256. + 0.5 * ((double)shortest + cost));
-  };
-  static const int parts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128};
-  auto cut = [&](int p) { return align_up((longest + p - 1) / p, period); };
-  double best = 1e30;
-  for (int p : parts) best = std::min(best, duration(cut(p)));
-  for (int p : parts)
-    if (duration(cut(p)) <= 1.03 * best) return (int)cut(p);
-  return (int)cut(1);
+// Chunks of a sequence of n unmasked keys when none is longer than kc: equal ones, of whole periods of the sample.
+struct Chunks { int count, keys; };
+static Chunks prune_chunks(const Plan &pl, int64_t n, int step, int64_t kc) {
+  if (n == 0) return {0, prune_tile_keys(pl)};
+  const int64_t count = (n + kc - 1) / kc, keys = align_up((n + count - 1) / count, (int64_t)prune_tile_keys(pl) << step);
+  return {(int)((n + keys - 1) / keys), (int)keys};
 }
 
-// Work below which the additional launches cost more than a sweep saves, in blocks of 32 rows x keys.  With all scores / pruned, d = 128:
-// 13M (3 layers of 32K) 331 / 400 us, 15M (2 layers of 64K) 290 / 337, 26M (32 layers of 8K) 646 / 568, 34M (8 layers of 32K) 644 / 566.
-constexpr int64_t kPruneMinWork = 24 << 20;
+// The most keys of a chunk.  References grow with what a chunk has seen, so that longer chunks have closer bounds and fewer keys to list: the
+// longest that costs the sweep little in CUs left idle at its end.
+static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) {
+  constexpr int kCUs = 256, kSimulated = 16;
+  constexpr double kCost = 190.;                        // of a workgroup, in keys
+  int64_t longest = 0;
+  for (int s = 0; s < pl.d.S; ++s)
+    if (step[s] != 0) longest = std::max<int64_t>(longest, pl.t.tail0[s]);
+  // The sweep's duration in key-times: the longest chunks first, each to the CU that is free first.  Beyond kSimulated sequences
+  // the chunks are many and of all lengths: an even spread and half a short one.
+  auto duration = [&](int64_t kc) {
+    std::vector<std::pair<double, int64_t>> todo;
+    double total = 0., shortest = 1e30;
+    for (int s = 0; s < pl.d.S; ++s) {
+      if (step[s] == 0) continue;
+      const Chunks c = prune_chunks(pl, pl.t.tail0[s], step[s], kc);
+      todo.push_back({std::min(c.keys, pl.t.tail0[s]) + kCost, c.count * units});
+      total += todo.back().first * (double)todo.back().second;
+      shortest = std::min(shortest, todo.back().first);
+    }
+    std::sort(todo.rbegin(), todo.rend());
+    if (todo.size() > kSimulated) return std::max(todo[0].first, total / kCUs + 0.5 * shortest);
+    std::vector<std::pair<double, int64_t>> free_at = {{0., kCUs}};         // CUs by the time they are free, ascending
+    for (auto [keys, n] : todo) {
+      while (n > 0) {
+        auto [at, cus] = free_at.front();
+        const int64_t k = std::min(cus, n);
+        n -= k;
+        if (k == cus) free_at.erase(free_at.begin());
+        else free_at.front().second -= k;
+        auto x = free_at.begin();
+        while (x != free_at.end() && x->first < at + keys) ++x;
+        if (x != free_at.end() && x->first == at + keys) x->second += k;
+        else free_at.insert(x, {at + keys, k});
+      }
+    }
+    return free_at.back().first;
+  };
+  static const int parts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128};
+  double best = 1e30, took[sizeof(parts) / sizeof(parts[0])];
+  for (size_t i = 0; i < sizeof(parts) / sizeof(parts[0]); ++i) best = std::min(best, took[i] = duration((longest + parts[i] - 1) / parts[i]));
+  size_t i = 0;
+  while (took[i] > 1.03 * best) ++i;
+  return (longest + parts[i] - 1) / parts[i];
+}
+
+// What pruning has to save of a whole sweep to pay for its additional launches, in blocks of 32 rows x keys.  All scores / pruned, us, d = 128:
+// 3.9M (3 layers of 32K) 331 / 385, 3M (31 layers of 7.6K, 1024 kept) 561 / 598, 10M (8 layers of 32K) 644 / 550, 6M (32 of 8K, 512 kept)
+// 646 / 568; d = 64: 6.3M (12 layers of 66K, 2 heads) 315 / 269, 2M (9 layers of 25K) 123 / 184.
+// Every further sequence makes the chunks shorter and the launches less even: 9M (2 layers of 7 prompts) 562 / 583, 6M (2 layers of 6, groups
+// of 7) 447 / 530.
+constexpr int64_t kPruneMinSaving = 6000000, kPruneMinPerSeq = 700000;
+// Of a sequence of m candidates, per cent of a whole sweep: the more of them are kept, the more have to be listed (2 to 8 % of the keys from
+// 32 c_max on, 10 % at 16, 20 to 35 % at 7 c_max).
+static int prune_saving(int64_t m, int64_t c_max) {
+  return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= 7 * c_max ? 12 : 0;
+}
 
 bool prune_plan(Plan *pl) {
   Dims &d = pl->d;
   ScoreGeom &g = pl->g;
-  if (d.elt != 2 || d.D != 128 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
+  if (d.elt != 2 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
       pl->hist0_words == 0 || d.c_max < 1)
     return false;
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
-  int64_t pruned = 0;
+  int64_t pruned = 0, saved = 0;
+  int step[kMaxSeqs];
   for (int s = 0; s < d.S; ++s) {
     const int64_t m = pl->t.cu[s + 1] - pl->t.cu[s] - d.w;
-    pl->step_log[s] = m < 7ll * d.c_max ? 0 : m < 16ll * d.c_max || m < 24000 ? 2 : m < 48ll * d.c_max || m < 60000 ? 3 : 4;
-    if (pl->step_log[s] != 0) pruned += pl->t.tail0[s];
+    const int saving = prune_saving(m, d.c_max);
+    step[s] = saving == 0 ? 0 : m < 16ll * d.c_max || m < 24000 ? 2 : m < 48ll * d.c_max || m < 60000 ? 3 : 4;
+    if (saving != 0) pruned += pl->t.tail0[s];
+    saved += (int64_t)pl->t.tail0[s] * saving / 100;
   }
-  if (pruned * d.L * d.Hkv * ((d.M + 31) / 32) < kPruneMinWork) return false;
+  if (saved * d.L * d.Hkv * ((d.M + 31) / 32) < kPruneMinSaving + kPruneMinPerSeq * (d.S - 1)) return false;
   // about a tenth of the keys is listed: one item per CU or more
   pl->item_keys = kPruneItemMax;
   while (pl->item_keys > kPruneItemMin && pl->item_keys * 2560ll > pruned * units) pl->item_keys /= 2;
-  const int kc = prune_chunk_keys(*pl, units);
-  pl->whole_chunk = std::min(kc, 4096);
-  int cc = 0, most = 0;
-  int length[kMaxSeqs];               // keys that a chunk of the sequence gives the longer one of its sweeps
+  const int64_t kc = prune_chunk_keys(*pl, step, units);
+  int cc = 0;
   for (int s = 0; s < d.S; ++s) {
-    const int step = pl->step_log[s], c = step != 0 ? kc : pl->whole_chunk, n = (pl->t.tail0[s] + c - 1) / c;
+    const Chunks c = prune_chunks(*pl, pl->t.tail0[s], step[s], step[s] != 0 ? kc : std::min<int64_t>(kc, 4096));
     pl->t.cc[s] = cc;
-    cc += n;
-    most = std::max(most, n);
-    length[s] = std::min(c, pl->t.tail0[s]);
+    cc += c.count;
+    pl->chunk_of[s] = c.keys + step[s];
     pl->order[s] = s;
   }
-  std::sort(pl->order, pl->order + d.S, [&](int a, int b) { return length[a] != length[b] ? length[a] > length[b] : a < b; });
+  // (a chunk that is all sample weighs less than one of as many keys: the sweep over the others has nothing to do for it)
+  std::sort(pl->order, pl->order + d.S, [&](int a, int b) {
+    return pl->chunk_of[a] != pl->chunk_of[b] ? pl->chunk_of[a] > pl->chunk_of[b] : a < b;
+  });
   pl->t.cc[d.S] = cc;
-  g.KC = kc;
   g.n_fast_chunks = cc;
   g.n_chunks = 2 * cc + d.S;
   size_t off = pl->total;
   auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
   pl->off_part = take((size_t)units * g.n_chunks * g.RSB * sizeof(float2) + (size_t)score_fail_words(d, g, cc) * sizeof(int32_t));
   const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
+  pl->off_squares = take((size_t)units * cc * g.RSB * sizeof(float));
+  pl->off_row_extra = take((size_t)units * d.S * g.RSB * sizeof(float));
   pl->off_prune_rows = take((size_t)rows * sizeof(PruneRow) + 2 * sizeof(int32_t));
   int64_t items = 0;
   for (int s = 0; s < d.S; ++s)
-    if (pl->step_log[s] != 0) items += (pl->t.tail0[s] + kPruneItemMin - 1) / kPruneItemMin;
+    if (step[s] != 0) items += (pl->t.tail0[s] + kPruneItemMin - 1) / kPruneItemMin;
   pl->off_prune_items = take((size_t)(items * d.L * d.Hkv) * sizeof(int2));
   pl->total_pruned = off;
   return true;
@@ -309,12 +346,12 @@ hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void 
   hipError_t e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   if ((e = launch(Sweep::SampleRows, b.A, st)) != hipSuccess) return e;
-  b.A.norm_from = kNormPairs;
+  if ((e = launch_prune_references(b.A, prune_tile_keys(pl), st)) != hipSuccess) return e;
   if ((e = launch(Sweep::Others, b.A, st)) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
   b.A.clear = clear;
   b.A.clear_words = clear != nullptr ? clear_words : 0;
-  if ((e = launch_lse_combine(b.A, true, st)) != hipSuccess) return e;
+  if ((e = launch_lse_combine(b.A, b.A.row_extra, st)) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;
   return hipSuccess;
 }
@@ -323,7 +360,7 @@ hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, vo
   Buffers b(pl, q, k, ws);
   hipError_t e;
   if ((e = launch(Sweep::SampleColumns, b.A, st)) != hipSuccess) return e;
-  if ((e = launch_prune_thresholds(pl, b.planes, b.rows, b.n_items, st)) != hipSuccess) return e;
+  if ((e = launch_prune_thresholds(pl, b.planes, b.A.row_extra, b.rows, b.n_items, st)) != hipSuccess) return e;
   if ((e = launch_prune_list(pl, b.planes, b.rows, b.list, b.items, b.n_items, st)) != hipSuccess) return e;
   return launch(Sweep::Listed, b.A, st);
 }

@@ -49,10 +49,23 @@ namespace {
 // (see do_tile): three tiles' worth is alive at a time, kept modulo four.
 constexpr int kCsumBuffers = 4;
 
+// (Out of its generic caller, in which an asm statement may not name its variable.)
+__device__ __forceinline__ void add_squares(float &q, float scale, float squares) {
+  q = fmaf(q * scale, scale, squares);
+  asm volatile("" : "+v"(q));
+}
+
 // Has the compiler compute x where this stands.
 __device__ __forceinline__ void stay_here(float (&x)[16]) {
 #pragma unroll
   for (int i = 0; i < 16; i += 4) asm volatile("" : "+v"(x[i]), "+v"(x[i + 1]), "+v"(x[i + 2]), "+v"(x[i + 3]));
+}
+
+// Row blocks (bit mask) of the rows whose lanes, as add_over_lanes has them, are set in `lanes`.
+template <int MB>
+__device__ __forceinline__ int row_blocks_of(uint64_t lanes) {
+  if (MB == 1) return lanes != 0 ? 1 : 0;
+  return ((lanes & 0x0000ffff0000ffffull) != 0 ? 1 : 0) | ((lanes & 0xffff0000ffff0000ull) != 0 ? 2 : 0);
 }
 
 // Sums 16 MB values per lane over the 32 lanes of its half; lane l gets the sum of value l % 16 of row block l / 16 (MB = 1: of
@@ -200,6 +213,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   static_assert(!REPAIR || (PASS == 1 && !MASKED && KEYS == kAllKeys), "only the row-statistics sweep is repaired");
   static_assert(KEYS == kAllKeys || (DT != kF32 && !MASKED), "pruned calls: 16-bit rows, unmasked keys");
   constexpr bool ROW_SUMS = PASS == 2 && KEYS == kOtherKeys;
+  constexpr bool SQUARES = PASS == 1 && KEYS == kSampleKeys;             // also sums of squared terms (prune_reference_kernel)
   static_assert(KEYS != kOtherKeys || !MAY_SHARE, "with the code for shared blocks the row sums do not fit the registers");
   constexpr int ELT = elt_bytes(DT);
   using OP = Operand<DT, D, MB>;
@@ -271,7 +285,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   const int m = n_s - d.w;
   const int chunk_tiles = (key_end - key_begin + KT - 1) / KT;
   int step_log = 0;                                       // the sample: every 2^step_log-th tile of a chunk
-  if constexpr (KEYS == kSampleKeys || KEYS == kOtherKeys) step_log = A.step_log[s];
+  if constexpr (KEYS == kSampleKeys || KEYS == kOtherKeys) step_log = prune_step(A.chunk_of[s]);
   const int sampled = (chunk_tiles + (1 << step_log) - 1) >> step_log;
   const int ntiles = KEYS == kSampleKeys ? sampled : KEYS == kOtherKeys ? chunk_tiles - sampled : chunk_tiles;
   // a tile's first key (place in the list)
@@ -310,11 +324,17 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   const char *kbase = A.k + ((int64_t)layer * d.kv_sl + (int64_t)A.t.cu[s] * d.kv_st + (int64_t)g * d.kv_sh) * ELT;
   const int64_t tokb = d.kv_st * ELT;
   const int st_row = (lane * 16) / ROWB, st_slot = ((lane * 16) % ROWB) / 16;
-  // unmasked sweep: the lane's byte offset inside a tile never changes, only the (uniform) base of the
-  // tile's segment moves, so the loads use a scalar base plus a 32-bit lane offset
+  // unmasked sweep: the lane's byte offset inside a tile never changes, only the (uniform) tile
+  // base moves, so the loads use a scalar base plus a 32-bit lane offset; where registers are short, one offset for all
+  // segments (d = 128, 4 layers x 60K, a caller's normalisers: 244.9 us with an offset a segment, 247.8 with one)
   static_assert(SPLIT || NW * RPS / TL::RPB % (TL::SWZ + 1) == 0, "a wave's segments of a tile are swizzled alike");
-  const uint32_t loff = (KEYS == kListedKeys ? 0u : (uint32_t)(wv * RPS + st_row) * (uint32_t)tokb) +
-                        (uint32_t)((st_slot ^ TL::swizzle(wv * RPS + st_row)) * 16);
+  constexpr int OFFSETS = KEYS == kAllKeys ? SEG_PER_WAVE : 1;
+  uint32_t loff[OFFSETS];
+#pragma unroll
+  for (int it = 0; it < OFFSETS; ++it) {
+    const int r_ = (it * NW + wv) * RPS + st_row;
+    loff[it] = (KEYS == kListedKeys ? 0u : (uint32_t)r_ * (uint32_t)tokb) + (uint32_t)((st_slot ^ TL::swizzle(r_)) * 16);
+  }
   // listed keys: the lane's keys of the next tile to be loaded, requested one tile ahead
   const int32_t *list = nullptr;
   int next_key[SEG_PER_WAVE];
@@ -341,9 +361,10 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
         /* rows past the end of the sequence re-read its last key; they are masked later */   \
         src_ = kbase + (int64_t)min(k0_ + r_, n_s - 1) * tokb + (st_slot ^ TL::swizzle(r_)) * 16; \
       } else if (KEYS == kListedKeys) {                                                       \
-        src_ = kbase + (int64_t)next_key[it] * tokb + loff;                                   \
+        src_ = kbase + (int64_t)next_key[it] * tokb + loff[0];                                \
       } else {                                                                                \
-        src_ = tbase_ + (int64_t)(it * NW * RPS) * tokb + loff;                               \
+        src_ = OFFSETS > 1 ? tbase_ + loff[it % OFFSETS]                                      \
+                           : tbase_ + (int64_t)(it * NW * RPS) * tokb + loff[0];              \
       }                                                                                       \
       __builtin_amdgcn_global_load_lds(                                                       \
           (const __attribute__((address_space(1))) void *)src_,                               \
@@ -423,8 +444,9 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
 
   // ---- per-pass row state
   float mrun[MB], lrun[MB];          // pass 1: lane = one query row per row block
+  float qrun[SQUARES ? MB : 1];
   // Pass 2 with row sums: what a wave knows of its rows between segments lies in LDS, [NW][MB][32] each: the row's negated
-  // reference, its sum, and the part of the sum that is in the first reference.  A lane keeps the row own_slot() for this:
+  // reference, its sum, and the sum over the sample and the tail.  A lane keeps the row own_slot() for this:
   // row l32 % 16, counted as in nlse, of row block l32 / 16 (MB = 1: lanes from 16 on repeat the others).
   float *own_ref = csum + (size_t)kCsumBuffers * NW * MB * KT, *own_sum = own_ref + RSB, *own_first = own_sum + RSB;
   auto own_slot = [&]() {
@@ -444,6 +466,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     for (int rb = 0; rb < MB; ++rb) {
       mrun[rb] = kNegBig;
       lrun[rb] = 0.f;
+      if constexpr (SQUARES) qrun[rb] = 0.f;
       if (MASKED) {
         int hh, io;
         (void)row_at(rb, l32, hh, io);
@@ -506,7 +529,9 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
       const int own = own_slot();
       own_ref[own] = norm[block_of((own >> 5) & (MB - 1)) * 32 + (own & 31)];
       own_sum[own] = 0.f;
-      own_first[own] = __builtin_amdgcn_exp2f(-kPruneShift);
+      const int own_row = block_of((own >> 5) & (MB - 1)) * 32 + (own & 31);
+      own_first[own] = __builtin_amdgcn_exp2f(-kPruneShift) *
+                       A.row_extra[(((int64_t)layer * d.Hkv + g) * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + own_row];
     }
     __syncthreads();
     // slots of skipped blocks must read as zero when the tile partials are merged
@@ -823,7 +848,8 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
 #pragma unroll
           for (int i = 0; i < 16; ++i) row_sum[rb][i] = 0.f;
       }
-      // The segment is over: its row sums, added up over the lanes, join the rows' sums, or it is left to the repair launch.
+      // The segment is over: its row sums, added up over the lanes, join the rows' sums.  A row block in which one overflowed is left
+      // to the repair launch, as is everything once the list is full.
       auto end_row_segment = [&](int segment) {
         if constexpr (ROW_SUMS) {
           const float t = add_over_lanes<MB>(row_sum);
@@ -831,14 +857,18 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
           for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
             for (int i = 0; i < 16; ++i) row_sum[rb][i] = 0.f;
-          if (__builtin_amdgcn_ballot_w64(!(t < kAnchorLimit)) != 0 || n_failed > kFailListed) {
+          const uint64_t over = __builtin_amdgcn_ballot_w64(!(t < kAnchorLimit));
+          if (over != 0 || n_failed > kFailListed) {           // seldom
+            const int blocks = row_blocks_of<MB>(over);
 #pragma unroll
             for (int i = 0; i <= kFailListed; ++i)
-              if (i == n_failed) listed[i] = segment;
+              if (i == n_failed) listed[i] = i < kFailListed ? segment | blocks << kFailBlocks : segment;
             ++n_failed;
-          } else {
+          }
+          if (n_failed <= kFailListed) {
             const int own = own_slot();
-            float sum = own_sum[own] + t, first = own_first[own];
+            const bool left_out = (row_blocks_of<MB>(over) >> (MB == 2 ? lane >> 4 & 1 : 0) & 1) != 0;
+            float sum = own_sum[own] + (left_out ? 0.f : t), first = own_first[own];
             // A bound is as close as the row's reference is to its normaliser: the reference follows what has been seen, in steps
             // that are exact (kPruneGrain).
             const float up = floorf((__builtin_amdgcn_logf(sum + first) + kPruneShift) * kPruneGrain) / kPruneGrain;
@@ -897,12 +927,17 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
           const float mnew = fmaxf(mrun[rb], tmax * c2);
           const float scale = __builtin_amdgcn_exp2f(mrun[rb] - mnew);
           const float nm = -mnew;
-          float sum = 0.f;
+          float sum = 0.f, squares = 0.f;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(x[i], c2, nm));
+          for (int i = 0; i < 16; ++i) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(x[i], c2, nm));
+            sum += p;
+            if (SQUARES) squares = fmaf(p, p, squares);
+          }
           lrun[rb] = fmaf(lrun[rb], scale, sum);
           mrun[rb] = mnew;
           asm volatile("" : "+v"(lrun[rb]), "+v"(mrun[rb]));
+          if constexpr (SQUARES) add_squares(qrun[rb], scale, squares);
         } else {
           if (rb == 0 || (RED == 1 && !merged)) colsum = 0.f;
           colsum = column_of(x, rb, colsum);
@@ -1165,23 +1200,33 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
       const float mo = __shfl_xor(mf, 32, 64), lo = __shfl_xor(lf, 32, 64);
       float mm = fmaxf(mf, mo);
       float ll = lf * __builtin_amdgcn_exp2f(mf - mm) + lo * __builtin_amdgcn_exp2f(mo - mm);
+      float qq = 0.f;                        // in units of the pair's reference, squared
+      if constexpr (SQUARES) {
+        const float unit_ = __builtin_amdgcn_exp2f(mrun[rb] - mm), mine_ = qrun[rb] * unit_ * unit_;
+        qq = mine_ + __shfl_xor(mine_, 32, 64);
+      }
       // a block that waves share: the first of them adds the others' pairs
       const bool in_share = per > 1 && rb == split.full / NW && wv >= share_w0 && wv < share_w0 + 4;
       if (per > 1 && rb == split.full / NW) {
         float2 *others = reinterpret_cast<float2 *>(csum);
+        float *others_qq = reinterpret_cast<float *>(others + 4 * 32);
         if (in_share && half == 0) others[(wv - share_w0) * 32 + l32] = make_float2(mm, ll);
+        if (SQUARES && in_share && half == 0) others_qq[(wv - share_w0) * 32 + l32] = qq;
         __syncthreads();
         if (in_share && phase == 0) {
           for (int u = 1; u < per; ++u) {
             const float2 v = others[(wv - share_w0 + u) * 32 + l32];
             const float m2 = fmaxf(mm, v.x);
-            ll = ll * __builtin_amdgcn_exp2f(mm - m2) + v.y * __builtin_amdgcn_exp2f(v.x - m2);
+            const float f1 = __builtin_amdgcn_exp2f(mm - m2), f2 = __builtin_amdgcn_exp2f(v.x - m2);
+            ll = ll * f1 + v.y * f2;
+            if (SQUARES) qq = qq * f1 * f1 + others_qq[(wv - share_w0 + u) * 32 + l32] * f2 * f2;
             mm = m2;
           }
         }
       }
       if (half == 0 && (!in_share || phase == 0)) {
         float2 *slot = &pp[block_of(rb) * 32 + l32];
+        if constexpr (SQUARES) A.squares[((int64_t)unit * A.g.n_fast_chunks + chunk) * RSB + block_of(rb) * 32 + l32] = qq;
         if (REPAIR) {                // add to what the first sweep (and earlier repairs) left there
           const float2 have = *slot;
           const float m2 = fmaxf(have.x, mm);

@@ -51,6 +51,7 @@ struct PlaneMerge {
 };
 
 // Merges the planes per key, writes raw (optional) and pooled for one row tile.
+template <bool PRUNED = false>
 __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge pm,
                                         float *__restrict__ raw, float *__restrict__ pooled,
                                         int n_s, int n_row, int m, int pool_k, int pool_avg, int j0,
@@ -140,13 +141,16 @@ __device__ inline void reduce_pool_tile(const float *__restrict__ in, PlaneMerge
       }
       if (first_digit != nullptr) {                         // selection's first digit
         const int digit = first_digit_of(ordered_key(best));
-        if (digit >= digit_from && digit < digit_to) atomicAdd(&first_digit[digit], 1u);
+        if (!PRUNED || (digit >= digit_from && digit < digit_to)) atomicAdd(&first_digit[digit], 1u);
       }
     }
     pooled[j] = best;
   }
 }
 
+// PRUNED: the scores of a pruned call (prune not null).  Only the ones from a row's digit on are certain.  They are counted at first,
+// the others by a second launch (repeat) over the rows of which every key has been computed.
+template <bool PRUNED>
 __global__ __launch_bounds__(kPoolThreads) void reduce_pool_kernel(
     Dims d, SeqTab t, PlaneMerge pm, const float *__restrict__ planes,
     float *__restrict__ raw, float *__restrict__ pooled, int groups_per_row, uint32_t *__restrict__ hist0,
@@ -161,10 +165,8 @@ __global__ __launch_bounds__(kPoolThreads) void reduce_pool_kernel(
   const int n_row = t.cu[s + 1] - t.cu[s];
   if (arrived != nullptr && j0 == 0 && threadIdx.x == 0) arrived[(int64_t)unit * kPartsWords] = 0u;    // for select_in_parts
   if (j0 >= n_row) return;
-  // Pruned scores: only the ones from the row's digit on are certain.  They are counted here, the others after every key
-  // of a row has been computed.
   int digit_from = 0, digit_to = 2048;
-  if (prune != nullptr) {
+  if (PRUNED) {
     if (repeat && prune[unit].failed == 0) return;
     (repeat ? digit_to : digit_from) = prune[unit].digit;
   }
@@ -175,10 +177,11 @@ __global__ __launch_bounds__(kPoolThreads) void reduce_pool_kernel(
   if (hist0 != nullptr)
     for (int b = threadIdx.x; b < 2048; b += kPoolThreads) first_digit[b] = 0;
   for (;;) {
-    reduce_pool_tile(planes + base, pm, raw ? raw + base : nullptr, pooled + base, n_s, n_row, n_s - d.w,
-                     d.pool_k, d.pool_avg, j0, tile, hist0 != nullptr ? first_digit : nullptr, digit_from, digit_to);
+    reduce_pool_tile<PRUNED>(planes + base, pm, raw ? raw + base : nullptr, pooled + base, n_s, n_row, n_s - d.w,
+                             d.pool_k, d.pool_avg, j0, tile, hist0 != nullptr ? first_digit : nullptr, digit_from, digit_to);
+    if (!PRUNED) break;                                    // a workgroup per tile
     j0 += groups_per_row * kPoolTile;
-    if (j0 >= n_row) break;                                // (as a rule at once: a workgroup per tile)
+    if (j0 >= n_row) break;
     __syncthreads();
   }
   if (hist0 != nullptr) {
@@ -1840,7 +1843,8 @@ hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, f
   const int tiles = repeat ? 32 : (max_n + kPoolTile - 1) / kPoolTile;
   const int64_t blocks = (int64_t)d.L * d.S * d.Hkv * tiles;
   const PlaneMerge pm = merge_of(pl);
-  hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)blocks), dim3(kPoolThreads), 0, st, d, pl.t,
+  const auto kernel = prune != nullptr ? reduce_pool_kernel<true> : reduce_pool_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kPoolThreads), 0, st, d, pl.t,
                      pm, planes, raw, pooled, tiles, hist0, arrived, prune, repeat);
   return hipGetLastError();
 }
@@ -1880,7 +1884,7 @@ hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t 
   PlaneMerge pm;
   pm.n_inner = 1; pm.n_outer = 1; pm.inner_max = 0; pm.outer_max = 0; pm.plane_stride = 0;
   const int tiles = ((int)d.T + kPoolTile - 1) / kPoolTile;
-  hipLaunchKernelGGL(reduce_pool_kernel, dim3((unsigned)tiles), dim3(kPoolThreads), 0, st, d, pl.t, pm, in, (float *)nullptr, out,
+  hipLaunchKernelGGL(reduce_pool_kernel<false>, dim3((unsigned)tiles), dim3(kPoolThreads), 0, st, d, pl.t, pm, in, (float *)nullptr, out,
                      tiles, hist0, arrived, (const PruneRow *)nullptr, false);
   return hipGetLastError();
 }

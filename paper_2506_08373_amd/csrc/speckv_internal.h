@@ -68,9 +68,9 @@ struct Plan {
   int32_t sel_parts, sel_part_len;
   size_t off_sel_hist, off_sel_state;
   // pruned scoring (score_prune.hip): sample step of every sequence, and scratch behind everything else
-  int32_t step_log[kMaxSeqs], order[kMaxSeqs];
-  int32_t whole_chunk, item_keys;
-  size_t off_prune_items, off_prune_rows, total_pruned;
+  int32_t chunk_of[kMaxSeqs], order[kMaxSeqs];     // see PruneArgs
+  int32_t item_keys;
+  size_t off_prune_items, off_prune_rows, off_squares, off_row_extra, total_pruned;
   int64_t prune_items;
   // first-digit histograms of the pooled rows (2048 counters per row), filled by the pooling kernel
   // of a fused call so that selection starts at the second read; hist0_words == 0: not used
@@ -213,6 +213,7 @@ struct PruneRow {
 };
 // An item of a listed sweep holds at most Plan::item_keys keys, and at least this many but for the last of a row.
 constexpr int kPruneItemMin = 512, kPruneItemMax = 2048;
+inline __host__ __device__ int prune_step(int32_t chunk_of) { return chunk_of & 7; }
 // Keys of a sample's tile: Operand::KT of the scoring kernels.
 inline int prune_tile_keys(const Plan &pl) { return pl.d.D == 64 && pl.g.MB == 2 ? 256 : 128; }
 // Turns the plan of a fused call into one of a pruned call where that is faster; false: it is not.
@@ -225,7 +226,7 @@ hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void 
 hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st);
 // After the pooling of these: column sums of all keys, and pooling, of the rows that failed.
 hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st);
-hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, PruneRow *rows, int32_t *n_items, hipStream_t st);
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st);
 hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
                              hipStream_t st);
 // hist0: the pooled scores' first digits.  Lists every key of the rows that failed.

@@ -87,13 +87,17 @@ def tensors(lens, n_layers, heads=8, group=4, rows=128, d=128, dtype=torch.bfloa
     ([65537], 10, {"rows": 41}),                                        # one row block a wave
     ([65537], 10, {"rows": 41, "reduce": "max"}),
     ([30001], 8, {"dtype": torch.float16, "c_max": 100}),
-    ([30001], 8, {"c_max": 3700}),
+    ([30001], 14, {"c_max": 3700}),
     ([30001], 8, {"gain": 0.2}),                                        # flat attention
     ([30001], 8, {"gain": 12.0}),                                       # one key a row
+    ([50001], 6, {"d": 64}),                                            # tiles of 256 keys
+    ([50001], 6, {"d": 64, "reduce": "max", "gain": 0.7}),
+    ([50001, 20000], 12, {"d": 64, "rows": 45, "gain": 1.0}),           # one row block a wave
+    ([66450], 12, {"d": 64, "heads": 2, "rows": 96, "gain": 0.7}),
 ])
 def test_pruned_calls_keep_what_complete_scores_say(S, lens, n_layers, kw):
     kw = dict(kw)
-    shape = {x: kw.pop(x) for x in ("heads", "group", "rows", "dtype", "gain") if x in kw}
+    shape = {x: kw.pop(x) for x in ("heads", "group", "rows", "d", "dtype", "gain") if x in kw}
     q, k = tensors(lens, n_layers, **shape)
     check(S, q, k, lens, 32, kw.pop("c_max", 512), **kw)
 
