@@ -368,7 +368,8 @@ size_t specpc_workspace_bytes(const speckv_params *p, int32_t top_k) {
   eff.reduce_op = SPECKV_REDUCE_SUM;
   eff.pool_op = SPECKV_POOL_MAX;
   if (build_plan(&eff, &pl, true, top_k) != SPECKV_OK) return 0;
-  return pl.total;
+  Plan pruned = pl;
+  return top_k > 0 && prune_plan(&pruned, top_k) ? pruned.total_pruned : pl.total;
 }
 
 static speckv_status score_impl(const speckv_params *p, const void *q, const void *k, const float *lse_in,
@@ -630,14 +631,25 @@ static speckv_status select_tokens_impl(const speckv_params *p, int32_t top_k, i
   float *planes = reinterpret_cast<float *>(ws + pl.off_planes);
   float *pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
   int32_t *sel = reinterpret_cast<int32_t *>(ws + pl.off_sel);
-  hipError_t e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part),
-                              reinterpret_cast<float *>(ws + pl.off_lse), planes, hs, ev);
-  if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
+  hipError_t e;
+  Plan pruned = pl;
+  const bool prune = top_k > 0 && prune_plan(&pruned, top_k) && workspace_bytes >= pruned.total_pruned;
+  if (prune) {
+    pl = pruned;
+    if ((e = launch_prune_rows(pl, q, k, workspace, hs, ev, nullptr, 0)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  } else if ((e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part),
+                               reinterpret_cast<float *>(ws + pl.off_lse), planes, hs, ev)) != hipSuccess) {
+    return SPECKV_ERR_RUNTIME;
+  }
   // a long row is ranked by several workgroups: its pooling is a pass of its own, which counts the first digit (scratch over
   // the partial pairs and the planes, which are read no more)
   uint32_t *scratch = reinterpret_cast<uint32_t *>(ws + pl.off_part);
-  const SelectParts sp = row_parts_of(m, count, pl.off_lse - pl.off_part);
-  if (sp.P > 1) {
+  const SelectParts sp = row_parts_of(m, count, (prune ? pl.off_squares : pl.off_lse) - pl.off_part);
+  if (prune) {                            // (what has to be computed shows in the counts, which any row has then)
+    if ((e = launch_prune_token_columns(pl, q, k, workspace, scratch, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+    if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
+    if ((e = launch_prune_token_repeat(pl, q, k, workspace, scratch, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  } else if (sp.P > 1) {
     float *merged = reinterpret_cast<float *>(ws + pl.off_pooled2);
     if ((e = launch_reduce_pool_all(pl, planes, merged, 1, scratch, 2048, hs)) != hipSuccess ||
         (e = launch_pool_row(pl, merged, pooled, pl.d.pool_k, scratch, scratch + 2048, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;

@@ -277,29 +277,44 @@ hipError_t launch_prune_references(const PruneArgs &A, int tile_keys, hipStream_
   return hipGetLastError();
 }
 
+// Output rows of a pruned call: of prompt tokens one, the merged planes.
+struct RowsOf {
+  Dims d;
+  unsigned n;
+  int planes, group_rows;
+  explicit RowsOf(const Plan &pl) : d(pl.d), planes(pl.g.RS), group_rows(pl.g.RS * pl.g.RSB) {
+    if (pl.prune_keep != 0) {
+      group_rows *= d.L * d.Hkv;
+      d.L = d.Hkv = planes = 1;
+      d.c_max = pl.prune_keep;
+    }
+    n = (unsigned)((int64_t)d.L * d.S * d.Hkv);
+  }
+};
+
 hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st) {
-  const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
-  hipLaunchKernelGGL(prune_threshold_kernel, dim3(n_rows), dim3(kThrThreads), 0, st, pl.d, pl.t, steps_of(pl), tile_log_of(pl), pl.g.RS,
-                     planes, row_extra, pl.g.RS * pl.g.RSB, rows, n_items);
+  const RowsOf r(pl);
+  hipLaunchKernelGGL(prune_threshold_kernel, dim3(r.n), dim3(kThrThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), r.planes,
+                     planes, row_extra, r.group_rows, rows, n_items);
   return hipGetLastError();
 }
 
 hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
                              hipStream_t st) {
+  const RowsOf r(pl);
   int most = 0;
   for (int s = 0; s < pl.d.S; ++s)
     if (prune_step(pl.chunk_of[s]) != 0) most = std::max(most, pl.t.tail0[s]);
   const int parts = (most + kListKeys - 1) / kListKeys;
-  const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
-  hipLaunchKernelGGL(prune_list_kernel, dim3(n_rows * (unsigned)parts), dim3(kListThreads), 0, st, pl.d, pl.t, steps_of(pl),
-                     tile_log_of(pl), pl.g.RS, parts, pl.item_keys, planes, rows, list, items, n_items);
+  hipLaunchKernelGGL(prune_list_kernel, dim3(r.n * (unsigned)parts), dim3(kListThreads), 0, st, r.d, pl.t, steps_of(pl),
+                     tile_log_of(pl), r.planes, parts, pl.item_keys, planes, rows, list, items, n_items);
   return hipGetLastError();
 }
 
 hipError_t launch_prune_check(const Plan &pl, const uint32_t *hist0, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
                               hipStream_t st) {
-  const unsigned n_rows = (unsigned)((int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
-  hipLaunchKernelGGL(prune_check_kernel, dim3(n_rows), dim3(kListThreads), 0, st, pl.d, pl.t, steps_of(pl), tile_log_of(pl), pl.item_keys, hist0,
+  const RowsOf r(pl);
+  hipLaunchKernelGGL(prune_check_kernel, dim3(r.n), dim3(kListThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), pl.item_keys, hist0,
                      rows, list, items, n_items);
   return hipGetLastError();
 }

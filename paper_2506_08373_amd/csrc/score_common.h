@@ -41,6 +41,7 @@ struct PruneArgs : ScoreArgs {
                                 // normaliser)
   const int32_t *list;          // [layer][Hkv*T], laid out like the scores: a row's listed keys
   const PruneRow *rows;
+  int32_t one_row;              // 1: one output row for all layers and heads (prompt tokens): every unit computes its list
   const int2 *items;            // (row, place): up to item_keys listed keys of the row from this place on
   const int32_t *n_items;
 };

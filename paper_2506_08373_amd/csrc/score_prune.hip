@@ -38,8 +38,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   else score_body<DT, D, MB, NW, 1, 0, true>(static_cast<const ScoreArgs &>(A), bid - A.chunk_blocks);
 }
 
+// (Four waves per SIMD, so that two workgroups share a CU, where the LDS has room for them.)
 template <int DT, int D, int MB, int NW, int RED>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void prune_sweep_kernel(PruneArgs A) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && MB == 1 ? 4 : 2))) void prune_sweep_kernel(PruneArgs A) {
   score_body<DT, D, MB, NW, 2, RED, false, false, false, kOtherKeys>(A, blockIdx.x);
 }
 
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(NW * 64) void prune_sample_columns_kernel(PruneArgs
 
 template <int DT, int D, int MB, int NW, int RED>
 __global__ __launch_bounds__(NW * 64) void prune_listed_kernel(PruneArgs A) {
-  const int n = *A.n_items * A.g.RS;
+  const int n = *A.n_items * A.g.RS * (A.one_row != 0 ? A.d.L * A.d.Hkv : 1);
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     score_body<DT, D, MB, NW, 2, RED, false, false, true, kListedKeys>(A, i);
     __syncthreads();
@@ -189,6 +190,8 @@ hipError_t launch(Sweep which, const PruneArgs &A, hipStream_t st) {
   return A.d.D == 128 ? launch_for_type<kF16, 128>(which, A, st) : launch_for_type<kF16, 64>(which, A, st);
 }
 
+int64_t prune_rows(const Plan &pl) { return pl.prune_keep != 0 ? 1 : (int64_t)pl.d.L * pl.d.S * pl.d.Hkv; }
+
 // The buffers of a pruned call.
 struct Buffers {
   PruneArgs A;
@@ -200,7 +203,7 @@ struct Buffers {
     char *ws = static_cast<char *>(workspace);
     planes = reinterpret_cast<float *>(ws + pl.off_planes);
     rows = reinterpret_cast<PruneRow *>(ws + pl.off_prune_rows);
-    n_items = reinterpret_cast<int32_t *>(rows + (int64_t)pl.d.L * pl.d.S * pl.d.Hkv);
+    n_items = reinterpret_cast<int32_t *>(rows + prune_rows(pl));
     items = reinterpret_cast<int2 *>(ws + pl.off_prune_items);
     list = reinterpret_cast<int32_t *>(ws + pl.off_pooled);      // read before the pooled scores are written
     A.d = pl.d; A.t = pl.t; A.g = pl.g;
@@ -215,6 +218,7 @@ struct Buffers {
     std::memcpy(A.chunk_of, pl.chunk_of, sizeof(A.chunk_of));
     std::memcpy(A.order, pl.order, sizeof(A.order));
     A.item_keys = pl.item_keys;
+    A.one_row = pl.prune_keep != 0;
     A.squares = reinterpret_cast<float *>(ws + pl.off_squares);
     A.row_extra = reinterpret_cast<float *>(ws + pl.off_row_extra);
     A.list = list; A.rows = rows; A.items = items; A.n_items = n_items;
@@ -289,19 +293,22 @@ static int prune_saving(int64_t m, int64_t c_max) {
   return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= 7 * c_max ? 12 : 0;
 }
 
-bool prune_plan(Plan *pl) {
+bool prune_plan(Plan *pl, int32_t keep) {
   Dims &d = pl->d;
   ScoreGeom &g = pl->g;
   if (d.elt != 2 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
-      pl->hist0_words == 0 || d.c_max < 1)
+      (keep == 0 && (pl->hist0_words == 0 || d.c_max < 1)))
     return false;
+  pl->prune_keep = keep;
+  const int64_t c_max = keep != 0 ? keep : d.c_max;
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
   int64_t pruned = 0, saved = 0;
   int step[kMaxSeqs];
   for (int s = 0; s < d.S; ++s) {
     const int64_t m = pl->t.cu[s + 1] - pl->t.cu[s] - d.w;
-    const int saving = prune_saving(m, d.c_max);
-    step[s] = saving == 0 ? 0 : m < 16ll * d.c_max || m < 24000 ? 2 : m < 48ll * d.c_max || m < 60000 ? 3 : 4;
+    const int saving = prune_saving(m, c_max);
+    // (the sum over all layers and heads has closer bounds: 7 % of 64K keys are listed with a sample of 1/4, 9 % with 1/8)
+    step[s] = saving == 0 ? 0 : m < 24000 || (keep == 0 && m < 16 * c_max) ? 2 : keep != 0 || m < 48 * c_max || m < 60000 ? 3 : 4;
     if (saving != 0) pruned += pl->t.tail0[s];
     saved += (int64_t)pl->t.tail0[s] * saving / 100;
   }
@@ -323,19 +330,20 @@ bool prune_plan(Plan *pl) {
     return pl->chunk_of[a] != pl->chunk_of[b] ? pl->chunk_of[a] > pl->chunk_of[b] : a < b;
   });
   pl->t.cc[d.S] = cc;
+  const int64_t most = 0x7fffffff / 8;                    // workgroups of a launch
+  if (score_chunk_workgroups(d, g, cc) > most || units * d.S > most || prune_rows(*pl) * (d.T / 4096 + 1) > most) return false;
   g.n_fast_chunks = cc;
   g.n_chunks = 2 * cc + d.S;
   size_t off = pl->total;
   auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
   pl->off_part = take((size_t)units * g.n_chunks * g.RSB * sizeof(float2) + (size_t)score_fail_words(d, g, cc) * sizeof(int32_t));
-  const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
   pl->off_squares = take((size_t)units * cc * g.RSB * sizeof(float));
   pl->off_row_extra = take((size_t)units * d.S * g.RSB * sizeof(float));
-  pl->off_prune_rows = take((size_t)rows * sizeof(PruneRow) + 2 * sizeof(int32_t));
+  pl->off_prune_rows = take((size_t)prune_rows(*pl) * sizeof(PruneRow) + 2 * sizeof(int32_t));
   int64_t items = 0;
   for (int s = 0; s < d.S; ++s)
     if (step[s] != 0) items += (pl->t.tail0[s] + kPruneItemMin - 1) / kPruneItemMin;
-  pl->off_prune_items = take((size_t)(items * d.L * d.Hkv) * sizeof(int2));
+  pl->off_prune_items = take((size_t)(items * (keep != 0 ? 1 : d.L * d.Hkv)) * sizeof(int2));
   pl->total_pruned = off;
   return true;
 }
@@ -373,6 +381,30 @@ hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, voi
   if ((e = launch(Sweep::Listed, b.A, st)) != hipSuccess) return e;
   float *pooled = reinterpret_cast<float *>(static_cast<char *>(ws) + pl.off_pooled);
   return launch_reduce_pool(pl, b.planes, nullptr, pooled, st, hist0, nullptr, b.rows, true);
+}
+
+hipError_t launch_prune_token_columns(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st) {
+  Buffers b(pl, q, k, ws);
+  float *merged = reinterpret_cast<float *>(static_cast<char *>(ws) + pl.off_pooled2);
+  hipError_t e;
+  if ((e = launch(Sweep::SampleColumns, b.A, st)) != hipSuccess) return e;
+  if ((e = launch_reduce_pool_all(pl, b.planes, merged, 1, nullptr, 0, st)) != hipSuccess) return e;
+  if ((e = launch_prune_thresholds(pl, merged, b.A.row_extra, b.rows, b.n_items, st)) != hipSuccess) return e;
+  if ((e = launch_prune_list(pl, merged, b.rows, b.list, b.items, b.n_items, st)) != hipSuccess) return e;
+  if ((e = launch(Sweep::Listed, b.A, st)) != hipSuccess) return e;
+  if ((e = launch_reduce_pool_all(pl, b.planes, merged, 1, scratch, 2048, st)) != hipSuccess) return e;
+  return launch_pool_row(pl, merged, reinterpret_cast<float *>(b.list), pl.d.pool_k, scratch, scratch + 2048, st, b.rows);
+}
+
+hipError_t launch_prune_token_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st) {
+  Buffers b(pl, q, k, ws);
+  float *merged = reinterpret_cast<float *>(static_cast<char *>(ws) + pl.off_pooled2);
+  b.A.n_items = b.n_items + 1;
+  hipError_t e;
+  if ((e = launch_prune_check(pl, scratch, b.rows, b.list, b.items, b.n_items + 1, st)) != hipSuccess) return e;
+  if ((e = launch(Sweep::Listed, b.A, st)) != hipSuccess) return e;
+  if ((e = launch_reduce_pool_all(pl, b.planes, merged, 1, nullptr, 0, st, b.rows)) != hipSuccess) return e;
+  return launch_pool_row(pl, merged, reinterpret_cast<float *>(b.list), pl.d.pool_k, scratch, nullptr, st, b.rows, true);
 }
 
 }  // namespace speckv

@@ -240,10 +240,11 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     s = bid / units;
     chunk = A.g.n_fast_chunks + s;
   } else if constexpr (KEYS == kListedKeys) {
-    const int2 item = A.items[bid / A.g.RS];
+    const int per_item = A.one_row != 0 ? d.L * d.Hkv * A.g.RS : A.g.RS;
+    const int2 item = A.items[bid / per_item];
     const int layer_seq = item.x / d.Hkv;
     s = layer_seq % d.S;
-    unit = (layer_seq / d.S * d.Hkv + item.x % d.Hkv) * A.g.RS + bid % A.g.RS;
+    unit = (layer_seq / d.S * d.Hkv + item.x % d.Hkv) * A.g.RS + bid % per_item;
     chunk = 0;
     key_begin = item.y;                                   // places in the row's list, not keys
     key_end = min(item.y + A.item_keys, A.rows[item.x].listed);
@@ -346,7 +347,8 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     }
   };
   if constexpr (KEYS == kListedKeys) {
-    list = A.list + (int64_t)layer * d.Hkv * d.T + (int64_t)d.Hkv * A.t.cu[s] + (int64_t)g * n_host;
+    list = A.list;
+    if (A.one_row == 0) list += (int64_t)layer * d.Hkv * d.T + (int64_t)d.Hkv * A.t.cu[s] + (int64_t)g * n_host;
     request_keys(0);
   }
 #define SPECKV_LOAD_TILE(tile_, buf_)                                                         \

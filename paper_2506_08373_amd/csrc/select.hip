@@ -201,7 +201,9 @@ constexpr int kAllTile = 64, kAllSlices = 4;
 
 __global__ __launch_bounds__(kAllTile * kAllSlices) void reduce_pool_all_kernel(
     int n_in, int n_window, int pool_k, int pool_avg, PlaneMerge pm, const float *__restrict__ planes,
-    float *__restrict__ raw, float *__restrict__ pooled, uint32_t *__restrict__ clear, int clear_words) {
+    float *__restrict__ raw, float *__restrict__ pooled, uint32_t *__restrict__ clear, int clear_words,
+    const PruneRow *__restrict__ if_failed) {
+  if (if_failed != nullptr && if_failed->failed == 0) return;
   const int id = blockIdx.x * (kAllTile * kAllSlices) + threadIdx.x;       // (at least as many threads as words: see launch)
   if (id < clear_words) clear[id] = 0u;
   __shared__ float part[kAllSlices][kAllTile + SPECKV_MAX_POOL_K + 1];
@@ -1850,7 +1852,7 @@ hipError_t launch_reduce_pool(const Plan &pl, const float *planes, float *raw, f
 }
 
 hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *pooled, int32_t pool_k, uint32_t *clear,
-                                  int32_t clear_words, hipStream_t st) {
+                                  int32_t clear_words, hipStream_t st, const PruneRow *if_failed) {
   const Dims &d = pl.d;
   const int n_in = (int)d.T;
   const int tiles = (n_in + kAllTile - 1) / kAllTile;
@@ -1863,18 +1865,18 @@ hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *po
   pm.outer_max = d.reduce_max && d.head_max;
   pm.plane_stride = n_in;
   hipLaunchKernelGGL(reduce_pool_all_kernel, dim3(tiles), dim3(kAllTile * kAllSlices), 0, st, n_in, d.w,
-                     pool_k, d.pool_avg, pm, planes, (float *)nullptr, pooled, clear, clear_words);
+                     pool_k, d.pool_avg, pm, planes, (float *)nullptr, pooled, clear, clear_words, if_failed);
   return hipGetLastError();
 }
 
 hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t pool_k, uint32_t *hist0, uint32_t *arrived,
-                           hipStream_t st) {
+                           hipStream_t st, const PruneRow *prune, bool repeat) {
   if (hist0 == nullptr) {
     const int n_in = (int)pl.d.T;
     PlaneMerge one;
     one.n_inner = 1; one.n_outer = 1; one.inner_max = 0; one.outer_max = 0; one.plane_stride = n_in;
     hipLaunchKernelGGL(reduce_pool_all_kernel, dim3((n_in + kAllTile - 1) / kAllTile), dim3(kAllTile * kAllSlices), 0, st, n_in,
-                       pl.d.w, pool_k, 0, one, in, (float *)nullptr, out, (uint32_t *)nullptr, 0);
+                       pl.d.w, pool_k, 0, one, in, (float *)nullptr, out, (uint32_t *)nullptr, 0, (const PruneRow *)nullptr);
     return hipGetLastError();
   }
   Dims d = pl.d;                      // the row as the only row of a call
@@ -1884,8 +1886,9 @@ hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t 
   PlaneMerge pm;
   pm.n_inner = 1; pm.n_outer = 1; pm.inner_max = 0; pm.outer_max = 0; pm.plane_stride = 0;
   const int tiles = ((int)d.T + kPoolTile - 1) / kPoolTile;
-  hipLaunchKernelGGL(reduce_pool_kernel<false>, dim3((unsigned)tiles), dim3(kPoolThreads), 0, st, d, pl.t, pm, in, (float *)nullptr, out,
-                     tiles, hist0, arrived, (const PruneRow *)nullptr, false);
+  const auto kernel = prune != nullptr ? reduce_pool_kernel<true> : reduce_pool_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(kPoolThreads), 0, st, d, pl.t, pm, in, (float *)nullptr, out,
+                     tiles, hist0, arrived, prune, repeat);
   return hipGetLastError();
 }
 

@@ -69,7 +69,7 @@ struct Plan {
   size_t off_sel_hist, off_sel_state;
   // pruned scoring (score_prune.hip): sample step of every sequence, and scratch behind everything else
   int32_t chunk_of[kMaxSeqs], order[kMaxSeqs];     // see PruneArgs
-  int32_t item_keys;
+  int32_t item_keys, prune_keep;                   // prune_keep: of prompt tokens, else 0
   size_t off_prune_items, off_prune_rows, off_squares, off_row_extra, total_pruned;
   int64_t prune_items;
   // first-digit histograms of the pooled rows (2048 counters per row), filled by the pooling kernel
@@ -217,13 +217,17 @@ inline __host__ __device__ int prune_step(int32_t chunk_of) { return chunk_of & 
 // Keys of a sample's tile: Operand::KT of the scoring kernels.
 inline int prune_tile_keys(const Plan &pl) { return pl.d.D == 64 && pl.g.MB == 2 ? 256 : 128; }
 // Turns the plan of a fused call into one of a pruned call where that is faster; false: it is not.
-bool prune_plan(Plan *pl);
+// keep: 0, or the tokens kept by a call for prompt tokens, whose layers and heads have one output row.
+bool prune_plan(Plan *pl, int32_t keep = 0);
 // Row statistics over the sample, then the sweep over the other keys (bounds into the planes), then the normalisers
 // (clear: see launch_score).
 hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, hipEvent_t *events,
                              uint32_t *clear, int64_t clear_words);
 // Column sums of the sample and the masked tails; thresholds and lists; column sums of the listed keys.
 hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st);
+// The same for prompt tokens, with the merged planes' pooling.  scratch: kRowScratchWords words, as launch_select_row_parts reads them.
+hipError_t launch_prune_token_columns(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st);
+hipError_t launch_prune_token_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st);
 // After the pooling of these: column sums of all keys, and pooling, of the rows that failed.
 hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st);
 hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st);
@@ -246,10 +250,10 @@ hipError_t launch_pool_select(const Plan &pl, const float *planes, int32_t *idx,
 // single output row merging every plane of a one-sequence call (prompt-token selection), pooled with pool_k (1: not at
 // all); leaves clear[0..clear_words) zeroed
 hipError_t launch_reduce_pool_all(const Plan &pl, const float *planes, float *pooled, int32_t pool_k, uint32_t *clear,
-                                  int32_t clear_words, hipStream_t st);
+                                  int32_t clear_words, hipStream_t st, const PruneRow *if_failed = nullptr);
 // max-pool (kernel pool_k, clipped to [0, n_in - n_window)) of one row of n_in scores; hist0, arrived: see launch_reduce_pool
 hipError_t launch_pool_row(const Plan &pl, const float *in, float *out, int32_t pool_k, uint32_t *hist0, uint32_t *arrived,
-                           hipStream_t st);
+                           hipStream_t st, const PruneRow *prune = nullptr, bool repeat = false);
 // hist0, when not null: the rows' first-digit histograms from launch_reduce_pool.  With them, and with list (a word per
 // score, laid out like pooled) and counters (kPartsWords per row: an arrival counter, which launch_reduce_pool zeroes, and from
 // word 64 on 2 * P counts; rows whose counters share a cache line would wait for each other's atomics), several workgroups

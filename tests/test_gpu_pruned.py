@@ -165,3 +165,39 @@ def test_captured_and_replayed_on_other_inputs(S):
         got = idx.clone()
         S.speckv_compress(p, q, k, None, idx, k_out, None, ws)
         assert torch.equal(got, idx)
+
+
+@pytest.mark.parametrize("n,n_layers,top_k,kw", [
+    (60000, 12, 2048, {"d": 64, "rows": 64, "gain": 3.0}),
+    (24000, 16, 1000, {"d": 64, "rows": 65, "gain": 2.0}),               # ranked by one workgroup; blocks shared by waves
+    (90001, 9, 8000, {"d": 128, "rows": 33, "dtype": torch.float16}),
+    (60000, 14, 8000, {"d": 64, "rows": 64, "gain": 0.02}),              # scores much alike: most keys listed
+])
+def test_prompt_tokens_are_those_of_complete_scores(S, n, n_layers, top_k, kw):
+    q, k = tensors([n], n_layers, planted=200, **kw)
+    p = params(S, q, k, [n], 32, 512)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda") * 3
+    got = []
+    most = S.specpc_workspace_bytes(p, top_k)
+    assert most > S.specpc_workspace_bytes(p, n) - 4 * (n - top_k)                # (nothing to prune where all are kept)
+    for size in (most, most - 256, most):                                         # (no room for pruning in the second)
+        out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros(1, dtype=torch.int32, device="cuda")]
+        S.specpc_select_tokens(p, top_k, 4, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        count = int(out[2])
+        got.append([count, out[0][:count].clone(), out[1][:count].clone()])
+    for other in got[1:]:
+        assert got[0][0] == other[0] and torch.equal(got[0][1], other[1]) and torch.equal(got[0][2], other[2])
+
+
+def test_prompt_tokens_whose_sample_misleads(S):
+    n = 60000
+    q, k = tensors([n], 12, d=64, rows=64, gain=1.0, planted=0)
+    k[:, :n // 256 * 256].view(12, -1, 256, 8, 64)[:, ::8] *= 3          # (every step of tiles of 128 keys has some of these)
+    p = params(S, q, k, [n], 32, 512)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+    got = []
+    for size in (S.specpc_workspace_bytes(p, 4000), S.specpc_workspace_bytes(p, 4000) - 256):
+        out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros(1, dtype=torch.int32, device="cuda")]
+        S.specpc_select_tokens(p, 4000, 0, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        got.append(out)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
