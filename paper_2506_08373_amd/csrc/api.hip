@@ -543,7 +543,8 @@ speckv_status speckv_compress_events(const speckv_params *p, const void *q, cons
 size_t speckv_ada_workspace_bytes(const speckv_params *p) {
   Plan pl;
   if (build_plan(p, &pl, false, 0) != SPECKV_OK || pl.d.Hkv > SPECKV_MAX_ADA_HEADS) return 0;
-  return pl.total_ada;
+  Plan pruned = pl;
+  return prune_plan(&pruned, 0, true) ? pruned.total_pruned : pl.total_ada;
 }
 
 static speckv_status ada_plan(const speckv_params *p, int32_t c_floor, Plan *pl) {
@@ -599,10 +600,21 @@ speckv_status speckv_compress_ada(const speckv_params *p, int32_t c_floor, const
   hipStream_t hs = static_cast<hipStream_t>(stream);
   float *planes = reinterpret_cast<float *>(ws + pl.off_planes);
   float *pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
-  hipError_t e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part),
-                              reinterpret_cast<float *>(ws + pl.off_lse), planes, hs);
-  if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
-  if ((e = launch_reduce_pool(pl, planes, nullptr, pooled, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  hipError_t e;
+  Plan pruned = pl;
+  if (prune_plan(&pruned, 0, true) && workspace_bytes >= pruned.total_pruned) {
+    pl = pruned;
+    uint32_t *hist0 = reinterpret_cast<uint32_t *>(ws + pl.off_hist0);
+    const PruneRow *rows = reinterpret_cast<const PruneRow *>(ws + pl.off_prune_rows);
+    if ((e = launch_prune_rows(pl, q, k, workspace, hs, nullptr, hist0, pl.hist0_words)) != hipSuccess ||
+        (e = launch_prune_columns(pl, q, k, workspace, hs, c_floor)) != hipSuccess ||
+        (e = launch_reduce_pool(pl, planes, nullptr, pooled, hs, hist0, nullptr, rows)) != hipSuccess ||
+        (e = launch_prune_repeat(pl, q, k, workspace, hist0, hs, c_floor)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  } else {
+    e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part), reinterpret_cast<float *>(ws + pl.off_lse), planes, hs);
+    if (e != hipSuccess) return SPECKV_ERR_RUNTIME;
+    if ((e = launch_reduce_pool(pl, planes, nullptr, pooled, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
+  }
   if ((e = launch_select_ada(pl, c_floor, pooled, idx, head_off, reinterpret_cast<uint32_t *>(ws + pl.off_ada_hist),
                              reinterpret_cast<uint32_t *>(ws + pl.off_ada_state), hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
   return from_hip(launch_compact_ada(pl, k, v, idx, head_off, k_out, v_out, hs));

@@ -35,6 +35,22 @@ __device__ __forceinline__ RowAt row_at(const Dims &d, const SeqTab &t, int row)
   return r;
 }
 
+// Of the sample's pooled scores, how many have to reach a threshold when `expected` of them are among the ones kept.
+__device__ __forceinline__ uint32_t wanted_of(float expected, int pool_k) {
+  return (uint32_t)ceilf(expected + 3.f * sqrtf(expected * (float)pool_k));
+}
+
+// A row whose scores from `digit` on are to be found; over: log2 of what its bounds may be too small by.
+__device__ __forceinline__ PruneRow row_from(int digit, float over) {
+  int open;
+  const uint32_t key = key_prefix_of((uint32_t)digit, &open);
+  const float threshold = key >= 0x80000000u ? __uint_as_float(key ^ 0x80000000u) : 0.f;
+  const float bound = threshold * __builtin_exp2f(-over);
+  // (written so that a threshold that is not a number lists every key)
+  if (bound < kPruneFloor) return {-1.f, 0, 0, 0, 0, {0, 0, 0}};
+  return {bound * (1.f - kPruneSlack) * __builtin_exp2f(-kPruneShift), digit, 0, 0, 0, {0, 0, 0}};
+}
+
 struct Steps { int32_t log[kMaxSeqs]; };
 
 // First references of the rows.  What the sample and the masked tail add up to, S + T, is a lower bound on a row's normaliser,
@@ -82,7 +98,8 @@ constexpr int kThrThreads = 1024, kThrEach = 8;
 __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes,
                                                                       const float *__restrict__ planes,
                                                                       const float *__restrict__ row_extra, int group_rows,
-                                                                      PruneRow *__restrict__ rows, int32_t *__restrict__ n_items) {
+                                                                      PruneRow *__restrict__ rows, int32_t *__restrict__ n_items,
+                                                                      int c_floor, uint32_t *__restrict__ counts) {
   __shared__ float score[kThrThreads * kThrEach];
   __shared__ uint32_t hist[2048];
   __shared__ uint32_t wave_tot[kThrThreads / 64];
@@ -93,7 +110,7 @@ __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, Se
   const RowAt r = row_at(d, t, row);
   const int step = steps.log[r.s], tile = 1 << tile_log;
   if (step == 0) {
-    if (tid == 0) rows[row] = {-1.f, 0, 0, 0};
+    if (tid == 0) rows[row] = {-1.f, 0, 0, 0, 0, {0, 0, 0}};
     return;
   }
   hist[tid] = hist[tid + kThrThreads] = 0;
@@ -132,8 +149,7 @@ __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, Se
     over = fmaxf(over, row_extra[(((int64_t)r.layer * d.Hkv + r.g) * d.S + r.s) * group_rows + x]);
   for (int o = 32; o > 0; o /= 2) over = fmaxf(over, __shfl_xor(over, o, 64));
   if (lane == 0) excess[tid >> 6] = over;
-  const float expected = (float)d.c_max * (float)n / (float)r.m;
-  const uint32_t wanted = (uint32_t)ceilf(expected + 3.f * sqrtf(expected * (float)d.pool_k));
+  const uint32_t wanted = wanted_of((float)(counts != nullptr ? min(c_floor, d.c_max) : d.c_max) * (float)n / (float)r.m, d.pool_k);
   // numbers of scores from digit b on, digits in descending order: thread i has digits 2047 - 2 i and 2046 - 2 i
   const uint32_t c0 = hist[2047 - 2 * tid], c1 = hist[2046 - 2 * tid];
   uint32_t sum = c0 + c1;
@@ -147,16 +163,43 @@ __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, Se
   const uint32_t upto1 = sum, upto0 = sum - c1, none = sum - c1 - c0;
   if (none < wanted && upto0 >= wanted) digit = 2047 - 2 * tid;
   else if (upto0 < wanted && upto1 >= wanted) digit = 2046 - 2 * tid;
+  if (counts != nullptr) {
+    counts[(int64_t)row * 2048 + 2047 - 2 * tid] = upto0;
+    counts[(int64_t)row * 2048 + 2046 - 2 * tid] = upto1;
+  }
   __syncthreads();
   if (tid != 0) return;
-  int open;
-  const uint32_t key = key_prefix_of((uint32_t)digit, &open);
-  const float threshold = key >= 0x80000000u ? __uint_as_float(key ^ 0x80000000u) : 0.f;
   for (int w = 0; w < kThrThreads / 64; ++w) over = fmaxf(over, excess[w]);
-  // (written so that a threshold that is not a number lists every key)
-  const float bound = threshold * __builtin_exp2f(-over);
-  if (bound < kPruneFloor) rows[row] = {-1.f, 0, 0, 0};
-  else rows[row] = {bound * (1.f - kPruneSlack) * __builtin_exp2f(-kPruneShift), digit, 0, 0};
+  if (counts != nullptr) rows[row] = {over, wanted == 0 ? 2047 : digit, 0, 0, 0, {0, 0, 0}};      // see prune_shared_threshold_kernel
+  else rows[row] = row_from(digit, over);
+}
+
+// Shared budget, one workgroup per (layer, sequence), after prune_threshold_kernel: the layer's digit is the largest that so many of the
+// samples' scores reach, beyond the heads' floors, as the layer keeps; a head's is no larger, and no larger than the one of its floor.
+// Whatever is kept then reaches its head's digit.
+__global__ __launch_bounds__(kThrThreads) void prune_shared_threshold_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int c_floor,
+                                                                             PruneRow *__restrict__ rows,
+                                                                             const uint32_t *__restrict__ counts) {
+  __shared__ int layer_digit;
+  const int ls = blockIdx.x, s = ls % d.S, tid = threadIdx.x;
+  const int step = steps.log[s];
+  if (step == 0) return;
+  const int n_tiles = ((t.tail0[s] >> tile_log) + (1 << step) - 1) >> step, m = t.cu[s + 1] - t.cu[s] - d.w;
+  const float share = (float)(n_tiles << tile_log) / (float)m;
+  const int kept = min(d.c_max, m), floor_ = min(c_floor, kept);
+  const float need = (float)wanted_of((float)d.Hkv * (float)(kept - floor_) * share, d.pool_k), in_floor = (float)floor_ * share;
+  if (tid == 0) layer_digit = 0;
+  __syncthreads();
+  for (int b = tid; b < 2048; b += kThrThreads) {
+    float beyond = 0.f;
+    for (int h = 0; h < d.Hkv; ++h) beyond += fmaxf((float)counts[((int64_t)ls * d.Hkv + h) * 2048 + b] - in_floor, 0.f);
+    if (beyond >= need) atomicMax(&layer_digit, b);
+  }
+  __syncthreads();
+  if (tid >= d.Hkv) return;
+  PruneRow *row = rows + (int64_t)ls * d.Hkv + tid;
+  *row = row_from(min(layer_digit, row->digit), row->bound);
+  row->layer_digit = layer_digit;
 }
 
 constexpr int kListThreads = 512, kListEach = 8, kListKeys = kListThreads * kListEach;
@@ -229,11 +272,11 @@ __global__ __launch_bounds__(kListThreads) void prune_list_kernel(Dims d, SeqTab
 static_assert(kListEach <= 32, "one bit per key");
 
 // The check that pruning found every score that matters: at least c_max pooled scores, counted by first digit, reach the row's
-// digit.  A row that falls short lists every key outside the sample, one workgroup per row.
+// digit (shared budget: see there).  A row that falls short lists every key outside the sample, one workgroup per row.
 __global__ __launch_bounds__(kListThreads) void prune_check_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int item_keys,
                                                                    const uint32_t *__restrict__ hist0, PruneRow *__restrict__ rows,
                                                                    int32_t *__restrict__ list, int2 *__restrict__ items,
-                                                                   int32_t *__restrict__ n_items) {
+                                                                   int32_t *__restrict__ n_items, int c_floor) {
   __shared__ int wave_tot[kListThreads / 64];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const RowAt r = row_at(d, t, row);
@@ -248,7 +291,27 @@ __global__ __launch_bounds__(kListThreads) void prune_check_kernel(Dims d, SeqTa
   __syncthreads();
   n = 0;
   for (int w = 0; w < kListThreads / 64; ++w) n += wave_tot[w];
-  if (n >= min(d.c_max, r.m)) return;
+  const int kept = min(d.c_max, r.m);
+  if (c_floor < 0) {
+    if (n >= kept) return;
+  } else {
+    // shared budget: the head's floor, and with the other heads what the layer keeps beyond the floors
+    const int floor_ = min(c_floor, kept), layer_digit = rows[row].layer_digit, row0 = row / d.Hkv * d.Hkv;
+    int beyond = 0;
+    for (int h = wave; h < d.Hkv; h += kListThreads / 64) {
+      const uint32_t *hist = hist0 + (int64_t)(row0 + h) * 2048;
+      int reach = 0;
+      for (int x = lane; x < 2048; x += 64) reach += x >= layer_digit ? (int)hist[x] : 0;
+      for (int o = 32; o > 0; o /= 2) reach += __shfl_xor(reach, o, 64);
+      beyond += max(reach - floor_, 0);
+    }
+    __syncthreads();
+    if (lane == 0) wave_tot[wave] = beyond;
+    __syncthreads();
+    beyond = 0;
+    for (int w = 0; w < kListThreads / 64; ++w) beyond += wave_tot[w];
+    if (n >= floor_ && beyond >= d.Hkv * (kept - floor_)) return;
+  }
   const int tiles = r.tail0 >> tile_log, other = tiles - ((tiles + (1 << step) - 1) >> step);
   if (tid == 0) {
     rows[row].failed = 1;
@@ -292,10 +355,14 @@ struct RowsOf {
   }
 };
 
-hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st) {
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st,
+                                   int32_t c_floor, uint32_t *counts) {
   const RowsOf r(pl);
   hipLaunchKernelGGL(prune_threshold_kernel, dim3(r.n), dim3(kThrThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), r.planes,
-                     planes, row_extra, r.group_rows, rows, n_items);
+                     planes, row_extra, r.group_rows, rows, n_items, c_floor, counts);
+  if (counts != nullptr)
+    hipLaunchKernelGGL(prune_shared_threshold_kernel, dim3((unsigned)(r.d.L * r.d.S)), dim3(kThrThreads), 0, st, r.d, pl.t, steps_of(pl),
+                       tile_log_of(pl), c_floor, rows, counts);
   return hipGetLastError();
 }
 
@@ -312,10 +379,10 @@ hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows
 }
 
 hipError_t launch_prune_check(const Plan &pl, const uint32_t *hist0, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
-                              hipStream_t st) {
+                              hipStream_t st, int32_t c_floor) {
   const RowsOf r(pl);
   hipLaunchKernelGGL(prune_check_kernel, dim3(r.n), dim3(kListThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), pl.item_keys, hist0,
-                     rows, list, items, n_items);
+                     rows, list, items, n_items, c_floor);
   return hipGetLastError();
 }
 

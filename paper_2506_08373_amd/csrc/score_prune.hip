@@ -293,7 +293,7 @@ static int prune_saving(int64_t m, int64_t c_max) {
   return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= 7 * c_max ? 12 : 0;
 }
 
-bool prune_plan(Plan *pl, int32_t keep) {
+bool prune_plan(Plan *pl, int32_t keep, bool ada) {
   Dims &d = pl->d;
   ScoreGeom &g = pl->g;
   if (d.elt != 2 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
@@ -313,9 +313,10 @@ bool prune_plan(Plan *pl, int32_t keep) {
     saved += (int64_t)pl->t.tail0[s] * saving / 100;
   }
   if (saved * d.L * d.Hkv * ((d.M + 31) / 32) < kPruneMinSaving + kPruneMinPerSeq * (d.S - 1)) return false;
-  // about a tenth of the keys is listed: one item per CU or more
+  // About a tenth of the keys is listed: an item per CU, if that makes items short.  (Twice as many of half the size measure the same, 8 layers
+  // x 32K, shared budget: 80 us for the listed sweep.)
   pl->item_keys = kPruneItemMax;
-  while (pl->item_keys > kPruneItemMin && pl->item_keys * 2560ll > pruned * units) pl->item_keys /= 2;
+  while (pl->item_keys > kPruneItemMin && pl->item_keys * 1280ll >= pruned * units) pl->item_keys /= 2;
   const int64_t kc = prune_chunk_keys(*pl, step, units);
   int cc = 0;
   for (int s = 0; s < d.S; ++s) {
@@ -334,7 +335,7 @@ bool prune_plan(Plan *pl, int32_t keep) {
   if (score_chunk_workgroups(d, g, cc) > most || units * d.S > most || prune_rows(*pl) * (d.T / 4096 + 1) > most) return false;
   g.n_fast_chunks = cc;
   g.n_chunks = 2 * cc + d.S;
-  size_t off = pl->total;
+  size_t off = ada ? pl->total_ada : pl->total;
   auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
   pl->off_part = take((size_t)units * g.n_chunks * g.RSB * sizeof(float2) + (size_t)score_fail_words(d, g, cc) * sizeof(int32_t));
   pl->off_squares = take((size_t)units * cc * g.RSB * sizeof(float));
@@ -364,20 +365,21 @@ hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void 
   return hipSuccess;
 }
 
-hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st) {
+hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, int32_t c_floor) {
   Buffers b(pl, q, k, ws);
   hipError_t e;
   if ((e = launch(Sweep::SampleColumns, b.A, st)) != hipSuccess) return e;
-  if ((e = launch_prune_thresholds(pl, b.planes, b.A.row_extra, b.rows, b.n_items, st)) != hipSuccess) return e;
+  uint32_t *counts = c_floor >= 0 ? reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + pl.off_ada_hist) : nullptr;
+  if ((e = launch_prune_thresholds(pl, b.planes, b.A.row_extra, b.rows, b.n_items, st, c_floor, counts)) != hipSuccess) return e;
   if ((e = launch_prune_list(pl, b.planes, b.rows, b.list, b.items, b.n_items, st)) != hipSuccess) return e;
   return launch(Sweep::Listed, b.A, st);
 }
 
-hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st) {
+hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st, int32_t c_floor) {
   Buffers b(pl, q, k, ws);
   b.A.n_items = b.n_items + 1;
   hipError_t e;
-  if ((e = launch_prune_check(pl, hist0, b.rows, b.list, b.items, b.n_items + 1, st)) != hipSuccess) return e;
+  if ((e = launch_prune_check(pl, hist0, b.rows, b.list, b.items, b.n_items + 1, st, c_floor)) != hipSuccess) return e;
   if ((e = launch(Sweep::Listed, b.A, st)) != hipSuccess) return e;
   float *pooled = reinterpret_cast<float *>(static_cast<char *>(ws) + pl.off_pooled);
   return launch_reduce_pool(pl, b.planes, nullptr, pooled, st, hist0, nullptr, b.rows, true);

@@ -210,6 +210,8 @@ struct PruneRow {
   int32_t digit;     // first digit of the scores that cannot come from an unlisted key; smaller digits are not counted
   int32_t listed;    // keys in the row's list
   int32_t failed;    // 1: fewer than c_max scores reached the digit, every key is computed
+  int32_t layer_digit;   // shared budget: the digit that the layer's threshold will reach
+  int32_t pad[3];
 };
 // An item of a listed sweep holds at most Plan::item_keys keys, and at least this many but for the last of a row.
 constexpr int kPruneItemMin = 512, kPruneItemMax = 2048;
@@ -217,25 +219,28 @@ inline __host__ __device__ int prune_step(int32_t chunk_of) { return chunk_of & 
 // Keys of a sample's tile: Operand::KT of the scoring kernels.
 inline int prune_tile_keys(const Plan &pl) { return pl.d.D == 64 && pl.g.MB == 2 ? 256 : 128; }
 // Turns the plan of a fused call into one of a pruned call where that is faster; false: it is not.
-// keep: 0, or the tokens kept by a call for prompt tokens, whose layers and heads have one output row.
-bool prune_plan(Plan *pl, int32_t keep = 0);
+// ada: for a shared budget (scratch behind that of the selection).  keep: 0, or the tokens kept by a call for prompt tokens, whose layers and heads have one output row.
+bool prune_plan(Plan *pl, int32_t keep = 0, bool ada = false);
 // Row statistics over the sample, then the sweep over the other keys (bounds into the planes), then the normalisers
 // (clear: see launch_score).
 hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, hipEvent_t *events,
                              uint32_t *clear, int64_t clear_words);
 // Column sums of the sample and the masked tails; thresholds and lists; column sums of the listed keys.
-hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st);
+// c_floor, from 0 on: of a shared budget.
+hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, int32_t c_floor = -1);
 // The same for prompt tokens, with the merged planes' pooling.  scratch: kRowScratchWords words, as launch_select_row_parts reads them.
 hipError_t launch_prune_token_columns(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st);
 hipError_t launch_prune_token_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st);
 // After the pooling of these: column sums of all keys, and pooling, of the rows that failed.
-hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st);
-hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st);
+hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st, int32_t c_floor = -1);
+// counts: of a shared budget, 2048 words per row of scratch.
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st,
+                                   int32_t c_floor = -1, uint32_t *counts = nullptr);
 hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
                              hipStream_t st);
 // hist0: the pooled scores' first digits.  Lists every key of the rows that failed.
 hipError_t launch_prune_check(const Plan &pl, const uint32_t *hist0, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
-                              hipStream_t st);
+                              hipStream_t st, int32_t c_floor = -1);
 
 // out rows = (layer, seq, head): pooled/raw in the "scores" layout from RS planes.
 // prune, when not null: smaller digits than a row's are not counted; repeat: only the rows that failed, only the smaller digits.

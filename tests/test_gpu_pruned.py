@@ -201,3 +201,36 @@ def test_prompt_tokens_whose_sample_misleads(S):
         S.specpc_select_tokens(p, 4000, 0, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
         got.append(out)
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("lens,n_layers,c_floor,kw", [
+    ([32771], 8, 256, {}),
+    ([32771], 8, 0, {"heads": 4, "group": 7}),
+    ([32771], 8, 1024, {"gain": 0.7}),                                     # floor = budget: every head keeps as much
+    ([9000, 30123, 700, 25000], 6, 100, {"dtype": torch.float16}),
+    ([32771], 8, 256, {"mislead": 4}),
+    ([32771], 8, 0, {"mislead": 3}),
+])
+def test_shared_budgets_are_those_of_complete_scores(S, lens, n_layers, c_floor, kw):
+    kw = dict(kw)
+    mislead = kw.pop("mislead", 0)
+    q, k = tensors(lens, n_layers, **kw)
+    # heads of different sharpness, so that their shares differ
+    q *= torch.linspace(0.6, 1.6, q.shape[3], device="cuda").to(q.dtype)[None, None, None, :, None]
+    if mislead:
+        k[2, :32640].view(-1, 128, k.shape[2], 128)[::8] *= mislead
+        k[4, :32640, 1].view(-1, 128, 128)[::8] *= mislead
+    p = params(S, q, k, lens, 32, 1024)
+    H, KT = k.shape[2], S.total_keep(p)
+    most = S.ada_workspace_bytes(p)
+    assert most > S.ada_workspace_bytes(params(S, q, k, lens, 32, 1024, pool="avg"))
+    got = []
+    for size in (most, most - 256, most):                                     # (no room for pruning in the second)
+        idx = torch.full((n_layers, H * KT), -7, dtype=torch.int32, device="cuda")
+        off = torch.full((n_layers, len(lens), H + 1), -7, dtype=torch.int32, device="cuda")
+        k_out = torch.empty(n_layers, H * KT, 128, dtype=k.dtype, device="cuda")
+        S.speckv_compress_ada(p, c_floor, q, k, None, idx, off, k_out, None, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        got.append((idx, off, k_out.view(torch.int16)))
+    assert got[0][1].diff(dim=-1).unique().numel() > 1 or c_floor >= 1024
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
