@@ -83,10 +83,23 @@ def _traffic_from_profile(stage: str, tag: str):
     return None, None
 
 
-def _scoring_kernel_symbol(S, p, w, stage: str) -> str:
+# Stages of a pruned call, whose second one computes exact scores only for keys that can be kept.
+PRUNED_NOTES = {
+    "score_pass1": "row statistics of the sample, one sweep over the other keys (row sums, and bounds on the keys' scores), repair of "
+                   "segments that overflowed: one Q.K^T",
+    "score_pass2": "exact column sums of the sample and of the keys whose bound reaches the threshold (a few per cent of a Q.K^T, "
+                   "not priced), thresholds and lists",
+    "pool": "pooling, and the check that enough scores reach the thresholds (rows where they do not are computed whole)",
+}
+
+
+def _scoring_kernel_symbol(S, p, w, stage: str, pruned: bool) -> str:
     """Name of the unmasked scoring kernel of this stage as a rocprofv3 kernel trace shows it."""
     info = S.plan_info(p)
     dt = {"bf16": 0, "f32": 1, "f16": 2}[w.dtype]
+    if pruned:
+        return "prune_%s_kernel<%d, %d, %d, %d, %d>" % ("sweep" if stage == "score_pass1" else "listed", dt, w.head_dim,
+                                                        info["blocks_per_wave"], info["waves"], info["reduce_max"])
     npass = 1 if stage == "score_pass1" else 2
     red = info["reduce_max"] if npass == 2 else info["fixed_reference_rows"]
     if info["q_stationary"] & npass:
@@ -297,11 +310,20 @@ def main() -> int:
     k_bytes = float(w.total_tokens) * H * d * elt * L                      # K read once
     peak_mfma = PEAK_MFMA_TFLOPS[w.dtype]
     kernels = {}
+    # a call that computes exact scores only where they matter has scratch of its own (averages, or keeping all, need every score)
+    if specpc:
+        pruned = S.specpc_workspace_bytes(p, top_k) > S.specpc_workspace_bytes(p, n) - 4 * (n - top_k)
+    else:
+        every = S.SpecKVParams.for_tensors(q, k, seq_lens=w.seq_lens, n_window=w.n_window, pool_k=w.pool_k, c_max=w.c_max,
+                                           sm_scale=w.sm_scale, reduce=reduce, pool="avg")
+        pruned = S.workspace_bytes(p) > S.workspace_bytes(every)
     for name, ms in zip(stage_names, mean_ms):
         entry = {"ms": round(float(ms), 4)}
-        if name in ("score_pass1", "score_pass2"):
+        if pruned and name in PRUNED_NOTES:
+            entry["note"] = PRUNED_NOTES[name]
+        if name == "score_pass1" or (name == "score_pass2" and not pruned):
             entry.update(bound="mfma", achieved=round(qk_flops / (ms * 1e-3) / 1e12, 2), peak=peak_mfma,
-                         unit="TFLOP/s", kernel=_scoring_kernel_symbol(S, p, w, name),
+                         unit="TFLOP/s", kernel=_scoring_kernel_symbol(S, p, w, name, pruned),
                          k_read_GBps=round(k_bytes / (ms * 1e-3) / 1e9, 1),
                          alu_TFLOPs=round(ALU_FLOPS_PER_SCORE * n_scores / (ms * 1e-3) / 1e12, 2))
         elif name == "compact":
@@ -309,12 +331,12 @@ def main() -> int:
             compact_bytes = 2.0 * 2.0 * H * KT * d * elt * L + 4.0 * H * KT * L   # K,V read + write, indices
             entry.update(bound="hbm", achieved=round(compact_bytes / (ms * 1e-3) / 1e9, 1), peak=PEAK_HBM_GBS,
                          unit="GB/s", kernel="compact_kernel<true>")
-        elif name in FOLDED_STAGES and not (specpc and name == "pool"):
+        elif name in FOLDED_STAGES and not (specpc and name == "pool") and not pruned:
             entry["note"] = FOLDED_STAGES[name]
         if "achieved" in entry:
             entry["frac"] = round(entry["achieved"] / entry["peak"], 4)
         kernels[name] = entry
-    dominant = max(("score_pass1", "score_pass2"), key=lambda n_: kernels[n_]["ms"])
+    dominant = "score_pass1" if pruned else max(("score_pass1", "score_pass2"), key=lambda n_: kernels[n_]["ms"])
     dk = kernels[dominant]
     traffic, traffic_src = (None, None) if tag is None else _traffic_from_profile(dominant, tag)
     if d == 64 and elt == 2:
@@ -330,7 +352,9 @@ def main() -> int:
         roofline = {"kernel": dk["kernel"], "stage": dominant, "bound": "mfma", "achieved": dk["achieved"],
                     "peak": peak_mfma, "unit": "TFLOP/s", "frac": dk["frac"]}
     roofline.update(traffic=traffic, traffic_source=traffic_src, avg_launch_ms=dk["ms"])
-    if dominant == "score_pass1" and S.plan_info(p)["fixed_reference_rows"]:
+    if pruned:
+        roofline["avg_launch_note"] = PRUNED_NOTES["score_pass1"]
+    elif dominant == "score_pass1" and S.plan_info(p)["fixed_reference_rows"]:
         roofline["avg_launch_note"] = ("the stage between two HIP events: the sweep and the repair launch behind it "
                                        "(score_kernel_rows_repair, 1 % of the stage)")
 
@@ -339,7 +363,7 @@ def main() -> int:
     # the same algorithmic flops (one Q.K^T; the two sweeps execute it twice) over the whole step
     step_tflops = qk_flops / (ms_per_step * 1e-3) / 1e12
     roofline["whole_step"] = {"achieved": round(step_tflops, 2), "unit": "TFLOP/s", "frac": round(step_tflops / peak_mfma, 4),
-                              "note": "algorithmic flops of one Q.K^T over the step time; each sweep executes them once"}
+                              "note": "algorithmic flops of one Q.K^T over the step time; each whole sweep executes them once"}
 
     # Context figure (not the headline): the same step when the caller already holds the row
     # log-sum-exps (e.g. from the prefill attention kernel) and scoring needs one sweep only.

@@ -35,9 +35,12 @@ __device__ __forceinline__ RowAt row_at(const Dims &d, const SeqTab &t, int row)
   return r;
 }
 
+// With three deviations one of 256 rows of 128K falls short in every third call (100 us of 5500 to compute it whole), with three and a half
+// seldom; a threshold lower by as much lists a tenth more keys (15 us).
+constexpr float kThresholdDeviations = 3.5f;
 // Of the sample's pooled scores, how many have to reach a threshold when `expected` of them are among the ones kept.
 __device__ __forceinline__ uint32_t wanted_of(float expected, int pool_k) {
-  return (uint32_t)ceilf(expected + 3.f * sqrtf(expected * (float)pool_k));
+  return (uint32_t)ceilf(expected + kThresholdDeviations * sqrtf(expected * (float)pool_k));
 }
 
 // A row whose scores from `digit` on are to be found; over: log2 of what its bounds may be too small by.
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(kRefThreads) void prune_reference_kernel(PruneArgs 
 constexpr int kThrThreads = 1024, kThrEach = 8;
 
 // A row's threshold: the lower end of the largest first digit that enough of the sample's pooled scores reach.  Neighbouring
-// pooled scores are one key's, so that `expected` of them are about expected / pool_k independent draws; three standard
+// pooled scores are one key's, so that `expected` of them are about expected / pool_k independent draws; some standard
 // deviations more are asked for, since a row that falls short is computed whole (launch_prune_repeat).
 // Bound: the latency of two or three rounds of loads; one workgroup per row.
 __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes,
