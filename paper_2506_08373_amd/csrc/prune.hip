@@ -59,7 +59,8 @@ struct Steps { int32_t log[kMaxSeqs]; };
 // First references of the rows.  What the sample and the masked tail add up to, S + T, is a lower bound on a row's normaliser,
 // but of a row that attends to many keys alike only the sample's share, and the bounds on scores are larger by as much.  The rest of
 // such a row is expected from its sample, (ratio - 1) S with ratio = keys / keys in the sample, less four standard deviations,
-// ratio sqrt(sum of squared terms): nothing is left of it where a few keys make up the row.  A reference that turns out above its
+// ratio sqrt(sum of squared terms), both without the largest term, which is often one key's that all rows attend to: nothing is left of it
+// where a few keys make up the row.  A reference that turns out above its
 // normaliser makes the bounds too small by as much, which prune_threshold_kernel allows for.
 // Keys listed of 32K with logits of standard deviation 1, a sample of 1/8: 84 % with S + T, 18 % with this; 2: 25 and 6 %; 3 to 8: level.
 constexpr float kSampleDeviations = 4.f;
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(kRefThreads) void prune_reference_kernel(PruneArgs 
   const float2 *pairs = A.part + (int64_t)unit * A.g.n_chunks * RSB + r;
   const float *squares = A.squares + (int64_t)unit * A.g.n_fast_chunks * RSB + r;
   const float2 tail = pairs[(int64_t)(A.g.n_fast_chunks + s) * RSB];
-  float top = tail.x, sum = 0.f, square = 0.f;             // of the sample
+  float top = kNegBig, sum = 0.f, square = 0.f;            // of the sample, in units of its largest term
   for (int e = 0; e < n; ++e) {
     const float2 p = pairs[(int64_t)(first + e) * RSB];
     const float m = fmaxf(top, p.x), f1 = __builtin_amdgcn_exp2f(top - m), f2 = __builtin_amdgcn_exp2f(p.x - m);
@@ -81,14 +82,14 @@ __global__ __launch_bounds__(kRefThreads) void prune_reference_kernel(PruneArgs 
     square = square * f1 * f1 + squares[(int64_t)(first + e) * RSB] * f2 * f2;
     top = m;
   }
-  const float seen = sum + tail.y * __builtin_amdgcn_exp2f(tail.x - top);
   const int step = prune_step(A.chunk_of[s]), tiles = A.t.tail0[s] / tile_keys, sampled = (tiles + (1 << step) - 1) >> step;
   const float ratio = sampled > 0 ? (float)tiles / (float)sampled : 1.f;
-  const float rest = (ratio - 1.f) * sum - kSampleDeviations * ratio * sqrtf(square);
-  const float all = seen + (rest > 0.f ? rest : 0.f);
+  const float rest = (ratio - 1.f) * (sum - 1.f) - kSampleDeviations * ratio * sqrtf(fmaxf(square - 1.f, 0.f));
+  const float m = fmaxf(top, tail.x), f1 = __builtin_amdgcn_exp2f(top - m);
+  const float seen = sum * f1 + tail.y * __builtin_amdgcn_exp2f(tail.x - m), all = seen + (rest > 0.f ? rest * f1 : 0.f);
   const int rs = unit % A.g.RS, lh = unit / A.g.RS;
   const int64_t at = ((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r;
-  A.lse[at] = top + log2f(all);
+  A.lse[at] = m + log2f(all);
   A.row_extra[at] = seen / all;
 }
 

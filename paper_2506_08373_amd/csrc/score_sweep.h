@@ -1196,8 +1196,9 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
       // A sum taken against a fixed reference can be many binary orders away from 1.  Its exponent
       // moves into the reference first, so that every pair handed on has a sum in [0.5, 1) (or 0)
       // and merging two pairs never multiplies a large sum by a factor that underflows.
-      int e2;
-      const float lf = __builtin_frexpf(lrun[rb], &e2);
+      // (The reference of a sample's pair is the sample's maximum: prune_reference_kernel.  Its sum is no larger than its keys are many.)
+      int e2 = 0;
+      const float lf = SQUARES ? lrun[rb] : __builtin_frexpf(lrun[rb], &e2);
       const float mf = mrun[rb] + (float)e2;
       const float mo = __shfl_xor(mf, 32, 64), lo = __shfl_xor(lf, 32, 64);
       float mm = fmaxf(mf, mo);
