@@ -24,7 +24,6 @@
 // fifth longer than without.
 #include <algorithm>
 #include <utility>
-#include <vector>
 
 #include "score_sweep.h"
 
@@ -246,32 +245,39 @@ static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) 
   // The sweep's duration in key-times: the longest chunks first, each to the CU that is free first.  Beyond kSimulated sequences
   // the chunks are many and of all lengths: an even spread and half a short one.
   auto duration = [&](int64_t kc) {
-    std::vector<std::pair<double, int64_t>> todo;
+    std::pair<double, int64_t> todo[kMaxSeqs];                              // keys and number of a sequence's workgroups
+    int n_todo = 0;
     double total = 0., shortest = 1e30;
     for (int s = 0; s < pl.d.S; ++s) {
       if (step[s] == 0) continue;
       const Chunks c = prune_chunks(pl, pl.t.tail0[s], step[s], kc);
-      todo.push_back({std::min(c.keys, pl.t.tail0[s]) + kCost, c.count * units});
-      total += todo.back().first * (double)todo.back().second;
-      shortest = std::min(shortest, todo.back().first);
+      todo[n_todo++] = {std::min(c.keys, pl.t.tail0[s]) + kCost, c.count * units};
+      total += todo[n_todo - 1].first * (double)todo[n_todo - 1].second;
+      shortest = std::min(shortest, todo[n_todo - 1].first);
     }
-    std::sort(todo.rbegin(), todo.rend());
-    if (todo.size() > kSimulated) return std::max(todo[0].first, total / kCUs + 0.5 * shortest);
-    std::vector<std::pair<double, int64_t>> free_at = {{0., kCUs}};         // CUs by the time they are free, ascending
-    for (auto [keys, n] : todo) {
-      while (n > 0) {
-        auto [at, cus] = free_at.front();
-        const int64_t k = std::min(cus, n);
+    std::sort(todo, todo + n_todo, [](auto &a, auto &b) { return a.first > b.first; });
+    if (n_todo > kSimulated) return std::max(todo[0].first, total / kCUs + 0.5 * shortest);
+    std::pair<double, int64_t> free_at[kCUs + 1] = {{0., kCUs}};            // CUs by the time they are free, ascending; none empty
+    int n_free = 1;
+    for (int i = 0; i < n_todo; ++i) {
+      for (int64_t n = todo[i].second; n > 0;) {
+        const double done = free_at[0].first + todo[i].first;
+        const int64_t k = std::min(free_at[0].second, n);
         n -= k;
-        if (k == cus) free_at.erase(free_at.begin());
-        else free_at.front().second -= k;
-        auto x = free_at.begin();
-        while (x != free_at.end() && x->first < at + keys) ++x;
-        if (x != free_at.end() && x->first == at + keys) x->second += k;
-        else free_at.insert(x, {at + keys, k});
+        free_at[0].second -= k;
+        if (free_at[0].second == 0) std::copy(free_at + 1, free_at + n_free--, free_at);
+        int x = 0;
+        while (x < n_free && free_at[x].first < done) ++x;
+        if (x < n_free && free_at[x].first == done) {
+          free_at[x].second += k;
+        } else {
+          std::copy_backward(free_at + x, free_at + n_free, free_at + n_free + 1);
+          free_at[x] = {done, k};
+          ++n_free;
+        }
       }
     }
-    return free_at.back().first;
+    return free_at[n_free - 1].first;
   };
   static const int parts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128};
   double best = 1e30, took[sizeof(parts) / sizeof(parts[0])];
