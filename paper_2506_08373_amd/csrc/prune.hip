@@ -11,11 +11,11 @@ namespace speckv {
 namespace {
 
 // A bound counts as below a threshold only if it is by this much: the bound's own rounding (probabilities to 2^-13 where
-// logits reach 1000, sums to 2^-20) stays inside.
+// logits reach 1000, sums to 2^-20) stays inside half of it, and what underflows in the bound inside the other half.
 constexpr float kPruneSlack = 1.f / 1024.f;
-// Smallest threshold that prunes.  A probability below 2^-126 underflows in a bound (2^(kPruneShift - 126) unscaled), 2^12 rows
-// of them add up to 2^-38, the slack's share of 2^-28.
-constexpr float kPruneFloor = 3.7252903e-9f;
+// Smallest threshold that prunes an output row to which `rows` rows add up (a group's, or all of a call for prompt tokens).  Each may
+// lose a probability below 2^(kPruneShift - 126).
+__device__ __forceinline__ float prune_floor(int rows) { return (float)rows * __builtin_exp2f(kPruneShift - 126.f) / (0.5f * kPruneSlack); }
 
 __device__ __forceinline__ uint32_t key_of(float x) {            // the selection's ordered key
   const uint32_t u = __float_as_uint(x + 0.0f);
@@ -43,14 +43,14 @@ __device__ __forceinline__ uint32_t wanted_of(float expected, int pool_k) {
   return (uint32_t)ceilf(expected + kThresholdDeviations * sqrtf(expected * (float)pool_k));
 }
 
-// A row whose scores from `digit` on are to be found; over: log2 of what its bounds may be too small by.
-__device__ __forceinline__ PruneRow row_from(int digit, float over) {
+// A row whose scores from `digit` on are to be found; over: log2 of what its bounds may be too small by; rows: see prune_floor.
+__device__ __forceinline__ PruneRow row_from(int digit, float over, int rows) {
   int open;
   const uint32_t key = key_prefix_of((uint32_t)digit, &open);
   const float threshold = key >= 0x80000000u ? __uint_as_float(key ^ 0x80000000u) : 0.f;
   const float bound = threshold * __builtin_exp2f(-over);
   // (written so that a threshold that is not a number lists every key)
-  if (bound < kPruneFloor) return {-1.f, 0, 0, 0, 0, {0, 0, 0}};
+  if (bound < prune_floor(rows)) return {-1.f, 0, 0, 0, 0, {0, 0, 0}};
   return {bound * (1.f - kPruneSlack) * __builtin_exp2f(-kPruneShift), digit, 0, 0, 0, {0, 0, 0}};
 }
 
@@ -175,14 +175,14 @@ __global__ __launch_bounds__(kThrThreads) void prune_threshold_kernel(Dims d, Se
   if (tid != 0) return;
   for (int w = 0; w < kThrThreads / 64; ++w) over = fmaxf(over, excess[w]);
   if (counts != nullptr) rows[row] = {over, wanted == 0 ? 2047 : digit, 0, 0, 0, {0, 0, 0}};      // see prune_shared_threshold_kernel
-  else rows[row] = row_from(digit, over);
+  else rows[row] = row_from(digit, over, group_rows);
 }
 
 // Shared budget, one workgroup per (layer, sequence), after prune_threshold_kernel: the layer's digit is the largest that so many of the
 // samples' scores reach, beyond the heads' floors, as the layer keeps; a head's is no larger, and no larger than the one of its floor.
 // Whatever is kept then reaches its head's digit.
 __global__ __launch_bounds__(kThrThreads) void prune_shared_threshold_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int c_floor,
-                                                                             PruneRow *__restrict__ rows,
+                                                                             int group_rows, PruneRow *__restrict__ rows,
                                                                              const uint32_t *__restrict__ counts) {
   __shared__ int layer_digit;
   const int ls = blockIdx.x, s = ls % d.S, tid = threadIdx.x;
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kThrThreads) void prune_shared_threshold_kernel(Dim
   __syncthreads();
   if (tid >= d.Hkv) return;
   PruneRow *row = rows + (int64_t)ls * d.Hkv + tid;
-  *row = row_from(min(layer_digit, row->digit), row->bound);
+  *row = row_from(min(layer_digit, row->digit), row->bound, group_rows);
   row->layer_digit = layer_digit;
 }
 
@@ -366,7 +366,7 @@ hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const fl
                      planes, row_extra, r.group_rows, rows, n_items, c_floor, counts);
   if (counts != nullptr)
     hipLaunchKernelGGL(prune_shared_threshold_kernel, dim3((unsigned)(r.d.L * r.d.S)), dim3(kThrThreads), 0, st, r.d, pl.t, steps_of(pl),
-                       tile_log_of(pl), c_floor, rows, counts);
+                       tile_log_of(pl), c_floor, r.group_rows, rows, counts);
   return hipGetLastError();
 }
 

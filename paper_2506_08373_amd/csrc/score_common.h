@@ -132,7 +132,7 @@ constexpr float kAnchorLimit = 8.507059e37f;
 // The sweep of a pruned call over the keys that are not in the sample sums 2^(score - e - kPruneShift) along rows and columns, with
 // e the log2 normaliser that the sample and the masked tail give the row.  A score may exceed e by 126 + kPruneShift binary
 // orders (140 nats) before the sum of a segment of kPruneSegment tiles overflows and is left to the repair launch; a column sum is
-// a bound as long as what underflows in it does not matter beside the threshold (kPruneFloor).
+// a bound as long as what underflows in it does not matter beside the threshold (prune_floor).
 // The references are multiples of 1 / kPruneGrain and grow by such, so that they are exact.
 constexpr float kPruneShift = 76.f, kPruneGrain = 8.f;
 // Segments that wavefronts leave out are listed as kFailWords says, but with the row blocks from bit kFailBlocks on.

@@ -20,7 +20,7 @@
 // listed keys (4 %) 250, the rest 200.  Calls, all scores / pruned: that one 8690 / 5560, eight prompts of 4K to 64K, groups of
 // 7, 28 layers 15990 / 10550, 32 layers x 16K, maximum 1010 / 870, 8 layers x 32K 644 / 550; d = 64: 31 layers x 31K 1511 / 1017, 32 layers x
 // 43K, 2 heads, flat attention 492 / 395.
-// Where nothing can be pruned (all scores alike, or a threshold under kPruneFloor) the listed sweep is a second whole one and the call a
+// Where nothing can be pruned (all scores alike, or a threshold under prune_floor) the listed sweep is a second whole one and the call a
 // fifth longer than without.
 #include <algorithm>
 #include <utility>

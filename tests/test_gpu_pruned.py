@@ -239,3 +239,45 @@ def test_shared_budgets_are_those_of_complete_scores(S, lens, n_layers, c_floor,
     assert got[0][1].diff(dim=-1).unique().numel() > 1 or c_floor >= 1024
     for other in got[1:]:
         assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+
+
+def test_many_probabilities_below_the_smallest_number_of_a_bound(S):
+    """A sink takes nearly all of every row.  The scores that decide are about 2^-28, each from one row, but for 100 keys: 0.4 % of
+    their score is from the other 32767 rows, 2^-50 each.  Without that part they are below the threshold and below the keys to be kept."""
+    n, n_layers, top_k = 48000, 16, 2000
+    q = torch.zeros(n_layers, 1, 64, 32, 64, dtype=torch.bfloat16, device="cuda")
+    k = torch.zeros(n_layers, n, 8, 64, dtype=torch.bfloat16, device="cuda")
+    few = torch.arange(100, device="cuda") * 384 + 128 + 7                   # in tiles 1, 4, 7 ..: below, only the odd ones are used
+    few = few[(few // 128) % 2 == 1]
+    others = torch.arange(3, 47000, 11, device="cuda")                       # about twice as many as are kept
+    others = others[~torch.isin(others, few)]
+    least = math.log2(2.0 ** -28 * (1 + 2 / 32))                             # lower end of a first digit
+    # channel 0: the sink, 2^60 in every row; channel 2: the other rows; channels 1 and 3: the row that decides
+    q[..., 0] = 1
+    q[..., 2] = 1
+    k[..., 2] = -40
+    k[:, 0, :, 0] = 60
+    k[:, few, :, 2] = -50.125 + 60
+    q[0, 0, 0, 0, 1:4] = torch.tensor([1, 0, 1], device="cuda")
+    k[0, :, 0, 1] = -40
+    for keys, score in ((few, least - 0.0058), (others, least + 0.0014)):
+        k[0, keys, 0, 1] = 32
+        k[0, keys, 0, 3] = score + 60 - 32
+    k[:, 0, :, 2] = 0
+    k[0, 0, 0, 1] = 0
+    sm_scale = math.log(2.0) * (1 + 2e-6)
+    p = S.SpecKVParams.for_tensors(q, k, seq_lens=[n], n_window=64, pool_k=1, c_max=512, sm_scale=sm_scale)
+    exact = torch.zeros(n, dtype=torch.float64, device="cuda")
+    for layer in range(n_layers):
+        for h in range(32):
+            # (rows of a layer and head are alike but for the first one of head 0 of layer 0; none sees the sink's window)
+            row = (q[layer, 0, :2, h].double() @ k[layer, :, h // 4].double().t()) * (sm_scale * math.log2(math.e))
+            prob = torch.exp2(row - torch.log2(torch.exp2(row - 60).sum(-1, keepdim=True)) - 60)
+            exact += prob[0] + 63 * prob[1]
+    want = exact[:n - 64].sort(descending=True, stable=True).indices[:top_k].sort().values
+    assert torch.isin(few, want).all() and exact[few].min() > exact[others].max() * (1 + 1e-3)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+    out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros(1, dtype=torch.int32, device="cuda")]
+    S.specpc_select_tokens(p, top_k, 0, q, k, ids, *out, torch.empty(S.specpc_workspace_bytes(p, top_k), dtype=torch.uint8, device="cuda"))
+    got = out[0][:int(out[2])].long()
+    assert torch.equal(got[:-64], want)
