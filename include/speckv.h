@@ -148,9 +148,11 @@ int64_t speckv_total_keep(const speckv_params *p);
 
 /* Bytes of 256-byte-aligned device workspace that speckv_score, speckv_select and
  * speckv_compress need for these parameters (the maximum over the three).  Returns 0 if
- * the parameters are invalid.  A part of it only saves time: large fused calls (this one's, the
- * shared budget's, the prompt tokens') compute exact scores only for keys that can be kept, which
- * takes scratch of its own, up to a few per cent more; without it they compute every score. */
+ * the parameters are invalid.  It is enough for every call that differs in shorter sequences only
+ * (a shorter prompt may be cut into more chunks).  A part of it only saves time: large fused calls
+ * (this one's, the shared budget's, the prompt tokens') compute exact scores only for keys that can
+ * be kept, which takes scratch of its own; without it they compute every score.  What is asked for
+ * beyond a call's own need with all scores is mostly a few MiB and at most some tens. */
 size_t speckv_workspace_bytes(const speckv_params *p);
 
 /* Launch plan the host derives for these parameters, for diagnostics and tests (no GPU needed):
@@ -217,9 +219,9 @@ speckv_status speckv_compress(const speckv_params *p, const void *q, const void 
  * results (where the scratch has no room for the part that only saves time, all scores are
  * computed, and keys whose scores differ by no more than rounding may change places); the scratch is a fixed array of SPECKV_STATIC_SCRATCH_BYTES inside the library's device
  * code (one copy per GPU, held until the process ends; its address is looked up on the first call
- * on each device).  The call allocates nothing and frees nothing.  Parameters whose
- * speckv_workspace_bytes, without the part that only saves time, exceeds SPECKV_STATIC_SCRATCH_BYTES are rejected with
- * SPECKV_ERR_WORKSPACE before anything is launched (32 MiB covers one layer of 8 KV heads at
+ * on each device).  The call allocates nothing and frees nothing.  Parameters that need more than
+ * SPECKV_STATIC_SCRATCH_BYTES themselves (speckv_workspace_bytes less what it holds for shorter
+ * prompts and the part that only saves time) are rejected with SPECKV_ERR_WORKSPACE before anything is launched (32 MiB covers one layer of 8 KV heads at
  * 256K tokens, or a few layers of shorter prompts).  Every call on a GPU shares that GPU's array:
  * calls that overlap on one GPU (two streams, two threads) race and must be serialised by the
  * caller.  The array keeps the previous call's contents; the kernels never read what they have

@@ -198,7 +198,19 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
     g.n_chunks = g.n_fast_chunks + d.S;
   };
   cut(kc);
-  int64_t room_chunks = g.n_fast_chunks;        // unmasked chunks the workspace has room for
+  pl->room_chunks = g.n_fast_chunks;
+  // A workspace that is large enough for a prompt is meant to be so for every shorter one, which may have more chunks: kc is at least
+  // 8192, or fast_keys / many, and then at least kChunkMin and kc_few.
+  {
+    int64_t of_floor = 0, of_min = 0, of_cap = 0;
+    for (int s = 0; s < d.S; ++s) {
+      of_floor += (t.tail0[s] + kChunkFloor - 1) / kChunkFloor;
+      of_min += (t.tail0[s] + kChunkMin - 1) / kChunkMin;
+      of_cap += (t.tail0[s] + kChunkSmallCap - 1) / kChunkSmallCap;
+    }
+    const int64_t ends = d.S - 1;                 // a sequence's last chunk may be short
+    pl->most_chunks = std::max(of_floor, std::min({many + ends, of_min, std::max(few + ends, of_cap)}));
+  }
   // A call that chunks of kChunkMin keys cannot spread over the CUs is a chain of latencies: set-up, then one tile after the
   // other.  Its workgroups take as few tiles each as keeps everything in one round of the CUs: one fp32 layer of 1K keys
   // 56.7 us with 512 keys each, 36.4 with 128 (its sweeps 19.5 and 21.2 us, then 9.8 and 12.1); one layer of 4K 45.1 us
@@ -210,11 +222,10 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
   // groups of 7: 48.3 us with 256 keys each, 62.5 with 512, 66.0 with 128).
   if (kc == kChunkMin && units <= kShortChunkUnits) {
     const int tile = rowb <= 128 && g.MB == 1 ? 128 : kt;            // Operand::KT of the scoring kernels
-    // A shorter prompt may have more chunks than this one, and a workspace that is large enough for a prompt is so for every
-    // shorter one: there is room for the most chunks that the rule below gives at any length up to this one.
+    // (here, too, a shorter prompt may have more chunks: as many as the rule below gives at any length up to this one)
     int64_t most_pieces = 0;
     for (int s = 0; s < d.S; ++s) most_pieces += std::min(kShortChunks, (t.tail0[s] + tile - 1) / tile);
-    room_chunks = std::max(room_chunks, std::min(most_pieces, (int64_t)kCUs / units - d.S));
+    pl->room_chunks = std::max(pl->room_chunks, std::min(most_pieces, (int64_t)kCUs / units - d.S));
     static_assert((kShortChunks + 1) * kShortChunkUnits <= kCUs, "short_chunk: one prompt's chunks and tails are one round");
     for (int64_t piece = tile; piece < kChunkMin; piece += tile) {
       cut(piece);
@@ -227,26 +238,24 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
     if (d.n_dev != nullptr) {
       g.short_log = __builtin_ctz((unsigned)tile);
       g.KC = kChunkMin;
-      t.cc[1] = g.n_fast_chunks = (int32_t)room_chunks;
+      t.cc[1] = g.n_fast_chunks = (int32_t)pl->room_chunks;
       g.n_chunks = g.n_fast_chunks + 1;
     }
   }
 
-  // workspace carve-up
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
-  // partial pairs of the row-statistics sweep, and behind them the segments its chunk workgroups
-  // leave for the repair launch (score_fail_words ints)
-  pl->off_part = take((size_t)units * (room_chunks + d.S) * g.RSB * sizeof(float2) +
-                      (size_t)score_fail_words(d, g, room_chunks) * sizeof(int32_t));
-  pl->off_lse = take((size_t)d.L * d.Hkv * d.S * g.RS * g.RSB * sizeof(float));
-  pl->off_planes = take((size_t)g.RS * d.L * d.Hkv * d.T * sizeof(float));
-  pl->off_pooled = take(one_row_per_call ? (size_t)d.T * sizeof(float) : (size_t)d.L * d.Hkv * d.T * sizeof(float));
-  pl->off_pooled2 = take(one_row_per_call ? (size_t)d.T * sizeof(float) : 0);
-  pl->off_sel = take(one_row_per_call ? (size_t)(top_k > 0 ? top_k : 0) * sizeof(int32_t) : 0);
+  // a call of the short rule's kind at any length up to this one
+  if (units <= kShortChunkUnits) {
+    const int tile = rowb <= 128 && g.MB == 1 ? 128 : kt;
+    int64_t pieces = 0;
+    for (int s = 0; s < d.S; ++s) pieces += std::min(kShortChunks, (t.tail0[s] + tile - 1) / tile);
+    pl->most_chunks = std::max(pl->most_chunks, std::min(pieces, (int64_t)kCUs / units - d.S));
+  }
+  pl->most_chunks = std::max(pl->most_chunks, pl->room_chunks);
+  pl->one_row = one_row_per_call;
+  pl->sel_kept = top_k;
   // Selection: one workgroup per row unless the call has few, long rows; then each row is cut into
   // parts so that about kSelSplitWorkgroups workgroups share the ranking.
-  pl->sel_parts = 1; pl->sel_part_len = 0; pl->off_sel_hist = 0; pl->off_sel_state = 0;
+  pl->sel_parts = pl->most_sel_parts = 1; pl->sel_part_len = 0;
   if (!one_row_per_call) {
     const int64_t rows = (int64_t)d.L * d.S * d.Hkv;
     int max_m = 0;
@@ -254,22 +263,12 @@ speckv_status build_plan(const speckv_params *p, Plan *pl, bool one_row_per_call
     if (max_m >= kSelSplitMinKeys && rows * 2 <= kSelSplitWorkgroups) {
       int parts = (int)(kSelSplitWorkgroups / rows);
       if (parts > kSelSplitMaxParts) parts = kSelSplitMaxParts;
+      pl->most_sel_parts = parts;
       pl->sel_part_len = (int32_t)align_up((max_m + parts - 1) / parts, 1024);
       pl->sel_parts = (max_m + pl->sel_part_len - 1) / pl->sel_part_len;
-      pl->off_sel_hist = take((size_t)rows * pl->sel_parts * 2048 * sizeof(uint32_t));
-      pl->off_sel_state = take((size_t)rows * (2 + 2 * (size_t)pl->sel_parts) * sizeof(uint32_t));
     }
   }
-  // first-digit histograms of the pooled rows for the one-workgroup selection of the fused calls
-  pl->off_hist0 = 0; pl->hist0_words = 0;
-  if (!one_row_per_call && pl->sel_parts == 1) {
-    pl->hist0_words = (int64_t)d.L * d.S * d.Hkv * 2048;
-    pl->off_hist0 = take((size_t)pl->hist0_words * sizeof(uint32_t));
-  }
-  pl->total = off;
-  pl->off_ada_hist = take((size_t)d.L * d.S * d.Hkv * 2048 * sizeof(uint32_t));
-  pl->off_ada_state = take((size_t)d.L * d.S * (2 + 3 * (size_t)d.Hkv) * sizeof(uint32_t));
-  pl->total_ada = off;
+  carve_workspace(pl, pl->room_chunks);
   return SPECKV_OK;
 }
 
@@ -304,6 +303,48 @@ speckv_status static_scratch(void **out) {
 }
 
 }  // namespace
+
+void carve_workspace(Plan *pl, int64_t chunks, size_t pooled) {
+  const Dims &d = pl->d;
+  const ScoreGeom &g = pl->g;
+  const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
+  // partial pairs of the row-statistics sweep, and behind them the segments its chunk workgroups
+  // leave for the repair launch (score_fail_words ints)
+  pl->off_part = take((size_t)units * (chunks + d.S) * g.RSB * sizeof(float2) + (size_t)score_fail_words(d, g, chunks) * sizeof(int32_t));
+  pl->off_lse = take((size_t)d.L * d.Hkv * d.S * g.RS * g.RSB * sizeof(float));
+  pl->off_planes = take((size_t)g.RS * d.L * d.Hkv * d.T * sizeof(float));
+  pl->off_pooled = take(std::max(pooled, (pl->one_row ? 1 : (size_t)d.L * d.Hkv) * (size_t)d.T * sizeof(float)));
+  pl->off_pooled2 = take(pl->one_row ? (size_t)d.T * sizeof(float) : 0);
+  pl->off_sel = take(pl->one_row ? (size_t)(pl->sel_kept > 0 ? pl->sel_kept : 0) * sizeof(int32_t) : 0);
+  const size_t rows = (size_t)d.L * d.S * d.Hkv;
+  pl->off_sel_hist = pl->off_sel_state = 0;
+  if (pl->sel_parts > 1) {
+    pl->off_sel_hist = take(rows * pl->sel_parts * 2048 * sizeof(uint32_t));
+    pl->off_sel_state = take(rows * (2 + 2 * (size_t)pl->sel_parts) * sizeof(uint32_t));
+  }
+  // first-digit histograms of the pooled rows for the one-workgroup selection of the fused calls
+  pl->off_hist0 = 0; pl->hist0_words = 0;
+  if (!pl->one_row && pl->sel_parts == 1) {
+    pl->hist0_words = (int64_t)rows * 2048;
+    pl->off_hist0 = take((size_t)pl->hist0_words * sizeof(uint32_t));
+  }
+  pl->total = off;
+  pl->off_ada_hist = take(rows * 2048 * sizeof(uint32_t));
+  pl->off_ada_state = take((size_t)d.L * d.S * (2 + 3 * (size_t)d.Hkv) * sizeof(uint32_t));
+  pl->total_ada = off;
+}
+
+// What the size queries answer: room for this call and, with as many sequences, for every one of prompts no longer, pruned where it
+// can be.  A call itself needs its own plan's total (check_ws).
+static size_t workspace_of(Plan pl, int32_t keep, bool ada) {
+  const size_t pruned = prune_workspace(pl, keep, ada);
+  pl.sel_parts = pl.most_sel_parts;
+  carve_workspace(&pl, pl.most_chunks);
+  return std::max(ada ? pl.total_ada : pl.total, pruned);
+}
+
 }  // namespace speckv
 
 using namespace speckv;
@@ -351,8 +392,7 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
 size_t speckv_workspace_bytes(const speckv_params *p) {
   Plan pl;
   if (build_plan(p, &pl, false, 0) != SPECKV_OK) return 0;
-  Plan pruned = pl;
-  return prune_plan(&pruned) ? pruned.total_pruned : pl.total;
+  return workspace_of(pl, 0, false);
 }
 
 size_t speckv_select_workspace_bytes(const speckv_params *p) {
@@ -368,8 +408,7 @@ size_t specpc_workspace_bytes(const speckv_params *p, int32_t top_k) {
   eff.reduce_op = SPECKV_REDUCE_SUM;
   eff.pool_op = SPECKV_POOL_MAX;
   if (build_plan(&eff, &pl, true, top_k) != SPECKV_OK) return 0;
-  Plan pruned = pl;
-  return top_k > 0 && prune_plan(&pruned, top_k) ? pruned.total_pruned : pl.total;
+  return workspace_of(pl, top_k, false);
 }
 
 static speckv_status score_impl(const speckv_params *p, const void *q, const void *k, const float *lse_in,
@@ -543,8 +582,7 @@ speckv_status speckv_compress_events(const speckv_params *p, const void *q, cons
 size_t speckv_ada_workspace_bytes(const speckv_params *p) {
   Plan pl;
   if (build_plan(p, &pl, false, 0) != SPECKV_OK || pl.d.Hkv > SPECKV_MAX_ADA_HEADS) return 0;
-  Plan pruned = pl;
-  return prune_plan(&pruned, 0, true) ? pruned.total_pruned : pl.total_ada;
+  return workspace_of(pl, 0, true);
 }
 
 static speckv_status ada_plan(const speckv_params *p, int32_t c_floor, Plan *pl) {
@@ -604,6 +642,8 @@ speckv_status speckv_compress_ada(const speckv_params *p, int32_t c_floor, const
   Plan pruned = pl;
   if (prune_plan(&pruned, 0, true) && workspace_bytes >= pruned.total_pruned) {
     pl = pruned;
+    planes = reinterpret_cast<float *>(ws + pl.off_planes);
+    pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
     uint32_t *hist0 = reinterpret_cast<uint32_t *>(ws + pl.off_hist0);
     const PruneRow *rows = reinterpret_cast<const PruneRow *>(ws + pl.off_prune_rows);
     if ((e = launch_prune_rows(pl, q, k, workspace, hs, nullptr, hist0, pl.hist0_words)) != hipSuccess ||
@@ -645,9 +685,12 @@ static speckv_status select_tokens_impl(const speckv_params *p, int32_t top_k, i
   int32_t *sel = reinterpret_cast<int32_t *>(ws + pl.off_sel);
   hipError_t e;
   Plan pruned = pl;
-  const bool prune = top_k > 0 && prune_plan(&pruned, top_k) && workspace_bytes >= pruned.total_pruned;
+  const bool prune = prune_plan(&pruned, top_k) && workspace_bytes >= pruned.total_pruned;
   if (prune) {
     pl = pruned;
+    planes = reinterpret_cast<float *>(ws + pl.off_planes);
+    pooled = reinterpret_cast<float *>(ws + pl.off_pooled);
+    sel = reinterpret_cast<int32_t *>(ws + pl.off_sel);
     if ((e = launch_prune_rows(pl, q, k, workspace, hs, ev, nullptr, 0)) != hipSuccess) return SPECKV_ERR_RUNTIME;
   } else if ((e = launch_score(pl, q, k, reinterpret_cast<float2 *>(ws + pl.off_part),
                                reinterpret_cast<float *>(ws + pl.off_lse), planes, hs, ev)) != hipSuccess) {
@@ -656,7 +699,7 @@ static speckv_status select_tokens_impl(const speckv_params *p, int32_t top_k, i
   // a long row is ranked by several workgroups: its pooling is a pass of its own, which counts the first digit (scratch over
   // the partial pairs and the planes, which are read no more)
   uint32_t *scratch = reinterpret_cast<uint32_t *>(ws + pl.off_part);
-  const SelectParts sp = row_parts_of(m, count, (prune ? pl.off_squares : pl.off_lse) - pl.off_part);
+  const SelectParts sp = row_parts_of(m, count, pl.off_lse - pl.off_part);
   if (prune) {                            // (what has to be computed shows in the counts, which any row has then)
     if ((e = launch_prune_token_columns(pl, q, k, workspace, scratch, hs)) != hipSuccess) return SPECKV_ERR_RUNTIME;
     if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return SPECKV_ERR_RUNTIME;
@@ -714,7 +757,7 @@ size_t specpc_compress_workspace_bytes(const speckv_params *p, int32_t l_skip) {
   Plan pl;
   speckv_params eff;
   if (alg2_plan(p, l_skip, &pl, &eff) != SPECKV_OK) return 0;
-  return pl.total;
+  return workspace_of(pl, 0, false);
 }
 
 speckv_status specpc_compress_prompt(const speckv_params *p, int32_t l_skip, int32_t n_neighbor,

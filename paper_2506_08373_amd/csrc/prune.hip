@@ -71,16 +71,27 @@ __global__ __launch_bounds__(kRefThreads) void prune_reference_kernel(PruneArgs 
   const int unit_row = blockIdx.x * kRefThreads + threadIdx.x, unit = unit_row / RSB, r = unit_row % RSB;
   if (unit >= d.L * d.Hkv * A.g.RS) return;
   const int first = A.t.cc[s], n = A.t.cc[s + 1] - first;
-  const float2 *pairs = A.part + (int64_t)unit * A.g.n_chunks * RSB + r;
+  float2 *pairs = A.part + (int64_t)unit * A.g.n_chunks * RSB + r;
   const float *squares = A.squares + (int64_t)unit * A.g.n_fast_chunks * RSB + r;
   const float2 tail = pairs[(int64_t)(A.g.n_fast_chunks + s) * RSB];
   float top = kNegBig, sum = 0.f, square = 0.f;            // of the sample, in units of its largest term
-  for (int e = 0; e < n; ++e) {
-    const float2 p = pairs[(int64_t)(first + e) * RSB];
-    const float m = fmaxf(top, p.x), f1 = __builtin_amdgcn_exp2f(top - m), f2 = __builtin_amdgcn_exp2f(p.x - m);
-    sum = sum * f1 + p.y * f2;
-    square = square * f1 * f1 + squares[(int64_t)(first + e) * RSB] * f2 * f2;
-    top = m;
+  for (int e0 = 0; e0 < n; e0 += kMergeNext) {
+    float2 in[kMergeNext];
+    float sq[kMergeNext];
+#pragma unroll
+    for (int u = 0; u < kMergeNext; ++u) {
+      in[u] = e0 + u < n ? pairs[(int64_t)(first + e0 + u) * RSB] : make_float2(kNegBig, 0.f);
+      sq[u] = e0 + u < n ? squares[(int64_t)(first + e0 + u) * RSB] : 0.f;
+    }
+    const float before = top;
+    merge_pairs<kMergeNext>(top, sum, in);
+    const float f = __builtin_amdgcn_exp2f(before - top);
+    square *= f * f;
+#pragma unroll
+    for (int u = 0; u < kMergeNext; ++u) {
+      const float fu = __builtin_amdgcn_exp2f(in[u].x - top);
+      square = __builtin_fmaf(sq[u] * fu, fu, square);
+    }
   }
   const int step = prune_step(A.chunk_of[s]), tiles = A.t.tail0[s] / tile_keys, sampled = (tiles + (1 << step) - 1) >> step;
   const float ratio = sampled > 0 ? (float)tiles / (float)sampled : 1.f;
@@ -91,6 +102,8 @@ __global__ __launch_bounds__(kRefThreads) void prune_reference_kernel(PruneArgs 
   const int64_t at = ((int64_t)lh * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + r;
   A.lse[at] = m + log2f(all);
   A.row_extra[at] = seen / all;
+  // the sample's pairs have served, and the chunks' places are free for those of the other keys
+  pairs[(int64_t)(A.g.n_fast_chunks + s) * RSB] = make_float2(m, seen);
 }
 
 constexpr int kThrThreads = 1024, kThrEach = 8;

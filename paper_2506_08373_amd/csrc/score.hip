@@ -23,7 +23,7 @@ constexpr int kMergeRows = 64;
 // workgroups' reads (the same pairs again for every chunk) outgrow the launch.
 constexpr int kMergeInSweep = 40;
 
-// row_extra: of a pruned call, whose chunks have a second pair each and whose first references stand in A.lse (score_prune.hip).
+// row_extra: of a pruned call, whose first references stand in A.lse (score_prune.hip).
 template <int SLICES>
 __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreArgs A, float *row_extra) {
   clear_scratch(A, ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
@@ -38,10 +38,7 @@ __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreA
   const int s = blockIdx.y;
   const int rs = unit % A.g.RS;
   const int lh = unit / A.g.RS;                       // layer * Hkv + head
-  const int n_first = A.t.cc[s + 1] - A.t.cc[s] + 1, n_entries = row_extra != nullptr ? 2 * n_first - 1 : n_first;
-  auto slot = [&](int e) {
-    return e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1 + (e < n_first ? 0 : A.g.n_fast_chunks + d.S - n_first + 1);
-  };
+  const int n_entries = A.t.cc[s + 1] - A.t.cc[s] + 1;
   const float2 *pp = A.part + ((int64_t)unit * A.g.n_chunks) * RSB + r;
   float top = kNegBig, sum = 0.f;
   constexpr int BATCH = kMergeFirst / SLICES;         // entries requested together
@@ -50,7 +47,7 @@ __global__ __launch_bounds__(kMergeRows * SLICES) void lse_combine_kernel(ScoreA
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
       const int e = e0 + u * SLICES;
-      in[u] = e < n_entries ? pp[(int64_t)slot(e) * RSB] : make_float2(kNegBig, 0.f);
+      in[u] = e < n_entries ? pp[(int64_t)(e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1) * RSB] : make_float2(kNegBig, 0.f);
     }
     if (e0 == slice) {
       merge_pairs(top, sum, in);

@@ -81,8 +81,6 @@ __device__ __forceinline__ PruneChunk prune_chunk(const PruneArgs &A, int bid) {
 __device__ __forceinline__ int other_tile(int tile, int step_log) {
   return tile + 1 + (int)((unsigned)tile / ((1u << step_log) - 1u));
 }
-// Place of the pairs over a chunk's other keys, behind those of all samples and tails.
-__device__ __forceinline__ int other_pairs(const PruneArgs &A, int chunk) { return A.g.n_fast_chunks + A.d.S + chunk; }
 
 // Zeroes A.clear (if any), the work spread over every thread of the grid; id: the thread's number in it.
 __device__ inline void clear_scratch(const ScoreArgs &A, int64_t id, int64_t n_threads) {
@@ -202,9 +200,9 @@ struct Tile {
 // The two sweeps over all chunks and masked tails of a call (score_rows.hip, score_cols.hip).
 hipError_t launch_row_statistics_sweep(const ScoreArgs &A, hipStream_t st);
 hipError_t launch_column_sweep(const ScoreArgs &A, hipStream_t st);
-// Merges the partial pairs of every row into A.lse; row_extra: not null in a pruned call, whose other keys have pairs, too (score.hip).
+// Merges the partial pairs of every row into A.lse; row_extra: not null in a pruned call, see there (score.hip).
 hipError_t launch_lse_combine(const ScoreArgs &A, float *row_extra, hipStream_t st);
-// First references of a pruned call, into A.lse and A.row_extra (prune.hip).
+// First references of a pruned call, into A.lse and A.row_extra; the samples' pairs join the tails' (prune.hip).
 hipError_t launch_prune_references(const PruneArgs &A, int tile_keys, hipStream_t st);
 bool qs_supported(const ScoreArgs &A, int pass);
 hipError_t launch_qs_sweep(const ScoreArgs &A, int pass, hipStream_t st);

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(512) void prune_repair_kernel(PruneArgs A) {
   __syncthreads();
   if (threadIdx.x < MB * 32) {
     const int r = threadIdx.x;
-    float2 *slot = A.part + ((int64_t)c.unit * A.g.n_chunks + other_pairs(A, c.chunk)) * RSB + block_of(r >> 5) * 32 + (r & 31);
+    float2 *slot = A.part + ((int64_t)c.unit * A.g.n_chunks + c.chunk) * RSB + block_of(r >> 5) * 32 + (r & 31);
     float2 have = *slot;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) merge_pairs<1>(have.x, have.y, &pairs[w][r]);
@@ -189,7 +189,7 @@ hipError_t launch(Sweep which, const PruneArgs &A, hipStream_t st) {
   return A.d.D == 128 ? launch_for_type<kF16, 128>(which, A, st) : launch_for_type<kF16, 64>(which, A, st);
 }
 
-int64_t prune_rows(const Plan &pl) { return pl.prune_keep != 0 ? 1 : (int64_t)pl.d.L * pl.d.S * pl.d.Hkv; }
+int64_t prune_rows(const Plan &pl) { return pl.one_row ? 1 : (int64_t)pl.d.L * pl.d.S * pl.d.Hkv; }
 
 // The buffers of a pruned call.
 struct Buffers {
@@ -204,10 +204,10 @@ struct Buffers {
     rows = reinterpret_cast<PruneRow *>(ws + pl.off_prune_rows);
     n_items = reinterpret_cast<int32_t *>(rows + prune_rows(pl));
     items = reinterpret_cast<int2 *>(ws + pl.off_prune_items);
-    list = reinterpret_cast<int32_t *>(ws + pl.off_pooled);      // read before the pooled scores are written
+    list = reinterpret_cast<int32_t *>(ws + pl.off_pooled);      // written after the pairs, read before the pooled scores are written
     A.d = pl.d; A.t = pl.t; A.g = pl.g;
     A.q = (const char *)q; A.k = (const char *)k;
-    A.part = reinterpret_cast<float2 *>(ws + pl.off_part);
+    A.part = reinterpret_cast<float2 *>(ws + pl.off_prune_pairs);
     A.lse = reinterpret_cast<float *>(ws + pl.off_lse);
     A.planes = planes; A.lse_in = nullptr; A.clear = nullptr; A.clear_words = 0;
     A.norm_from = kNormMerged;
@@ -226,11 +226,26 @@ struct Buffers {
 
 }  // namespace
 
-// Chunks of a sequence of n unmasked keys when none is longer than kc: equal ones, of whole periods of the sample.
+// The most chunks a pruned call is cut into: about kPruneRounds rounds of the CUs, or as many as the call has anyway.  Shorter ones even out the end
+// of the sweep a little better (model, one sequence of 4K to 250K: 3 % in one of 100 calls), but take room in the workspace, whose size
+// has to be that of the longest prompt whatever the number of chunks of a shorter one.
+constexpr int kPruneRounds = 12, kPruneChunkMin = 512;
+static int64_t prune_most_chunks(const Plan &pl) {
+  const int64_t units = (int64_t)pl.d.L * pl.d.Hkv * pl.g.RS;
+  int64_t of_min = 0;
+  for (int s = 0; s < pl.d.S; ++s) of_min += (pl.t.tail0[s] + kPruneChunkMin - 1) / kPruneChunkMin;
+  return std::max(pl.most_chunks, std::min((kPruneRounds * 256 + units - 1) / units + pl.d.S - 1, of_min));
+}
+
+// Chunks of a sequence when none is longer than kc: equal ones, of whole periods of the sample.  (Of a sequence that is all sample a
+// workgroup has every key to do, and they should not be the last ones of the sample's sweep.)
 struct Chunks { int count, keys; };
-static Chunks prune_chunks(const Plan &pl, int64_t n, int step, int64_t kc) {
+static Chunks prune_chunks(const Plan &pl, int s, int step, int64_t kc) {
+  const int64_t n = pl.t.tail0[s];
   if (n == 0) return {0, prune_tile_keys(pl)};
-  const int64_t count = (n + kc - 1) / kc, keys = align_up((n + count - 1) / count, (int64_t)prune_tile_keys(pl) << step);
+  if (step == 0) kc = std::min<int64_t>(kc, std::max(4096, pl.g.KC));
+  const int64_t count = (n + kc - 1) / kc;
+  const int64_t keys = std::max<int64_t>(align_up((n + count - 1) / count, (int64_t)prune_tile_keys(pl) << step), kPruneChunkMin);
   return {(int)((n + keys - 1) / keys), (int)keys};
 }
 
@@ -250,7 +265,7 @@ static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) 
     double total = 0., shortest = 1e30;
     for (int s = 0; s < pl.d.S; ++s) {
       if (step[s] == 0) continue;
-      const Chunks c = prune_chunks(pl, pl.t.tail0[s], step[s], kc);
+      const Chunks c = prune_chunks(pl, s, step[s], kc);
       todo[n_todo++] = {std::min(c.keys, pl.t.tail0[s]) + kCost, c.count * units};
       total += todo[n_todo - 1].first * (double)todo[n_todo - 1].second;
       shortest = std::min(shortest, todo[n_todo - 1].first);
@@ -280,8 +295,17 @@ static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) 
     return free_at[n_free - 1].first;
   };
   static const int parts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128};
-  double best = 1e30, took[sizeof(parts) / sizeof(parts[0])];
-  for (size_t i = 0; i < sizeof(parts) / sizeof(parts[0]); ++i) best = std::min(best, took[i] = duration((longest + parts[i] - 1) / parts[i]));
+  constexpr size_t kParts = sizeof(parts) / sizeof(parts[0]);
+  const int64_t most = prune_most_chunks(pl);            // (at least as many as one chunk a sequence with a sample makes)
+  double best = 1e30, took[kParts];
+  size_t n = 0;
+  for (; n < kParts; ++n) {
+    const int64_t kc = (longest + parts[n] - 1) / parts[n];
+    int64_t chunks = 0;
+    for (int s = 0; s < pl.d.S; ++s) chunks += prune_chunks(pl, s, step[s], kc).count;
+    if (n > 0 && chunks > most) break;
+    best = std::min(best, took[n] = duration(kc));
+  }
   size_t i = 0;
   while (took[i] > 1.03 * best) ++i;
   return (longest + parts[i] - 1) / parts[i];
@@ -302,27 +326,71 @@ static int prune_saving(int64_t m, int64_t c_max) {
   return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= 7 * c_max ? 12 : 0;
 }
 
+// Whether a call is pruned, each sequence's sample step and the keys of those that have one.
+static bool prune_pays(const Plan &pl, int32_t keep, bool ada, int *step, int64_t *pruned) {
+  const Dims &d = pl.d;
+  const ScoreGeom &g = pl.g;
+  if (d.elt != 2 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
+      (pl.one_row ? keep < 1 : d.c_max < 1))
+    return false;
+  const int64_t c_max = pl.one_row ? keep : d.c_max;
+  int64_t saved = 0;
+  *pruned = 0;
+  for (int s = 0; s < d.S; ++s) {
+    const int64_t m = pl.t.cu[s + 1] - pl.t.cu[s] - d.w;
+    const int saving = prune_saving(m, c_max);
+    // (the sum over all layers and heads has closer bounds: 7 % of 64K keys are listed with a sample of 1/4, 9 % with 1/8)
+    step[s] = saving == 0 ? 0 : m < 24000 || (!pl.one_row && m < 16 * c_max) ? 2 : pl.one_row || m < 48 * c_max || m < 60000 ? 3 : 4;
+    if (saving != 0) *pruned += pl.t.tail0[s];
+    saved += (int64_t)pl.t.tail0[s] * saving / 100;
+  }
+  const int64_t least = kPruneMinSaving * (pl.one_row || ada || g.MB == 1 ? 3 : 2) / 2 + kPruneMinPerSeq * (d.S - 1);
+  if (saved * d.L * d.Hkv * ((d.M + 31) / 32) < least) return false;
+  const int64_t most = 0x7fffffff / 8, units = (int64_t)d.L * d.Hkv * g.RS;           // workgroups of a launch
+  return score_chunk_workgroups(d, g, prune_most_chunks(pl)) <= most && units * d.S <= most && prune_rows(pl) * (d.T / 4096 + 1) <= most;
+}
+
+// Lays out the workspace of a pruned call of up to `chunks` unmasked chunks, in a workspace with room for `all` of a call that is not.  The
+// pairs and the samples' squares are read for the last time before the lists are written, in the place of the pooled scores.
+static void prune_carve(Plan *pl, bool ada, const int *step, int64_t chunks, int64_t all) {
+  const Dims &d = pl->d;
+  const ScoreGeom &g = pl->g;
+  const size_t units = (size_t)d.L * d.Hkv * g.RS;
+  const size_t pairs = (size_t)align_up((int64_t)(units * (chunks + d.S) * g.RSB * sizeof(float2) +
+                                                  (size_t)score_fail_words(d, g, chunks) * sizeof(int32_t)), 256);
+  carve_workspace(pl, all, pairs + units * chunks * g.RSB * sizeof(float));
+  pl->off_prune_pairs = pl->off_pooled;
+  pl->off_squares = pl->off_pooled + pairs;
+  size_t off = ada ? pl->total_ada : pl->total;
+  auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
+  pl->off_row_extra = take(units * d.S * g.RSB * sizeof(float));
+  pl->off_prune_rows = take((size_t)prune_rows(*pl) * sizeof(PruneRow) + 2 * sizeof(int32_t));
+  int64_t items = 0;
+  for (int s = 0; s < d.S; ++s)
+    if (step[s] != 0) items += (pl->t.tail0[s] + kPruneItemMin - 1) / kPruneItemMin;
+  pl->off_prune_items = take((size_t)(items * (pl->one_row ? 1 : d.L * d.Hkv)) * sizeof(int2));
+  pl->total_pruned = off;
+}
+
+size_t prune_workspace(const Plan &pl, int32_t keep, bool ada) {
+  int step[kMaxSeqs];
+  int64_t pruned;
+  if (!prune_pays(pl, keep, ada, step, &pruned)) return 0;
+  Plan most = pl;
+  most.sel_parts = pl.most_sel_parts;
+  prune_carve(&most, ada, step, prune_most_chunks(pl), pl.most_chunks);
+  return most.total_pruned;
+}
+
 bool prune_plan(Plan *pl, int32_t keep, bool ada) {
   Dims &d = pl->d;
   ScoreGeom &g = pl->g;
-  if (d.elt != 2 || g.NW != 8 || g.PPH != 1 || d.pool_avg || d.head_max || d.pool_k > 16 || d.n_dev != nullptr ||
-      (keep == 0 && (pl->hist0_words == 0 || d.c_max < 1)))
-    return false;
-  pl->prune_keep = keep;
-  const int64_t c_max = keep != 0 ? keep : d.c_max;
-  const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
-  int64_t pruned = 0, saved = 0;
   int step[kMaxSeqs];
-  for (int s = 0; s < d.S; ++s) {
-    const int64_t m = pl->t.cu[s + 1] - pl->t.cu[s] - d.w;
-    const int saving = prune_saving(m, c_max);
-    // (the sum over all layers and heads has closer bounds: 7 % of 64K keys are listed with a sample of 1/4, 9 % with 1/8)
-    step[s] = saving == 0 ? 0 : m < 24000 || (keep == 0 && m < 16 * c_max) ? 2 : keep != 0 || m < 48 * c_max || m < 60000 ? 3 : 4;
-    if (saving != 0) pruned += pl->t.tail0[s];
-    saved += (int64_t)pl->t.tail0[s] * saving / 100;
-  }
-  const int64_t least = kPruneMinSaving * (keep != 0 || ada || g.MB == 1 ? 3 : 2) / 2 + kPruneMinPerSeq * (d.S - 1);
-  if (saved * d.L * d.Hkv * ((d.M + 31) / 32) < least) return false;
+  int64_t pruned;
+  // (rows that are ranked in parts have no counts of first digits)
+  if ((!pl->one_row && pl->hist0_words == 0) || !prune_pays(*pl, keep, ada, step, &pruned)) return false;
+  pl->prune_keep = pl->one_row ? keep : 0;
+  const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
   // About a tenth of the keys is listed: an item per CU, if that makes items short.  (Twice as many of half the size measure the same, 8 layers
   // x 32K, shared budget: 80 us for the listed sweep.)
   pl->item_keys = kPruneItemMax;
@@ -330,7 +398,7 @@ bool prune_plan(Plan *pl, int32_t keep, bool ada) {
   const int64_t kc = prune_chunk_keys(*pl, step, units);
   int cc = 0;
   for (int s = 0; s < d.S; ++s) {
-    const Chunks c = prune_chunks(*pl, pl->t.tail0[s], step[s], step[s] != 0 ? kc : std::min<int64_t>(kc, 4096));
+    const Chunks c = prune_chunks(*pl, s, step[s], kc);
     pl->t.cc[s] = cc;
     cc += c.count;
     pl->chunk_of[s] = c.keys + step[s];
@@ -341,21 +409,9 @@ bool prune_plan(Plan *pl, int32_t keep, bool ada) {
     return pl->chunk_of[a] != pl->chunk_of[b] ? pl->chunk_of[a] > pl->chunk_of[b] : a < b;
   });
   pl->t.cc[d.S] = cc;
-  const int64_t most = 0x7fffffff / 8;                    // workgroups of a launch
-  if (score_chunk_workgroups(d, g, cc) > most || units * d.S > most || prune_rows(*pl) * (d.T / 4096 + 1) > most) return false;
   g.n_fast_chunks = cc;
-  g.n_chunks = 2 * cc + d.S;
-  size_t off = ada ? pl->total_ada : pl->total;
-  auto take = [&](size_t bytes) { size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
-  pl->off_part = take((size_t)units * g.n_chunks * g.RSB * sizeof(float2) + (size_t)score_fail_words(d, g, cc) * sizeof(int32_t));
-  pl->off_squares = take((size_t)units * cc * g.RSB * sizeof(float));
-  pl->off_row_extra = take((size_t)units * d.S * g.RSB * sizeof(float));
-  pl->off_prune_rows = take((size_t)prune_rows(*pl) * sizeof(PruneRow) + 2 * sizeof(int32_t));
-  int64_t items = 0;
-  for (int s = 0; s < d.S; ++s)
-    if (step[s] != 0) items += (pl->t.tail0[s] + kPruneItemMin - 1) / kPruneItemMin;
-  pl->off_prune_items = take((size_t)(items * (keep != 0 ? 1 : d.L * d.Hkv)) * sizeof(int2));
-  pl->total_pruned = off;
+  g.n_chunks = cc + d.S;
+  prune_carve(pl, ada, step, cc, pl->room_chunks);
   return true;
 }
 

@@ -1185,7 +1185,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     int e2;
     const float sum = own_sum[own], lf = __builtin_frexpf(sum, &e2);
     if (l32 < MB * 16)
-      A.part[((int64_t)unit * A.g.n_chunks + other_pairs(A, chunk)) * RSB + block_of(own_rb) * 32 + (own & 31)] =
+      A.part[((int64_t)unit * A.g.n_chunks + chunk) * RSB + block_of(own_rb) * 32 + (own & 31)] =
           sum > 0.f ? make_float2((float)e2 - own_ref[own], lf) : make_float2(kNegBig, 0.f);
   }
   if (PASS == 1) {

@@ -61,17 +61,18 @@ struct Plan {
   Dims d;
   SeqTab t;
   ScoreGeom g;
-  // workspace carve-up (byte offsets, 256-aligned)
+  // workspace carve-up (byte offsets, 256-aligned): carve_workspace
+  int32_t one_row, sel_kept;               // prompt tokens: one output row for all layers and heads, tokens kept in it
+  int64_t room_chunks, most_chunks;        // unmasked chunks that there is room for; the most of any prompt no longer than this one
   size_t off_part, off_lse, off_planes, off_pooled, off_pooled2, off_sel, total;
   size_t off_ada_hist, off_ada_state, total_ada;   // extra scratch of the shared-budget selection
   // selection of long rows in calls with few rows: parts per row (1: not split), keys per part, scratch
-  int32_t sel_parts, sel_part_len;
+  int32_t sel_parts, sel_part_len, most_sel_parts;       // most_sel_parts: of any prompt
   size_t off_sel_hist, off_sel_state;
-  // pruned scoring (score_prune.hip): sample step of every sequence, and scratch behind everything else
+  // pruned scoring (score_prune.hip): sample step of every sequence; the pairs, in the pooled scores' place; scratch behind everything else
   int32_t chunk_of[kMaxSeqs], order[kMaxSeqs];     // see PruneArgs
   int32_t item_keys, prune_keep;                   // prune_keep: of prompt tokens, else 0
-  size_t off_prune_items, off_prune_rows, off_squares, off_row_extra, total_pruned;
-  int64_t prune_items;
+  size_t off_prune_items, off_prune_rows, off_prune_pairs, off_squares, off_row_extra, total_pruned;
   // first-digit histograms of the pooled rows (2048 counters per row), filled by the pooling kernel
   // of a fused call so that selection starts at the second read; hist0_words == 0: not used
   size_t off_hist0;
@@ -112,6 +113,9 @@ __device__ inline int live_tail0(const Dims &d, const SeqTab &t, int s, int n, i
   const int visible = n - d.w + 1 < n ? n - d.w + 1 : n;
   return visible / kt * kt;
 }
+
+// Lays out the workspace of a call with up to `chunks` unmasked chunks; pooled: the least bytes for pooled scores.
+void carve_workspace(Plan *pl, int64_t chunks, size_t pooled = 0);
 
 // Raises a kernel's dynamic LDS limit; the runtime call is made once per (device, kernel, size)
 // and remembered (score.hip).
@@ -221,6 +225,8 @@ inline int prune_tile_keys(const Plan &pl) { return pl.d.D == 64 && pl.g.MB == 2
 // Turns the plan of a fused call into one of a pruned call where that is faster; false: it is not.
 // ada: for a shared budget (scratch behind that of the selection).  keep: 0, or the tokens kept by a call for prompt tokens, whose layers and heads have one output row.
 bool prune_plan(Plan *pl, int32_t keep = 0, bool ada = false);
+// Bytes of workspace with which such a call is pruned, and every one with prompts no longer (0: it is not).
+size_t prune_workspace(const Plan &pl, int32_t keep, bool ada);
 // Row statistics over the sample, then the sweep over the other keys (bounds into the planes), then the normalisers
 // (clear: see launch_score).
 hipError_t launch_prune_rows(const Plan &pl, const void *q, const void *k, void *ws, hipStream_t st, hipEvent_t *events,

@@ -346,6 +346,26 @@ def test_workspace_of_a_prompt_suffices_for_every_shorter_one(lib, units, d, dty
                 before = now
 
 
+@pytest.mark.parametrize("heads,kv_heads,d,rows,n_layers,c_max", [
+    (32, 8, 128, 128, 3, 512), (32, 8, 128, 128, 32, 2048), (32, 8, 128, 128, 1, 1024), (28, 4, 128, 69, 13, 2048), (28, 4, 128, 128, 28, 512),
+    (16, 1, 128, 80, 27, 256), (16, 1, 128, 88, 1, 256), (32, 8, 64, 128, 18, 512), (32, 8, 64, 128, 2, 1024), (8, 2, 64, 96, 67, 256),
+    (8, 2, 64, 96, 29, 256),
+])
+def test_workspace_of_a_long_prompt_suffices_for_every_shorter_one(lib, heads, kv_heads, d, rows, n_layers, c_max):
+    """How many chunks a prompt is cut into goes up and down with its length, and with it the scratch of a call, pruned or not."""
+    def params(*lens):
+        return S.SpecKVParams(n_layers=n_layers, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=d, seq_lens=lens, n_window=64,
+                              n_lookahead=rows - 64, pool_k=7, c_max=c_max, sm_scale=0.1, dtype=torch.bfloat16)
+    for lens in ([(n,) for n in range(700, 140000, 509)] + [(n,) for n in range(140000, 600000, 9973)],
+                 [(n, 17001, 700) for n in range(700, 90000, 1021)]):
+        before = (0, 0, 0)
+        for ls in lens:
+            p = params(*ls)
+            now = (S.workspace_bytes(p), S.ada_workspace_bytes(p), S.specpc_workspace_bytes(p, c_max) if len(ls) == 1 else 0)
+            assert all(x >= y for x, y in zip(now, before)), (ls, now, before)
+            before = now
+
+
 def test_plain_c_caller(lib, repo_root, tmp_path):
     """The header and the library from a C99 program (host-side entry points only)."""
     import shutil
