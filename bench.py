@@ -310,13 +310,7 @@ def main() -> int:
     k_bytes = float(w.total_tokens) * H * d * elt * L                      # K read once
     peak_mfma = PEAK_MFMA_TFLOPS[w.dtype]
     kernels = {}
-    # a call that computes exact scores only where they matter has scratch of its own (averages, or keeping all, need every score)
-    if specpc:
-        pruned = S.specpc_workspace_bytes(p, top_k) > S.specpc_workspace_bytes(p, n) - 4 * (n - top_k)
-    else:
-        every = S.SpecKVParams.for_tensors(q, k, seq_lens=w.seq_lens, n_window=w.n_window, pool_k=w.pool_k, c_max=w.c_max,
-                                           sm_scale=w.sm_scale, reduce=reduce, pool="avg")
-        pruned = S.workspace_bytes(p) > S.workspace_bytes(every)
+    pruned = bool(S.prune_info(p, "tokens" if specpc else "compress", top_k if specpc else 0)["pruned"])
     for name, ms in zip(stage_names, mean_ms):
         entry = {"ms": round(float(ms), 4)}
         if pruned and name in PRUNED_NOTES:

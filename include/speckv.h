@@ -166,10 +166,26 @@ size_t speckv_workspace_bytes(const speckv_params *p);
  * when the column-reduction sweep keeps the query rows stationary in LDS (clear: key tiles streamed
  * through LDS), [9] 1 for max reduction, [10] 1 when the key-tile row-statistics sweep sums
  * against fixed reference exponents and is followed by a repair launch (sweeps of several rounds of
- * workgroups), 0 when it takes the online maximum step on every key block.  Returns SPECKV_OK or
- * the reason the parameters are rejected. */
+ * workgroups), 0 when it takes the online maximum step on every key block.  [3], [4], [8] and [10] are
+ * those of a call that computes every score, speckv_score for one; for a fused call that does not see
+ * speckv_prune_info.  Returns SPECKV_OK or the reason the parameters are rejected. */
 #define SPECKV_PLAN_INFO_WORDS 11
 speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_INFO_WORDS]);
+
+/* Whether a fused call with these parameters computes exact scores only for keys that can be kept, and
+ * how, for diagnostics and tests (no GPU needed).  call: speckv_fused_call; top_k: of the prompt tokens'
+ * call, else ignored.  info[0] 1 if it does, given the workspace of [1] bytes or more; all words are 0 if not.  [2] unmasked chunks over all sequences, [3] keys of the longest one, [4] in the longest
+ * sequence every [4]-th tile, the first one among them, is in the sample whose scores are all computed, [5] keys per tile.
+ * What the call leaves in the workspace, by byte offsets: [6] the output rows, [7] of them, in the
+ * order layer, sequence, head (prompt tokens: one), 32 bytes each: float, the bound from which keys were listed
+ * (negative: every one); int32, the first digit that the kept scores have to reach; int32 keys listed; int32 1 where
+ * fewer scores than are kept reached it and every key was computed.  [8] the row normalisers, fp32 log2,
+ * [layer][head][sequence][row of the group's super-blocks].  Returns SPECKV_OK or the reason the parameters
+ * are rejected. */
+typedef enum { SPECKV_CALL_COMPRESS = 0, SPECKV_CALL_ADA = 1, SPECKV_CALL_TOKENS = 2 } speckv_fused_call;
+#define SPECKV_PRUNE_INFO_WORDS 9
+speckv_status speckv_prune_info(const speckv_params *p, int32_t call, int32_t top_k,
+                                int64_t info[SPECKV_PRUNE_INFO_WORDS]);
 
 /* Importance scores (Eq. 1; Alg. 1 CrossAttention, reduce and pooling steps).
  * For every (layer, sequence, KV head): softmax over the visible prompt keys of

@@ -13,6 +13,7 @@ from .binding import (  # noqa: F401
     n_keep,
     plan_info,
     probe_ceiling,
+    prune_info,
     select_workspace_bytes,
     specpc_compress_prompt,
     specpc_compress_workspace_bytes,

@@ -49,7 +49,7 @@ EXPORTS = ("speckv_status_string", "speckv_n_keep", "speckv_total_keep", "speckv
            "specpc_workspace_bytes", "specpc_select_tokens", "specpc_compress_workspace_bytes",
            "specpc_compress_prompt", "speckv_ada_workspace_bytes", "speckv_select_ada",
            "speckv_compact_ada", "speckv_compress_ada", "speckv_plan_info", "speckv_compress_static",
-           "specpc_select_tokens_events", "speckv_select_workspace_bytes", "speckv_probe_ceiling")
+           "specpc_select_tokens_events", "speckv_select_workspace_bytes", "speckv_probe_ceiling", "speckv_prune_info")
 
 
 def library_path() -> str:
@@ -97,6 +97,8 @@ def load_library() -> ctypes.CDLL:
                                            ctypes.POINTER(ctypes.c_void_p), ctypes.c_int32]
     lib.speckv_plan_info.restype = ctypes.c_int
     lib.speckv_plan_info.argtypes = [P, ctypes.POINTER(ctypes.c_int64)]
+    lib.speckv_prune_info.restype = ctypes.c_int
+    lib.speckv_prune_info.argtypes = [P, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64)]
     lib.speckv_ada_workspace_bytes.restype = ctypes.c_size_t
     lib.speckv_ada_workspace_bytes.argtypes = [P]
     lib.speckv_select_ada.restype = ctypes.c_int
@@ -288,6 +290,16 @@ def plan_info(p: SpecKVParams) -> dict:
     _check(load_library().speckv_plan_info(p.ref(), out), "speckv_plan_info")
     keys = ("waves", "blocks_per_wave", "row_super_blocks", "chunk_keys", "n_chunks", "tile_keys",
             "select_parts", "select_part_keys", "q_stationary", "reduce_max", "fixed_reference_rows")
+    return dict(zip(keys, (int(x) for x in out)))
+
+
+def prune_info(p: SpecKVParams, call: str = "compress", top_k: int = 0) -> dict:
+    """How a fused call ("compress", "ada" or "tokens") avoids computing every score, if it does (diagnostics; needs no GPU)."""
+    out = (ctypes.c_int64 * 9)()
+    _check(load_library().speckv_prune_info(p.ref(), ("compress", "ada", "tokens").index(call), int(top_k), out),
+           "speckv_prune_info")
+    keys = ("pruned", "workspace_bytes", "n_chunks", "chunk_keys", "sample_step", "tile_keys", "rows_at", "n_rows",
+            "normalisers_at")
     return dict(zip(keys, (int(x) for x in out)))
 
 

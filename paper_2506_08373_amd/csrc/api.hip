@@ -389,6 +389,31 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
   return SPECKV_OK;
 }
 
+speckv_status speckv_prune_info(const speckv_params *p, int32_t call, int32_t top_k, int64_t info[SPECKV_PRUNE_INFO_WORDS]) {
+  if (p == nullptr || info == nullptr || call < SPECKV_CALL_COMPRESS || call > SPECKV_CALL_TOKENS) return SPECKV_ERR_INVALID_ARG;
+  const bool tokens = call == SPECKV_CALL_TOKENS, ada = call == SPECKV_CALL_ADA;
+  if (tokens && top_k < 0) return SPECKV_ERR_INVALID_ARG;
+  speckv_params eff = *p;
+  if (tokens) {
+    eff.reduce_op = SPECKV_REDUCE_SUM;
+    eff.pool_op = SPECKV_POOL_MAX;
+  }
+  Plan pl;
+  const speckv_status st = build_plan(&eff, &pl, tokens, tokens ? top_k : 0);
+  if (st != SPECKV_OK) return st;
+  if (ada && pl.d.Hkv > SPECKV_MAX_ADA_HEADS) return SPECKV_ERR_UNSUPPORTED;
+  std::memset(info, 0, SPECKV_PRUNE_INFO_WORDS * sizeof(info[0]));
+  if (!prune_plan(&pl, tokens ? top_k : 0, ada)) return SPECKV_OK;
+  int longest = 0;
+  for (int s = 1; s < pl.d.S; ++s)
+    if (pl.t.tail0[s] > pl.t.tail0[longest]) longest = s;
+  const int step = prune_step(pl.chunk_of[longest]);
+  info[0] = 1; info[1] = (int64_t)pl.total_pruned; info[2] = pl.g.n_fast_chunks; info[3] = pl.chunk_of[pl.order[0]] & ~7;
+  info[4] = (int64_t)1 << step; info[5] = prune_tile_keys(pl);
+  info[6] = (int64_t)pl.off_prune_rows; info[7] = tokens ? 1 : (int64_t)pl.d.L * pl.d.S * pl.d.Hkv; info[8] = (int64_t)pl.off_lse;
+  return SPECKV_OK;
+}
+
 size_t speckv_workspace_bytes(const speckv_params *p) {
   Plan pl;
   if (build_plan(p, &pl, false, 0) != SPECKV_OK) return 0;

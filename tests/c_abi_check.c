@@ -18,6 +18,8 @@ int main(void) {
 
   int64_t info[SPECKV_PLAN_INFO_WORDS];
   if (speckv_plan_info(&p, info) != SPECKV_OK) return 1;
+  int64_t pruned[SPECKV_PRUNE_INFO_WORDS];
+  if (speckv_prune_info(&p, SPECKV_CALL_COMPRESS, 0, pruned) != SPECKV_OK || pruned[0] != 1) return 7;
   if (speckv_n_keep(&p, 0) != 2048 + 64 || speckv_total_keep(&p) != 2112) return 2;
   if (speckv_workspace_bytes(&p) == 0) return 3;
   p.head_dim = 96;                                   /* unsupported head dimension */

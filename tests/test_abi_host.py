@@ -44,6 +44,27 @@ def test_plan_info_word_count_matches_the_header(repo_root):
     assert int(re.search(r"#define SPECKV_PLAN_INFO_WORDS (\d+)", header).group(1)) == PLAN_INFO_WORDS
 
 
+def test_prune_info_words_match_the_header_and_agree_with_the_queries(lib, repo_root):
+    header = open(os.path.join(repo_root, "include", "speckv.h")).read()
+    assert int(re.search(r"#define SPECKV_PRUNE_INFO_WORDS (\d+)", header).group(1)) == len(S.prune_info(base_params())) == 9
+    assert set(S.prune_info(base_params()).values()) == {0}
+    shape = dict(n_layers=16, n_q_heads=32, n_kv_heads=8, n_window=64, n_lookahead=64, sm_scale=0.1, dtype=torch.bfloat16)
+    for lens in ([131072], [70001], [60000, 5000, 300], [40000] * 3):
+        p = S.SpecKVParams(head_dim=128, seq_lens=lens, pool_k=7, c_max=1024, **shape)
+        info, ada = S.prune_info(p), S.prune_info(p, "ada")
+        assert info["pruned"] == ada["pruned"] == 1 and info["n_rows"] == 16 * 8 * len(lens) and info["tile_keys"] == 128
+        assert info["rows_at"] + 32 * info["n_rows"] < info["workspace_bytes"] <= S.workspace_bytes(p)
+        assert info["workspace_bytes"] < ada["workspace_bytes"] <= S.ada_workspace_bytes(p)
+        assert info["sample_step"] in (4, 8, 16) and info["n_chunks"] >= len([n for n in lens if n > 1000])
+        assert info["chunk_keys"] % (128 * info["sample_step"]) == 0
+    # a size that hides in the rounding of the token list's: 24000 tokens, 1000 kept
+    small = S.SpecKVParams(head_dim=64, seq_lens=[24000], pool_k=7, c_max=512, **{**shape, "n_layers": 4})
+    assert S.prune_info(small, "tokens", 1000)["pruned"] == 0
+    large = S.SpecKVParams(head_dim=64, seq_lens=[60000], pool_k=7, c_max=512, **shape)
+    assert S.prune_info(large, "tokens", 1000)["pruned"] == 1 and S.prune_info(large, "tokens", 59000)["pruned"] == 0
+    assert S.prune_info(large, "tokens", 1000)["n_rows"] == 1
+
+
 def test_status_strings(lib):
     assert lib.speckv_status_string(0) == b"ok"
     assert b"workspace" in lib.speckv_status_string(-3)

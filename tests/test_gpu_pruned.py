@@ -28,8 +28,7 @@ def params(S, q, k, lens, n_window, c_max, **kw):
 def check(S, q, k, lens, n_window, c_max, ws=None, **kw):
     L, T, H, d = k.shape
     p = params(S, q, k, lens, n_window, c_max, **kw)
-    assert ws is not None or S.workspace_bytes(p) > S.workspace_bytes(params(S, q, k, lens, n_window, c_max, **{**kw, "pool": "avg"})), \
-        "not a pruned call"
+    assert S.prune_info(p)["pruned"]
     KT = S.total_keep(p)
     ws = parity.alloc_ws(S, p) if ws is None else ws
     pooled = torch.empty(L, H * T, device="cuda")
@@ -143,8 +142,9 @@ def test_numbers_that_are_none(S):
 
 def test_a_workspace_without_room_for_it_is_enough(S):
     q, k = tensors([24897], 9)
-    avg = params(S, q, k, [24897], 32, 512, pool="avg")
-    check(S, q, k, [24897], 32, 512, ws=torch.empty(S.workspace_bytes(avg), dtype=torch.uint8, device="cuda"))
+    size = S.prune_info(params(S, q, k, [24897], 32, 512))["workspace_bytes"]
+    for room in (size, size - 1):
+        check(S, q, k, [24897], 32, 512, ws=torch.empty(room, dtype=torch.uint8, device="cuda"))
 
 
 def test_captured_and_replayed_on_other_inputs(S):
@@ -178,9 +178,9 @@ def test_prompt_tokens_are_those_of_complete_scores(S, n, n_layers, top_k, kw):
     p = params(S, q, k, [n], 32, 512)
     ids = torch.arange(n, dtype=torch.int32, device="cuda") * 3
     got = []
-    most = S.specpc_workspace_bytes(p, top_k)
-    assert most > S.specpc_workspace_bytes(p, n) - 4 * (n - top_k)                # (nothing to prune where all are kept)
-    for size in (most, most - 256, most):                                         # (no room for pruning in the second)
+    most = S.prune_info(p, "tokens", top_k)["workspace_bytes"]
+    assert most > 0
+    for size in (most, most - 1, most):                                           # (no room for pruning in the second)
         out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros(1, dtype=torch.int32, device="cuda")]
         S.specpc_select_tokens(p, top_k, 4, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
         count = int(out[2])
@@ -201,7 +201,9 @@ def test_prompt_tokens_whose_sample_misleads(S):
     p = params(S, q, k, [n], 32, 512)
     ids = torch.arange(n, dtype=torch.int32, device="cuda")
     got = []
-    for size in (S.specpc_workspace_bytes(p, 4000), S.specpc_workspace_bytes(p, 4000) - 256):
+    most = S.prune_info(p, "tokens", 4000)["workspace_bytes"]
+    assert most > 0
+    for size in (most, most - 1):
         out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros(1, dtype=torch.int32, device="cuda")]
         S.specpc_select_tokens(p, 4000, 0, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
         got.append(out)
@@ -227,10 +229,10 @@ def test_shared_budgets_are_those_of_complete_scores(S, lens, n_layers, c_floor,
         k[4, :32640, 1].view(-1, 128, 128)[::8] *= mislead
     p = params(S, q, k, lens, 32, 1024)
     H, KT = k.shape[2], S.total_keep(p)
-    most = S.ada_workspace_bytes(p)
-    assert most > S.ada_workspace_bytes(params(S, q, k, lens, 32, 1024, pool="avg"))
+    most = S.prune_info(p, "ada")["workspace_bytes"]
+    assert most > 0
     got = []
-    for size in (most, most - 256, most):                                     # (no room for pruning in the second)
+    for size in (most, most - 1, most):                                     # (no room for pruning in the second)
         idx = torch.full((n_layers, H * KT), -7, dtype=torch.int32, device="cuda")
         off = torch.full((n_layers, len(lens), H + 1), -7, dtype=torch.int32, device="cuda")
         k_out = torch.empty(n_layers, H * KT, 128, dtype=k.dtype, device="cuda")
