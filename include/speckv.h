@@ -174,7 +174,9 @@ speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_
 
 /* Whether a fused call with these parameters computes exact scores only for keys that can be kept, and
  * how, for diagnostics and tests (no GPU needed).  call: speckv_fused_call; top_k: of the prompt tokens'
- * call, else ignored.  info[0] 1 if it does, given the workspace of [1] bytes or more; all words are 0 if not.  [2] unmasked chunks over all sequences, [3] keys of the longest one, [4] in the longest
+ * call, else ignored.  info[0] 1 if it does, given the workspace of [1] bytes or more (SPECKV_SCORE_KERNEL and
+ * SPECKV_ROW_STATISTICS in the environment, which choose kernels that compute every score, turn it off); all
+ * words are 0 if not.  [2] unmasked chunks over all sequences, [3] keys of the longest one, [4] in the longest
  * sequence every [4]-th tile, the first one among them, is in the sample whose scores are all computed, [5] keys per tile.
  * What the call leaves in the workspace, by byte offsets: [6] the output rows, [7] of them, in the
  * order layer, sequence, head (prompt tokens: one), 32 bytes each: float, the bound from which keys were listed

@@ -382,13 +382,19 @@ size_t prune_workspace(const Plan &pl, int32_t keep, bool ada) {
   return most.total_pruned;
 }
 
+// The environment's choices among the kernels that compute every score (score_uses_qs, score_rows_fixed_reference) are for fused calls, too.
+static bool whole_kernels_asked_for() {
+  const char *kernel = std::getenv("SPECKV_SCORE_KERNEL"), *rows = std::getenv("SPECKV_ROW_STATISTICS");
+  return (kernel != nullptr && kernel[0] != '\0') || (rows != nullptr && rows[0] != '\0');
+}
+
 bool prune_plan(Plan *pl, int32_t keep, bool ada) {
   Dims &d = pl->d;
   ScoreGeom &g = pl->g;
   int step[kMaxSeqs];
   int64_t pruned;
   // (rows that are ranked in parts have no counts of first digits)
-  if ((!pl->one_row && pl->hist0_words == 0) || !prune_pays(*pl, keep, ada, step, &pruned)) return false;
+  if ((!pl->one_row && pl->hist0_words == 0) || whole_kernels_asked_for() || !prune_pays(*pl, keep, ada, step, &pruned)) return false;
   pl->prune_keep = pl->one_row ? keep : 0;
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
   // About a tenth of the keys is listed: an item per CU, if that makes items short.  (Twice as many of half the size measure the same, 8 layers

@@ -65,6 +65,17 @@ def test_prune_info_words_match_the_header_and_agree_with_the_queries(lib, repo_
     assert S.prune_info(large, "tokens", 1000)["n_rows"] == 1
 
 
+def test_the_environment_chooses_the_kernels_of_fused_calls_too(lib, monkeypatch):
+    p = S.SpecKVParams(n_layers=16, n_q_heads=32, n_kv_heads=8, head_dim=128, seq_lens=[70001], n_window=64, n_lookahead=64, pool_k=7,
+                       c_max=1024, sm_scale=0.1, dtype=torch.bfloat16)
+    need = S.workspace_bytes(p)
+    for name, value in (("SPECKV_SCORE_KERNEL", "qs"), ("SPECKV_SCORE_KERNEL", "tile"), ("SPECKV_ROW_STATISTICS", "online")):
+        assert S.prune_info(p)["pruned"] == 1
+        with monkeypatch.context() as m:
+            m.setenv(name, value)
+            assert S.prune_info(p)["pruned"] == 0 and S.workspace_bytes(p) == need
+
+
 def test_status_strings(lib):
     assert lib.speckv_status_string(0) == b"ok"
     assert b"workspace" in lib.speckv_status_string(-3)
