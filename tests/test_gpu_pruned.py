@@ -25,6 +25,19 @@ def params(S, q, k, lens, n_window, c_max, **kw):
                                       sm_scale=kw.pop("sm_scale", k.shape[-1] ** -0.5), **kw)
 
 
+def rows_of(info, ws):
+    """Keys listed, and 1 where every key was computed, of the output rows of the last call that had this workspace."""
+    table = ws[info["rows_at"]:][:32 * info["n_rows"]].view(torch.int32).view(-1, 8)
+    return table[:, 2], table[:, 3]
+
+
+def sampled(info, keys):
+    """The part of `keys` (dimension 0, whole periods of the sample) that the sample has."""
+    period = info["tile_keys"] * info["sample_step"]
+    whole = keys[:keys.shape[0] // period * period]
+    return whole.view(-1, period, *keys.shape[1:])[:, :info["tile_keys"]]
+
+
 def check(S, q, k, lens, n_window, c_max, ws=None, **kw):
     L, T, H, d = k.shape
     p = params(S, q, k, lens, n_window, c_max, **kw)
@@ -104,18 +117,58 @@ def test_pruned_calls_keep_what_complete_scores_say(S, lens, n_layers, kw):
 def test_rows_whose_sample_misleads_are_computed_whole(S):
     """The best keys of one layer lie in the sample, so that its threshold is too high for the others."""
     q, k = tensors([30001], 8, gain=1.0, planted=0)
-    k[3].view(-1, 8, 128)[:29952].view(-1, 128, 8, 128)[::8] *= 4
-    k[5].view(-1, 8, 128)[:29952].view(-1, 128, 8, 128)[::8] *= 1.5
-    check(S, q, k, [30001], 32, 512)
+    info = S.prune_info(params(S, q, k, [30001], 32, 512))
+    sampled(info, k[3]).mul_(4)
+    sampled(info, k[5]).mul_(1.5)
+    ws = torch.empty(info["workspace_bytes"], dtype=torch.uint8, device="cuda")
+    check(S, q, k, [30001], 32, 512, ws=ws)
+    whole = rows_of(info, ws)[1].view(8, 8).sum(1)
+    assert whole[3] == 8 and whole[[0, 1, 2, 4, 6, 7]].sum() == 0, whole
 
 
 def test_heavy_keys_outside_the_sample(S):
-    """Scores 400 binary orders above a row's reference overflow the sums of their segment, in many segments of one chunk."""
+    """Scores far above a row's reference overflow the sums of their segment, in more segments of one chunk than a list has."""
     q, k = tensors([30001], 8, gain=1.0, planted=0)
-    for i, x in enumerate(range(200, 29000, 700)):
-        k[2, x] = 40.0 * q[2, 0, i % 128, ::4]
-    k[4, 777] = 40.0 * q[4, 0, 5, ::4]
+    info = S.prune_info(params(S, q, k, [30001], 32, 512))
+    keys = [x for x in range(200, 29000, 700) if x // info["tile_keys"] % info["sample_step"]]
+    period = info["tile_keys"] * info["sample_step"]
+    segments = {(x // period * (info["sample_step"] - 1) + x // info["tile_keys"] % info["sample_step"] - 1) // 8
+                for x in keys if x < info["chunk_keys"]}                        # of eight tiles each; a list has room for six
+    assert len(segments) > 6
+    for i, x in enumerate(keys):
+        k[2, x] = 60.0 * q[2, 0, i % 8, ::4]                                    # eight rows of the same wavefront
+    k[4, 779] = 60.0 * q[4, 0, 5, ::4]
+    for layer, x, row in [(2, x, i % 8) for i, x in enumerate(keys)] + [(4, 779, 5)]:
+        products = q[layer, 0, row, ::4].float()[:, None] * k[layer].float().transpose(0, 1)
+        scores = products.sum(-1) * (128 ** -0.5 * math.log2(math.e))          # [head][key]
+        seen = torch.logsumexp(sampled(info, scores.t()).reshape(-1, 8) * math.log(2), 0) / math.log(2)
+        assert (scores[:, x] - seen).min() > 126 + 76 + 8                       # the sums' largest number, what exponents are lowered by, margin
     check(S, q, k, [30001], 32, 512)
+
+
+@pytest.mark.parametrize("lens,n_layers,kw", [([30001], 9, {}), ([50001], 8, {"d": 64}), ([40000], 9, {"rows": 67, "reduce": "max"})])
+def test_rows_of_keys_and_queries_apart_in_memory(S, lens, n_layers, kw):
+    """Heads before tokens, every row with room behind it; segments left to the repair, gathered keys and rows by these strides."""
+    kw = dict(kw)
+    shape = {x: kw.pop(x) for x in ("rows", "d") if x in kw}
+    q, k = tensors(lens, n_layers, gain=1.0, **shape)
+    k[2, 777] = 40.0 * q[2, 0, 5, ::4]
+    L, T, H, d = k.shape
+    k2 = torch.full((L, H + 1, T, d + 24), float("nan"), dtype=k.dtype, device="cuda")[:, :H, :, :d].transpose(1, 2)
+    q2 = torch.full((q.shape[1], L, q.shape[3], q.shape[2], d + 8), float("nan"), dtype=q.dtype, device="cuda")[..., :d].permute(1, 0, 3, 2, 4)
+    k2.copy_(k)
+    q2.copy_(q)
+    assert torch.equal(check(S, q2, k2, lens, 32, 512, **kw)[0], check(S, q, k, lens, 32, 512, **kw)[0])
+
+
+def test_more_sequences_than_the_plan_simulates(S):
+    """Beyond 16 sequences of a length the chunks are made from an even spread; long and short ones in any order, some all sample."""
+    lens = [6001 + 977 * ((7 * s) % 20) for s in range(20)] + [40, 130, 900, 3001]
+    q, k = tensors(lens, 4, rows=96)
+    info = S.prune_info(params(S, q, k, lens, 32, 256))
+    assert info["n_chunks"] >= 22
+    check(S, q, k, lens, 32, 256)
+    check(S, q, k, lens, 32, 256, reduce="max")
 
 
 def test_all_scores_alike(S):
@@ -138,6 +191,9 @@ def test_numbers_that_are_none(S):
     S.speckv_compress(p, q, k, None, idx, k_out, None, parity.alloc_ws(S, p))
     same = (idx.view(64, -1) == clean.view(64, -1)).all(-1)
     assert same[[i for i in range(64) if i not in (10, 28)]].all()
+    odd = idx.view(64, -1)[[10, 28]]
+    assert (odd.diff(dim=-1) > 0).all() and (odd[:, 0] >= 0).all()
+    assert torch.equal(odd[:, 512:], torch.arange(30001 - 32, 30001, device="cuda").to(idx).expand(2, 32))
 
 
 def test_a_workspace_without_room_for_it_is_enough(S):
@@ -197,15 +253,19 @@ def test_prompt_tokens_are_those_of_complete_scores(S, n, n_layers, top_k, kw):
 def test_prompt_tokens_whose_sample_misleads(S):
     n = 60000
     q, k = tensors([n], 12, d=64, rows=64, gain=1.0, planted=0)
-    k[:, :n // 256 * 256].view(12, -1, 256, 8, 64)[:, ::8] *= 3          # (every step of tiles of 128 keys has some of these)
     p = params(S, q, k, [n], 32, 512)
+    info = S.prune_info(p, "tokens", 4000)
+    for layer in range(12):
+        sampled(info, k[layer]).mul_(3)
     ids = torch.arange(n, dtype=torch.int32, device="cuda")
     got = []
-    most = S.prune_info(p, "tokens", 4000)["workspace_bytes"]
+    most = info["workspace_bytes"]
     assert most > 0
     for size in (most, most - 1):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
         out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros(1, dtype=torch.int32, device="cuda")]
-        S.specpc_select_tokens(p, 4000, 0, q, k, ids, *out, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        S.specpc_select_tokens(p, 4000, 0, q, k, ids, *out, ws)
+        assert size < most or rows_of(info, ws)[1].item() == 1
         got.append(out)
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
@@ -224,19 +284,23 @@ def test_shared_budgets_are_those_of_complete_scores(S, lens, n_layers, c_floor,
     q, k = tensors(lens, n_layers, **kw)
     # heads of different sharpness, so that their shares differ
     q *= torch.linspace(0.6, 1.6, q.shape[3], device="cuda").to(q.dtype)[None, None, None, :, None]
-    if mislead:
-        k[2, :32640].view(-1, 128, k.shape[2], 128)[::8] *= mislead
-        k[4, :32640, 1].view(-1, 128, 128)[::8] *= mislead
     p = params(S, q, k, lens, 32, 1024)
+    info = S.prune_info(p, "ada")
+    if mislead:
+        sampled(info, k[2]).mul_(mislead)
+        sampled(info, k[4])[:, :, 1].mul_(mislead)
     H, KT = k.shape[2], S.total_keep(p)
-    most = S.prune_info(p, "ada")["workspace_bytes"]
+    most = info["workspace_bytes"]
     assert most > 0
     got = []
     for size in (most, most - 1, most):                                     # (no room for pruning in the second)
         idx = torch.full((n_layers, H * KT), -7, dtype=torch.int32, device="cuda")
         off = torch.full((n_layers, len(lens), H + 1), -7, dtype=torch.int32, device="cuda")
         k_out = torch.empty(n_layers, H * KT, 128, dtype=k.dtype, device="cuda")
-        S.speckv_compress_ada(p, c_floor, q, k, None, idx, off, k_out, None, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        S.speckv_compress_ada(p, c_floor, q, k, None, idx, off, k_out, None, ws)
+        if mislead and size == most:
+            assert rows_of(info, ws)[1].view(n_layers, H)[2].all()
         got.append((idx, off, k_out.view(torch.int16)))
     assert got[0][1].diff(dim=-1).unique().numel() > 1 or c_floor >= 1024
     for other in got[1:]:
