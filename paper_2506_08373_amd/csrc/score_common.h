@@ -52,6 +52,8 @@ constexpr int kNormMerged = 0, kNormPairs = 1, kNormCaller = 2;
 
 namespace {
 
+// Super-block of chunk workgroup `bid` of a pruned call.
+__device__ __forceinline__ int prune_super_block(const PruneArgs &A, int bid) { return bid % (8 * A.g.RS) >> 3; }
 // Chunk workgroup `bid` of a pruned call (unit < 0: it has none).  The workgroups of all layers and heads take a chunk of a sequence
 // before those of the next chunk, the longest chunks first.  For the super-blocks of a group see score_sweep.h.
 struct PruneChunk { int unit, s, chunk, key_begin, key_end; };
@@ -62,7 +64,7 @@ __device__ __forceinline__ PruneChunk prune_chunk(const PruneArgs &A, int bid) {
   c.unit = -1;
   if (item >= A.g.n_fast_chunks * groups) return c;
   int rank = item / groups, i = 0;
-  c.unit = item % groups * A.g.RS + (bid % per_group >> 3);
+  c.unit = item % groups * A.g.RS + prune_super_block(A, bid);
   int s = A.order[0];
   for (;;) {
     const int n = A.t.cc[s + 1] - A.t.cc[s];

@@ -37,10 +37,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   else score_body<DT, D, MB, NW, 1, 0, true>(static_cast<const ScoreArgs &>(A), bid - A.chunk_blocks);
 }
 
-// (Four waves per SIMD, so that two workgroups share a CU, where the LDS has room for them.)
+// (Four waves per SIMD, so that two workgroups share a CU, where the LDS has room for them.  The maximum of a head's rows by pairs of blocks
+// and by single ones are two bodies: one that does either does not fit the registers at d = 128, 12 of them spilled into the loop.)
 template <int DT, int D, int MB, int NW, int RED>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && MB == 1 ? 4 : 2))) void prune_sweep_kernel(PruneArgs A) {
-  score_body<DT, D, MB, NW, 2, RED, false, false, false, kOtherKeys>(A, blockIdx.x);
+  if constexpr (RED == 1 && MB == 2) {
+    const int rs = prune_super_block(A, blockIdx.x);
+    int first;
+    if (!sweep_pairs_blocks<RED, MB, NW>(A, super_block_blocks(A.d, A.g, rs, &first))) {
+      score_body<DT, D, MB, NW, 2, RED, false, false, false, kOtherKeys, 0>(A, blockIdx.x);
+      return;
+    }
+  }
+  score_body<DT, D, MB, NW, 2, RED, false, false, false, kOtherKeys, RED == 1 && MB == 2>(A, blockIdx.x);
 }
 
 // The segments that wavefronts of the sweep left out of their sums, with the online step; one workgroup per wavefront's list

@@ -190,6 +190,8 @@ __device__ __forceinline__ bool sweep_pairs_blocks(const ScoreArgs &A, int nblk)
   return RED == 1 && MB == 2 && nblk == NW * MB && (blocks_per_head % 2 == 0 || A.g.packed != 0);
 }
 
+constexpr int kAskPairs = -1;
+
 // One workgroup's sweep over a chunk of keys; bid = its index among the workgroups of its kind.
 //   PASS    1: row statistics, 2: column reduction
 //   RED     (pass 2) 0: sum over the rows of a head, 1: max over the rows of a head;
@@ -206,12 +208,17 @@ __device__ __forceinline__ bool sweep_pairs_blocks(const ScoreArgs &A, int nblk)
 //   MAY_SHARE  the code for row blocks that waves share (split_blocks)
 //   KEYS    which of a chunk's keys: all, or for a pruned call (score_prune.hip) its sample, the others or a list.
 //           Pass 2 over the others also sums the rows, in segments of kPruneSegment tiles.
+//   PAIRED  what sweep_pairs_blocks says, where that is known (0, 1); kAskPairs: it is asked
 template <int DT, int D, int MB, int NW, int PASS, int RED, bool MASKED, bool REPAIR = false, bool MAY_SHARE = true,
-          int KEYS = kAllKeys, typename Args = ScoreArgs>
+          int KEYS = kAllKeys, int PAIRED = kAskPairs, typename Args = ScoreArgs>
 __device__ __forceinline__ void score_body(const Args &A, const int bid, const int seg = 0,
                                            const bool wave_takes_part = true) {
   static_assert(!REPAIR || (PASS == 1 && !MASKED && KEYS == kAllKeys), "only the row-statistics sweep is repaired");
   static_assert(KEYS == kAllKeys || (DT != kF32 && !MASKED), "pruned calls: 16-bit rows, unmasked keys");
+  // What prune_plan has decided: one head a super-block or more, sums or maxima of a head's rows added up over heads, the host's
+  // length, normalisers merged beforehand.
+  constexpr bool PRUNED = KEYS != kAllKeys;
+  if constexpr (PRUNED) __builtin_assume(A.g.PPH == 1);
   constexpr bool ROW_SUMS = PASS == 2 && KEYS == kOtherKeys;
   constexpr bool SQUARES = PASS == 1 && KEYS == kSampleKeys;             // also sums of squared terms (prune_reference_kernel)
   static_assert(KEYS != kOtherKeys || !MAY_SHARE, "with the code for shared blocks the row sums do not fit the registers");
@@ -270,8 +277,10 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     while (s + 1 < d.S && A.t.cc[s + 1] <= chunk) ++s;
   }
   const int n_host = A.t.cu[s + 1] - A.t.cu[s];          // row stride of the score layouts
-  const int n_s = live_len(d, A.t, s);                    // tokens that exist (device-side count honoured)
-  const int tail0 = live_tail0(d, A.t, s, n_s, OP::ALIGN);
+  const int n_s = PRUNED ? n_host : live_len(d, A.t, s);  // tokens that exist (device-side count honoured)
+  const int tail0 = PRUNED ? A.t.tail0[s] : live_tail0(d, A.t, s, n_s, OP::ALIGN);
+  const bool head_max = !PRUNED && d.head_max != 0;
+  const int norm_from = PRUNED ? kNormMerged : A.norm_from;
   if (MASKED) {
     key_begin = tail0;
     key_end = n_s;
@@ -313,9 +322,9 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   // column maxima in registers and hands one value per key to the flush, not two.  A maximum
   // does not depend on the order, so the result is the same bit for bit.
   const int blocks_per_head = (A.g.PPH != 1 ? RSB : A.g.packed != 0 ? 32 : A.g.Rp) / 32;
-  const bool paired = PASS == 2 && !MASKED && sweep_pairs_blocks<RED, MB, NW>(A, nblk);
+  const bool paired = PASS == 2 && !MASKED && (PAIRED == kAskPairs ? sweep_pairs_blocks<RED, MB, NW>(A, nblk) : PAIRED == 1);
   // ... and where heads are combined by maximum too, a wave merges whatever blocks it has.
-  const bool merged = paired || (PASS == 2 && RED == 1 && !MASKED && d.head_max != 0);
+  const bool merged = paired || (PASS == 2 && RED == 1 && !MASKED && head_max);
   auto block_of = [&](int rb) { return paired ? wv * MB + rb : block_of_slot(split, rb * NW + wv); };
   // row r32 of the wave's row block rb: its head and observation row; false for padding
   auto row_at = [&](int rb, int r32, int &hh, int &i) { return decode_row(d, A.g, rs, block_of(rb) * 32 + r32, &hh, &i); };
@@ -405,7 +414,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     return e < n_entries ? pairs_of_row[(int64_t)(e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1) * RSB] : make_float2(kNegBig, 0.f);
   };
   float2 first_pairs[BATCH];
-  if (PASS == 2 && A.norm_from == kNormPairs) {
+  if (PASS == 2 && norm_from == kNormPairs) {
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) first_pairs[u] = entry(norm_slice + u * RSB_SLICES);
   }
@@ -486,7 +495,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     int hh, io;
     const bool valid = decode_row(d, A.g, rs, lr, &hh, &io);
     float v = 0.f;                                        // log2 normaliser of row lr
-    if (A.norm_from == kNormPairs) {
+    if (norm_from == kNormPairs) {
       float top = kNegBig, sum = 0.f;
       merge_pairs(top, sum, first_pairs);
       for (int e0 = slice + BATCH * RSB_SLICES; e0 < n_entries; e0 += RSB_SLICES * kMergeNext) {
@@ -506,7 +515,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
         }
       }
       v = top + log2f(sum);
-    } else if (A.norm_from == kNormCaller) {
+    } else if (norm_from == kNormCaller) {
       if (valid) v = A.lse_in[(((int64_t)layer * d.S + s) * d.R + io) * d.Hq + g * d.G + hh] * 1.4426950408889634f;
     } else {
       v = A.lse[(((int64_t)layer * d.Hkv + g) * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + lr];
@@ -514,7 +523,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     if (slice == 0) {
       v = -v;
       if constexpr (ROW_SUMS) v = ceilf(v * kPruneGrain) / kPruneGrain - kPruneShift;      // see kPruneShift
-      if (d.weight_rows && valid && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
+      if (!PRUNED && d.weight_rows && valid && io < d.w) v += log2f((float)(io + 1) / (float)d.w);     // row weight folded in
       norm[lr] = valid ? v : -INFINITY;                   // padded rows contribute 2^-inf = 0
       if (MASKED) row_last[lr] = io < d.w ? m + io : n_s - 1;
     }
@@ -597,7 +606,6 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   float *plane_out = nullptr;
   if (PASS == 2)
     plane_out = A.planes + ((int64_t)rs * d.L + layer) * d.Hkv * d.T + (int64_t)d.Hkv * A.t.cu[s] + (int64_t)g * n_host;
-  const bool head_max = d.head_max != 0;
   const int slots_per_head = paired && blocks_per_head > 1 ? blocks_per_head / 2 : blocks_per_head;
   // sum, unmasked: a wave with a block of its own keeps the column sums of the one it shares in a second slot
   const bool share_slots = per > 1 && split.full >= NW;
