@@ -152,7 +152,7 @@ int64_t speckv_total_keep(const speckv_params *p);
  * (a shorter prompt may be cut into more chunks).  A part of it only saves time: large fused calls
  * (this one's, the shared budget's, the prompt tokens') compute exact scores only for keys that can
  * be kept, which takes scratch of its own; without it they compute every score.  What is asked for
- * beyond a call's own need with all scores is mostly a few MiB and at most some tens. */
+ * beyond a call's own need with all scores is mostly a per cent and at most some tens of MiB. */
 size_t speckv_workspace_bytes(const speckv_params *p);
 
 /* Launch plan the host derives for these parameters, for diagnostics and tests (no GPU needed):

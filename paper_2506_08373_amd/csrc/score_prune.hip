@@ -235,15 +235,31 @@ struct Buffers {
 
 }  // namespace
 
-// The most chunks a pruned call is cut into: about kPruneRounds rounds of the CUs, or as many as the call has anyway.  Shorter ones even out the end
-// of the sweep a little better (model, one sequence of 4K to 250K: 3 % in one of 100 calls), but take room in the workspace, whose size
-// has to be that of the longest prompt whatever the number of chunks of a shorter one.
-constexpr int kPruneRounds = 12, kPruneChunkMin = 512;
+// Of a sequence of m candidates, per cent of a whole sweep: the more of them are kept, the more have to be listed (2 to 8 % of the keys from
+// 32 c_max on, 10 % at 16, 20 to 35 % at 7 c_max).
+constexpr int kPruneLeast = 7;
+static int prune_saving(int64_t m, int64_t c_max) {
+  return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= kPruneLeast * c_max ? 12 : 0;
+}
+// Keys of a chunk where there is no sample but every key is in it.
+constexpr int kPruneAllSample = 4096;
+
+// The most chunks a pruned call is cut into: about kPruneRounds rounds of the CUs, or chunks of kPruneLong keys, or what sequences that are
+// all sample need.  Short chunks even out the end of the sweep, but in each the references begin anew with what the sample gives, and more
+// keys are listed; and they take room in the workspace, whose size has to be that of the longest prompt whatever the number of chunks of a
+// shorter one.  Calls, us, with up to 12 rounds / with this: 3 layers of 54K (53 chunks / 9) 486 / 341, 18 of 63K, one KV head, 928 / 784, 28 of 98K
+// the same, shared budget 1671 / 1500, 26 of 57K, groups of 7, maximum 1724 / 1557; of 51 random ones none slower.
+constexpr int kPruneRounds = 4, kPruneLong = 16384, kPruneChunkMin = 512;
 static int64_t prune_most_chunks(const Plan &pl) {
-  const int64_t units = (int64_t)pl.d.L * pl.d.Hkv * pl.g.RS;
-  int64_t of_min = 0;
-  for (int s = 0; s < pl.d.S; ++s) of_min += (pl.t.tail0[s] + kPruneChunkMin - 1) / kPruneChunkMin;
-  return std::max(pl.most_chunks, std::min((kPruneRounds * 256 + units - 1) / units + pl.d.S - 1, of_min));
+  const int64_t units = (int64_t)pl.d.L * pl.d.Hkv * pl.g.RS, c_max = pl.one_row ? pl.sel_kept : pl.d.c_max;
+  int64_t of_min = 0, of_long = 0, whole = 0;
+  for (int s = 0; s < pl.d.S; ++s) {
+    const int64_t n = pl.t.tail0[s];
+    of_min += (n + kPruneChunkMin - 1) / kPruneChunkMin;
+    of_long += (n + kPruneLong - 1) / kPruneLong;
+    whole += (std::min(n, kPruneLeast * c_max) + kPruneAllSample - 1) / kPruneAllSample;
+  }
+  return std::max({whole, of_long, std::min((kPruneRounds * 256 + units - 1) / units + pl.d.S - 1, of_min)});
 }
 
 // Chunks of a sequence when none is longer than kc: equal ones, of whole periods of the sample.  (Of a sequence that is all sample a
@@ -252,7 +268,7 @@ struct Chunks { int count, keys; };
 static Chunks prune_chunks(const Plan &pl, int s, int step, int64_t kc) {
   const int64_t n = pl.t.tail0[s];
   if (n == 0) return {0, prune_tile_keys(pl)};
-  if (step == 0) kc = std::min<int64_t>(kc, std::max(4096, pl.g.KC));
+  if (step == 0) kc = std::min<int64_t>(kc, std::max(kPruneAllSample, pl.g.KC));
   const int64_t count = (n + kc - 1) / kc;
   const int64_t keys = std::max<int64_t>(align_up((n + count - 1) / count, (int64_t)prune_tile_keys(pl) << step), kPruneChunkMin);
   return {(int)((n + keys - 1) / keys), (int)keys};
@@ -329,12 +345,6 @@ constexpr int64_t kPruneMinSaving = 6000000, kPruneMinPerSeq = 700000;
 // Half as much again where there are more launches (prompt tokens, shared budgets) or a whole sweep has two workgroups a CU (8 waves of one row
 // block): 7.8M (prompt tokens, 9 layers of 41K) 326 / 365, 7.2M (shared budget, 20 layers of 68K, 2 heads) 363 / 378, 8.7M (25 layers of
 // 19K, 64 rows) 671 / 712; 18.8M (prompt tokens, 16 layers of 64K) 855 / 700, 9.4M (shared budget, 8 of 32K) 645 / 595.
-// Of a sequence of m candidates, per cent of a whole sweep: the more of them are kept, the more have to be listed (2 to 8 % of the keys from
-// 32 c_max on, 10 % at 16, 20 to 35 % at 7 c_max).
-static int prune_saving(int64_t m, int64_t c_max) {
-  return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= 7 * c_max ? 12 : 0;
-}
-
 // Whether a call is pruned, each sequence's sample step and the keys of those that have one.
 static bool prune_pays(const Plan &pl, int32_t keep, bool ada, int *step, int64_t *pruned) {
   const Dims &d = pl.d;
