@@ -279,8 +279,6 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   const int n_host = A.t.cu[s + 1] - A.t.cu[s];          // row stride of the score layouts
   const int n_s = PRUNED ? n_host : live_len(d, A.t, s);  // tokens that exist (device-side count honoured)
   const int tail0 = PRUNED ? A.t.tail0[s] : live_tail0(d, A.t, s, n_s, OP::ALIGN);
-  const bool head_max = !PRUNED && d.head_max != 0;
-  const int norm_from = PRUNED ? kNormMerged : A.norm_from;
   if (MASKED) {
     key_begin = tail0;
     key_end = n_s;
@@ -324,7 +322,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   const int blocks_per_head = (A.g.PPH != 1 ? RSB : A.g.packed != 0 ? 32 : A.g.Rp) / 32;
   const bool paired = PASS == 2 && !MASKED && (PAIRED == kAskPairs ? sweep_pairs_blocks<RED, MB, NW>(A, nblk) : PAIRED == 1);
   // ... and where heads are combined by maximum too, a wave merges whatever blocks it has.
-  const bool merged = paired || (PASS == 2 && RED == 1 && !MASKED && head_max);
+  const bool merged = paired || (PASS == 2 && RED == 1 && !MASKED && !PRUNED && d.head_max != 0);
   auto block_of = [&](int rb) { return paired ? wv * MB + rb : block_of_slot(split, rb * NW + wv); };
   // row r32 of the wave's row block rb: its head and observation row; false for padding
   auto row_at = [&](int rb, int r32, int &hh, int &i) { return decode_row(d, A.g, rs, block_of(rb) * 32 + r32, &hh, &i); };
@@ -414,7 +412,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     return e < n_entries ? pairs_of_row[(int64_t)(e == 0 ? A.g.n_fast_chunks + s : A.t.cc[s] + e - 1) * RSB] : make_float2(kNegBig, 0.f);
   };
   float2 first_pairs[BATCH];
-  if (PASS == 2 && norm_from == kNormPairs) {
+  if (PASS == 2 && !PRUNED && A.norm_from == kNormPairs) {
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) first_pairs[u] = entry(norm_slice + u * RSB_SLICES);
   }
@@ -495,7 +493,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
     int hh, io;
     const bool valid = decode_row(d, A.g, rs, lr, &hh, &io);
     float v = 0.f;                                        // log2 normaliser of row lr
-    if (norm_from == kNormPairs) {
+    if (!PRUNED && A.norm_from == kNormPairs) {
       float top = kNegBig, sum = 0.f;
       merge_pairs(top, sum, first_pairs);
       for (int e0 = slice + BATCH * RSB_SLICES; e0 < n_entries; e0 += RSB_SLICES * kMergeNext) {
@@ -515,7 +513,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
         }
       }
       v = top + log2f(sum);
-    } else if (norm_from == kNormCaller) {
+    } else if (!PRUNED && A.norm_from == kNormCaller) {
       if (valid) v = A.lse_in[(((int64_t)layer * d.S + s) * d.R + io) * d.Hq + g * d.G + hh] * 1.4426950408889634f;
     } else {
       v = A.lse[(((int64_t)layer * d.Hkv + g) * d.S + s) * ((int64_t)A.g.RS * RSB) + rs * RSB + lr];
@@ -606,6 +604,7 @@ __device__ __forceinline__ void score_body(const Args &A, const int bid, const i
   float *plane_out = nullptr;
   if (PASS == 2)
     plane_out = A.planes + ((int64_t)rs * d.L + layer) * d.Hkv * d.T + (int64_t)d.Hkv * A.t.cu[s] + (int64_t)g * n_host;
+  const bool head_max = !PRUNED && d.head_max != 0;
   const int slots_per_head = paired && blocks_per_head > 1 ? blocks_per_head / 2 : blocks_per_head;
   // sum, unmasked: a wave with a block of its own keeps the column sums of the one it shares in a second slot
   const bool share_slots = per > 1 && split.full >= NW;
