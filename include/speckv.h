@@ -235,16 +235,17 @@ speckv_status speckv_compress(const speckv_params *p, const void *q, const void 
 /* speckv_compress for callers that cannot allocate or pass a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels and bit-identical
  * results (where the scratch has no room for the part that only saves time, all scores are
- * computed, and keys whose scores differ by no more than rounding may change places); the scratch is a fixed array of SPECKV_STATIC_SCRATCH_BYTES inside the library's device
- * code (one copy per GPU, held until the process ends; its address is looked up on the first call
- * on each device).  The call allocates nothing and frees nothing.  Parameters that need more than
+ * computed, and keys whose scores differ by no more than rounding may change places); the scratch
+ * is a fixed array of SPECKV_STATIC_SCRATCH_BYTES inside the library's device code (one copy per
+ * GPU, held until the process ends; its address is looked up on the first call on each device).
+ * The call allocates nothing and frees nothing.  Parameters that need more than
  * SPECKV_STATIC_SCRATCH_BYTES themselves (speckv_workspace_bytes less what it holds for shorter
- * prompts and the part that only saves time) are rejected with SPECKV_ERR_WORKSPACE before anything is launched (32 MiB covers one layer of 8 KV heads at
- * 256K tokens, or a few layers of shorter prompts).  Every call on a GPU shares that GPU's array:
- * calls that overlap on one GPU (two streams, two threads) race and must be serialised by the
- * caller.  The array keeps the previous call's contents; the kernels never read what they have
- * not written in the same call, and the counters that must start at zero are zeroed by a kernel of
- * the same call (no memset). */
+ * prompts and the part that only saves time) are rejected with SPECKV_ERR_WORKSPACE before
+ * anything is launched (32 MiB covers one layer of 8 KV heads at 256K tokens, or a few layers of
+ * shorter prompts).  Every call on a GPU shares that GPU's array: calls that overlap on one GPU
+ * (two streams, two threads) race and must be serialised by the caller.  The array keeps the
+ * previous call's contents; the kernels never read what they have not written in the same call,
+ * and the counters that must start at zero are zeroed by a kernel of the same call (no memset). */
 #define SPECKV_STATIC_SCRATCH_BYTES (32u << 20)
 speckv_status speckv_compress_static(const speckv_params *p, const void *q, const void *k,
                                      const void *v, int32_t *idx, void *k_out, void *v_out,
@@ -261,6 +262,9 @@ speckv_status speckv_compress_lse(const speckv_params *p, const void *q, const v
  *   [0] start  [1] after scoring pass 1 (row statistics)  [2] after the row-statistics merge
  *   [3] after scoring pass 2 (column sums)  [4] after pooling  [5] after selection
  *   [6] after compaction.  Same results as speckv_compress (Alg. 1 loop body).
+ * Of a call that computes exact scores only for keys that can be kept (speckv_prune_info), pass 1
+ * also bounds the scores of the keys outside the sample, pass 2 holds the exact scores of the sample
+ * and of the keys whose bound is large enough, and pooling those of rows that have to be computed whole.
  * Two stages may hold no kernel, their work is then part of the next one: [1]-[2] where the workgroups of
  * pass 2 merge the statistics of their rows (up to 40 chunks a sequence), [3]-[4] where one launch pools
  * and selects (no sequence above 8192 tokens, pool_k up to 16, groups of one or two row super-blocks). */

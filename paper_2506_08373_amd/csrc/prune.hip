@@ -59,9 +59,9 @@ struct Steps { int32_t log[kMaxSeqs]; };
 // First references of the rows.  What the sample and the masked tail add up to, S + T, is a lower bound on a row's normaliser,
 // but of a row that attends to many keys alike only the sample's share, and the bounds on scores are larger by as much.  The rest of
 // such a row is expected from its sample, (ratio - 1) S with ratio = keys / keys in the sample, less four standard deviations,
-// ratio sqrt(sum of squared terms), both without the largest term, which is often one key's that all rows attend to: nothing is left of it
-// where a few keys make up the row.  A reference that turns out above its
-// normaliser makes the bounds too small by as much, which prune_threshold_kernel allows for.
+// ratio sqrt(sum of squared terms), both without the largest term, which is often one key's that all rows attend to: nothing is left
+// of it where a few keys make up the row.  A reference that turns out above its normaliser makes the bounds too small by as much,
+// which prune_threshold_kernel allows for.  What was seen, S + T, takes the tail's place among the row's pairs.
 // Keys listed of 32K with logits of standard deviation 1, a sample of 1/8: 84 % with S + T, 18 % with this; 2: 25 and 6 %; 3 to 8: level.
 constexpr float kSampleDeviations = 4.f;
 constexpr int kRefThreads = 256;
@@ -235,7 +235,8 @@ __device__ __forceinline__ int reserve(PruneRow *rows, int row, int n, int item_
 
 // Lists the keys outside the sample whose bound reaches the row's threshold, kListKeys of the row's keys a workgroup.
 // Bound: reading the bounds once.
-__global__ __launch_bounds__(kListThreads) void prune_list_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes, int parts, int item_keys,
+__global__ __launch_bounds__(kListThreads) void prune_list_kernel(Dims d, SeqTab t, Steps steps, int tile_log, int n_planes, int parts,
+                                                                  int item_keys,
                                                                   const float *__restrict__ planes, PruneRow *__restrict__ rows,
                                                                   int32_t *__restrict__ list, int2 *__restrict__ items,
                                                                   int32_t *__restrict__ n_items) {
@@ -372,8 +373,8 @@ struct RowsOf {
   }
 };
 
-hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st,
-                                   int32_t c_floor, uint32_t *counts) {
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items,
+                                   hipStream_t st, int32_t c_floor, uint32_t *counts) {
   const RowsOf r(pl);
   hipLaunchKernelGGL(prune_threshold_kernel, dim3(r.n), dim3(kThrThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), r.planes,
                      planes, row_extra, r.group_rows, rows, n_items, c_floor, counts);
@@ -398,8 +399,8 @@ hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows
 hipError_t launch_prune_check(const Plan &pl, const uint32_t *hist0, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
                               hipStream_t st, int32_t c_floor) {
   const RowsOf r(pl);
-  hipLaunchKernelGGL(prune_check_kernel, dim3(r.n), dim3(kListThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), pl.item_keys, hist0,
-                     rows, list, items, n_items, c_floor);
+  hipLaunchKernelGGL(prune_check_kernel, dim3(r.n), dim3(kListThreads), 0, st, r.d, pl.t, steps_of(pl), tile_log_of(pl), pl.item_keys,
+                     hist0, rows, list, items, n_items, c_floor);
   return hipGetLastError();
 }
 

@@ -16,12 +16,14 @@
 //
 // The indices are those of all scores, whatever the data; only the time depends on them.
 // One sweep instead of two is what there is to gain.  Sum of 32 layers x 128K keys, 4 heads x 128 rows, d = 128, us: the two sweeps
-// 4350 + 4400; here sample 330, sweep 4500 (a block's 16 more additions and the row sums cost it 8 %), sample's columns 310,
-// listed keys (4 %) 250, the rest 200.  Calls, all scores / pruned: that one 8690 / 5560, eight prompts of 4K to 64K, groups of
-// 7, 28 layers 15990 / 10550, 32 layers x 16K, maximum 1010 / 870, 8 layers x 32K 644 / 550; d = 64: 31 layers x 31K 1511 / 1017, 32 layers x
-// 43K, 2 heads, flat attention 492 / 395.
-// Where nothing can be pruned (all scores alike, or a threshold under prune_floor) the listed sweep is a second whole one and the call a
-// fifth longer than without.
+// 4260 + 4400; here sample 330, sweep 4410 (a block's 16 more additions and the row sums cost it 8 %), sample's columns 290,
+// listed keys (4 %) 250, the rest 180.  Calls, all scores / pruned: that one 8540 / 5500, eight prompts of 4K to 64K, groups of 7,
+// 28 layers 15860 / 10480, 32 layers x 16K, maximum 1010 / 775, 8 layers x 32K 590 / 470; d = 64, prompt tokens, 16 layers x 64K
+// 844 / 694.
+// Where nothing can be pruned (scores all alike, or a threshold under prune_floor) the listed sweep is a second whole one, a tenth
+// slower than a column sweep, and the sample and the small launches come on top.  Calls of rows that attend to all keys alike, all
+// scores / pruned: 32 layers x 128K 8470 / 9510, 8 layers x 32K 610 / 715, maximum, 32 x 16K 768 / 935; prompt tokens, whose score
+// is a sum over all rows, also where the rows have nothing to do with each other, 16 x 64K 856 / 1013.
 #include <algorithm>
 #include <utility>
 
@@ -37,10 +39,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   else score_body<DT, D, MB, NW, 1, 0, true>(static_cast<const ScoreArgs &>(A), bid - A.chunk_blocks);
 }
 
-// (Four waves per SIMD, so that two workgroups share a CU, where the LDS has room for them.  The maximum of a head's rows by pairs of blocks
-// and by single ones are two bodies: one that does either does not fit the registers at d = 128, 12 of them spilled into the loop.)
+// (Four waves per SIMD, so that two workgroups share a CU, where the LDS has room for them.  The maximum of a head's rows by pairs of
+// blocks and by single ones are two bodies: one that does either does not fit the registers at d = 128, where 12 were spilled into the
+// loop.  Sweep over 32 layers x 128K keys 4760 us beside the sum's 4380, with two bodies 4270 beside 4410; call of 32 x 16K keys, 12
+// blocks, 911 / 833.)
 template <int DT, int D, int MB, int NW, int RED>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && MB == 1 ? 4 : 2))) void prune_sweep_kernel(PruneArgs A) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && MB == 1 ? 4 : 2)))
+void prune_sweep_kernel(PruneArgs A) {
   if constexpr (RED == 1 && MB == 2) {
     const int rs = prune_super_block(A, blockIdx.x);
     int first;
@@ -235,8 +240,8 @@ struct Buffers {
 
 }  // namespace
 
-// Of a sequence of m candidates, per cent of a whole sweep: the more of them are kept, the more have to be listed (2 to 8 % of the keys from
-// 32 c_max on, 10 % at 16, 20 to 35 % at 7 c_max).
+// Of a sequence of m candidates, per cent of a whole sweep: the more of them are kept, the more have to be listed (2 to 8 % of the keys
+// from 32 c_max on, 10 % at 16, 20 to 35 % at 7 c_max).
 constexpr int kPruneLeast = 7;
 static int prune_saving(int64_t m, int64_t c_max) {
   return m >= 32 * c_max ? 33 : m >= 16 * c_max ? 28 : m >= 11 * c_max ? 20 : m >= kPruneLeast * c_max ? 12 : 0;
@@ -244,11 +249,12 @@ static int prune_saving(int64_t m, int64_t c_max) {
 // Keys of a chunk where there is no sample but every key is in it.
 constexpr int kPruneAllSample = 4096;
 
-// The most chunks a pruned call is cut into: about kPruneRounds rounds of the CUs, or chunks of kPruneLong keys, or what sequences that are
-// all sample need.  Short chunks even out the end of the sweep, but in each the references begin anew with what the sample gives, and more
-// keys are listed; and they take room in the workspace, whose size has to be that of the longest prompt whatever the number of chunks of a
-// shorter one.  Calls, us, with up to 12 rounds / with this: 3 layers of 54K (53 chunks / 9) 486 / 341, 18 of 63K, one KV head, 928 / 784, 28 of 98K
-// the same, shared budget 1671 / 1500, 26 of 57K, groups of 7, maximum 1724 / 1557; of 51 random ones none slower.
+// The most chunks a pruned call is cut into: about kPruneRounds rounds of the CUs, or chunks of kPruneLong keys, or what sequences
+// that are all sample need.  Short chunks even out the end of the sweep, but in each the references begin anew with what the sample
+// gives, and more keys are listed; and they take room in the workspace, whose size has to be that of the longest prompt whatever the
+// number of chunks of a shorter one.  Calls, us, with up to 12 rounds / with this: 3 layers of 54K (53 chunks / 9) 486 / 341, 18 of
+// 63K, one KV head, 928 / 784, 28 of 98K the same, shared budget 1671 / 1500, 26 of 57K, groups of 7, maximum 1724 / 1557; of 51
+// random ones none slower.
 constexpr int kPruneRounds = 4, kPruneLong = 16384, kPruneChunkMin = 512;
 static int64_t prune_most_chunks(const Plan &pl) {
   const int64_t units = (int64_t)pl.d.L * pl.d.Hkv * pl.g.RS, c_max = pl.one_row ? pl.sel_kept : pl.d.c_max;
@@ -274,8 +280,8 @@ static Chunks prune_chunks(const Plan &pl, int s, int step, int64_t kc) {
   return {(int)((n + keys - 1) / keys), (int)keys};
 }
 
-// The most keys of a chunk.  References grow with what a chunk has seen, so that longer chunks have closer bounds and fewer keys to list: the
-// longest that costs the sweep little in CUs left idle at its end.
+// The most keys of a chunk.  References grow with what a chunk has seen, so that longer chunks have closer bounds and fewer keys to
+// list: the longest that costs the sweep little in CUs left idle at its end.
 static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) {
   constexpr int kCUs = 256, kSimulated = 16;
   constexpr double kCost = 190.;                        // of a workgroup, in keys
@@ -336,15 +342,17 @@ static int64_t prune_chunk_keys(const Plan &pl, const int *step, int64_t units) 
   return (longest + parts[i] - 1) / parts[i];
 }
 
-// What pruning has to save of a whole sweep to pay for its additional launches, in blocks of 32 rows x keys.  All scores / pruned, us, d = 128:
-// 3.9M (3 layers of 32K) 331 / 385, 3M (31 layers of 7.6K, 1024 kept) 561 / 598, 10M (8 layers of 32K) 644 / 550, 6M (32 of 8K, 512 kept)
-// 646 / 568; d = 64: 6.3M (12 layers of 66K, 2 heads) 315 / 269, 2M (9 layers of 25K) 123 / 184.
-// Every further sequence makes the chunks shorter and the launches less even: 9M (2 layers of 7 prompts) 562 / 583, 6M (2 layers of 6, groups
-// of 7) 447 / 530.
+// What pruning has to save of a whole sweep to pay for its additional launches, in blocks of 32 rows x keys.  All scores / pruned, us,
+// d = 128: 3.5M (3 layers of 32K) 332 / 363, 5.5M (one of 128K) 311 / 343, (2 of 64K) 314 / 362, 6.6M (32 of 8K, 512 kept) 659 / 597,
+// 9.4M (8 of 32K) 638 / 562; d = 64: 6.3M (12 layers of 66K, 2 heads) 309 / 259.  Below the line a call gains where its own sweeps fill
+// the last round of the CUs badly: 5.9M (5 of 32K) 528 / 426, 4.1M (6 of 16K) 352 / 339.
+// Every further sequence makes the chunks shorter and the launches less even: 12.6M (2 layers of 7 prompts) 864 / 838; with groups of 7
+// 8.6M (2 of 6) 732 / 609, below the line.
 constexpr int64_t kPruneMinSaving = 6000000, kPruneMinPerSeq = 700000;
-// Half as much again where there are more launches (prompt tokens, shared budgets) or a whole sweep has two workgroups a CU (8 waves of one row
-// block): 7.8M (prompt tokens, 9 layers of 41K) 326 / 365, 7.2M (shared budget, 20 layers of 68K, 2 heads) 363 / 378, 8.7M (25 layers of
-// 19K, 64 rows) 671 / 712; 18.8M (prompt tokens, 16 layers of 64K) 855 / 700, 9.4M (shared budget, 8 of 32K) 645 / 595.
+// Half as much again where there are more launches (prompt tokens, shared budgets) or a whole sweep has two workgroups a CU (8 waves
+// of one row block): 4.7M (shared budget, 4 layers of 32K) 353 / 397, 4.7M (d = 64, 9 of 25K, 64 rows) 233 / 252, 6.6M (prompt
+// tokens, 9 of 41K) 350 / 348; 9.4M (shared budget, 8 of 32K) 664 / 613, 10M (25 of 19K, 64 rows) 675 / 654, 13.4M (prompt tokens,
+// 16 of 64K) 856 / 728.
 // Whether a call is pruned, each sequence's sample step and the keys of those that have one.
 static bool prune_pays(const Plan &pl, int32_t keep, bool ada, int *step, int64_t *pruned) {
   const Dims &d = pl.d;
@@ -401,7 +409,8 @@ size_t prune_workspace(const Plan &pl, int32_t keep, bool ada) {
   return most.total_pruned;
 }
 
-// The environment's choices among the kernels that compute every score (score_uses_qs, score_rows_fixed_reference) are for fused calls, too.
+// The environment's choices among the kernels that compute every score (score_uses_qs, score_rows_fixed_reference) are for fused
+// calls, too.
 static bool whole_kernels_asked_for() {
   const char *kernel = std::getenv("SPECKV_SCORE_KERNEL"), *rows = std::getenv("SPECKV_ROW_STATISTICS");
   return (kernel != nullptr && kernel[0] != '\0') || (rows != nullptr && rows[0] != '\0');
@@ -416,8 +425,8 @@ bool prune_plan(Plan *pl, int32_t keep, bool ada) {
   if ((!pl->one_row && pl->hist0_words == 0) || whole_kernels_asked_for() || !prune_pays(*pl, keep, ada, step, &pruned)) return false;
   pl->prune_keep = pl->one_row ? keep : 0;
   const int64_t units = (int64_t)d.L * d.Hkv * g.RS;
-  // About a tenth of the keys is listed: an item per CU, if that makes items short.  (Twice as many of half the size measure the same, 8 layers
-  // x 32K, shared budget: 80 us for the listed sweep.)
+  // About a tenth of the keys is listed: an item per CU, if that makes items short.  (Twice as many of half the size measure the same,
+  // 8 layers x 32K, shared budget: 80 us for the listed sweep.)
   pl->item_keys = kPruneItemMax;
   while (pl->item_keys > kPruneItemMin && pl->item_keys * 1280ll >= pruned * units) pl->item_keys /= 2;
   const int64_t kc = prune_chunk_keys(*pl, step, units);

@@ -147,7 +147,7 @@ inline int64_t score_chunk_workgroups(const Dims &d, const ScoreGeom &g, int64_t
 // 640 (16 x 16K) 583 / 603.  They cross near one round, below the line, which dates from kernels before the reference
 // came from a whole tile.
 // The environment can override the choice (read on every call so that a test can switch it):
-// SPECKV_ROW_STATISTICS=fixed (always) or online (never).
+// SPECKV_ROW_STATISTICS=fixed (always) or online (never); with either, fused calls are not pruned.
 inline bool score_rows_fixed_reference(const Dims &d, const ScoreGeom &g) {
   const char *e = std::getenv("SPECKV_ROW_STATISTICS");
   if (e != nullptr && std::strcmp(e, "fixed") == 0) return true;
@@ -223,7 +223,8 @@ inline __host__ __device__ int prune_step(int32_t chunk_of) { return chunk_of & 
 // Keys of a sample's tile: Operand::KT of the scoring kernels.
 inline int prune_tile_keys(const Plan &pl) { return pl.d.D == 64 && pl.g.MB == 2 ? 256 : 128; }
 // Turns the plan of a fused call into one of a pruned call where that is faster; false: it is not.
-// ada: for a shared budget (scratch behind that of the selection).  keep: 0, or the tokens kept by a call for prompt tokens, whose layers and heads have one output row.
+// ada: for a shared budget (scratch behind that of the selection).  keep: 0, or the tokens kept by a call for prompt tokens, whose
+// layers and heads have one output row.
 bool prune_plan(Plan *pl, int32_t keep = 0, bool ada = false);
 // Bytes of workspace with which such a call is pruned, and every one with prompts no longer (0: it is not).
 size_t prune_workspace(const Plan &pl, int32_t keep, bool ada);
@@ -238,10 +239,11 @@ hipError_t launch_prune_columns(const Plan &pl, const void *q, const void *k, vo
 hipError_t launch_prune_token_columns(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st);
 hipError_t launch_prune_token_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *scratch, hipStream_t st);
 // After the pooling of these: column sums of all keys, and pooling, of the rows that failed.
-hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st, int32_t c_floor = -1);
+hipError_t launch_prune_repeat(const Plan &pl, const void *q, const void *k, void *ws, uint32_t *hist0, hipStream_t st,
+                               int32_t c_floor = -1);
 // counts: of a shared budget, 2048 words per row of scratch.
-hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items, hipStream_t st,
-                                   int32_t c_floor = -1, uint32_t *counts = nullptr);
+hipError_t launch_prune_thresholds(const Plan &pl, const float *planes, const float *row_extra, PruneRow *rows, int32_t *n_items,
+                                   hipStream_t st, int32_t c_floor = -1, uint32_t *counts = nullptr);
 hipError_t launch_prune_list(const Plan &pl, const float *planes, PruneRow *rows, int32_t *list, int2 *items, int32_t *n_items,
                              hipStream_t st);
 // hist0: the pooled scores' first digits.  Lists every key of the rows that failed.
