@@ -173,7 +173,9 @@ size_t speckv_workspace_bytes(const speckv_params *p);
 speckv_status speckv_plan_info(const speckv_params *p, int64_t info[SPECKV_PLAN_INFO_WORDS]);
 
 /* Whether a fused call with these parameters computes exact scores only for keys that can be kept, and
- * how, for diagnostics and tests (no GPU needed).  call: speckv_fused_call; top_k: of the prompt tokens'
+ * how, for diagnostics and tests (no GPU needed).  Large calls do, of 16-bit types, more than 128 rows a
+ * group (each head's padded to 32), max pooling with pool_k up to 16 and the length on the host, whose rows
+ * are not ranked in parts (speckv_plan_info [6]).  call: speckv_fused_call; top_k: of the prompt tokens'
  * call, else ignored.  info[0] 1 if it does, given the workspace of [1] bytes or more (SPECKV_SCORE_KERNEL and
  * SPECKV_ROW_STATISTICS in the environment, which choose kernels that compute every score, turn it off); all
  * words are 0 if not.  [2] unmasked chunks over all sequences, [3] keys of the longest one, [4] in the longest
